@@ -303,6 +303,148 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   }
 }
 
+template <int NP, int NT>
+struct StreamDepth {   // k-steps in flight per wave: what the register file holds next to the accumulators
+  static constexpr int value = NP + NT <= 4 ? 8 : NP == 1 ? 6 : 4;
+};
+// ---- few token rows: weights streamed into operand registers -------------------------------
+// At most a few dozen rows make the product a read of W and nothing else, so this kernel is built
+// for the HBM stream and not for the matrix pipe.  A workgroup owns 32 NP features x 32 NT tokens and
+// its 8 waves split K: each wave loads its own 1 KB operand pieces of W (non-temporal: one reader)
+// and of X straight into MFMA operand registers, kept D k-steps ahead by a register ring, with no LDS and no
+// barrier until the 8 partial tiles meet in LDS at the end.  32-feature tiles give 344 .. 688 workgroups
+// (two of them resident on a CU) where the LDS tiles above have 96 .. 172, and the split of K
+// inside the workgroup needs no partial sums in memory.  Lanes of token columns beyond T repeat
+// the last row's address, so that a 5-row batch fetches 5 rows of X and not 32.
+// Bound by the HBM stream: QKV of the 7B shape (100 MB) at 5 rows 31.0 -> 22.0 us (3.2 -> 4.6 TB/s, launch and
+// drain included), gate/up (180 MB) 36.9 -> 33.5 us (5.4 TB/s); QKV at 96 rows 35.8 -> 31.5 us.
+template <int NP, int NT, int EPI>
+__global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(HatGemm g, int ksplit) {
+  constexpr int NW = 8;
+  constexpr int D = StreamDepth<NP, NT>::value;
+  constexpr int TILES = NP * NT;
+  constexpr int GRP = TILES < 2 ? TILES : 2;   // 32 x 32 tiles summed per LDS round
+  __shared__ __attribute__((aligned(16))) f32x4 red[NW][GRP][4][64];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int nF = g.Nw / (32 * NP);
+  const int ft = blockIdx.x % nF, tt = blockIdx.x / nF;
+  const int KS = g.K >> 4;                     // k-steps of 16
+  const int part = blockIdx.z * NW + wave, parts = ksplit * NW;
+  const int s0 = (int)((long)part * KS / parts), s1 = (int)((long)(part + 1) * KS / parts);
+  const int cnt = s1 - s0;
+
+  const size_t krow = (size_t)(g.K >> 3) * 256;
+  const act_t* wsrc[NP];
+  const act_t* xsrc[NT];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) wsrc[i] = g.W + (size_t)(ft * NP + i) * krow + (size_t)s0 * 512 + lane * 8;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    int row = (tt * NT + j) * 32 + n;
+    row = row < g.T ? row : g.T - 1;
+    xsrc[j] = g.X + (size_t)(row >> 5) * krow + (size_t)s0 * 512 + h * 256 + (row & 31) * 8;
+  }
+  f32x16 acc[NP][NT];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  f16x8 a[D][NP], b[D][NT];
+  auto load = [&](auto dc, int s) {
+    constexpr int d = decltype(dc)::value;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) a[d][i] = __builtin_nontemporal_load((const f16x8*)(wsrc[i] + (size_t)s * 512));
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[d][j] = *(const f16x8*)(xsrc[j] + (size_t)s * 512);
+  };
+  auto mma = [&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[d][i], b[d][j], acc[i][j], 0, 0, 0);
+  };
+  // the main loop's loads are unconditional (a load under a branch would make every wait behind it a
+  // wait for all loads); the last D .. 2D-1 k-steps, or a K share shorter than D, take the guarded tail
+  int s = 0;
+  if (cnt >= D) {
+    static_for<D>([&](auto d) { load(d, d); });
+    for (; s + 2 * D <= cnt; s += D)
+      static_for<D>([&](auto d) {
+        mma(d);
+        load(d, s + D + d);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+  } else {
+    static_for<D>([&](auto d) {
+      if (d < cnt) load(d, d);
+    });
+  }
+  const int rem = cnt - s;   // below 2D; the first min(rem, D) of them are in registers
+  static_for<D>([&](auto d) {
+    if (d < rem) mma(d);
+    if (D + d < rem) load(d, s + D + d);
+  });
+  static_for<D>([&](auto d) {
+    if (D + d < rem) mma(d);
+  });
+
+  // ---- sum of the 8 waves' tiles and epilogue: thread = 4 consecutive features of one token
+#pragma unroll
+  for (int t0 = 0; t0 < TILES; t0 += GRP) {
+    if (t0 > 0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < GRP; ++u)
+      if (t0 + u < TILES) {
+        const int i = (t0 + u) / NT, j = (t0 + u) % NT;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& v = acc[i][j];
+          red[wave][u][q][lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        }
+      }
+    __syncthreads();
+    for (int unit = wave; unit < 4 * GRP; unit += NW) {   // one (tile, run of features) per wave at a time
+      const int u = unit >> 2, q = unit & 3;
+      if (t0 + u >= TILES || (EPI == HAT_EPI_SWIGLU && q >= 2)) continue;
+      const int i = (t0 + u) / NT, j = (t0 + u) % NT;
+      const int tok = (tt * NT + j) * 32 + n;
+      const int fb = (ft * NP + i) * (EPI == HAT_EPI_SWIGLU ? 16 : 32);
+      auto total = [&](int qq) {
+        f32x4 v = red[0][u][qq][lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w][u][qq][lane];
+        return v;
+      };
+      if (tok < g.T && fb < g.Nout) {
+        const int f = fb + 8 * q + 4 * h;
+        const f32x4 v = total(q);
+        if constexpr (EPI == HAT_EPI_RESID) {
+          float* p = (ksplit == 1 ? g.resid : g.part + (size_t)blockIdx.z * g.T * g.Nout) + (size_t)tok * g.Nout + f;
+          *(f32x4*)p = ksplit == 1 ? *(const f32x4*)p + v : v;
+        } else {
+          f16x4 o;
+          if constexpr (EPI == HAT_EPI_SWIGLU) {
+            const f32x4 up = total(q + 2);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = to_act(silu_f(v[e]) * up[e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = to_act(v[e]);
+          }
+          *(f16x4*)(g.outP + p32_index(tok, f, g.Nout)) = o;
+        }
+      }
+    }
+  }
+}
+
 // tile table: id, features x tokens, waves along features x tokens, k per stage, stages.
 // Heights of 96 and 192 rows exist so that the tile count can match the 256 CUs where
 // 128 / 256 leave a quarter or a third of them idle (7B-shaped QKV and gate/up at T <= 256).
@@ -338,24 +480,36 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   X(21, 256, 192, 2, 2, 32, 4, EPI) \
   X(22, 256, 160, 4, 1, 64, 3, EPI) \
   X(23, 128, 160, 4, 1, 64, 3, EPI)
-constexpr int kNumTiles = 24;
+constexpr int kNumLdsTiles = 24;
+// the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
+// 64 x 32 measured level with or behind these at every size.
+#define HAT_FOR_STREAM(X, EPI) \
+  X(24, 1, 1, EPI)             \
+  X(25, 2, 2, EPI)             \
+  X(26, 2, 3, EPI)
+constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26;
+constexpr int kNumTiles = 27;
 
 struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
 // `planned`: offered to the automatic choice; the others are alternative stagings of the
 // same shapes, used only when forced
-constexpr bool kPlanned[kNumTiles] = {false, true, true, true, true, true, true, true, true, true,
+constexpr bool kPlanned[kNumLdsTiles] = {false, true, true, true, true, true, true, true, true, true,
                                       false, false, false, true, true, true, true, true, true, true,
                                       true, true, true, true};
 // Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, fitted to
 // sweeps at T = 512 .. 5220 (7B shapes, all four products, K split 1 .. 8); 0 = not measured
 // there, the tile is only offered to batches of at most kSmallT rows.
-constexpr float kEff[kNumTiles] = {0.f, 0.585f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
+constexpr float kEff[kNumLdsTiles] = {0.f, 0.585f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
                                    0.f, 0.f, 0.f, 0.514f, 0.f, 1.209f, 0.f, 0.504f, 0.f, 0.629f,
                                    0.518f, 0.565f, 0.564f, 0.f};
 constexpr int kSmallT = 384;
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, bkt, ns, epi) {bf, bt, (wf) * (wt), bkt, ns, kPlanned[id], kEff[id]},
     HAT_FOR_TILES(HAT_INFO, 0)
+#undef HAT_INFO
+// "stages" of a streaming tile: its register ring counted in 32-k pieces
+#define HAT_INFO(id, np, nt, epi) {32 * (np), 32 * (nt), 8, 32, StreamDepth<np, nt>::value / 2, false, 0.f},
+    HAT_FOR_STREAM(HAT_INFO, 0)
 #undef HAT_INFO
 };
 
@@ -370,6 +524,14 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
     return hipGetLastError();                                           \
   }
   HAT_FOR_TILES(HAT_TRY, EPI)
+#undef HAT_TRY
+#define HAT_TRY(id, np, nt, epi)                                                     \
+  if (p.tile == id) {                                                                \
+    dim3 grid(((g.T + 32 * (nt) - 1) / (32 * (nt))) * (g.Nw / (32 * (np))), 1, p.ksplit); \
+    gemm_stream_kernel<np, nt, epi><<<grid, dim3(512), 0, st>>>(g, p.ksplit);        \
+    return hipGetLastError();                                                        \
+  }
+  HAT_FOR_STREAM(HAT_TRY, EPI)
 #undef HAT_TRY
   return hipErrorInvalidValue;
 }
@@ -408,6 +570,37 @@ hipError_t hat_gemm_init() {
   return hipSuccess;
 }
 
+// Where the streaming kernel is the faster one.  Swept over the 7B-, 13B- and hd-64-shaped layers at 5 .. 128 rows; times
+// in us against the best LDS tile:
+//  - no split of K in memory (QKV, gate/up), up to 32 rows: QKV 31.0 -> 22.0 (7B, 5 rows), 32.4 -> 24.7 (32 rows), 38.7 -> 26.8
+//    (13B), 17.3 -> 8.7 (hd 64).  Beyond 16 rows the X operand's traffic shows once there are more than three
+//    workgroups per CU: gate/up at 32 rows 36.6 -> 35.8 with 688 workgroups (7B), but 51.3 -> 56.1 with 864 (13B).
+//  - 33 .. 96 rows: 64-feature tiles, two or three token panels per workgroup, as long as every workgroup has a CU of
+//    its own (256 registers): QKV 33.5 -> 27.6 (7B, 64 rows), 35.8 -> 31.5 (96 rows), 42.8 -> 34.1 (13B, 64); gate/up 18.9 ->
+//    16.9 (hd 64, 176 workgroups), but 37.9 -> 52 with 344 (7B).  Three panels only where that leaves half the CUs busy.
+//  - O and down: K split until the workgroups fill the CUs once; the gain is the few partial sums (RMSNorm 8.2 -> 6.7),
+//    the products themselves are level (O 10.9 -> 10.3, down 20.3 -> 20.0 at 5 rows; 14.8 -> 14.2 and 26.1 -> 25.5 at 77).
+//    With the 160 panels of the 13B shape the CUs are not filled: up to 16 rows still 23.9 -> 20.4 with the norm, at
+//    32 rows 24.2 -> 25.8; at 33 .. 64 rows down loses more (22.9 -> 25.4) than the norm gains.
+static bool stream_plan(const HatGemm& g, HatGemmPlan* p) {
+  if (g.T > 96) return false;
+  p->ksplit = 1;
+  if (g.epilogue != HAT_EPI_RESID) {
+    if (g.T <= 32) {
+      p->tile = kStream32;
+      return g.T <= 16 || g.Nw / 32 <= 768;
+    }
+    p->tile = g.T > 64 && g.Nw / 64 >= 128 ? kStream96 : kStream64;
+    const int bt = p->tile == kStream96 ? 96 : 64;
+    return (g.T + bt - 1) / bt * (g.Nw / 64) <= 256;
+  }
+  if (g.T > 32 && g.T <= 64) return false;
+  p->tile = g.T <= 32 ? kStream32 : kStream96;
+  const int tiles = g.Nw / (g.T <= 32 ? 32 : 64);
+  while (p->ksplit < 4 && tiles * p->ksplit * 2 <= 256 && g.part && (long)p->ksplit * 2 * g.T <= g.part_rows) p->ksplit *= 2;
+  return tiles * p->ksplit >= (g.T <= 16 ? 128 : 192);
+}
+
 HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // Estimated time of a candidate = rounds of 256 workgroups x the larger of the
   // MFMA time and the L2->LDS streaming time of one workgroup; split-K (only where
@@ -420,6 +613,8 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     while (best.ksplit > 1 && ((long)best.ksplit * g.T > g.part_rows || g.K / 64 / best.ksplit < 1)) --best.ksplit;
     return best;
   }
+  HatGemmPlan stream;
+  if (stream_plan(g, &stream)) return stream;
   // Two regimes, each with constants fitted to tile sweeps on MI355X (7B shapes).
   // Up to kSmallT rows (T = 32 .. 384) the weight stream decides: a CU moves about 36 B/clk
   // through direct-to-LDS loads, the MFMA loop runs at about 85 % of the matrix peak on its own,
@@ -435,7 +630,7 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   double best_cost = 1e300;
   const int KT = g.K / 64;
   const bool large = g.T > kSmallT;
-  for (int c = 0; c < kNumTiles; ++c) {
+  for (int c = 0; c < kNumLdsTiles; ++c) {
     const TileInfo& q = kTiles[c];
     if (!q.planned) continue;
     // 160/192/224-row token tiles: large batches only, except the 128 x 160 tile (23), which exists for batches
