@@ -828,10 +828,18 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     nparts = 0;
     HatGemm g{};
     g.W = ld.wqkv; g.X = h->b.xn; g.K = s.d; g.T = T; g.Nw = s.Nqkv; g.Nout = 3 * s.d; g.outP = h->b.qkv;
-    g.epilogue = HAT_EPI_P32;
-    hat_status_t rc = run_gemm(HAT_K_GEMM_QKV, g, nullptr);
-    if (rc != HAT_OK) return rc;
-    LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
+    g.epilogue = HAT_EPI_QKV;
+    g.qkv = HatQkvOut{h->b.table, pd.kv_dst, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16};
+    g.force_tile = h->force_tile[0];
+    hat_status_t rc;
+    const HatGemmPlan qp = hat_gemm_plan(g);
+    if (qp.tile >= 0) {
+      LAUNCH(h, st, HAT_K_GEMM_QKV, hat_launch_gemm(g, qp, st));
+    } else {
+      g.epilogue = HAT_EPI_P32;
+      if ((rc = run_gemm(HAT_K_GEMM_QKV, g, nullptr)) != HAT_OK) return rc;
+      LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
+    }
     HatAttn a{};
     a.qkv = h->b.qkv; a.pool_layer = pool_l; a.outP = h->b.attn; a.part_o = h->b.part_o; a.part_ml = h->b.part_ml;
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;

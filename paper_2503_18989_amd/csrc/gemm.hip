@@ -36,6 +36,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef kv_t kvx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -303,6 +304,52 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   }
 }
 
+// One thread's share of the QKV result: features i0 .. i0+3 of panel `panel` (lo) and their partners hd/2 further (hi) of
+// token tok.  q and k are rotated in fp32 and rounded once; k and v go to the token's cache slot.
+__device__ __forceinline__ void store_qkv(const HatGemm& g, int tok, int panel, int i0, f32x4 lo, f32x4 hi) {
+  const HatQkvOut& o = g.qkv;
+  const int ppd = o.hd >> 5;                 // panels per head
+  const int head3 = panel / ppd, which = head3 / o.H, head = head3 - which * o.H;
+  const int f = (panel % ppd) * 32 + i0, half = o.hd >> 1;   // feature within the head, below half
+  if (which < 2) {
+    const f32x4 c01 = *(const f32x4*)(o.table + (size_t)tok * half + f), c23 = *(const f32x4*)(o.table + (size_t)tok * half + f + 2);
+    const float c[4] = {c01[0], c01[2], c23[0], c23[2]}, s[4] = {c01[1], c01[3], c23[1], c23[3]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = lo[e], b = hi[e];
+      lo[e] = a * c[e] - b * s[e];
+      hi[e] = b * c[e] + a * s[e];
+    }
+  }
+  if (which == 0) {
+    f16x4 a, b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { a[e] = to_act(lo[e]); b[e] = to_act(hi[e]); }
+    *(f16x4*)(g.outP + p32_index(tok, head * o.hd + f, g.Nout)) = a;
+    *(f16x4*)(g.outP + p32_index(tok, head * o.hd + f + half, g.Nout)) = b;
+    return;
+  }
+  const int dst = o.kv_dst[tok], slot = dst & 15;
+  kv_t* rec = o.pool + ((size_t)head * o.n_pages + (dst >> 4)) * kv_head_elems(o.hd);
+  kvx4 a, b;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    a[e] = o.kv_f16 ? __builtin_bit_cast(kv_t, to_act(lo[e])) : __builtin_bit_cast(kv_t, (__bf16)lo[e]);
+    b[e] = o.kv_f16 ? __builtin_bit_cast(kv_t, to_act(hi[e])) : __builtin_bit_cast(kv_t, (__bf16)hi[e]);
+  }
+  if (which == 1) {
+    *(kvx4*)(rec + ktile_index(slot, f)) = a;
+    *(kvx4*)(rec + ktile_index(slot, f + half)) = b;
+  } else {   // a V tile is feature-major: two-byte stores (few rows take this way)
+    kv_t* vt = rec + 16 * o.hd;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      vt[vtile_index(slot, f + e)] = a[e];
+      vt[vtile_index(slot, f + half + e)] = b[e];
+    }
+  }
+}
+
 template <int NP, int NT>
 struct StreamDepth {   // k-steps in flight per wave: what the register file holds next to the accumulators
   static constexpr int value = NP + NT <= 4 ? 8 : NP == 1 ? 6 : 4;
@@ -324,13 +371,28 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   constexpr int D = StreamDepth<NP, NT>::value;
   constexpr int TILES = NP * NT;
   constexpr int GRP = TILES < 2 ? TILES : 2;   // 32 x 32 tiles summed per LDS round
+  static_assert(TILES % GRP == 0 && (EPI != HAT_EPI_QKV || GRP == NP), "a round is whole, and holds a rotation pair's halves");
   __shared__ __attribute__((aligned(16))) f32x4 red[NW][GRP][4][64];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int nF = g.Nw / (32 * NP);
+  const int nF = (EPI == HAT_EPI_QKV ? g.Nout : g.Nw) / (32 * NP);
   const int ft = blockIdx.x % nF, tt = blockIdx.x / nF;
+  // This lane's row of W.  With HAT_EPI_QKV a workgroup holds both halves of its rotation pairs (features i and i + hd/2
+  // of a head), so that a thread of the epilogue ends up with both: two panels hd/64 apart, or with one panel's
+  // worth of rows 16 rows from each of the two.
+  int panel0 = ft * NP, pstep = 1, row0 = 0, wrow = n, wpanel = 0;
+  if constexpr (EPI == HAT_EPI_QKV) {
+    pstep = g.qkv.hd >> 6;
+    const int pair = NP == 1 ? ft >> 1 : ft;
+    panel0 = pair / pstep * (2 * pstep) + pair % pstep;
+    if constexpr (NP == 1) {
+      row0 = (ft & 1) * 16;
+      wrow = row0 + (n & 15);
+      wpanel = n < 16 ? 0 : pstep;
+    }
+  }
   const int KS = g.K >> 4;                     // k-steps of 16
   const int part = blockIdx.z * NW + wave, parts = ksplit * NW;
   const int s0 = (int)((long)part * KS / parts), s1 = (int)((long)(part + 1) * KS / parts);
@@ -340,7 +402,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   const act_t* wsrc[NP];
   const act_t* xsrc[NT];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) wsrc[i] = g.W + (size_t)(ft * NP + i) * krow + (size_t)s0 * 512 + lane * 8;
+  for (int i = 0; i < NP; ++i) wsrc[i] = g.W + (size_t)(panel0 + wpanel + i * pstep) * krow + (size_t)s0 * 512 + h * 256 + wrow * 8;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     int row = (tt * NT + j) * 32 + n;
@@ -400,38 +462,37 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   for (int t0 = 0; t0 < TILES; t0 += GRP) {
     if (t0 > 0) __syncthreads();
 #pragma unroll
-    for (int u = 0; u < GRP; ++u)
-      if (t0 + u < TILES) {
-        const int i = (t0 + u) / NT, j = (t0 + u) % NT;
+    for (int u = 0; u < GRP; ++u) {
+      const f32x16& v = acc[(t0 + u) % NP][(t0 + u) / NP];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& v = acc[i][j];
-          red[wave][u][q][lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-        }
-      }
+      for (int q = 0; q < 4; ++q) red[wave][u][q][lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    }
     __syncthreads();
-    for (int unit = wave; unit < 4 * GRP; unit += NW) {   // one (tile, run of features) per wave at a time
-      const int u = unit >> 2, q = unit & 3;
-      if (t0 + u >= TILES || (EPI == HAT_EPI_SWIGLU && q >= 2)) continue;
-      const int i = (t0 + u) / NT, j = (t0 + u) % NT;
-      const int tok = (tt * NT + j) * 32 + n;
-      const int fb = (ft * NP + i) * (EPI == HAT_EPI_SWIGLU ? 16 : 32);
-      auto total = [&](int qq) {
-        f32x4 v = red[0][u][qq][lane];
+    auto total = [&](int u, int q) {
+      f32x4 v = red[0][u][q][lane];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) v += red[w][u][qq][lane];
-        return v;
-      };
-      if (tok < g.T && fb < g.Nout) {
+      for (int w = 1; w < NW; ++w) v += red[w][u][q][lane];
+      return v;
+    };
+    if constexpr (EPI == HAT_EPI_QKV) {
+      // lower halves of the pairs: tile 0 of the round (upper: tile 1), or the tile's rows 0 .. 15 (upper: 16 .. 31)
+      const int tok = (tt * NT + t0 / NP) * 32 + n, q = wave;
+      if (q < (NP == 1 ? 2 : 4) && tok < g.T)
+        store_qkv(g, tok, panel0, row0 + 8 * q + 4 * h, total(0, q), NP == 1 ? total(0, q + 2) : total(1, q));
+    } else {
+      const int u = threadIdx.x >> 8, q = (threadIdx.x >> 6) & 3;
+      const int tok = (tt * NT + (t0 + u) / NP) * 32 + n;
+      const int fb = (ft * NP + (t0 + u) % NP) * (EPI == HAT_EPI_SWIGLU ? 16 : 32);
+      if (u < GRP && (EPI != HAT_EPI_SWIGLU || q < 2) && tok < g.T && fb < g.Nout) {
         const int f = fb + 8 * q + 4 * h;
-        const f32x4 v = total(q);
+        const f32x4 v = total(u, q);
         if constexpr (EPI == HAT_EPI_RESID) {
           float* p = (ksplit == 1 ? g.resid : g.part + (size_t)blockIdx.z * g.T * g.Nout) + (size_t)tok * g.Nout + f;
           *(f32x4*)p = ksplit == 1 ? *(const f32x4*)p + v : v;
         } else {
           f16x4 o;
           if constexpr (EPI == HAT_EPI_SWIGLU) {
-            const f32x4 up = total(q + 2);
+            const f32x4 up = total(u, q + 2);
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = to_act(silu_f(v[e]) * up[e]);
           } else {
@@ -482,13 +543,15 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   X(23, 128, 160, 4, 1, 64, 3, EPI)
 constexpr int kNumLdsTiles = 24;
 // the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
-// 64 x 32 measured level with or behind these at every size.
+// 32 x 96 measured level with
+// or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
 #define HAT_FOR_STREAM(X, EPI) \
   X(24, 1, 1, EPI)             \
   X(25, 2, 2, EPI)             \
-  X(26, 2, 3, EPI)
-constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26;
-constexpr int kNumTiles = 27;
+  X(26, 2, 3, EPI)             \
+  X(27, 2, 1, EPI)
+constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26, kStream64x32 = 27;
+constexpr int kNumTiles = 28;
 
 struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
 // `planned`: offered to the automatic choice; the others are alternative stagings of the
@@ -534,6 +597,17 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
   HAT_FOR_STREAM(HAT_TRY, EPI)
 #undef HAT_TRY
   return hipErrorInvalidValue;
+}
+
+// the QKV product with rotary embedding and append: streaming tiles only
+hipError_t launch_qkv(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
+  const int nF = g.Nout / 64;
+  if (p.tile == kStream32) gemm_stream_kernel<1, 1, HAT_EPI_QKV><<<(g.T + 31) / 32 * nF * 2, 512, 0, st>>>(g, 1);
+  else if (p.tile == kStream64x32) gemm_stream_kernel<2, 1, HAT_EPI_QKV><<<(g.T + 31) / 32 * nF, 512, 0, st>>>(g, 1);
+  else if (p.tile == kStream64) gemm_stream_kernel<2, 2, HAT_EPI_QKV><<<(g.T + 63) / 64 * nF, 512, 0, st>>>(g, 1);
+  else if (p.tile == kStream96) gemm_stream_kernel<2, 3, HAT_EPI_QKV><<<(g.T + 95) / 96 * nF, 512, 0, st>>>(g, 1);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 template <int EPI>
@@ -606,6 +680,14 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // MFMA time and the L2->LDS streaming time of one workgroup; split-K (only where
   // the result is accumulated in fp32) adds the traffic of its partial sums.
   HatGemmPlan best{0, 1};
+  if (g.epilogue == HAT_EPI_QKV) {
+    // wherever the plain product would stream: the epilogue costs less than the rotary and append kernel it replaces (5 us).
+    // 64-feature tiles from 17 rows on: 24.4 against 27.0 us at 32 rows of the 7B shape (half the reads of X and
+    // whole panels of W), but 22.3 against 21.0 at 5 rows (192 workgroups instead of 384).
+    if (g.force_tile >= 0 || !stream_plan(g, &best)) best.tile = -1;
+    if (best.tile == kStream32 && g.T > 16) best.tile = kStream64x32;
+    return best;
+  }
   if (g.force_tile >= 0 && g.force_tile < kNumTiles) {
     best.tile = g.force_tile;
     best.ksplit = g.force_ksplit > 0 ? g.force_ksplit : 1;
@@ -682,6 +764,7 @@ hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t s
     case HAT_EPI_P32: return launch_epi<HAT_EPI_P32>(g, p, st);
     case HAT_EPI_SWIGLU: return launch_epi<HAT_EPI_SWIGLU>(g, p, st);
     case HAT_EPI_RESID: return launch_epi<HAT_EPI_RESID>(g, p, st);
+    case HAT_EPI_QKV: return launch_qkv(g, p, st);
   }
   return hipErrorInvalidValue;
 }

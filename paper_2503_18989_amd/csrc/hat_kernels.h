@@ -18,7 +18,17 @@ constexpr int HAT_CHUNK_QROWS = 256;
 enum HatEpilogue {
   HAT_EPI_P32 = 0,     // fp16 (act_t) result, P32 layout, row length Nout
   HAT_EPI_SWIGLU = 1,  // W rows interleaved (16 gate, 16 up): silu(gate)*up, P32, row length Nout
-  HAT_EPI_RESID = 2    // resid[t, f] += result  (fp32 row-major, leading dim Nout)
+  HAT_EPI_RESID = 2,   // resid[t, f] += result  (fp32 row-major, leading dim Nout)
+  HAT_EPI_QKV = 3      // rotary embedding and KV append on the way out (few rows): q rotated to outP (P32, row
+                       // length Nout, columns [0, Nout/3)), k rotated and v to the cache; k and v are not in outP
+};
+
+// what HAT_EPI_QKV needs besides the product
+struct HatQkvOut {
+  const float2* table;    // [T][hd/2] (cos, sin)
+  const int32_t* kv_dst;  // [T] page*16 + slot
+  kv_t* pool;             // this layer's pages
+  int n_pages, H, hd, kv_f16;
 };
 
 struct HatGemm {
@@ -33,11 +43,12 @@ struct HatGemm {
   float* part;      // EPI_RESID, K split s ways: part[z][t][f] = partial sum of split z (may be null: no split)
   int part_rows;    // capacity of `part` in rows of Nout floats (bounds ksplit * T)
   int epilogue;
+  HatQkvOut qkv;    // EPI_QKV
   int force_tile;   // >= 0: use this tile id (tuning); -1: choose
   int force_ksplit; // with force_tile: K split (0/1 = none)
 };
 struct HatGemmPlan {
-  int tile;    // index into the tile table of gemm.hip
+  int tile;    // index into the tile table of gemm.hip; -1: HAT_EPI_QKV is not the way for this batch
   int ksplit;  // 1 = K not split
 };
 HatGemmPlan hat_gemm_plan(const HatGemm& g);
