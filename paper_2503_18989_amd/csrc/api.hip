@@ -807,8 +807,10 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   pd.in_ptr = (const uint64_t*)(D + o_in); pd.out_ptr = (const uint64_t*)(D + o_out);
   pd.append = (const HatAppendItem*)(D + o_app); pd.n_append = n_append;
 
+  pd.first = HatFirstNorm{h->b.inv_freq, h->b.table, s.hd / 2, h->b.layers[0].g_attn, h->b.xn, c.rms_eps};
+  const bool gather_norms = hat_gather_norms(T);   // the gather launch fills the rotary table and applies the first norm too
   LAUNCH(h, st, HAT_K_GATHER, hat_launch_gather(pd, h->b.resid, s.d, c.io_dtype, st));
-  LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
+  if (!gather_norms) LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
 
   int nparts = 0;  // split-K partial sums of the previous residual GEMM still to be folded in
   auto run_gemm = [&](int id, HatGemm& g, int* ksplit_out) -> hat_status_t {
@@ -823,8 +825,9 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   for (int l = 0; l < s.L; ++l) {
     const LayerDev& ld = h->b.layers[l];
     kv_t* pool_l = h->pool + (size_t)l * h->layer_pool_elems;
-    LAUNCH(h, st, HAT_K_RMSNORM,
-           hat_launch_rmsnorm(h->b.resid, h->b.gemm_part, nparts, ld.g_attn, h->b.xn, T, s.d, c.rms_eps, st));
+    if (l > 0 || !gather_norms)
+      LAUNCH(h, st, HAT_K_RMSNORM,
+             hat_launch_rmsnorm(h->b.resid, h->b.gemm_part, nparts, ld.g_attn, h->b.xn, T, s.d, c.rms_eps, st));
     nparts = 0;
     HatGemm g{};
     g.W = ld.wqkv; g.X = h->b.xn; g.K = s.d; g.T = T; g.Nw = s.Nqkv; g.Nout = 3 * s.d; g.outP = h->b.qkv;

@@ -98,15 +98,17 @@ __global__ void scatter_kernel(HatPlanDev p, const float* __restrict__ resid, co
 // ---------------------------------------------------------------- rotary table
 // table[t][i] = (cos, sin)(pos[t] * inv_freq[i]), angle and functions in double:
 // positions reach several thousand radians, where float arguments lose digits.
+__device__ __forceinline__ void rope_entry(int pos, double inv_freq, float2* out) {
+  double s, c;
+  sincos((double)pos * inv_freq, &s, &c);
+  *out = make_float2((float)c, (float)s);
+}
 __global__ void rope_table_kernel(HatPlanDev p, const double* __restrict__ inv_freq, float2* __restrict__ table,
                                   int half) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= p.T * half) return;
   const int t = idx / half, i = idx % half;
-  const double ang = (double)p.pos[t] * inv_freq[i];
-  double s, c;
-  sincos(ang, &s, &c);
-  table[idx] = make_float2((float)c, (float)s);
+  rope_entry(p.pos[t], inv_freq[i], table + idx);
 }
 
 // a, b += the 8 floats at pp of each of the nparts split-K partial sums (pstride floats apart), added in
@@ -132,30 +134,17 @@ __device__ __forceinline__ void fold_partials(f32x4& a, f32x4& b, const float* _
 }
 
 // ---------------------------------------------------------------- RMSNorm
-// one workgroup (256 threads) per row: x = resid + pending split-K partial sums
-// (written back), y = x * rsqrt(mean(x^2) + eps) * gain as fp16 in P32 layout.
-// A row (<= 8192 floats) stays in registers between the two passes.
-__global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ resid, const float* __restrict__ part,
-                                                       int nparts, int T, const float* __restrict__ gain,
-                                                       act_t* __restrict__ outP, int d, float eps) {
-  const int t = blockIdx.x;
-  float* x = resid + (size_t)t * d;
-  const size_t pstride = (size_t)T * d;
-  constexpr int MAXV = 4;  // 256 threads * 8 floats * 4 = 8192 columns held in registers
-  f32x4 va[MAXV], vb[MAXV];
+// y = x * rsqrt(mean(x^2) + eps) * gain of one row that the 256 threads of a workgroup hold in registers
+template <int MAXV>
+__device__ __forceinline__ void norm_row(const f32x4 (&va)[MAXV], const f32x4 (&vb)[MAXV], int t, const float* __restrict__ gain,
+                                         act_t* __restrict__ outP, int d, float eps) {
   float ss = 0.f;
 #pragma unroll
-  for (int v = 0; v < MAXV; ++v) {
-    const int i = (v * 256 + threadIdx.x) * 8;
-    if (i < d) {
-      f32x4 a = *(const f32x4*)(x + i), b = *(const f32x4*)(x + i + 4);
-      fold_partials(a, b, part + (size_t)t * d + i, pstride, nparts);
-      if (nparts > 0) { *(f32x4*)(x + i) = a; *(f32x4*)(x + i + 4) = b; }
+  for (int v = 0; v < MAXV; ++v)
+    if ((v * 256 + (int)threadIdx.x) * 8 < d) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ss += a[e] * a[e] + b[e] * b[e];
-      va[v] = a; vb[v] = b;
+      for (int e = 0; e < 4; ++e) ss += va[v][e] * va[v][e] + vb[v][e] * vb[v][e];
     }
-  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
   __shared__ float red[4];
@@ -174,6 +163,63 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ resid,
       *(f16x8*)(outP + p32_index(t, i, d)) = o;
     }
   }
+}
+
+// one workgroup (256 threads) per row: x = resid + pending split-K partial sums
+// (written back), y = x * rsqrt(mean(x^2) + eps) * gain as fp16 in P32 layout.
+// A row (<= 8192 floats) stays in registers between the two passes.
+__global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ resid, const float* __restrict__ part,
+                                                       int nparts, int T, const float* __restrict__ gain,
+                                                       act_t* __restrict__ outP, int d, float eps) {
+  const int t = blockIdx.x;
+  float* x = resid + (size_t)t * d;
+  const size_t pstride = (size_t)T * d;
+  constexpr int MAXV = 4;  // 256 threads * 8 floats * 4 = 8192 columns held in registers
+  f32x4 va[MAXV], vb[MAXV];
+#pragma unroll
+  for (int v = 0; v < MAXV; ++v) {
+    const int i = (v * 256 + threadIdx.x) * 8;
+    if (i < d) {
+      f32x4 a = *(const f32x4*)(x + i), b = *(const f32x4*)(x + i + 4);
+      fold_partials(a, b, part + (size_t)t * d + i, pstride, nparts);
+      if (nparts > 0) { *(f32x4*)(x + i) = a; *(f32x4*)(x + i + 4) = b; }
+      va[v] = a; vb[v] = b;
+    }
+  }
+  norm_row<MAXV>(va, vb, t, gain, outP, d, eps);
+}
+
+// gather_kernel with the rotary table of its row and the first layer's RMSNorm: a row is read once, kept in
+// registers and leaves as fp32 residual and as normalised fp16 operand.
+template <typename IO>
+__global__ __launch_bounds__(256) void gather_norm_kernel(HatPlanDev p, float* __restrict__ resid, int d) {
+  const int t = blockIdx.x;
+  const int s = p.tok_seg[t];
+  const int row = t - p.tok_off[s];
+  const IO* src = (const IO*)p.in_ptr[s] + (size_t)row * d;
+  float* dst = resid + (size_t)t * d;
+  constexpr int MAXV = 4;
+  f32x4 va[MAXV], vb[MAXV];
+#pragma unroll
+  for (int v = 0; v < MAXV; ++v) {
+    const int i = (v * 256 + threadIdx.x) * 8;
+    if (i < d) {
+      f32x4 a, b;
+      if constexpr (sizeof(IO) == 2) {
+        const bf16x8 x = *(const bf16x8*)(src + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { a[e] = (float)x[e]; b[e] = (float)x[4 + e]; }
+      } else {
+        a = *(const f32x4*)(src + i);
+        b = *(const f32x4*)(src + i + 4);
+      }
+      *(f32x4*)(dst + i) = a;
+      *(f32x4*)(dst + i + 4) = b;
+      va[v] = a; vb[v] = b;
+    }
+  }
+  if ((int)threadIdx.x < p.first.half) rope_entry(p.pos[t], p.first.inv_freq[threadIdx.x], p.first.table + (size_t)t * p.first.half + threadIdx.x);
+  norm_row<MAXV>(va, vb, t, p.first.gain, p.first.xn, d, p.first.eps);
 }
 
 // The same for batches of many rows: a workgroup takes R consecutive rows (one wave per row, the
@@ -478,7 +524,13 @@ inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / 
 }  // namespace
 
 hipError_t hat_launch_gather(const HatPlanDev& p, float* resid, int d, int io_dtype, hipStream_t st) {
-  gather_kernel<<<p.T, 256, 0, st>>>(p, resid, d, io_dtype);
+  if (!hat_gather_norms(p.T)) {
+    gather_kernel<<<p.T, 256, 0, st>>>(p, resid, d, io_dtype);
+    return hipGetLastError();
+  }
+  if (d > 8192 || (d & 7) || p.first.half > 256) return hipErrorInvalidValue;
+  if (io_dtype == 0) gather_norm_kernel<bf16_t><<<p.T, 256, 0, st>>>(p, resid, d);
+  else gather_norm_kernel<float><<<p.T, 256, 0, st>>>(p, resid, d);
   return hipGetLastError();
 }
 hipError_t hat_launch_scatter(const HatPlanDev& p, const float* resid, const float* part, int nparts, int d,

@@ -671,6 +671,7 @@ static bool stream_plan(const HatGemm& g, HatGemmPlan* p) {
   if (g.T > 32 && g.T <= 64) return false;
   p->tile = g.T <= 32 ? kStream32 : kStream96;
   const int tiles = g.Nw / (g.T <= 32 ? 32 : 64);
+  if (g.T <= 32 && (long)g.Nw * g.K <= 1 << 18) return true;   // nothing to stream: the K split among a workgroup's waves is the gain
   while (p->ksplit < 4 && tiles * p->ksplit * 2 <= 256 && g.part && (long)p->ksplit * 2 * g.T <= g.part_rows) p->ksplit *= 2;
   return tiles * p->ksplit >= (g.T <= 16 ? 128 : 192);
 }

@@ -78,6 +78,16 @@ struct HatAppendItem {
   int32_t pad0, pad1, pad2;
 };
 
+// What the launch that gathers the hidden rows also does: the rotary table and the first layer's RMSNorm
+struct HatFirstNorm {
+  const double* inv_freq;   // [half]
+  float2* table;            // [T][half] (cos, sin)
+  int half;
+  const float* gain;
+  act_t* xn;                // P32 [., d]
+  float eps;
+};
+
 struct HatPlanDev {
   int T, S;
   const int32_t* pos;       // [T] absolute position of each row
@@ -91,7 +101,12 @@ struct HatPlanDev {
   const uint64_t* out_ptr;  // [S] hidden_out
   const HatAppendItem* append;  // pages written by this step
   int n_append;
+  HatFirstNorm first;       // used by hat_launch_gather, and only where hat_gather_norms(T) says so
 };
+// batches whose gather launch also fills the rotary table and applies the first RMSNorm (one launch instead of three: the
+// 16-row step of the tiny model is a chain of nine or ten launches of 3 .. 7 us).  From 1024 rows on the norm
+// takes its rows in groups (hat_launch_rmsnorm) and the launches are small beside the step.
+inline bool hat_gather_norms(int T) { return T < 1024; }
 
 hipError_t hat_launch_gather(const HatPlanDev& p, float* resid, int d, int io_dtype, hipStream_t st);
 hipError_t hat_launch_scatter(const HatPlanDev& p, const float* resid, const float* part, int nparts, int d,
