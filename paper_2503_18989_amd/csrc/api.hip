@@ -546,7 +546,7 @@ struct StepPlan {
   int T = 0, S = 0, n_append = 0;
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_vi = 0, o_mi = 0, words = 0;
-  int n_citems = 0, n_vitems = 0, n_mitems = 0;
+  int n_citems = 0, n_narrow = 0, n_vitems = 0, n_mitems = 0;
 };
 
 // Host half of a step: validates every segment, commits the page movements, and writes the plan
@@ -720,15 +720,21 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // chunk segments: tiles of HAT_CHUNK_QROWS rows, split along the keys so that no work item
     // is larger than a third of one workgroup slot's share of the launch (all heads do the same
     // work, so a head has attn_target / H slots): the items, sorted by cost, then pack evenly.
+    // Items of at most HAT_NARROW_QROWS rows are bound by the cache stream: key ranges of about equal size instead, for
+    // three eighths of verify_target workgroups (8 x 32 rows over 4096 keys: 118 us and 7 us of merging with 768 workgroups
+    // wanted, 130 and 9 with 2048).
     double total_cost = 0;
+    long narrow_keys = 0;
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
       for (int q0 = 0; q0 < segs[i].n; q0 += HAT_CHUNK_QROWS) {
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
-        total_cost += (double)nq * (segs[i].start_pos + q0 + 0.5 * nq);
+        if (nq <= HAT_NARROW_QROWS) narrow_keys += segs[i].start_pos + q0 + nq;
+        else total_cost += (double)nq * (segs[i].start_pos + q0 + 0.5 * nq);
       }
     }
-    if (total_cost > 0) {
+    if (total_cost > 0 || narrow_keys > 0) {
+      const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
       const double slots = std::max(1, s.attn_target / s.H);
       const double cost_cap = std::max(256.0 * 256.0, total_cost / (3.0 * slots));
       for (int i = 0; i < S; ++i) {
@@ -737,8 +743,9 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
           const int need = segs[i].start_pos + q0 + nq;
           const double cost = (double)nq * (need - 0.5 * nq);
-          int ns = (int)std::ceil(cost / cost_cap);
-          ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), 16));
+          const bool narrow = nq <= HAT_NARROW_QROWS;
+          int ns = narrow ? (int)((need + narrow_step - 1) / narrow_step) : (int)std::ceil(cost / cost_cap);
+          ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), narrow ? 32 : 16));
           if ((int)citems.size() + ns > s.chunk_items_cap - 1 || part_row + ns * nq > s.part_rows_cap ||
               (int)mitems.size() + 9 >= s.merge_cap)
             ns = 1;
@@ -765,6 +772,8 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     };
     std::stable_sort(citems.begin(), citems.end(), by_cost);
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
+    const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [](const HatAttnItem& a) { return a.nq > HAT_NARROW_QROWS; });
+    sp->n_narrow = (int)(citems.end() - narrow0);
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_vi = take(12 * vitems.size(), 4), o_mi = take(8 * mitems.size(), 8);
   const size_t plan_cap = h->plan_limit ? std::min(h->plan_limit, s.plan_words) : s.plan_words;
@@ -847,7 +856,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.qkv = h->b.qkv; a.pool_layer = pool_l; a.outP = h->b.attn; a.part_o = h->b.part_o; a.part_ml = h->b.part_ml;
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
-      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems;
+      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
     if (sp.n_vitems > 0) {

@@ -159,23 +159,34 @@ __device__ __forceinline__ f16x8 kv_to_f16(u32x4 raw) { return __builtin_bit_cas
 __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin_amdgcn_fmed3f(x, -65504.f, 65504.f); }
 
 // ------------------------------------------------------------------ verify
-template <int HD, bool KVF16>
+// ROWS = 8: a verify segment, visibility of its own rows from the work item.  ROWS = 32: a narrow chunk item, causal; all 32
+// columns of the MFMA are rows, so the stream pays for the same arithmetic and only the merge at the end grows.
+// Narrow items are bound by the cache stream and by latency, not by the matrix pipe: 8 x 32 rows over 4096 keys of the 13B
+// shape 164 -> 118 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 21.2 us with the merge.  From 33 rows on every
+// form of this kernel that was built (two row blocks per wave, two sets of waves, two workgroups) measured level with or
+// behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
+template <int HD, bool KVF16, int ROWS>
 __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
   constexpr int NC = HD / 32;  // 32-row blocks of O^T
   constexpr int REC = 2 * 16 * HD;  // elements of one (page, head) record
-  __shared__ float lds_o[4][HAT_MAX_VERIFY_ROWS][HD];
-  __shared__ float lds_m[4][HAT_MAX_VERIFY_ROWS], lds_l[4][HAT_MAX_VERIFY_ROWS];
+  constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
+  // element (row, feature) of a wave's result: feature-major for 32 rows, where lanes are rows (padded: no bank conflicts)
+  constexpr int RSTR = NARROW ? 1 : HD, FSTR = NARROW ? ROWS + 1 : 1;
+  __shared__ __attribute__((aligned(16))) float lds_o[4][NARROW ? HD * (ROWS + 1) : ROWS * HD];
+  __shared__ float lds_m[4][ROWS], lds_l[4][ROWS];
 
   const HatAttnItem it = a.items[blockIdx.x];
   const int head = blockIdx.y;
   const SegInfo sg = seg_info(p, it);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, n = lane & 31;
+  const float scale_log2 = kLog2e / sqrtf((float)HD);
+
   const int qi = n < it.nq ? n : it.nq - 1;  // clamp idle columns onto a real row
   const int qrow = sg.tok0 + it.q0 + qi;
+  const int qpos = sg.start + it.q0 + qi;
   const uint32_t vis = ((qi < 4 ? it.vis_lo : it.vis_hi) >> (8 * (qi & 3))) & 0xffu;  // q0 = 0 for verify items
-  const float scale_log2 = kLog2e / sqrtf((float)HD);
 
   f16x8 qreg[NS];
 #pragma unroll
@@ -189,7 +200,8 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
     for (int r = 0; r < 16; ++r) o[c][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  int kv_end = it.kv_end < sg.kv_len ? it.kv_end : sg.kv_len;
+  const int need = NARROW ? sg.start + it.q0 + it.nq : sg.kv_len;   // keys beyond the last row's position are not read
+  const int kv_end = it.kv_end < need ? it.kv_end : need;
   const int pair0 = it.kv_begin >> 5, pair1 = (kv_end + 31) >> 5;
   const kv_t* pool = a.pool_layer + (size_t)head * a.n_pages * REC;  // this head's pages are contiguous
   const size_t page_stride = REC;
@@ -250,7 +262,10 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
       }
     }
     f16x8 p0, p1;
-    if (key0 + 31 >= sg.start) {
+    if (NARROW) {
+      if (key0 + 31 > sg.start + it.q0) softmax_step<NC, 1>(sacc, scale_log2, key0, half, qpos, m_run, l_run, o, p0, p1);
+      else softmax_step<NC, 0>(sacc, scale_log2, key0, half, 0, m_run, l_run, o, p0, p1);
+    } else if (key0 + 31 >= sg.start) {
       // keys start-32 .. start+31 as one 64-bit set: the cache below the segment is visible, the
       // segment's own rows as the query row's byte says, nothing beyond; the tile's 32 keys begin at
       // bit key0 - start + 32 (1..39 here, as start - 31 <= key0 <= start + 7), and this lane
@@ -274,15 +289,17 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) lds_o[wave][n][32 * c + 8 * (r >> 2) + 4 * half + (r & 3)] = o[c][r];
+      for (int r = 0; r < 16; ++r) lds_o[wave][n * RSTR + (32 * c + 8 * (r >> 2) + 4 * half + (r & 3)) * FSTR] = o[c][r];
     if (half == 0) {
       lds_m[wave][n] = m_run;
       lds_l[wave][n] = l_run;
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < it.nq * (HD / 4); idx += 256) {
-    const int q = idx / (HD / 4), e = (idx % (HD / 4)) * 4;
+  const int cells = (NARROW ? ROWS : it.nq) * (HD / 4);   // (row, 4 features) each
+  for (int idx = threadIdx.x; idx < cells; idx += 256) {
+    const int q = NARROW ? idx % ROWS : idx / (HD / 4), e = (NARROW ? idx / ROWS : idx % (HD / 4)) * 4;
+    if (q >= it.nq) continue;
     float M = fmaxf(fmaxf(lds_m[0][q], lds_m[1][q]), fmaxf(lds_m[2][q], lds_m[3][q]));
     const float Ms = (M == -INFINITY) ? 0.f : M;
     float L = 0.f;
@@ -291,24 +308,19 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
     for (int w = 0; w < 4; ++w) {
       const float f = exp2f(lds_m[w][q] - Ms);
       L += lds_l[w][q] * f;
-      const f32x4 v = *(const f32x4*)&lds_o[w][q][e];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) acc[x] += v[x] * f;
+      for (int x = 0; x < 4; ++x) acc[x] += lds_o[w][q * RSTR + (e + x) * FSTR] * f;
     }
-    if (it.part_row < 0) {
-      const float inv = 1.0f / L;
-      f16x4 ov;
+    // a partial result travels normalised by its own sum, in the activation type: the merge
+    // weighs it by that sum.  A key range that this row does not see at all has L = 0.
+    const float inv = (it.part_row < 0 || L > 0.f) ? 1.0f / L : 0.f;
+    f16x4 ov;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) ov[x] = to_act(acc[x] * inv);
+    for (int x = 0; x < 4; ++x) ov[x] = to_act(acc[x] * inv);
+    if (it.part_row < 0) {
       *(f16x4*)(a.outP + p32_index(sg.tok0 + it.q0 + q, head * HD + e, a.d)) = ov;
     } else {
-      // a partial result travels normalised by its own sum, in the activation type: the merge
-      // weighs it by that sum.  A key range that this row does not see at all has L = 0.
       const size_t pr = (size_t)(it.part_row + q) * a.H + head;
-      const float inv = L > 0.f ? 1.0f / L : 0.f;
-      f16x4 ov;
-#pragma unroll
-      for (int x = 0; x < 4; ++x) ov[x] = to_act(acc[x] * inv);
       *(f16x4*)(a.part_o + pr * HD + e) = ov;
       if (e == 0) a.part_ml[pr] = make_float2(M, L);
     }
@@ -753,26 +765,39 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
 
 }  // namespace
 
-hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
-  if (a.n_items <= 0) return hipSuccess;
+template <int ROWS>
+static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   dim3 grid(a.n_items, a.H);
-  if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-  else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-  else if (a.hd == 64 && a.kv_f16) attn_chunk_kernel<64, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-  else if (a.hd == 64) attn_chunk_kernel<64, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS><<<grid, 256, 0, st>>>(p, a);
+  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS><<<grid, 256, 0, st>>>(p, a);
+  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS><<<grid, 256, 0, st>>>(p, a);
+  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS><<<grid, 256, 0, st>>>(p, a);
   else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
+  const int wide = a.n_items - a.n_narrow;
+  if (wide > 0) {
+    dim3 grid(wide, a.H);
+    if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 64 && a.kv_f16) attn_chunk_kernel<64, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 64) attn_chunk_kernel<64, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else return hipErrorInvalidValue;
+  }
+  if (a.n_narrow > 0) {
+    HatAttn n = a;
+    n.items = a.items + wide;
+    n.n_items = a.n_narrow;
+    return launch_stream<HAT_NARROW_QROWS>(p, n, st);
+  }
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_verify(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  dim3 grid(a.n_items, a.H);
-  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 128) attn_verify_kernel<128, false><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 64) attn_verify_kernel<64, false><<<grid, 256, 0, st>>>(p, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  return launch_stream<HAT_MAX_VERIFY_ROWS>(p, a, st);
 }
 
 hipError_t hat_launch_attn_verify_probe(const HatPlanDev& p, const HatAttn& a, uint32_t* sink, hipStream_t st) {

@@ -13,6 +13,7 @@ constexpr int HAT_MAX_VERIFY_ROWS = 8;  // query rows of a verify work item
 // query rows of one chunk-attention workgroup: 8 waves x 32 rows (the 64-key K/V stage that a
 // workgroup loads and widens is shared by all of them)
 constexpr int HAT_CHUNK_QROWS = 256;
+constexpr int HAT_NARROW_QROWS = 32;   // chunk items of at most this many rows stream the cache like verify items
 
 // ---- GEMM: out[t, f] = sum_k X[t, k] * W[f, k], operands in P32 layout ------
 enum HatEpilogue {
@@ -156,6 +157,7 @@ struct HatAttn {
   float2* part_ml;           // [part rows][H] (running max in log2 units, sum)
   const HatAttnItem* items;
   int n_items;
+  int n_narrow;              // chunk items: the last n_narrow of them have at most HAT_NARROW_QROWS rows
   int H, hd, d;
   int n_pages;               // pool capacity (pages per head and layer)
 };
