@@ -325,7 +325,8 @@ hat_status_t hat_mid_debug_force_gemm(hat_mid_t* h, int32_t which, int32_t tile,
 /* The automatic choice for a GEMM of T rows: Nw = weight rows (padded to 256), Nout = logical
  * output features, K = inner dimension (multiple of 64), epilogue 0 = fp16 output, 1 = SwiGLU,
  * 2 = accumulate into the residual (the only one whose K may be split; part_rows = capacity of
- * the partial-sum buffer in rows, 0 = no buffer).  Host code only, no GPU work; for tests of the
+ * the partial-sum buffer in rows, 0 = no buffer).  *ksplit is 1 also where only the last token tiles of a
+ * large batch are split.  Host code only, no GPU work; for tests of the
  * planner.  Returns HAT_EINVAL on a null pointer. */
 hat_status_t hat_mid_debug_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t epilogue,
                                      int32_t part_rows, int32_t* tile, int32_t* ksplit);

@@ -809,7 +809,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   h->plan_ev_used[bi] = true;
 
   const int32_t* D = h->b.plan_dev;
-  HatPlanDev pd;
+  HatPlanDev pd{};
   pd.T = T; pd.S = S;
   pd.pos = D + o_pos; pd.kv_dst = D + o_dst; pd.tok_seg = D + o_tseg; pd.tok_off = D + o_toff;
   pd.seg_start = D + o_sstart; pd.seg_pt = D + o_spt; pd.page_tbl = D + o_pt;
@@ -821,35 +821,47 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   LAUNCH(h, st, HAT_K_GATHER, hat_launch_gather(pd, h->b.resid, s.d, c.io_dtype, st));
   if (!gather_norms) LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
 
-  int nparts = 0;  // split-K partial sums of the previous residual GEMM still to be folded in
-  auto run_gemm = [&](int id, HatGemm& g, int* ksplit_out) -> hat_status_t {
+  int nparts = 0;  // split-K partial sums of the previous residual GEMM still to be folded in,
+  int prow0 = 0;   // for the rows from this one on
+  auto run_gemm = [&](int id, HatGemm& g) -> hat_status_t {
     const int cls = id == HAT_K_GEMM_QKV ? 0 : id == HAT_K_GEMM_O ? 1 : id == HAT_K_GEMM_GATEUP ? 2 : 3;
     g.force_tile = h->force_tile[cls];
     g.force_ksplit = h->force_ksplit[cls];
     const HatGemmPlan gp = hat_gemm_plan(g);
-    if (ksplit_out) *ksplit_out = gp.ksplit;
+    if (g.epilogue == HAT_EPI_RESID) {
+      nparts = gp.ksplit > 1 ? gp.ksplit : 0;
+      int bt = 0;
+      if (gp.full > 0) hat_gemm_tile_info(gp.tile, nullptr, &bt, nullptr, nullptr, nullptr);
+      prow0 = gp.full * bt;
+    }
     LAUNCH(h, st, id, hat_launch_gemm(g, gp, st));
+    return HAT_OK;
+  };
+  // RMSNorm of all rows; rows from prow0 on first take in their partial sums
+  auto run_norm = [&](const float* gain, act_t* out) -> hat_status_t {
+    if (prow0 > 0) LAUNCH(h, st, HAT_K_RMSNORM, hat_launch_rmsnorm(h->b.resid, h->b.gemm_part, 0, gain, out, prow0, s.d, c.rms_eps, st));
+    LAUNCH(h, st, HAT_K_RMSNORM,
+           hat_launch_rmsnorm(h->b.resid + (size_t)prow0 * s.d, h->b.gemm_part, nparts, gain, out + p32_index(prow0, 0, s.d), T - prow0, s.d,
+                              c.rms_eps, st));
+    nparts = prow0 = 0;
     return HAT_OK;
   };
   for (int l = 0; l < s.L; ++l) {
     const LayerDev& ld = h->b.layers[l];
     kv_t* pool_l = h->pool + (size_t)l * h->layer_pool_elems;
-    if (l > 0 || !gather_norms)
-      LAUNCH(h, st, HAT_K_RMSNORM,
-             hat_launch_rmsnorm(h->b.resid, h->b.gemm_part, nparts, ld.g_attn, h->b.xn, T, s.d, c.rms_eps, st));
-    nparts = 0;
+    hat_status_t rc;
+    if ((l > 0 || !gather_norms) && (rc = run_norm(ld.g_attn, h->b.xn)) != HAT_OK) return rc;
     HatGemm g{};
     g.W = ld.wqkv; g.X = h->b.xn; g.K = s.d; g.T = T; g.Nw = s.Nqkv; g.Nout = 3 * s.d; g.outP = h->b.qkv;
     g.epilogue = HAT_EPI_QKV;
     g.qkv = HatQkvOut{h->b.table, pd.kv_dst, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16};
     g.force_tile = h->force_tile[0];
-    hat_status_t rc;
     const HatGemmPlan qp = hat_gemm_plan(g);
     if (qp.tile >= 0) {
       LAUNCH(h, st, HAT_K_GEMM_QKV, hat_launch_gemm(g, qp, st));
     } else {
       g.epilogue = HAT_EPI_P32;
-      if ((rc = run_gemm(HAT_K_GEMM_QKV, g, nullptr)) != HAT_OK) return rc;
+      if ((rc = run_gemm(HAT_K_GEMM_QKV, g)) != HAT_OK) return rc;
       LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
     }
     HatAttn a{};
@@ -872,23 +884,18 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     g.W = ld.wo; g.X = h->b.attn; g.K = s.d; g.T = T; g.Nw = s.No; g.Nout = s.d; g.resid = h->b.resid;
     g.part = h->b.gemm_part; g.part_rows = s.gemm_part_rows;
     g.epilogue = HAT_EPI_RESID;
-    int ks = 1;
-    if ((rc = run_gemm(HAT_K_GEMM_O, g, &ks)) != HAT_OK) return rc;
-    nparts = ks > 1 ? ks : 0;
-    LAUNCH(h, st, HAT_K_RMSNORM,
-           hat_launch_rmsnorm(h->b.resid, h->b.gemm_part, nparts, ld.g_ffn, h->b.xn2, T, s.d, c.rms_eps, st));
-    nparts = 0;
+    if ((rc = run_gemm(HAT_K_GEMM_O, g)) != HAT_OK || (rc = run_norm(ld.g_ffn, h->b.xn2)) != HAT_OK) return rc;
     g = HatGemm{};
     g.W = ld.wgu; g.X = h->b.xn2; g.K = s.d; g.T = T; g.Nw = s.Ngu; g.Nout = s.Fpad; g.outP = h->b.act;
     g.epilogue = HAT_EPI_SWIGLU;
-    if ((rc = run_gemm(HAT_K_GEMM_GATEUP, g, nullptr)) != HAT_OK) return rc;
+    if ((rc = run_gemm(HAT_K_GEMM_GATEUP, g)) != HAT_OK) return rc;
     g = HatGemm{};
     g.W = ld.wd; g.X = h->b.act; g.K = s.Fpad; g.T = T; g.Nw = s.Nd; g.Nout = s.d; g.resid = h->b.resid;
     g.part = h->b.gemm_part; g.part_rows = s.gemm_part_rows;
     g.epilogue = HAT_EPI_RESID;
-    if ((rc = run_gemm(HAT_K_GEMM_DOWN, g, &ks)) != HAT_OK) return rc;
-    nparts = ks > 1 ? ks : 0;
+    if ((rc = run_gemm(HAT_K_GEMM_DOWN, g)) != HAT_OK) return rc;
   }
+  pd.part_row0 = prow0;
   LAUNCH(h, st, HAT_K_SCATTER, hat_launch_scatter(pd, h->b.resid, h->b.gemm_part, nparts, s.d, c.io_dtype, st));
   HIP_TRY(h, hipEventRecord(h->ev_end, st));
   h->have_step = true;
@@ -1223,7 +1230,7 @@ hat_status_t hat_mid_debug_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_
   g.force_tile = -1;
   const HatGemmPlan p = hat_gemm_plan(g);
   *tile = p.tile;
-  *ksplit = p.ksplit;
+  *ksplit = p.full > 0 ? 1 : p.ksplit;   // a split of the last token tiles only is not reported
   return HAT_OK;
 }
 

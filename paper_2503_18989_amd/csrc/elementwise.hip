@@ -74,11 +74,12 @@ __global__ void scatter_kernel(HatPlanDev p, const float* __restrict__ resid, co
   const int s = p.tok_seg[t];
   const int row = t - p.tok_off[s];
   const float* src = resid + (size_t)t * d;
-  const size_t pstride = (size_t)p.T * d;
+  const size_t pstride = (size_t)(p.T - p.part_row0) * d;
+  if (t < p.part_row0) nparts = 0;
   for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) {
     f32x4 a = *(const f32x4*)(src + i);
     for (int q = 0; q < nparts; ++q) {
-      const f32x4 b = *(const f32x4*)(part + q * pstride + (size_t)t * d + i);
+      const f32x4 b = *(const f32x4*)(part + q * pstride + (size_t)(t - p.part_row0) * d + i);
 #pragma unroll
       for (int e = 0; e < 4; ++e) a[e] += b[e];
     }

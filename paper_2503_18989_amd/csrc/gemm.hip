@@ -72,7 +72,7 @@ struct Tile {
 };
 
 template <int BF, int BT, int WF, int WT, int BKT, int NSTAGE, int EPI>
-__global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit) {
+__global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
   using TL = Tile<BF, BT, WF, WT, BKT, NSTAGE>;
   constexpr int MI = TL::MI, NJ = TL::NJ, PF = TL::PF, PT = TL::PT, SLAB = TL::SLAB, CPS = TL::CPS;
   constexpr int LPW = TL::LPW, STAGE = TL::STAGE, KS = TL::KS;
@@ -87,10 +87,22 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   // workgroup -> tile.  Consecutive hardware ids go round-robin over the 8 XCDs;
   // give each XCD a contiguous run of tiles so that tiles sharing a weight panel
   // meet in one L2.
-  const int nT = (g.T + BT - 1) / BT;
   const int nF = (g.Nw + BF - 1) / BF;
+  int nT = (g.T + BT - 1) / BT;
+  int b = blockIdx.x, kz = blockIdx.z, tt0 = 0;
+  if (full > 0) {   // whole tiles first, then the split ones (one-dimensional grid)
+    if (b < full * nF) {
+      nT = full;
+      ksplit = 1;
+    } else {
+      b -= full * nF;
+      tt0 = full;
+      nT -= full;
+      kz = b / (nT * nF);
+      b -= kz * nT * nF;
+    }
+  }
   const int nblk = nT * nF;
-  int b = blockIdx.x;
   {
     const int per = nblk / 8, rem = nblk % 8;
     const int x = b % 8, i = b / 8;
@@ -107,13 +119,13 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
     const int gf = (nF - f0) < GF ? (nF - f0) : GF;
     const int r = b - grp * GF * nT;
     ft = f0 + r % gf;
-    tt = r / gf;
+    tt = tt0 + r / gf;
   }
   const int Tpanels = (g.T + 31) >> 5;
 
   const int KT = g.K / BKT;
-  const int kt0 = (int)((long)blockIdx.z * KT / ksplit);
-  const int kt1 = (int)((long)(blockIdx.z + 1) * KT / ksplit);
+  const int kt0 = (int)((long)kz * KT / ksplit);
+  const int kt1 = (int)((long)(kz + 1) * KT / ksplit);
   const int nkt = kt1 - kt0;
 
   // per-wave chunk sources (per-lane address); destinations are wave-uniform
@@ -279,7 +291,9 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
     } else {
       // fp32 result: added into the residual when K is not split, else stored as this
       // split's partial sum (the next consumer of the residual folds the partials in)
-      float* outb = (ksplit == 1) ? g.resid : g.part + (size_t)blockIdx.z * g.T * g.Nout;
+      const int row0 = tt0 * BT;   // first row of the partial sums
+      float* outb = (ksplit == 1) ? g.resid + (size_t)tok * g.Nout
+                                  : g.part + ((size_t)kz * (g.T - row0) + (tok - row0)) * g.Nout;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         const int fb = f_base + i * 32;
@@ -287,7 +301,7 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int f = fb + 8 * q + 4 * h;
-          float* p = outb + (size_t)tok * g.Nout + f;
+          float* p = outb + f;
           f32x4 v;
           if (ksplit == 1) {
             v = *(f32x4*)p;
@@ -581,9 +595,11 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
 #define HAT_TRY(id, bf, bt, wf, wt, bkt, ns, epi)                       \
   if (p.tile == id) {                                                   \
     using TL = Tile<bf, bt, wf, wt, bkt, ns>;                           \
-    dim3 grid(((g.T + bt - 1) / bt) * ((g.Nw + bf - 1) / bf), 1, p.ksplit); \
+    const int nT = (g.T + bt - 1) / bt, nF = (g.Nw + bf - 1) / bf;      \
+    dim3 grid(nT * nF, 1, p.ksplit);                                    \
+    if (p.full > 0) grid = dim3(p.full * nF + (nT - p.full) * nF * p.ksplit); \
     auto kern = gemm_kernel<bf, bt, wf, wt, bkt, ns, epi>;              \
-    kern<<<grid, dim3(wf * wt * 64), TL::LDS_BYTES, st>>>(g, p.ksplit); \
+    kern<<<grid, dim3(wf * wt * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
     return hipGetLastError();                                           \
   }
   HAT_FOR_TILES(HAT_TRY, EPI)
@@ -696,7 +712,7 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     while (best.ksplit > 1 && ((long)best.ksplit * g.T > g.part_rows || g.K / 64 / best.ksplit < 1)) --best.ksplit;
     return best;
   }
-  HatGemmPlan stream;
+  HatGemmPlan stream{};
   if (stream_plan(g, &stream)) return stream;
   // Two regimes, each with constants fitted to tile sweeps on MI355X (7B shapes).
   // Up to kSmallT rows (T = 32 .. 384) the weight stream decides: a CU moves about 36 B/clk
@@ -751,7 +767,24 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
       const double bw = std::min(5.5e12, inflight / 1.2e-6);
       const double hbm_cyc = 2.0 * g.Nw * g.K / bw * 2.4e9 + 7000.0;
       const double cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                // tie-break below the HBM floor
-      if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; }
+      if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; best.full = 0; }
+    }
+    // A last round that leaves most CUs idle: the token tiles that fill whole rounds stay whole, the rest is split
+    // along K until its pieces fill about a round.  320 tiles on 256 CUs (4096 rows of the 13B shape) take 1.35 rounds
+    // instead of 2.  The matrix pipes draw the chip's power limit in a step of this size (clock 1.6 GHz in a
+    // full round), so the idle CUs were not all loss: 60 us of the 3050 us layer, O and down together.
+    if (!large || max_split == 1) continue;
+    const int whole = nT * nF / 256, full = whole * 256 / nF;
+    if (full < 1 || full >= nT) continue;
+    for (int ks = 2; ks <= max_split && KT / ks >= 4 && (long)ks * (g.T - full * q.bt) <= g.part_rows; ++ks) {
+      const double pieces = (double)(nT - full) * nF * ks - (256.0 * whole - (double)full * nF);   // idle CUs take some early
+      const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff), load_cyc = (q.bf + q.bt) * 64 * 2 / 28.1;
+      const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.073 * std::min(mfma_cyc, load_cyc);
+      const double part_rounds = std::ceil(pieces / 256.0);
+      double cyc = whole * ((KT + 2.0) * tile_cyc + 8938.0) + part_rounds * ((std::ceil((double)KT / ks) + 2.0) * tile_cyc + 8938.0);
+      cyc += full * q.bt * (double)g.Nout / 256.0 * 8.0 / 6.2 + (g.T - full * q.bt) * (double)g.Nout / 256.0 * 8.0 * ks / 7.15;
+      cyc += 12000.0;   // the norm that follows takes two launches
+      if (cyc * 1.001 < best_cost) { best_cost = cyc * 1.001; best.tile = c; best.ksplit = ks; best.full = full; }
     }
   }
   return best;

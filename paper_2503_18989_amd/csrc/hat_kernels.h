@@ -51,6 +51,8 @@ struct HatGemm {
 struct HatGemmPlan {
   int tile;    // index into the tile table of gemm.hip; -1: HAT_EPI_QKV is not the way for this batch
   int ksplit;  // 1 = K not split
+  int full;    // EPI_RESID, ksplit > 1: the first `full` token tiles are whole (added to resid), the rest is split; the
+               // partial sums then hold the rows from full * (token rows of the tile) on.  0: every tile is split
 };
 HatGemmPlan hat_gemm_plan(const HatGemm& g);
 hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t st);
@@ -102,6 +104,7 @@ struct HatPlanDev {
   const uint64_t* out_ptr;  // [S] hidden_out
   const HatAppendItem* append;  // pages written by this step
   int n_append;
+  int part_row0;            // first row that hat_launch_scatter finds in the partial sums
   HatFirstNorm first;       // used by hat_launch_gather, and only where hat_gather_norms(T) says so
 };
 // batches whose gather launch also fills the rotary table and applies the first RMSNorm (one launch instead of three: the
