@@ -90,7 +90,7 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   const int nF = (g.Nw + BF - 1) / BF;
   int nT = (g.T + BT - 1) / BT;
   int b = blockIdx.x, kz = blockIdx.z, tt0 = 0;
-  if (full > 0) {   // whole tiles first, then the split ones (one-dimensional grid)
+  if (EPI == HAT_EPI_RESID && full > 0) {   // whole tiles first, then the split ones (one-dimensional grid)
     if (b < full * nF) {
       nT = full;
       ksplit = 1;
