@@ -723,16 +723,28 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // Items of at most HAT_NARROW_QROWS rows are bound by the cache stream: key ranges of about equal size instead, for
     // three eighths of verify_target workgroups (8 x 32 rows over 4096 keys: 118 us and 7 us of merging with 768 workgroups
     // wanted, 130 and 9 with 2048).
-    double total_cost = 0;
+    // Next to larger items that is a second launch (10 us a layer at worst): only where a narrow item would be the
+    // long one of the common launch, which does not split it (1024 keys: 16 stages of 2.7 us).
+    double total_cost = 0, narrow_cost = 0;
     long narrow_keys = 0;
+    int narrow_longest = 0;
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
       for (int q0 = 0; q0 < segs[i].n; q0 += HAT_CHUNK_QROWS) {
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
-        if (nq <= HAT_NARROW_QROWS) narrow_keys += segs[i].start_pos + q0 + nq;
-        else total_cost += (double)nq * (segs[i].start_pos + q0 + 0.5 * nq);
+        const int need = segs[i].start_pos + q0 + nq;
+        const double cost = (double)nq * (need - 0.5 * nq);
+        if (nq > HAT_NARROW_QROWS) {
+          total_cost += cost;
+        } else {
+          narrow_cost += cost;
+          narrow_keys += need;
+          narrow_longest = std::max(narrow_longest, need);
+        }
       }
     }
+    const bool stream_narrow = total_cost == 0 || narrow_longest >= 1024;
+    if (!stream_narrow) total_cost += narrow_cost;
     if (total_cost > 0 || narrow_keys > 0) {
       const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
       const double slots = std::max(1, s.attn_target / s.H);
@@ -743,7 +755,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
           const int need = segs[i].start_pos + q0 + nq;
           const double cost = (double)nq * (need - 0.5 * nq);
-          const bool narrow = nq <= HAT_NARROW_QROWS;
+          const bool narrow = stream_narrow && nq <= HAT_NARROW_QROWS;
           int ns = narrow ? (int)((need + narrow_step - 1) / narrow_step) : (int)std::ceil(cost / cost_cap);
           ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), narrow ? 32 : 16));
           if ((int)citems.size() + ns > s.chunk_items_cap - 1 || part_row + ns * nq > s.part_rows_cap ||
@@ -772,7 +784,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     };
     std::stable_sort(citems.begin(), citems.end(), by_cost);
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
-    const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [](const HatAttnItem& a) { return a.nq > HAT_NARROW_QROWS; });
+    const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [&](const HatAttnItem& a) { return !stream_narrow || a.nq > HAT_NARROW_QROWS; });
     sp->n_narrow = (int)(citems.end() - narrow0);
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_vi = take(12 * vitems.size(), 4), o_mi = take(8 * mitems.size(), 8);
@@ -816,8 +828,9 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   pd.in_ptr = (const uint64_t*)(D + o_in); pd.out_ptr = (const uint64_t*)(D + o_out);
   pd.append = (const HatAppendItem*)(D + o_app); pd.n_append = n_append;
 
-  pd.first = HatFirstNorm{h->b.inv_freq, h->b.table, s.hd / 2, h->b.layers[0].g_attn, h->b.xn, c.rms_eps};
-  const bool gather_norms = hat_gather_norms(T);   // the gather launch fills the rotary table and applies the first norm too
+  // the gather launch fills the rotary table and applies the first norm too, unless each is to be timed by itself
+  const bool gather_norms = hat_gather_norms(T) && !h->profiling;
+  if (gather_norms) pd.first = HatFirstNorm{h->b.inv_freq, h->b.table, s.hd / 2, h->b.layers[0].g_attn, h->b.xn, c.rms_eps};
   LAUNCH(h, st, HAT_K_GATHER, hat_launch_gather(pd, h->b.resid, s.d, c.io_dtype, st));
   if (!gather_norms) LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
 

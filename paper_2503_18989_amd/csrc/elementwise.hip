@@ -525,7 +525,7 @@ inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / 
 }  // namespace
 
 hipError_t hat_launch_gather(const HatPlanDev& p, float* resid, int d, int io_dtype, hipStream_t st) {
-  if (!hat_gather_norms(p.T)) {
+  if (!p.first.xn) {
     gather_kernel<<<p.T, 256, 0, st>>>(p, resid, d, io_dtype);
     return hipGetLastError();
   }

@@ -105,7 +105,7 @@ struct HatPlanDev {
   const HatAppendItem* append;  // pages written by this step
   int n_append;
   int part_row0;            // first row that hat_launch_scatter finds in the partial sums
-  HatFirstNorm first;       // used by hat_launch_gather, and only where hat_gather_norms(T) says so
+  HatFirstNorm first;       // first.xn null: hat_launch_gather only gathers
 };
 // batches whose gather launch also fills the rotary table and applies the first RMSNorm (one launch instead of three: the
 // 16-row step of the tiny model is a chain of nine or ten launches of 3 .. 7 us).  From 1024 rows on the norm
