@@ -135,7 +135,9 @@ __device__ __forceinline__ void fold_partials(f32x4& a, f32x4& b, const float* _
 }
 
 // ---------------------------------------------------------------- RMSNorm
-// y = x * rsqrt(mean(x^2) + eps) * gain of one row that the 256 threads of a workgroup hold in registers
+// y = x * rsqrt(mean(x^2) + eps) * gain of one row that the 256 threads of a workgroup hold in registers.
+// The squares are summed with explicit fused multiply-adds: left to the compiler, one kernel rounds a^2 first and another
+// b^2, and a row's last bits would depend on which launch normalised it.
 template <int MAXV>
 __device__ __forceinline__ void norm_row(const f32x4 (&va)[MAXV], const f32x4 (&vb)[MAXV], int t, const float* __restrict__ gain,
                                          act_t* __restrict__ outP, int d, float eps) {
@@ -144,7 +146,7 @@ __device__ __forceinline__ void norm_row(const f32x4 (&va)[MAXV], const f32x4 (&
   for (int v = 0; v < MAXV; ++v)
     if ((v * 256 + (int)threadIdx.x) * 8 < d) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ss += va[v][e] * va[v][e] + vb[v][e] * vb[v][e];
+      for (int e = 0; e < 4; ++e) ss += fmaf(va[v][e], va[v][e], vb[v][e] * vb[v][e]);
     }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
