@@ -66,6 +66,7 @@ struct Shapes {
   int verify_target;      // workgroups a verify-attention launch should reach
   int chunk_items_cap, verify_items_cap, merge_cap;
   int part_rows_cap;
+  int part32_cap;         // fp32 partial rows (narrow chunk items); their numbers follow those of the part_rows_cap others
   int gemm_part_rows;     // rows of the split-K partial-sum buffer
   size_t plan_words;
 };
@@ -100,6 +101,8 @@ Shapes make_shapes(const hat_mid_config_t& c) {
   s.chunk_items_cap = 2 * per_head + s.Tcap / 128 + c.max_devices + 2;
   s.verify_items_cap = 2 * per_head + c.max_devices + 2;
   s.merge_cap = s.Tcap / 16 + s.Tcap / 128 + 2 * c.max_devices + 2;
+  // n narrow items wanted: key ranges of sum / n keys leave fewer than 2 n + 1 ranges in the items that have more than one
+  s.part32_cap = HAT_NARROW_QROWS * (2 * (per_head * 3 / 8) + 2);
   s.part_rows_cap = HAT_CHUNK_QROWS * (2 * per_head + 2) + HAT_MAX_VERIFY * s.verify_items_cap;
   s.gemm_part_rows = 4096;
   s.plan_words = (size_t)3 * s.Tcap + 8 * ((size_t)s.Tcap / 16 + 2 * (size_t)c.max_devices + 2) + 8 * (size_t)c.max_devices + 16 + (size_t)c.n_pages + c.max_devices +
@@ -128,6 +131,7 @@ struct Buffers {
   act_t *xn, *xn2, *qkv, *attn, *act;
   float2* table;
   act_t* part_o;
+  float* part_o32;
   float2* part_ml;
   float* gemm_part;
   int32_t* plan_dev;
@@ -157,7 +161,8 @@ size_t carve(const hat_mid_config_t& c, const Shapes& s, void* base, Buffers* ou
   b.act = cv.take<act_t>((size_t)s.Tcap * s.Fpad);
   b.table = cv.take<float2>((size_t)s.Tcap * (s.hd / 2));
   b.part_o = cv.take<act_t>((size_t)s.part_rows_cap * s.d);
-  b.part_ml = cv.take<float2>((size_t)s.part_rows_cap * s.H);
+  b.part_o32 = cv.take<float>((size_t)s.part32_cap * s.d);
+  b.part_ml = cv.take<float2>((size_t)(s.part_rows_cap + s.part32_cap) * s.H);
   b.gemm_part = cv.take<float>((size_t)s.gemm_part_rows * s.d);
   b.plan_dev = cv.take<int32_t>(s.plan_words);
   b.fixture_pages = cv.take<int32_t>((size_t)(c.max_pos + 15) / 16 + 2);
@@ -673,7 +678,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
   // ---- attention work lists
   {
     const int per_head = (s.verify_target + s.H - 1) / s.H;  // verify items wanted
-    int part_row = 0;
+    int part_row = 0, part_row32 = s.part_rows_cap;
     // rows of a split item are merged in groups of 16 (one workgroup per group and head)
     auto push_merge = [&](int row0, int nrows, int prow, int nsplit) {
       for (int g0 = 0; g0 < nrows; g0 += 16) {
@@ -758,7 +763,9 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           const bool narrow = stream_narrow && nq <= HAT_NARROW_QROWS;
           int ns = narrow ? (int)((need + narrow_step - 1) / narrow_step) : (int)std::ceil(cost / cost_cap);
           ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), narrow ? 32 : 16));
-          if ((int)citems.size() + ns > s.chunk_items_cap - 1 || part_row + ns * nq > s.part_rows_cap ||
+          int& prow = narrow ? part_row32 : part_row;
+          const int prow_end = narrow ? s.part_rows_cap + s.part32_cap : s.part_rows_cap;
+          if ((int)citems.size() + ns > s.chunk_items_cap - 1 || prow + ns * nq > prow_end ||
               (int)mitems.size() + 9 >= s.merge_cap)
             ns = 1;
           const int step = round_up((need + ns - 1) / ns, 64);
@@ -769,12 +776,12 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
             it.start = segs[i].start_pos; it.tok0 = P[o_toff + i]; it.kv_len = segs[i].start_pos + segs[i].n;
             it.pt_off = P[o_spt + i];
             it.kv_begin = k * step; it.kv_end = std::min(need, (k + 1) * step);
-            it.part_row = ns > 1 ? part_row + k * nq : -1;
+            it.part_row = ns > 1 ? prow + k * nq : -1;
             citems.push_back(it);
           }
           if (ns > 1) {
-            push_merge(P[o_toff + i] + q0, nq, part_row, ns);
-            part_row += ns * nq;
+            push_merge(P[o_toff + i] + q0, nq, prow, ns);
+            prow += ns * nq;
           }
         }
       }
@@ -878,7 +885,8 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
       LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
     }
     HatAttn a{};
-    a.qkv = h->b.qkv; a.pool_layer = pool_l; a.outP = h->b.attn; a.part_o = h->b.part_o; a.part_ml = h->b.part_ml;
+    a.qkv = h->b.qkv; a.pool_layer = pool_l; a.outP = h->b.attn; a.part_o = h->b.part_o; a.part_o32 = h->b.part_o32; a.part_ml = h->b.part_ml;
+    a.part32_row0 = s.part_rows_cap;
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
       a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;

@@ -311,8 +311,9 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] += lds_o[w][q * RSTR + (e + x) * FSTR] * f;
     }
-    // a partial result travels normalised by its own sum, in the activation type: the merge
-    // weighs it by that sum.  A key range that this row does not see at all has L = 0.
+    // a partial result travels normalised by its own sum, and the merge weighs it by that sum: in the
+    // activation type for a verify item; in fp32 for a narrow one, whose key ranges are cut for the stream's sake
+    // where larger items keep one accumulator.  A key range that this row does not see at all has L = 0.
     const float inv = (it.part_row < 0 || L > 0.f) ? 1.0f / L : 0.f;
     f16x4 ov;
 #pragma unroll
@@ -321,7 +322,8 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
       *(f16x4*)(a.outP + p32_index(sg.tok0 + it.q0 + q, head * HD + e, a.d)) = ov;
     } else {
       const size_t pr = (size_t)(it.part_row + q) * a.H + head;
-      *(f16x4*)(a.part_o + pr * HD + e) = ov;
+      if constexpr (NARROW) *(f32x4*)(a.part_o32 + (pr - (size_t)a.part32_row0 * a.H) * HD + e) = acc * inv;
+      else *(f16x4*)(a.part_o + pr * HD + e) = ov;
       if (e == 0) a.part_ml[pr] = make_float2(M, L);
     }
   }
@@ -715,10 +717,9 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
 
 // ------------------------------------------------------------------ merge
 // one workgroup per (group of <= 16 rows, head); one thread per (row, 8 features)
-template <int HD>
-__global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMergeItem* __restrict__ items) {
-  const HatMergeItem it = items[blockIdx.x];
-  const int head = blockIdx.y;
+template <int HD, bool F32>
+__device__ __forceinline__ void merge_rows(const HatAttn& a, const HatMergeItem& it, int head) {
+  const size_t base32 = (size_t)a.part32_row0 * a.H;
   for (int idx = threadIdx.x; idx < it.nrows * (HD / 8); idx += 256) {
     const int r = idx / (HD / 8), e = (idx % (HD / 8)) * 8;
     // both passes take the key ranges four at a time, loads first: a loop that loads one range per
@@ -739,12 +740,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
     for (int s0 = 0; s0 < it.nsplit; s0 += 4) {
       float2 ml[4];
       f16x8 v[4];
+      f32x4 lo[4], hi[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (s0 + u < it.nsplit) {
           const size_t pr = pr0 + (s0 + u) * prs;
           ml[u] = a.part_ml[pr];
-          v[u] = *(const f16x8*)(a.part_o + pr * HD + e);
+          if constexpr (F32) {
+            const float* src = a.part_o32 + (pr - base32) * HD + e;
+            lo[u] = *(const f32x4*)src;
+            hi[u] = *(const f32x4*)(src + 4);
+          } else {
+            v[u] = *(const f16x8*)(a.part_o + pr * HD + e);
+          }
         }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -752,7 +760,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
           const float f = ml[u].y * exp2f(ml[u].x - M);   // weight of this key range: its sum, on the common scale
           L += f;
 #pragma unroll
-          for (int x = 0; x < 8; ++x) acc[x] += (float)v[u][x] * f;
+          for (int x = 0; x < 8; ++x) acc[x] += (F32 ? (x < 4 ? lo[u][x & 3] : hi[u][x & 3]) : (float)v[u][x]) * f;
         }
     }
     const float inv = 1.0f / L;
@@ -761,6 +769,12 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
     for (int x = 0; x < 8; ++x) ov[x] = to_act(acc[x] * inv);
     *(f16x8*)(a.outP + p32_index(it.row0 + r, head * HD + e, a.d)) = ov;
   }
+}
+template <int HD>
+__global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMergeItem* __restrict__ items) {
+  const HatMergeItem it = items[blockIdx.x];
+  if (it.part_row >= a.part32_row0) merge_rows<HD, true>(a, it, blockIdx.y);
+  else merge_rows<HD, false>(a, it, blockIdx.y);
 }
 
 }  // namespace

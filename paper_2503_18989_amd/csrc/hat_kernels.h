@@ -146,7 +146,7 @@ struct HatAttnItem {
 struct HatMergeItem {
   int32_t row0;      // first batch row of this group
   int32_t nrows;     // rows in the group (<= 16)
-  int32_t part_row;  // partial row of split 0 for row0; split i is at part_row + i*stride
+  int32_t part_row;  // partial row of split 0 for row0 (fp32 rows from HatAttn::part32_row0 on); split i is at part_row + i*stride
   int32_t nsplit;
   int32_t stride;    // partial rows between consecutive splits (= rows of the attention item)
   int32_t pad0, pad1, pad2;
@@ -157,6 +157,8 @@ struct HatAttn {
   int kv_f16;                // cache elements are fp16 (else bf16, widened to fp16 on their way to the MFMA)
   act_t* outP;               // P32 [., d]
   act_t* part_o;             // [part rows][H][hd] partial outputs, each normalised by its own sum
+  float* part_o32;           // the same of the partial rows numbered from part32_row0 on, in fp32: narrow chunk items
+  int part32_row0;
   float2* part_ml;           // [part rows][H] (running max in log2 units, sum)
   const HatAttnItem* items;
   int n_items;

@@ -226,3 +226,31 @@ def test_plan_capacity_failure_undoes_the_page_movements():
     for d in range(4):
         assert a.kv_query(d) == b.kv_query(d) == pm.query(d)
     a.close(); b.close()
+
+
+@pytest.mark.parametrize("case", ["equal", "skewed", "one", "many short", "with a wide one"])
+def test_partial_rows_of_narrow_chunks_fit_their_own_buffer(case):
+    # chunk items of at most 32 rows are cut into key ranges of about equal size whose fp32 partial rows have a buffer
+    # sized for the ranges wanted: no mix of cache lengths may run out of it (an item would then stay whole)
+    rng = np.random.default_rng(5)
+    lens = {"equal": [4096] * 20, "skewed": [6000] * 3 + [300] * 17, "one": [5900], "many short": list(rng.integers(257, 700, 24)),
+            "with a wide one": [3000, 1024, 5000]}[case]
+    rows = [int(r) for r in rng.integers(1, 33, len(lens))]
+    lib, pm = both(sum(int(n) // 16 + 50 for n in lens), max_devices=24, max_step_tokens=8192, max_pos=6500)
+    for d, n in enumerate(lens):
+        lib.plan([(d, hi.CHUNK, 0, int(n))])
+    segs = [(d, hi.CHUNK, int(n), r) for d, (n, r) in enumerate(zip(lens, rows))]
+    if case == "with a wide one":
+        segs[1] = (1, hi.CHUNK, 1024, 300)          # items of 256 and 44 rows
+    plan = lib.plan(segs)
+    part_rows = []
+    check_items(plan, segs, part_rows)
+    disjoint(part_rows)
+    narrow = [it for it in plan["chunk_items"] if it["nq"] <= 32]
+    wanted = -(-2048 // SHAPE["n_heads"]) * 3 // 8
+    keys = sum(n + r for d, _, n, r in segs if r <= 32)
+    step = max(256, -(-(keys // wanted) // 128) * 128)
+    assert max(it["kv_end"] - it["kv_begin"] for it in narrow) <= max(step + 64, 511)
+    first_narrow = min([it["part_row"] for it in narrow if it["part_row"] >= 0], default=None)
+    assert first_narrow is None or all(it["part_row"] < first_narrow for it in plan["chunk_items"] if it["nq"] > 32)
+    lib.close()
