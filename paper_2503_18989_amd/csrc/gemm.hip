@@ -325,6 +325,12 @@ __device__ __forceinline__ void store_qkv(const HatGemm& g, int tok, int panel, 
   const int ppd = o.hd >> 5;                 // panels per head
   const int head3 = panel / ppd, which = head3 / o.H, head = head3 - which * o.H;
   const int f = (panel % ppd) * 32 + i0, half = o.hd >> 1;   // feature within the head, below half
+  // q, k and v saturate at the fp16 range before anything else happens to them, as they do on their way through qkv
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    lo[e] = __builtin_amdgcn_fmed3f(lo[e], -65504.f, 65504.f);
+    hi[e] = __builtin_amdgcn_fmed3f(hi[e], -65504.f, 65504.f);
+  }
   if (which < 2) {
     const f32x4 c01 = *(const f32x4*)(o.table + (size_t)tok * half + f), c23 = *(const f32x4*)(o.table + (size_t)tok * half + f + 2);
     const float c[4] = {c01[0], c01[2], c23[0], c23[2]}, s[4] = {c01[1], c01[3], c23[1], c23[3]};

@@ -30,3 +30,26 @@ def test_streaming_tiles_forced_and_planned(cfg, T):
         e, ea = rel_err(out, ref), added_err(out, ref, x)
         assert e <= TOL and ea <= TOL, "tile %d ksplit %d: %.3e, vs added %.3e" % (tile, ks, e, ea)
     p.close()
+
+
+@pytest.mark.parametrize("kv", ["bf16", "f16"])
+@pytest.mark.parametrize("cfg", CFGS, ids=["k320", "k4096"])
+def test_rows_beyond_the_fp16_range_saturate_as_in_larger_batches(cfg, kv):
+    # q, k and v beyond +-65504 are clamped there before anything else happens to them, whether the product that makes them
+    # also rotates and appends (up to 96 rows) or not (97 rows).  Both round what they clamp: to fp16 once more in the
+    # larger batch (2^-11 of 65504 an element, sqrt(2) times that after the rotation), to the cache type (2^-9 for bf16).
+    import torch
+    from gpu_util import dev_weights
+    from paper_2503_18989_amd import HatMid, Segment
+    w = hi.layer_weights(cfg, 0, 9)
+    w = {k: v * np.float32(2.0 ** 20) if k in ("wq", "wk", "wv") else v for k, v in w.items()}
+    x = torch.from_numpy(hi.hidden_rows(97, cfg["d_model"], 9, 0, 0)).cuda()
+    rows = {}
+    for T in (97, 1, 32, 64, 96):
+        m = HatMid(cfg, [dev_weights(w)], n_pages=8, max_devices=1, max_step_tokens=128, max_pos=128, io_dtype="f32", kv_dtype=kv)
+        m.forward([Segment(0, hi.CHUNK, 0, x[:T])])
+        rows[T] = [to_np(m.debug_dump("q", T))] + [to_np(t).reshape(T, -1) for t in m.kv_export(0, 0, 0, T)]
+        m.close()
+        assert np.max(np.abs(rows[97][2])) == 65536, "the inputs were meant to exceed the range (65504 is 65536 in bf16)"
+        for name, got, ref in zip("qkv", rows[T], rows[97]):
+            assert np.max(np.abs(got - ref[:T])) <= 2.0 ** -7 * 65536, (name, T)
