@@ -320,11 +320,14 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
  * (which: 0 = QKV, 1 = O, 2 = gate/up, 3 = down; tile: index into the library's
  * tile table, -1 = automatic choice; ksplit: 1 = none, only honoured where the
  * result is accumulated).  For sweeps of launch shapes; results do not change
- * beyond fp32 summation order. */
+ * beyond fp32 summation order, and for QKV by whether k and v are rounded to fp16 on their way to the cache type: the
+ * streaming tiles (the last four) rotate and append by themselves.  A streaming tile that is not built for a class (tile
+ * 27 for gate/up, 25 and 27 for O and down) leaves its choice automatic. */
 hat_status_t hat_mid_debug_force_gemm(hat_mid_t* h, int32_t which, int32_t tile, int32_t ksplit);
 
 /* The automatic choice for a GEMM of T rows: Nw = weight rows (padded to 256), Nout = logical
- * output features, K = inner dimension (multiple of 64), epilogue 0 = fp16 output, 1 = SwiGLU,
+ * output features, K = inner dimension (multiple of 64), epilogue 0 = fp16 output, 1 = SwiGLU, 3 = QKV with rotary
+ * embedding and append (*tile -1: not for this batch, which takes epilogue 0 and a launch for the rest),
  * 2 = accumulate into the residual (the only one whose K may be split; part_rows = capacity of
  * the partial-sum buffer in rows, 0 = no buffer).  *ksplit is 1 also where only the last token tiles of a
  * large batch are split.  Host code only, no GPU work; for tests of the

@@ -510,15 +510,10 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
           float* p = (ksplit == 1 ? g.resid : g.part + (size_t)blockIdx.z * g.T * g.Nout) + (size_t)tok * g.Nout + f;
           *(f32x4*)p = ksplit == 1 ? *(const f32x4*)p + v : v;
         } else {
+          const f32x4 up = total(u, q + 2);
           f16x4 o;
-          if constexpr (EPI == HAT_EPI_SWIGLU) {
-            const f32x4 up = total(u, q + 2);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = to_act(silu_f(v[e]) * up[e]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = to_act(v[e]);
-          }
+          for (int e = 0; e < 4; ++e) o[e] = to_act(silu_f(v[e]) * up[e]);
           *(f16x4*)(g.outP + p32_index(tok, f, g.Nout)) = o;
         }
       }
@@ -570,6 +565,10 @@ constexpr int kNumLdsTiles = 24;
   X(25, 2, 2, EPI)             \
   X(26, 2, 3, EPI)             \
   X(27, 2, 1, EPI)
+// Which of them exist for an epilogue: those that stream_plan gives it.
+constexpr bool stream_built(int id, int epi) {
+  return epi == HAT_EPI_QKV ? id >= 24 && id <= 27 : epi == HAT_EPI_SWIGLU ? id >= 24 && id <= 26 : epi == HAT_EPI_RESID ? id == 24 || id == 26 : false;
+}
 constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26, kStream64x32 = 27;
 constexpr int kNumTiles = 28;
 
@@ -608,28 +607,22 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
     kern<<<grid, dim3(wf * wt * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
     return hipGetLastError();                                           \
   }
-  HAT_FOR_TILES(HAT_TRY, EPI)
+  if constexpr (EPI != HAT_EPI_QKV) {
+    HAT_FOR_TILES(HAT_TRY, EPI)
+  }
 #undef HAT_TRY
 #define HAT_TRY(id, np, nt, epi)                                                     \
-  if (p.tile == id) {                                                                \
-    dim3 grid(((g.T + 32 * (nt) - 1) / (32 * (nt))) * (g.Nw / (32 * (np))), 1, p.ksplit); \
-    gemm_stream_kernel<np, nt, epi><<<grid, dim3(512), 0, st>>>(g, p.ksplit);        \
-    return hipGetLastError();                                                        \
+  if constexpr (stream_built(id, epi)) {                                             \
+    if (p.tile == id) {                                                              \
+      const int nF = (epi == HAT_EPI_QKV ? g.Nout : g.Nw) / (32 * (np));             \
+      dim3 grid(((g.T + 32 * (nt) - 1) / (32 * (nt))) * nF, 1, p.ksplit);            \
+      gemm_stream_kernel<np, nt, epi><<<grid, dim3(512), 0, st>>>(g, p.ksplit);      \
+      return hipGetLastError();                                                      \
+    }                                                                                \
   }
   HAT_FOR_STREAM(HAT_TRY, EPI)
 #undef HAT_TRY
   return hipErrorInvalidValue;
-}
-
-// the QKV product with rotary embedding and append: streaming tiles only
-hipError_t launch_qkv(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
-  const int nF = g.Nout / 64;
-  if (p.tile == kStream32) gemm_stream_kernel<1, 1, HAT_EPI_QKV><<<(g.T + 31) / 32 * nF * 2, 512, 0, st>>>(g, 1);
-  else if (p.tile == kStream64x32) gemm_stream_kernel<2, 1, HAT_EPI_QKV><<<(g.T + 31) / 32 * nF, 512, 0, st>>>(g, 1);
-  else if (p.tile == kStream64) gemm_stream_kernel<2, 2, HAT_EPI_QKV><<<(g.T + 63) / 64 * nF, 512, 0, st>>>(g, 1);
-  else if (p.tile == kStream96) gemm_stream_kernel<2, 3, HAT_EPI_QKV><<<(g.T + 95) / 96 * nF, 512, 0, st>>>(g, 1);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
 }
 
 template <int EPI>
@@ -679,7 +672,7 @@ hipError_t hat_gemm_init() {
 //    With the 160 panels of the 13B shape the CUs are not filled: up to 16 rows still 23.9 -> 20.4 with the norm, at
 //    32 rows 24.2 -> 25.8; at 33 .. 64 rows down loses more (22.9 -> 25.4) than the norm gains.
 static bool stream_plan(const HatGemm& g, HatGemmPlan* p) {
-  if (g.T > 96) return false;
+  if (g.T > 96 || g.epilogue == HAT_EPI_P32) return false;
   p->ksplit = 1;
   if (g.epilogue != HAT_EPI_RESID) {
     if (g.T <= 32) {
@@ -704,14 +697,18 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // the result is accumulated in fp32) adds the traffic of its partial sums.
   HatGemmPlan best{0, 1};
   if (g.epilogue == HAT_EPI_QKV) {
-    // wherever the plain product would stream: the epilogue costs less than the rotary and append kernel it replaces (5 us).
+    // wherever the product streams: the epilogue costs less than the rotary and append kernel it replaces (5 us).
     // 64-feature tiles from 17 rows on: 24.4 against 27.0 us at 32 rows of the 7B shape (half the reads of X and
     // whole panels of W), but 22.3 against 21.0 at 5 rows (192 workgroups instead of 384).
-    if (g.force_tile >= 0 || !stream_plan(g, &best)) best.tile = -1;
+    if (g.force_tile >= 0) {
+      best.tile = stream_built(g.force_tile, HAT_EPI_QKV) ? g.force_tile : -1;
+      return best;
+    }
+    if (!stream_plan(g, &best)) best.tile = -1;
     if (best.tile == kStream32 && g.T > 16) best.tile = kStream64x32;
     return best;
   }
-  if (g.force_tile >= 0 && g.force_tile < kNumTiles) {
+  if (g.force_tile >= 0 && (g.force_tile < kNumLdsTiles || stream_built(g.force_tile, g.epilogue))) {
     best.tile = g.force_tile;
     best.ksplit = g.force_ksplit > 0 ? g.force_ksplit : 1;
     if (g.epilogue != HAT_EPI_RESID || !g.part) best.ksplit = 1;
@@ -804,7 +801,7 @@ hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t s
     case HAT_EPI_P32: return launch_epi<HAT_EPI_P32>(g, p, st);
     case HAT_EPI_SWIGLU: return launch_epi<HAT_EPI_SWIGLU>(g, p, st);
     case HAT_EPI_RESID: return launch_epi<HAT_EPI_RESID>(g, p, st);
-    case HAT_EPI_QKV: return launch_qkv(g, p, st);
+    case HAT_EPI_QKV: return launch_epi<HAT_EPI_QKV>(g, p, st);
   }
   return hipErrorInvalidValue;
 }

@@ -53,3 +53,40 @@ def test_rows_beyond_the_fp16_range_saturate_as_in_larger_batches(cfg, kv):
         assert np.max(np.abs(rows[97][2])) == 65536, "the inputs were meant to exceed the range (65504 is 65536 in bf16)"
         for name, got, ref in zip("qkv", rows[T], rows[97]):
             assert np.max(np.abs(got - ref[:T])) <= 2.0 ** -7 * 65536, (name, T)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "f16"])
+@pytest.mark.parametrize("cfg", CFGS, ids=["hd64", "hd128"])
+@pytest.mark.parametrize("tile", STREAM_TILES)
+def test_rotation_and_append_inside_the_product_equal_the_separate_launch(cfg, kv, tile):
+    # every streaming tile, over ragged segments that begin and end inside pages and cross token tiles: queries and cache
+    # rows against those of an LDS tile with its own rotary launch (to one rounding: the fp16 one on the way, 2^-12 of a value,
+    # moves an element by at most one step of its type, the exported bf16 by 2^-7 of its binade's lower end); rows of the
+    # pages that are not new stay bit for bit
+    import torch
+    from gpu_util import dev_weights
+    from paper_2503_18989_amd import HatMid, Segment
+    H, hd, starts, rows = cfg["n_heads"], cfg["head_dim"], [0, 3, 40, 17], [1, 30, 14, 53]
+    w = dev_weights(hi.layer_weights(cfg, 0, 4))
+    gen = torch.Generator(device="cuda").manual_seed(tile)
+    old = [torch.randn((96, H, hd), device="cuda", generator=gen).bfloat16() for _ in range(2)]
+    xs = [torch.from_numpy(hi.hidden_rows(n, cfg["d_model"], 4, 0, i)).cuda() for i, n in enumerate(rows)]
+    got = {}
+    for forced in (1, tile):
+        m = HatMid(cfg, [w], n_pages=40, max_devices=4, max_step_tokens=128, max_pos=128, io_dtype="f32", kv_dtype=kv)
+        for dev in range(4):
+            m.kv_import(dev, 0, 0, *old)
+        kept = m.kv_export(0, 0, 0, 96)       # (an fp16 cache rounds the smallest of the imported values)
+        m.force_gemm(0, forced, 1)
+        m.set_profiling(True)
+        m.forward([Segment(i, hi.CHUNK, s, x) for i, (s, x) in enumerate(zip(starts, xs))])
+        torch.cuda.synchronize()
+        assert m.kernel_times()["rope_append"][1] == (2 if forced == 1 else 1)     # the rotary table, and the launch per layer
+        got[forced] = [to_np(m.debug_dump("q", sum(rows)))]
+        for dev, (s, n) in enumerate(zip(starts, rows)):
+            k, v = m.kv_export(dev, 0, 0, s + n)
+            assert torch.equal(k[:s], kept[0][:s]) and torch.equal(v[:s], kept[1][:s])
+            got[forced] += [to_np(k[s:]), to_np(v[s:])]
+        m.close()
+    for a, b in zip(got[tile], got[1]):
+        assert np.max(np.abs(a - b)) <= 2.0 ** -7 * np.max(np.abs(b))
