@@ -314,6 +314,10 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
                                 int32_t* verify_items, int32_t* n_verify_items, int32_t* merge_items,
                                 int32_t* n_merge_items, int32_t cap_items);
 
+/* Of the chunk items of the last hat_mid_debug_plan, how many (the last ones of the array) stream the cache in the
+ * verify kernel's manner instead of staging it: items of at most 32 rows, unless they ride along with larger ones. */
+hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
+
 /* ---- tuning aid ------------------------------------------------------------------ */
 
 /* Forces the tile shape and K split of one GEMM class in later forwards
@@ -330,10 +334,15 @@ hat_status_t hat_mid_debug_force_gemm(hat_mid_t* h, int32_t which, int32_t tile,
  * embedding and append (*tile -1: not for this batch, which takes epilogue 0 and a launch for the rest),
  * 2 = accumulate into the residual (the only one whose K may be split; part_rows = capacity of
  * the partial-sum buffer in rows, 0 = no buffer).  *ksplit is 1 also where only the last token tiles of a
- * large batch are split.  Host code only, no GPU work; for tests of the
+ * large batch are split (hat_mid_debug_gemm_split tells).  Host code only, no GPU work; for tests of the
  * planner.  Returns HAT_EINVAL on a null pointer. */
 hat_status_t hat_mid_debug_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t epilogue,
                                      int32_t part_rows, int32_t* tile, int32_t* ksplit);
+
+/* How the automatic choice for an accumulating GEMM (epilogue 2) splits K: the rows below *first_row are whole, those from
+ * it on are split *ksplit ways and leave that many partial sums.  *first_row > 0 only where *ksplit > 1.  Host code only. */
+hat_status_t hat_mid_debug_gemm_split(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t part_rows, int32_t* tile,
+                                      int32_t* first_row, int32_t* ksplit);
 
 /* Workgroup counts that the attention work lists aim for (chunk kernel, verify kernel): long key
  * ranges are split over several workgroups until a launch has about that many.  0 keeps a value.

@@ -25,7 +25,8 @@ EXPORTED_SYMBOLS = [
     "hat_mid_destroy", "hat_mid_last_error", "hat_mid_kv_query", "hat_mid_kv_compact", "hat_mid_kv_import", "hat_mid_kv_export",
     "hat_mid_kv_export_static",
     "hat_mid_last_step_stats", "hat_mid_set_profiling", "hat_mid_kernel_times", "hat_mid_debug_dump", "hat_mid_debug_force_gemm",
-    "hat_mid_debug_gemm_tile_count", "hat_mid_debug_gemm_tile_info", "hat_mid_debug_gemm_plan", "hat_mid_debug_create_host_only", "hat_mid_debug_plan",
+    "hat_mid_debug_gemm_tile_count", "hat_mid_debug_gemm_tile_info", "hat_mid_debug_gemm_plan", "hat_mid_debug_gemm_split",
+    "hat_mid_debug_create_host_only", "hat_mid_debug_plan", "hat_mid_debug_plan_narrow",
     "hat_mid_debug_set_attn_targets", "hat_mid_debug_limit_plan", "hat_mid_debug_set_verify_probe", "hat_mid_debug_peak",
     "hat_sched_create", "hat_sched_destroy", "hat_sched_observe", "hat_sched_mu", "hat_sched_predict",
     "hat_sched_chunk_size", "hat_sched_parallel_draft_steps",
@@ -115,6 +116,8 @@ def load_library():
     lib.hat_mid_debug_gemm_tile_info.argtypes = [i32] + [C.POINTER(i32)] * 5
     lib.hat_mid_debug_gemm_plan.restype = i32
     lib.hat_mid_debug_gemm_plan.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
+    lib.hat_mid_debug_gemm_split.restype = i32
+    lib.hat_mid_debug_gemm_split.argtypes = [i32] * 5 + [C.POINTER(i32)] * 3
     lib.hat_mid_debug_create_host_only.restype = i32
     lib.hat_mid_debug_create_host_only.argtypes = [C.POINTER(Config), C.POINTER(vp)]
     lib.hat_mid_debug_set_attn_targets.restype = i32
@@ -128,6 +131,8 @@ def load_library():
     pi = C.POINTER(i32)
     lib.hat_mid_debug_plan.restype = i32
     lib.hat_mid_debug_plan.argtypes = [vp, C.POINTER(CSegment), i32, pi, pi, i32, pi, pi, pi, pi, pi, pi, i32]
+    lib.hat_mid_debug_plan_narrow.restype = i32
+    lib.hat_mid_debug_plan_narrow.argtypes = [vp, pi]
     f64 = C.c_double
     lib.hat_sched_create.restype = i32
     lib.hat_sched_create.argtypes = [C.POINTER(i32), i32, f64, C.POINTER(vp)]
@@ -406,6 +411,12 @@ class HatPlanner:
         merges = [dict(zip(self.MERGE_FIELDS, [mi[8 * k + j] for j in range(5)])) for k in range(nm.value)]
         return dict(pos=list(pos[:rows]), kv_dst=list(dst[:rows]), chunk_items=items(ci, nc.value),
                     verify_items=items(vi, nv.value), merge_items=merges)
+
+    def narrow_items(self):
+        """How many of the last plan's chunk items (the last ones) stream the cache (hat_mid_debug_plan_narrow)."""
+        n = C.c_int32()
+        self._check(self.lib.hat_mid_debug_plan_narrow(self._handle, C.byref(n)))
+        return n.value
 
     def release(self, device_id):
         self._check(self.lib.hat_mid_release(self._handle, device_id))

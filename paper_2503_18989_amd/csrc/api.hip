@@ -236,6 +236,7 @@ struct hat_mid {
 
   bool host_only = false;                  // built by hat_mid_debug_create_host_only: no GPU memory, no HIP calls
   std::vector<int32_t> host_plan;          // its plan words
+  int host_narrow = 0;                     // StepPlan::n_narrow of its last plan
   int force_tile[4] = {-1, -1, -1, -1};   // tuning overrides per GEMM class (qkv, o, gate/up, down)
   int force_ksplit[4] = {0, 0, 0, 0};
 
@@ -1174,6 +1175,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
   if (n_chunk_items) *n_chunk_items = 0;
   if (n_verify_items) *n_verify_items = 0;
   if (n_merge_items) *n_merge_items = 0;
+  h->host_narrow = 0;
   if (n_segs == 0) return HAT_OK;
   try {
     StepPlan sp;
@@ -1181,6 +1183,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     const hat_status_t rc = plan_step(h, segs, n_segs, h->host_plan.data(), &sp);
     if (rc != HAT_OK) return rc;
     undo_commit(h);
+    h->host_narrow = sp.n_narrow;
     if (sp.T > cap_rows || std::max(sp.n_citems, std::max(sp.n_vitems, sp.n_mitems)) > cap_items)
       return fail(h, HAT_EINVAL, "output arrays too small for %d rows / %d, %d, %d items (the step has been planned)", sp.T,
                   sp.n_citems, sp.n_vitems, sp.n_mitems);
@@ -1197,6 +1200,12 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     if (h->undo_on) undo_rollback(h);
     return fail(h, HAT_EHIP, "host allocation failed while planning the step");
   }
+}
+
+hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow) {
+  if (!h || !h->host_only || !n_narrow) return HAT_EINVAL;
+  *n_narrow = h->host_narrow;
+  return HAT_OK;
 }
 
 hat_status_t hat_mid_debug_force_gemm(hat_mid_t* h, int32_t which, int32_t tile, int32_t ksplit) {
@@ -1240,18 +1249,34 @@ hat_status_t hat_mid_debug_limit_plan(hat_mid_t* h, int64_t max_words) {
   return HAT_OK;
 }
 
-hat_status_t hat_mid_debug_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t epilogue,
-                                     int32_t part_rows, int32_t* tile, int32_t* ksplit) {
-  if (!tile || !ksplit) return HAT_EINVAL;
+static HatGemmPlan auto_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t epilogue, int32_t part_rows) {
   HatGemm g{};
   static float dummy;   // only its non-nullness is looked at
   g.T = T; g.Nw = Nw; g.Nout = Nout; g.K = K; g.epilogue = epilogue;
   g.part = part_rows > 0 ? &dummy : nullptr;
   g.part_rows = part_rows;
   g.force_tile = -1;
-  const HatGemmPlan p = hat_gemm_plan(g);
+  return hat_gemm_plan(g);
+}
+
+hat_status_t hat_mid_debug_gemm_plan(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t epilogue,
+                                     int32_t part_rows, int32_t* tile, int32_t* ksplit) {
+  if (!tile || !ksplit) return HAT_EINVAL;
+  const HatGemmPlan p = auto_gemm_plan(T, Nw, Nout, K, epilogue, part_rows);
   *tile = p.tile;
-  *ksplit = p.full > 0 ? 1 : p.ksplit;   // a split of the last token tiles only is not reported
+  *ksplit = p.full > 0 ? 1 : p.ksplit;   // of the whole product; hat_mid_debug_gemm_split reports a split tail
+  return HAT_OK;
+}
+
+hat_status_t hat_mid_debug_gemm_split(int32_t T, int32_t Nw, int32_t Nout, int32_t K, int32_t part_rows, int32_t* tile,
+                                      int32_t* first_row, int32_t* ksplit) {
+  if (!tile || !first_row || !ksplit) return HAT_EINVAL;
+  const HatGemmPlan p = auto_gemm_plan(T, Nw, Nout, K, HAT_EPI_RESID, part_rows);
+  int bt = 0;
+  hat_gemm_tile_info(p.tile, nullptr, &bt, nullptr, nullptr, nullptr);
+  *tile = p.tile;
+  *first_row = p.full * bt;
+  *ksplit = p.ksplit;
   return HAT_OK;
 }
 

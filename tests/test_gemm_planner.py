@@ -99,3 +99,40 @@ def test_small_batches_keep_power_of_two_token_tiles_and_large_ones_use_the_big_
         Nw, Nout, K, epi = SHAPES[name]
         tile, ks = plan(lib, 2200, Nw, Nout, K, epi, 4096)
         assert tile_info(lib, tile)[1][1] in (160, 192)
+
+
+WIDTHS = {   # d_model, d_ffn (padded to 64): the workloads' shapes, head-dim-64 shapes of middling width, the widest model accepted
+    "tiny": (256, 704), "1k": (1024, 2816), "2k": (2048, 5504), "3k": (3072, 8192), "7b": (4096, 11008), "13b": (5120, 13824), "8k": (8192, 28672),
+}
+
+
+@pytest.mark.parametrize("name", list(WIDTHS))
+def test_partial_sums_fit_their_buffer_at_every_batch_size(lib, name):
+    d, f = WIDTHS[name]
+    pad = lambda n: (n + 255) // 256 * 256
+    for K in (d, f):
+        for part_rows in (0, 100, 4096):
+            for T in list(range(1, 400)) + list(range(400, 8193, 7)) + [512, 1024, 2048, 4096, 8192]:
+                v = [C.c_int32(-7) for _ in range(3)]
+                assert lib.hat_mid_debug_gemm_split(T, pad(d), d, K, part_rows, *[C.byref(x) for x in v]) == 0
+                tile, first, ks = (x.value for x in v)
+                bt = tile_info(lib, tile)[1][1]
+                assert ks >= 1 and K // 64 // ks >= 1
+                assert 0 <= first < T and first % bt == 0 and (first == 0 or ks > 1)
+                assert ks == 1 or ks * (T - first) <= part_rows, (T, K, tile, first, ks)
+                assert (tile, 1 if first else ks) == plan(lib, T, pad(d), d, K, 2, part_rows)
+    assert lib.hat_mid_debug_gemm_split(256, 4096, 4096, 4096, 4096, None, None, None) == -1
+
+
+@pytest.mark.parametrize("T", [1, 16, 17, 32, 33, 64, 65, 96, 97, 256])
+def test_qkv_of_few_rows_takes_a_streaming_tile_built_for_it(lib, T):
+    for name in ("qkv7", "qkv13", "qkvT"):
+        Nw, Nout, K, _ = SHAPES[name]
+        tile, ks = plan(lib, T, Nw, Nout, K, 3, 4096)
+        assert ks == 1 and (24 <= tile < 28 if tile >= 0 else T > 16), (name, tile)
+        if tile >= 0:
+            bf, bt = tile_info(lib, tile)[1][:2]
+            assert bt >= min(T, 32) and Nout % bf == 0
+        plain, _ = plan(lib, T, Nw, Nout, K, 0, 4096)
+        assert plain < 24                             # the plain product has LDS tiles only
+    assert plan(lib, T, 12288, 12288, 4096, 3, 4096)[0] == (24 if T <= 16 else 27 if T <= 32 else 25 if T <= 64 else 26 if T <= 96 else -1)

@@ -246,11 +246,30 @@ def test_partial_rows_of_narrow_chunks_fit_their_own_buffer(case):
     part_rows = []
     check_items(plan, segs, part_rows)
     disjoint(part_rows)
-    narrow = [it for it in plan["chunk_items"] if it["nq"] <= 32]
+    n_wide = len(plan["chunk_items"]) - lib.narrow_items()
+    wide, narrow = plan["chunk_items"][:n_wide], plan["chunk_items"][n_wide:]
+    assert all(it["nq"] > 32 for it in wide) and narrow and all(it["nq"] <= 32 for it in narrow)
     wanted = -(-2048 // SHAPE["n_heads"]) * 3 // 8
     keys = sum(n + r for d, _, n, r in segs if r <= 32)
     step = max(256, -(-(keys // wanted) // 128) * 128)
     assert max(it["kv_end"] - it["kv_begin"] for it in narrow) <= max(step + 64, 511)
     first_narrow = min([it["part_row"] for it in narrow if it["part_row"] >= 0], default=None)
-    assert first_narrow is None or all(it["part_row"] < first_narrow for it in plan["chunk_items"] if it["nq"] > 32)
+    assert first_narrow is None or all(it["part_row"] < first_narrow for it in wide)
+    lib.close()
+
+
+def test_narrow_chunks_next_to_larger_ones_stream_only_when_long():
+    lib, _ = both(400, max_devices=4, max_step_tokens=4096, max_pos=4096)
+    for d in (0, 1):
+        lib.plan([(d, hi.CHUNK, 0, 2000)])
+    for start, n, want in [(991, 32, 0), (992, 32, 1), (1500, 33, 0), (1023, 1, 1), (1022, 1, 0)]:
+        plan = lib.plan([(0, hi.CHUNK, 300, 200), (1, hi.CHUNK, start, n)])
+        count = lib.narrow_items()
+        assert (count > 0) == bool(want), (start, n)
+        assert all((it["seg"] == 1) == (k >= len(plan["chunk_items"]) - count) for k, it in enumerate(plan["chunk_items"]) if count)
+        lib.plan([(1, hi.CHUNK, start, 2000 - start)])
+    lib.plan([(1, hi.CHUNK, 100, 32)])
+    assert lib.narrow_items() == 1                   # alone: always
+    lib.plan([(1, hi.VERIFY, 100, 8)])
+    assert lib.narrow_items() == 0
     lib.close()
