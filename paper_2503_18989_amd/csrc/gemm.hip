@@ -729,7 +729,8 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // prologue and drain, and the epilogue's traffic is not hidden: 14 B/clk per CU for the
   // fp16 stores, 6.2 for the read-modify-write of the fp32 residual, 7.2 for split-K partial
   // sums (written here, read back by the consumer of the residual).
-  double best_cost = 1e300;
+  double best_cost = 1e300, tail_cost = 1e300;
+  HatGemmPlan tail{0, 1};
   const int KT = g.K / 64;
   const bool large = g.T > kSmallT;
   for (int c = 0; c < kNumLdsTiles; ++c) {
@@ -770,16 +771,21 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
       const double bw = std::min(5.5e12, inflight / 1.2e-6);
       const double hbm_cyc = 2.0 * g.Nw * g.K / bw * 2.4e9 + 7000.0;
       const double cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                // tie-break below the HBM floor
-      if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; best.full = 0; }
+      if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; }
     }
     // A last round that leaves most CUs idle: the token tiles that fill whole rounds stay whole, the rest is split
     // along K until its pieces fill about a round.  320 tiles on 256 CUs (4096 rows of the 13B shape) take 1.35 rounds
     // instead of 2.  The matrix pipes draw the chip's power limit in a step of this size (clock 1.6 GHz in a
-    // full round), so the idle CUs were not all loss: 60 us of the 3050 us layer, O and down together.
+    // full round), so the idle CUs are not all loss.  Only where it is predicted to win by more than the cost model's rms error
+    // (4.5 %), and in at most 8 pieces.  Measured in whole layers, O and down each with and without it, at 100 batch sizes of six
+    // widths: where the rule takes it, 2756 -> 2655 us a layer (5120 x 13824, 4096 rows), 2292 -> 2213 (3213 rows), 2763 -> 2688 (6144 x
+    // 16384, 2785 rows), 4561 -> 4421 (8192 x 28672, 2260 rows), 8 us at the least for down, 0 to 20 for O; at predicted gains
+    // below it, or in 13 .. 16 pieces, 1 .. 9 us a layer lost at 2048 x 5504, 3072 x 8192 and 4096 x 11008 (2065 rows of
+    // 3072 x 8192, 16 pieces, predicted 5 %: 594 -> 598) and as often 4 .. 8 won.
     if (!large || max_split == 1) continue;
     const int whole = nT * nF / 256, full = whole * 256 / nF;
     if (full < 1 || full >= nT) continue;
-    for (int ks = 2; ks <= max_split && KT / ks >= 4 && (long)ks * (g.T - full * q.bt) <= g.part_rows; ++ks) {
+    for (int ks = 2; ks <= 8 && KT / ks >= 4 && (long)ks * (g.T - full * q.bt) <= g.part_rows; ++ks) {
       const double pieces = (double)(nT - full) * nF * ks - (256.0 * whole - (double)full * nF);   // idle CUs take some early
       const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff), load_cyc = (q.bf + q.bt) * 64 * 2 / 28.1;
       const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.073 * std::min(mfma_cyc, load_cyc);
@@ -787,10 +793,10 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
       double cyc = whole * ((KT + 2.0) * tile_cyc + 8938.0) + part_rounds * ((std::ceil((double)KT / ks) + 2.0) * tile_cyc + 8938.0);
       cyc += full * q.bt * (double)g.Nout / 256.0 * 8.0 / 6.2 + (g.T - full * q.bt) * (double)g.Nout / 256.0 * 8.0 * ks / 7.15;
       cyc += 12000.0;   // the norm that follows takes two launches
-      if (cyc * 1.001 < best_cost) { best_cost = cyc * 1.001; best.tile = c; best.ksplit = ks; best.full = full; }
+      if (cyc * 1.001 < tail_cost) { tail_cost = cyc * 1.001; tail.tile = c; tail.ksplit = ks; tail.full = full; }
     }
   }
-  return best;
+  return tail_cost < 0.955 * best_cost ? tail : best;
 }
 
 hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {

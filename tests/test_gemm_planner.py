@@ -136,3 +136,19 @@ def test_qkv_of_few_rows_takes_a_streaming_tile_built_for_it(lib, T):
         plain, _ = plan(lib, T, Nw, Nout, K, 0, 4096)
         assert plain < 24                             # the plain product has LDS tiles only
     assert plan(lib, T, 12288, 12288, 4096, 3, 4096)[0] == (24 if T <= 16 else 27 if T <= 32 else 25 if T <= 64 else 26 if T <= 96 else -1)
+
+
+def test_the_tail_is_split_only_where_it_is_predicted_to_win_clearly(lib):
+    # measured in whole layers: at most 8 pieces, and not where the cost model's error exceeds its advantage
+    def split(T, d, K):
+        v = [C.c_int32() for _ in range(3)]
+        assert lib.hat_mid_debug_gemm_split(T, d, d, K, 4096, *[C.byref(x) for x in v]) == 0
+        return v[1].value, v[2].value
+    for name, (d, f) in WIDTHS.items():
+        for K in (d, f):
+            for T in range(385, 4097):
+                first, ks = split(T, d, K)
+                assert first == 0 or ks <= 8, (name, K, T)
+                assert first == 0 or name in ("13b", "8k"), (name, K, T)
+    for T in (3213, 4037, 4096):
+        assert split(T, 5120, 5120)[0] == 3072 and split(T, 5120, 13824)[0] == 3072
