@@ -699,13 +699,16 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   if (g.epilogue == HAT_EPI_QKV) {
     // wherever the product streams: the epilogue costs less than the rotary and append kernel it replaces (5 us).
     // 64-feature tiles from 17 rows on: 24.4 against 27.0 us at 32 rows of the 7B shape (half the reads of X and
-    // whole panels of W), but 22.3 against 21.0 at 5 rows (192 workgroups instead of 384).
+    // whole panels of W), but 22.3 against 21.0 at 5 rows (192 workgroups instead of 384).  One such workgroup fits a CU:
+    // above 256 of them (d_model 5504 and up) a second round costs more than it saves, and the 32-feature tile is ahead of the LDS
+    // tiles up to 24 rows only (layer of 6144 x 4096 at 17 / 24 / 32 rows: LDS 121.7 / 115.1 / 120.3 us, 32-feature tile 115.9 / 112.2 /
+    // 121.4, 64-feature tile 118.2 / 115.9 / 122.3).
     if (g.force_tile >= 0) {
       best.tile = stream_built(g.force_tile, HAT_EPI_QKV) ? g.force_tile : -1;
       return best;
     }
     if (!stream_plan(g, &best)) best.tile = -1;
-    if (best.tile == kStream32 && g.T > 16) best.tile = kStream64x32;
+    if (best.tile == kStream32 && g.T > 16) best.tile = g.Nout / 64 <= 256 ? kStream64x32 : g.T <= 24 ? kStream32 : -1;
     return best;
   }
   if (g.force_tile >= 0 && (g.force_tile < kNumLdsTiles || stream_built(g.force_tile, g.epilogue))) {

@@ -152,3 +152,9 @@ def test_the_tail_is_split_only_where_it_is_predicted_to_win_clearly(lib):
                 assert first == 0 or name in ("13b", "8k"), (name, K, T)
     for T in (3213, 4037, 4096):
         assert split(T, 5120, 5120)[0] == 3072 and split(T, 5120, 13824)[0] == 3072
+
+
+def test_qkv_tiles_of_wide_models_do_not_run_over_into_a_second_round(lib):
+    for d, T, want in [(5120, 17, 27), (5120, 32, 27), (5504, 16, 24), (5504, 17, 24), (6144, 24, 24), (6144, 25, -1), (8192, 32, -1)]:
+        N = (3 * d + 255) // 256 * 256
+        assert plan(lib, T, N, 3 * d, d, 3, 4096)[0] == want, (d, T)
