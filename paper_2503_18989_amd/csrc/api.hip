@@ -729,8 +729,10 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // Items of at most HAT_NARROW_QROWS rows are bound by the cache stream: key ranges of about equal size instead, for
     // three eighths of verify_target workgroups (8 x 32 rows over 4096 keys: 118 us and 7 us of merging with 768 workgroups
     // wanted, 130 and 9 with 2048).
-    // Next to larger items that is a second launch (10 us a layer at worst): only where a narrow item would be the
-    // long one of the common launch, which does not split it (1024 keys: 16 stages of 2.7 us).
+    // Next to larger items that is a second launch and a merge (4 .. 14 us a layer with narrow items of 500 keys): only where a
+    // narrow item is so long that the common launch, which does not split it, would wait for it.  Measured in whole layers over 30
+    // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
+    // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
     double total_cost = 0, narrow_cost = 0;
     long narrow_keys = 0;
     int narrow_longest = 0;
@@ -749,7 +751,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         }
       }
     }
-    const bool stream_narrow = total_cost == 0 || narrow_longest >= 1024;
+    const bool stream_narrow = total_cost == 0 || narrow_longest >= 1536;
     if (!stream_narrow) total_cost += narrow_cost;
     if (total_cost > 0 || narrow_keys > 0) {
       const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);

@@ -262,7 +262,7 @@ def test_narrow_chunks_next_to_larger_ones_stream_only_when_long():
     lib, _ = both(400, max_devices=4, max_step_tokens=4096, max_pos=4096)
     for d in (0, 1):
         lib.plan([(d, hi.CHUNK, 0, 2000)])
-    for start, n, want in [(991, 32, 0), (992, 32, 1), (1500, 33, 0), (1023, 1, 1), (1022, 1, 0)]:
+    for start, n, want in [(1503, 32, 0), (1504, 32, 1), (1700, 33, 0), (1535, 1, 1), (1534, 1, 0)]:
         plan = lib.plan([(0, hi.CHUNK, 300, 200), (1, hi.CHUNK, start, n)])
         count = lib.narrow_items()
         assert (count > 0) == bool(want), (start, n)
