@@ -267,7 +267,10 @@ typedef enum {
 } hat_kernel_id_t;
 
 /* on != 0: later forwards bracket every kernel launch with HIP events on the
- * launch stream.  Slows the step slightly; off by default. */
+ * launch stream.  Slows the step slightly; off by default.  A step of fewer than 1024 rows gathers, fills the rotary
+ * table (counted under HAT_K_ROPE_APPEND) and applies the first norm in one launch; profiled, these are three, so that each
+ * is timed by itself.  The results are the same bits.  Where the last rows of an O or down product are split along K
+ * (hat_mid_debug_gemm_split), the norm that follows is two launches. */
 hat_status_t hat_mid_set_profiling(hat_mid_t* h, int32_t on);
 
 /* Sums since the last call, per kernel id: GPU milliseconds and launch counts
@@ -385,7 +388,8 @@ hat_status_t hat_mid_debug_peak(int32_t kind, void* buf, size_t bytes, int32_t i
 int32_t hat_mid_debug_gemm_tile_count(void);
 
 /* Shape of entry `tile` of that table: output features x token rows of one workgroup tile, its
- * waves, the k extent of one ring stage and the number of stages (host pointers; any may be null).
+ * waves, the k extent of one ring stage and the number of stages (host pointers; any may be null).  The last four are the
+ * streaming tiles: their waves split K among themselves, each holding the whole tile, and the ring is one of registers.
  * HAT_EINVAL if `tile` is out of range.  No GPU work; for tests of the planner. */
 hat_status_t hat_mid_debug_gemm_tile_info(int32_t tile, int32_t* features, int32_t* tokens, int32_t* waves,
                                           int32_t* k_per_stage, int32_t* stages);

@@ -162,7 +162,7 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // ROWS = 8: a verify segment, visibility of its own rows from the work item.  ROWS = 32: a narrow chunk item, causal; all 32
 // columns of the MFMA are rows, so the stream pays for the same arithmetic and only the merge at the end grows.
 // Narrow items are bound by the cache stream and by latency, not by the matrix pipe: 8 x 32 rows over 4096 keys of the 13B
-// shape 164 -> 118 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 21.2 us with the merge.  From 33 rows on every
+// shape 164 -> 118 .. 121 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 20.8 us with the merge.  From 33 rows on every
 // form of this kernel that was built (two row blocks per wave, two sets of waves, two workgroups) measured level with or
 // behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
 template <int HD, bool KVF16, int ROWS>

@@ -377,10 +377,11 @@ struct StreamDepth {   // k-steps in flight per wave: what the register file hol
 // ---- few token rows: weights streamed into operand registers -------------------------------
 // At most a few dozen rows make the product a read of W and nothing else, so this kernel is built
 // for the HBM stream and not for the matrix pipe.  A workgroup owns 32 NP features x 32 NT tokens and
-// its 8 waves split K: each wave loads its own 1 KB operand pieces of W (non-temporal: one reader)
+// its 8 waves split K: each wave loads its own 1 KB operand pieces of W (non-temporal: one reader, or two where 65 .. 96
+// rows make two token tiles)
 // and of X straight into MFMA operand registers, kept D k-steps ahead by a register ring, with no LDS and no
-// barrier until the 8 partial tiles meet in LDS at the end.  32-feature tiles give 344 .. 688 workgroups
-// (two of them resident on a CU) where the LDS tiles above have 96 .. 172, and the split of K
+// barrier until the 8 partial tiles meet in LDS at the end.  32-feature tiles give QKV and gate/up of the 7B shape 384 and
+// 688 workgroups (two of them resident on a CU) where the LDS tiles above have 96 and 172, and the split of K
 // inside the workgroup needs no partial sums in memory.  Lanes of token columns beyond T repeat
 // the last row's address, so that a 5-row batch fetches 5 rows of X and not 32.
 // Bound by the HBM stream: QKV of the 7B shape (100 MB) at 5 rows 31.0 -> 22.0 us (3.2 -> 4.6 TB/s, launch and
@@ -393,6 +394,9 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   constexpr int GRP = TILES < 2 ? TILES : 2;   // 32 x 32 tiles summed per LDS round
   static_assert(TILES % GRP == 0 && (EPI != HAT_EPI_QKV || GRP == NP), "a round is whole, and holds a rotation pair's halves");
   __shared__ __attribute__((aligned(16))) f32x4 red[NW][GRP][4][64];
+  // accumulators and ring, with 40 registers for addresses; two workgroups of the smallest tile on a CU, one of the others
+  static_assert(TILES * 16 + D * (NP + NT) * 4 + 40 <= (TILES <= 1 ? 128 : 256), "a lane's registers");
+  static_assert(sizeof(red) * (TILES <= 1 ? 2 : 1) <= 160 * 1024, "the LDS of a CU");
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -558,8 +562,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   X(23, 128, 160, 4, 1, 64, 3, EPI)
 constexpr int kNumLdsTiles = 24;
 // the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
-// 32 x 96 measured level with
-// or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
+// 32 x 96 measured level with or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
 #define HAT_FOR_STREAM(X, EPI) \
   X(24, 1, 1, EPI)             \
   X(25, 2, 2, EPI)             \
@@ -671,6 +674,16 @@ hipError_t hat_gemm_init() {
 //    the products themselves are level (O 10.9 -> 10.3, down 20.3 -> 20.0 at 5 rows; 14.8 -> 14.2 and 26.1 -> 25.5 at 77).
 //    With the 160 panels of the 13B shape the CUs are not filled: up to 16 rows still 23.9 -> 20.4 with the norm, at
 //    32 rows 24.2 -> 25.8; at 33 .. 64 rows down loses more (22.9 -> 25.4) than the norm gains.
+// Whole layers with and without it, weights out of reach of the caches, at eight widths from 1024 x 2816 to 8192 x 28672:
+//   rows          16                 32                 64                 96
+//   1024    47.2 ->  29.4      48.2 ->  37.5      46.8 ->  43.4      47.1 ->  43.2
+//   2048    65.7 ->  44.5      66.6 ->  48.5      68.8 ->  61.4      71.1 ->  65.6
+//   3072    91.5 ->  69.2      93.0 ->  73.4      95.7 ->  87.7     106.1 ->  97.4
+//   4096   118.5 ->  97.6     120.8 -> 103.6     127.8 -> 119.9     145.7 -> 136.0
+//   5120   154.3 -> 133.5     159.0 -> 143.4     170.0 -> 156.7     196.7 -> 187.1
+//   6144   203.4 -> 173.8     203.5 -> 202.7     214.3 -> 214.1     246.0 -> 250.2
+//   8192   370.2 -> 321.8     375.0 -> 361.0     389.6 -> 389.7     425.3 -> 419.8
+// (one product lost more than the runs differ: down of 6144 x 16384 at 96 rows, 2 us of 250).
 static bool stream_plan(const HatGemm& g, HatGemmPlan* p) {
   if (g.T > 96 || g.epilogue == HAT_EPI_P32) return false;
   p->ksplit = 1;
