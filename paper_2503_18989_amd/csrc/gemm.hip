@@ -292,8 +292,8 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
       // fp32 result: added into the residual when K is not split, else stored as this
       // split's partial sum (the next consumer of the residual folds the partials in)
       const int row0 = tt0 * BT;   // first row of the partial sums
-      float* outb = (ksplit == 1) ? g.resid + (size_t)tok * g.Nout
-                                  : g.part + ((size_t)kz * (g.T - row0) + (tok - row0)) * g.Nout;
+      float* outb = (ksplit == 1) ? g.resid : g.part;
+      const long shift = (ksplit == 1) ? 0 : (long)kz * (g.T - row0) - row0;   // uniform: no address registers across the loop
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         const int fb = f_base + i * 32;
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int f = fb + 8 * q + 4 * h;
-          float* p = outb + f;
+          float* p = outb + (size_t)(tok + shift) * g.Nout + f;
           f32x4 v;
           if (ksplit == 1) {
             v = *(f32x4*)p;
