@@ -720,9 +720,10 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
 template <int HD, bool F32>
 __device__ __forceinline__ void merge_rows(const HatAttn& a, const HatMergeItem& it, int head) {
   const size_t base32 = (size_t)a.part32_row0 * a.H;
+  constexpr int GRP = F32 ? 2 : 4;   // key ranges whose loads are issued together: the same registers either way
   for (int idx = threadIdx.x; idx < it.nrows * (HD / 8); idx += 256) {
     const int r = idx / (HD / 8), e = (idx % (HD / 8)) * 8;
-    // both passes take the key ranges four at a time, loads first: a loop that loads one range per
+    // both passes take the key ranges several at a time, loads first: a loop that loads one range per
     // pass waits out a memory round trip per range (the order of the sums is unchanged)
     const size_t pr0 = (size_t)(it.part_row + r) * a.H + head, prs = (size_t)it.stride * a.H;
     float M = -INFINITY;
@@ -737,12 +738,12 @@ __device__ __forceinline__ void merge_rows(const HatAttn& a, const HatMergeItem&
     }
     float L = 0.f;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int s0 = 0; s0 < it.nsplit; s0 += 4) {
-      float2 ml[4];
-      f16x8 v[4];
-      f32x4 lo[4], hi[4];
+    for (int s0 = 0; s0 < it.nsplit; s0 += GRP) {
+      float2 ml[GRP];
+      f16x8 v[GRP];
+      f32x4 lo[GRP], hi[GRP];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < GRP; ++u)
         if (s0 + u < it.nsplit) {
           const size_t pr = pr0 + (s0 + u) * prs;
           ml[u] = a.part_ml[pr];
@@ -755,7 +756,7 @@ __device__ __forceinline__ void merge_rows(const HatAttn& a, const HatMergeItem&
           }
         }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < GRP; ++u)
         if (s0 + u < it.nsplit) {
           const float f = ml[u].y * exp2f(ml[u].x - M);   // weight of this key range: its sum, on the common scale
           L += f;
