@@ -13,9 +13,10 @@ SOURCES = ["api.hip", "gemm.hip", "attention.hip", "elementwise.hip", "peaks.hip
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU forms
          "-Wno-unused-result"]
-# The GEMM main loops start on a 32-byte boundary.  Left to chance, their place moves with every instruction of the code before
-# them, and with it the time of the 256 x 256 tile: gate/up of 1024 rows (13B shape) 272 .. 280 us over the eight places.
-EXTRA = {"gemm.hip": ["-Xarch_device", "-falign-loops=32"]}
+# The GEMM main loops start on a 128-byte boundary.  Left to chance, their place moves with every instruction of the code before
+# them, and with it their time: 28.3 .. 30.9 us for the down product of 256 rows (7B shape) unaligned and at 32, 64, 128 and 256 bytes,
+# 143 .. 145 us for gate/up of 512 rows (13B shape, 256 x 128 tile) against 148 unaligned.
+EXTRA = {"gemm.hip": ["-Xarch_device", "-falign-loops=128"]}
 
 
 def _compile(src):

@@ -5,7 +5,7 @@
 //   out[t, f] = sum_k X[t, k] * W[f, k]      X: activations, W: weights [out, in]
 //
 // Both operands are in the P32 layout (hat_layout.h).  The kernel computes the
-// transposed product C^T = W * X^T with v_mfma_f32_32x32x16_f16: MFMA rows are
+// transposed product C^T = W * X^T with v_mfma_f32_16x16x32_f16: MFMA rows are
 // output features, MFMA columns are tokens.  In the accumulator a lane then owns
 // one token and runs of 4 consecutive features, which is exactly an 8-byte piece
 // of the P32 layout of the *next* operand, so every epilogue stores coalesced.
@@ -53,27 +53,37 @@ __device__ __forceinline__ void wait_vmcnt() { hat_wait_vmcnt<N>(); }
 template <int N>
 __device__ __forceinline__ void wait_operands(f16x8 (&v)[N]) { hat_wait_operands(v); }
 
-template <int BF, int BT, int WF, int WT, int BKT, int NSTAGE>
+template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE>
 struct Tile {
-  static constexpr int NW = WF * WT;
-  static constexpr int MI = BF / WF / 32;   // feature blocks per wave
-  static constexpr int NJ = BT / WT / 32;   // token blocks per wave
+  static constexpr int NW = WF * WT * WK;
+  static constexpr int MI = BF / WF / 16;   // 16-row feature blocks per wave
+  static constexpr int NJ = BT / WT / 16;   // 16-row token blocks per wave
   static constexpr int PF = BF / 32, PT = BT / 32;
   static constexpr int SLAB = (BKT / 8) * 512;  // bytes of one panel's k-slab
   static constexpr int CPS = SLAB / 1024;       // 1 KB wave-chunks per slab
   static constexpr int NCH = (PF + PT) * CPS;
-  static constexpr int LPW = NCH / NW;          // direct-to-LDS loads per wave per stage
+  static constexpr int LPW = (NCH + NW - 1) / NW;  // direct-to-LDS loads per wave per stage (the last waves: one less, where they don't divide)
   static constexpr int STAGE = (PF + PT) * SLAB;
-  static constexpr int KS = BKT / 16;
+  static constexpr int KS = BKT / 32 / WK;      // k-steps of one wave per stage
   static constexpr int LDS_BYTES = NSTAGE * STAGE;
-  static_assert(NCH % NW == 0, "chunks must divide over waves");
-  static_assert((NSTAGE - 2) * LPW <= 63, "vmcnt is 6 bits");
+  static_assert(BF % (WF * 32) == 0 && BT % (WT * 16) == 0 && (WT == 1 || WT % 2 == 0), "whole 32-row panels of features, 16-row blocks of tokens");
+  static_assert(KS >= 1 && BKT % (32 * WK) == 0 && (WK == 1 || WK == 2), "whole k-steps");
+  static_assert(NSTAGE >= 2 && NSTAGE <= 4 && (NSTAGE - 1) * LPW <= 63, "wait_pending covers up to 3 pending tiles; vmcnt is 6 bits");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
+  static_assert(WK == 1 || WF * WT * MI * NJ * 1024 <= LDS_BYTES, "the two halves of K meet in the ring");
 };
 
-template <int BF, int BT, int WF, int WT, int BKT, int NSTAGE, int EPI>
-__global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
-  using TL = Tile<BF, BT, WF, WT, BKT, NSTAGE>;
+// Matrix instruction: v_mfma_f32_16x16x32_f16.  Random operands drive the matrix pipes into the chip's power limit, and this
+// shape takes less power than 32x32x16: a loop of nothing but MFMAs runs at 1960 TFLOP/s against 1430 .. 1730 (2420 both on
+// zeros), gate/up of 4096 rows (13B shape) at 1290 against 1155.  It needs two waves on a SIMD: with one, its 16 clocks do not hide
+// the issue of the next operand reads and loads (256 x 192 on four waves: 359 -> 437 us), so every large tile has eight
+// waves.  Where eight wave tiles would read too much LDS per product (192 x 128: 48 rows each), WK = 2 gives the two waves of a
+// SIMD the same output block and each half of a stage's k; they meet in LDS at the end.
+// Against the 32x32x16 loop on four waves, weights in reach of the caches: gate/up of the 7B shape at 256 rows 53.8 -> 48.2 us, QKV
+// 34.1 -> 30.9, O 16.9 -> 15.7, down 31.4 -> 28.3; 13B shape at 512 rows 138 -> 124, 81 -> 73.2 and (down) 76.9 -> 69.8.
+template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE, int EPI>
+__global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
+  using TL = Tile<BF, BT, WF, WT, WK, BKT, NSTAGE>;
   constexpr int MI = TL::MI, NJ = TL::NJ, PF = TL::PF, PT = TL::PT, SLAB = TL::SLAB, CPS = TL::CPS;
   constexpr int LPW = TL::LPW, STAGE = TL::STAGE, KS = TL::KS;
 
@@ -82,7 +92,8 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wf = wave / WT, wt = wave % WT;
+  const int wk = wave / (WF * WT), wq = wave % (WF * WT);
+  const int wf = wq / WT, wt = wq % WT;
 
   // workgroup -> tile.  Consecutive hardware ids go round-robin over the 8 XCDs;
   // give each XCD a contiguous run of tiles so that tiles sharing a weight panel
@@ -129,11 +140,14 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
   const int nkt = kt1 - kt0;
 
   // per-wave chunk sources (per-lane address); destinations are wave-uniform
+  constexpr int EXTRA = TL::NCH % TL::NW;            // that many waves bring LPW chunks, the others one less (0: all bring LPW)
+  const bool more = EXTRA == 0 || wave < EXTRA;
+  const int ch0 = more ? wave * LPW : EXTRA * LPW + (wave - EXTRA) * (LPW - 1);
   const act_t* src[LPW];
   const size_t krow = (size_t)(g.K >> 3) * 256;  // elements per panel
 #pragma unroll
   for (int c = 0; c < LPW; ++c) {
-    const int ch = wave * LPW + c;
+    const int ch = c + 1 < LPW || more ? ch0 + c : ch0;
     const int q = ch / CPS, sub = ch % CPS;
     const act_t* base;
     if (q < PF) {
@@ -147,146 +161,171 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
     }
     src[c] = base + (size_t)kt0 * (BKT / 8) * 256 + sub * 512 + lane * 8;
   }
-  auto issue = [&](int i) {  // i: k-tile index relative to kt0
-    unsigned char* dstb = lds + (i % NSTAGE) * STAGE + wave * (LPW * 1024);
-#pragma unroll
-    for (int c = 0; c < LPW; ++c)
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(src[c] + (size_t)i * (BKT / 8) * 256),
-          (__attribute__((address_space(3))) void*)(dstb + c * 1024), 16, 0, 0);
+  auto issue_chunk = [&](int i, int c) {  // chunk c of k-tile i (relative to kt0)
+    if (EXTRA != 0 && c + 1 == LPW && !more) return;
+    __builtin_amdgcn_global_load_lds(
+        (const __attribute__((address_space(1))) void*)(src[c] + (size_t)i * (BKT / 8) * 256),
+        (__attribute__((address_space(3))) void*)(lds + (i % NSTAGE) * STAGE + (ch0 + c) * 1024), 16, 0, 0);
+  };
+  auto wait_tiles = [&](auto tc) {  // at most tc k-tiles of my loads still in flight
+    constexpr int t = decltype(tc)::value < NSTAGE ? decltype(tc)::value : NSTAGE - 1;
+    if (more) wait_vmcnt<t * LPW>();
+    else wait_vmcnt<t * (LPW - 1)>();
+  };
+  auto wait_pending = [&](int tiles) {
+    switch (tiles) {
+      case 0: wait_tiles(std::integral_constant<int, 0>{}); break;
+      case 1: wait_tiles(std::integral_constant<int, 1>{}); break;
+      case 2: wait_tiles(std::integral_constant<int, 2>{}); break;
+      default: wait_tiles(std::integral_constant<int, 3>{}); break;
+    }
   };
 
-  f32x16 acc[MI][NJ];
+  f32x4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // One continuous pipeline over k-steps.  The operands of k-step s+1 are read from LDS
-  // while the MFMAs of k-step s run, also across k-tile boundaries: at the last k-step of
+#pragma unroll
+  for (int s = 0; s < NSTAGE; ++s)
+    if (s < nkt) {
+#pragma unroll
+      for (int c = 0; c < LPW; ++c) issue_chunk(s, c);
+    }
+
+  // An operand is 16 rows x 32 k: lane l holds row l%16, k-octet l/16.  A wave's feature blocks are consecutive; its token
+  // blocks are every WT-th of the tile, so that any number of them keeps the same distance in LDS for every wave.
+  const uint32_t lane_off = lds_base + (lane >> 4) * 512 + (lane & 15) * 16 + wk * (KS * 2048);
+  const uint32_t offW = lane_off + (wf * MI / 2) * SLAB;
+  const uint32_t offX = lane_off + PF * SLAB + (wt >> 1) * SLAB + (wt & 1) * 256;
+  f16x8 a[2][MI], bb[2][NJ];
+  constexpr int NMFMA = MI * NJ;
+  auto read_operands = [&](auto setc, auto ksc, int i) {
+    constexpr int set = decltype(setc)::value, ks = decltype(ksc)::value;
+    const uint32_t aW = offW + (i % NSTAGE) * STAGE, aX = offX + (i % NSTAGE) * STAGE;
+    static_for<MI>([&](auto ii) { a[set][ii] = lds_read<(ii / 2) * SLAB + (ii % 2) * 256 + ks * 2048>(aW); });
+    static_for<NJ>([&](auto jj) {
+      constexpr int off = WT == 1 ? (jj / 2) * SLAB + (jj % 2) * 256 : jj * (WT / 2) * SLAB;
+      bb[set][jj] = lds_read<off + ks * 2048>(aX);
+    });
+  };
+  // One continuous pipeline over k-steps of 32.  The operands of the next k-step are read from LDS
+  // while the MFMAs of this one run, also across k-tile boundaries: at the last k-step of
   // tile i a wave first makes sure tile i+1 has landed (its own loads: vmcnt; everyone's:
   // barrier -- which also says everyone is done reading tile i), reads tile i+1's first
   // operands, and only then issues tile i's last MFMAs.  The direct-to-LDS loads of tile
   // i+NSTAGE (into the buffer tile i just vacated) are slotted between the MFMAs of the
-  // following KS k-steps.
-  static_assert(KS % 2 == 0, "operand register sets alternate per k-step");
-  static_assert((NSTAGE - 1) * LPW <= 63, "vmcnt is 6 bits");
-  auto issue_chunk = [&](int i, int c) {
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void*)(src[c] + (size_t)i * (BKT / 8) * 256),
-        (__attribute__((address_space(3))) void*)(lds + (i % NSTAGE) * STAGE + wave * (LPW * 1024) + c * 1024), 16, 0, 0);
-  };
-  auto wait_pending = [&](int tiles) {  // at most `tiles` k-tiles of my loads still in flight
-    switch (tiles) {
-      case 0: wait_vmcnt<0>(); break;
-      case 1: wait_vmcnt<(NSTAGE >= 2 ? 1 : 0) * LPW>(); break;
-      case 2: wait_vmcnt<(NSTAGE >= 3 ? 2 : 0) * LPW>(); break;
-      default: wait_vmcnt<(NSTAGE >= 4 ? 3 : 0) * LPW>(); break;
+  // following KS k-steps, in KS parts: part 0 right after that boundary, parts 1.. over the next tile's k-steps 0..KS-2.
+  // They are spread thinly because a direct-to-LDS load holds the issuing wave for on the order of a hundred cycles.
+  // `steady`: tile i + NSTAGE exists (and with several k-steps per tile, i is not the first), so nothing has to be asked.
+  auto kstep = [&](auto curc, auto ksc, int i, auto steadyc) {
+    constexpr int cur = decltype(curc)::value, ks = decltype(ksc)::value;
+    constexpr bool steady = decltype(steadyc)::value;
+    constexpr std::integral_constant<int, cur ^ 1> next{};
+    wait_operands(a[cur]);
+    wait_operands(bb[cur]);
+    if constexpr (ks + 1 < KS) {
+      read_operands(next, std::integral_constant<int, ks + 1>{}, i);
+    } else if (steady || i + 1 < nkt) {
+      const int after = nkt - 2 - i;  // tiles issued behind tile i+1
+      if (steady || after >= NSTAGE - 2) wait_tiles(std::integral_constant<int, NSTAGE - 2>{});
+      else wait_pending(after);
+      __builtin_amdgcn_s_barrier();
+      read_operands(next, std::integral_constant<int, 0>{}, i + 1);
     }
+    constexpr int part = (ks + 1) % KS, CPP = (LPW + KS - 1) / KS;
+    const int rtile = (ks + 1 == KS) ? i + NSTAGE : i - 1 + NSTAGE;
+    const bool refill = rtile < nkt && ((ks + 1 == KS) ? (i + 1 < nkt) : (i >= 1));
+    // keep the operand reads ahead of this k-step's MFMAs (the scheduler would otherwise
+    // sink them behind the MFMAs and expose the LDS latency)
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NMFMA>([&](auto n) {
+      // back and forth along the token blocks: each MFMA shares an operand with the one before it
+      constexpr int ii = n / NJ, jj = (ii & 1) ? NJ - 1 - n % NJ : n % NJ;
+      acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[cur][ii], bb[cur][jj], acc[ii][jj], 0, 0, 0);
+      static_for<CPP>([&](auto q) {
+        constexpr int slot = q * NMFMA / CPP + NMFMA / CPP / 2;
+        constexpr int c = part * CPP + q;
+        if constexpr (slot == n && c < LPW) {
+          if (steady || refill) issue_chunk(rtile, c);
+        }
+      });
+    });
+    __builtin_amdgcn_sched_barrier(0);
   };
-  static_assert(NSTAGE <= 4, "wait_pending covers up to 3 pending tiles");
-#pragma unroll
-  for (int s = 0; s < NSTAGE; ++s)
-    if (s < nkt) issue(s);
-
-  const uint32_t offW = (wf * MI) * SLAB + lane * 16;
-  const uint32_t offX = (PF + wt * NJ) * SLAB + lane * 16;
-  f16x8 a[2][MI], bb[2][NJ];
-  constexpr int NMFMA = MI * NJ;
-  constexpr int CPP = (LPW + KS - 1) / KS;  // loads of one refill part (one k-step's share of a tile)
-
+  auto ktile = [&](auto curc, int i, auto steadyc) {
+    static_for<KS>([&](auto ks) { kstep(std::integral_constant<int, (decltype(curc)::value + ks) & 1>{}, ks, i, steadyc); });
+  };
+  constexpr std::integral_constant<int, 0> set0{};
+  constexpr std::integral_constant<int, KS & 1> set1{};   // the register set on which an odd tile starts
   if (nkt > 0) {
     wait_pending(nkt - 1 < NSTAGE - 1 ? nkt - 1 : NSTAGE - 1);
     __builtin_amdgcn_s_barrier();
-    const uint32_t aW = lds_base + offW, aX = lds_base + offX;
-    static_for<MI>([&](auto ii) { a[0][ii] = lds_read<ii * SLAB>(aW); });
-    static_for<NJ>([&](auto jj) { bb[0][jj] = lds_read<jj * SLAB>(aX); });
+    read_operands(set0, std::integral_constant<int, 0>{}, 0);
   }
-  for (int i = 0; i < nkt; ++i) {
-    const uint32_t sbase = lds_base + (i % NSTAGE) * STAGE;
-    const uint32_t aW = sbase + offW, aX = sbase + offX;
-    static_for<KS>([&](auto ks) {
-      constexpr int cur = ks & 1;
-      wait_operands(a[cur]);
-      wait_operands(bb[cur]);
-      if constexpr (ks + 1 < KS) {
-        static_for<MI>([&](auto ii) { a[cur ^ 1][ii] = lds_read<ii * SLAB + (ks + 1) * 1024>(aW); });
-        static_for<NJ>([&](auto jj) { bb[cur ^ 1][jj] = lds_read<jj * SLAB + (ks + 1) * 1024>(aX); });
-      } else if (i + 1 < nkt) {
-        const int after = nkt - 2 - i;  // tiles issued behind tile i+1
-        wait_pending(after < NSTAGE - 2 ? after : NSTAGE - 2);
-        __builtin_amdgcn_s_barrier();
-        const uint32_t nbase = lds_base + ((i + 1) % NSTAGE) * STAGE;
-        const uint32_t nW = nbase + offW, nX = nbase + offX;
-        static_for<MI>([&](auto ii) { a[cur ^ 1][ii] = lds_read<ii * SLAB>(nW); });
-        static_for<NJ>([&](auto jj) { bb[cur ^ 1][jj] = lds_read<jj * SLAB>(nX); });
-      }
-      // The refill of the ring is spread thinly over the MFMAs: a direct-to-LDS load holds
-      // the issuing wave for on the order of a hundred cycles, so a burst of them would
-      // stall the matrix pipe.  The tile going into the buffer vacated at the last
-      // boundary is issued in KS parts: part 0 right after that boundary (last k-step of
-      // the previous tile), parts 1.. over this tile's k-steps 0..KS-2.
-      constexpr int part = (ks + 1) % KS;
-      const int rtile = (ks + 1 == KS) ? i + NSTAGE : i - 1 + NSTAGE;
-      const bool refill = rtile < nkt && ((ks + 1 == KS) ? (i + 1 < nkt) : (i >= 1));
-      // keep the operand reads ahead of this k-step's MFMAs (the scheduler would otherwise
-      // sink them behind the MFMAs and expose the LDS latency)
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<NMFMA>([&](auto n) {
-        constexpr int ii = n / NJ, jj = n % NJ;
-        acc[ii][jj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[cur][ii], bb[cur][jj], acc[ii][jj], 0, 0, 0);
-        static_for<CPP>([&](auto q) {
-          constexpr int slot = (q * NMFMA / CPP) < NMFMA ? (q * NMFMA / CPP) : NMFMA - 1;
-          constexpr int c = part * CPP + q;
-          if constexpr (slot == n && c < LPW) {
-            if (refill) issue_chunk(rtile, c);
-          }
-        });
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    });
+  int i = 0;
+  if constexpr (KS == 1) {
+    for (; i + 1 + NSTAGE < nkt; i += 2) {
+      ktile(set0, i, std::true_type{});
+      ktile(set1, i + 1, std::true_type{});
+    }
+  }
+  for (; i < nkt; i += 2) {
+    ktile(set0, i, std::false_type{});
+    if (i + 1 < nkt) ktile(set1, i + 1, std::false_type{});
   }
 
-  // ---- epilogue.  lane: token = t0 + 32j + lane%32 ; feature = f0 + 32i + 8*(r/4) + 4*(lane/32) + r%4
-  const int h = lane >> 5, n = lane & 31;
-  const int t_base = tt * BT + wt * NJ * 32;
-  const int f_base = ft * BF + wf * MI * 32;
+  // the two halves of K: a wave hands its partner one half of the token blocks and finishes the other
+  constexpr int NJO = WK == 1 ? NJ : (NJ + 1) / 2;
+  int j0 = 0, jn = NJ;
+  if constexpr (WK == 2) {
+    __syncthreads();   // everyone is done with the ring
+    f32x4* red = (f32x4*)lds + wq * (MI * NJ * 64) + lane;
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int tok = t_base + j * 32 + n;
-    if (tok >= g.T) continue;
+    for (int ii = 0; ii < MI; ++ii)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if ((j < NJO) == (wk == 1)) red[(ii * NJ + j) * 64] = acc[ii][j];
+    __syncthreads();
+    j0 = wk * NJO;
+    jn = wk == 0 ? NJO : NJ - NJO;
+#pragma unroll
+    for (int ii = 0; ii < MI; ++ii)
+#pragma unroll
+      for (int j = 0; j < NJO; ++j) {
+        if (wk == 1 && j + NJO < NJ) acc[ii][j] = acc[ii][j + NJO < NJ ? j + NJO : j];
+        if (j < jn) acc[ii][j] += red[(ii * NJ + j0 + j) * 64];
+      }
+  }
+
+  // ---- epilogue.  lane: token = 16 * (token block) + lane%16 ; feature = f0 + 16i + 4*(lane/16) + r
+  const int h4 = (lane >> 4) * 4, n = lane & 15;
+  const int f_base = ft * BF + wf * MI * 16;
+#pragma unroll
+  for (int j = 0; j < NJO; ++j) {
+    const int tok = tt * BT + (wt + WT * (j0 + j)) * 16 + n;
+    if (tok >= g.T || j >= jn) continue;
     if constexpr (EPI == HAT_EPI_P32) {
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int fb = f_base + i * 32;
+        const int fb = f_base + i * 16;
         if (fb >= g.Nout) continue;
+        f16x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = fb + 8 * q + 4 * h;
-          f16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = to_act(acc[i][j][4 * q + e]);
-          *(f16x4*)(g.outP + p32_index(tok, f, g.Nout)) = v;
-        }
+        for (int e = 0; e < 4; ++e) v[e] = to_act(acc[i][j][e]);
+        *(f16x4*)(g.outP + p32_index(tok, fb + h4, g.Nout)) = v;
       }
     } else if constexpr (EPI == HAT_EPI_SWIGLU) {
-      // a 32-row block of W holds 16 gate rows then the 16 up rows of the same features:
-      // accumulator elements 4q+e (q = 0,1) and 4(q+2)+e of a lane are gate and up of
-      // output feature fb + 8q + 4h + e
+      // a 32-row block of W holds 16 gate rows then the 16 up rows of the same features
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const int fb = (f_base + i * 32) / 2;  // output feature block (16 wide)
+      for (int i = 0; i < MI; i += 2) {
+        const int fb = (f_base + i * 16) / 2;  // output feature block (16 wide)
         if (fb >= g.Nout) continue;
+        f16x4 v;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int f = fb + 8 * q + 4 * h;
-          f16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = to_act(silu_f(acc[i][j][4 * q + e]) * acc[i][j][4 * (q + 2) + e]);
-          *(f16x4*)(g.outP + p32_index(tok, f, g.Nout)) = v;
-        }
+        for (int e = 0; e < 4; ++e) v[e] = to_act(silu_f(acc[i][j][e]) * acc[i + 1][j][e]);
+        *(f16x4*)(g.outP + p32_index(tok, fb + h4, g.Nout)) = v;
       }
     } else {
       // fp32 result: added into the residual when K is not split, else stored as this
@@ -296,23 +335,10 @@ __global__ __launch_bounds__(WF* WT * 64) void gemm_kernel(HatGemm g, int ksplit
       const long shift = (ksplit == 1) ? 0 : (long)kz * (g.T - row0) - row0;   // uniform: no address registers across the loop
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int fb = f_base + i * 32;
+        const int fb = f_base + i * 16;
         if (fb >= g.Nout) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = fb + 8 * q + 4 * h;
-          float* p = outb + (size_t)(tok + shift) * g.Nout + f;
-          f32x4 v;
-          if (ksplit == 1) {
-            v = *(f32x4*)p;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] += acc[i][j][4 * q + e];
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
-          }
-          *(f32x4*)p = v;
-        }
+        float* p = outb + (size_t)(tok + shift) * g.Nout + fb + h4;
+        *(f32x4*)p = ksplit == 1 ? *(const f32x4*)p + acc[i][j] : acc[i][j];
       }
     }
   }
@@ -525,41 +551,42 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   }
 }
 
-// tile table: id, features x tokens, waves along features x tokens, k per stage, stages.
+// tile table: id, features x tokens, waves along features x tokens, halves of K, k per stage, stages.
 // Heights of 96 and 192 rows exist so that the tile count can match the 256 CUs where
 // 128 / 256 leave a quarter or a third of them idle (7B-shaped QKV and gate/up at T <= 256).
-// Tile 19 is tile 1 on eight waves (two per SIMD, 64 x 128 each): measured 2-8 % faster
-// at T = 512 .. 4096 wherever the 256 x 256 shape is the right one.  Tiles 20-22 take 224, 192
-// and 160 token rows: for batches whose row count leaves the last 256-row tile mostly empty
-// or the tile count just above a multiple of the 256 CUs (measured up to 25 % at T = 2200).  Tile 23
+// Tiles 20-22 take 224, 192 and 160 token rows: for batches whose row count leaves the last 256-row tile mostly empty
+// or the tile count just above a multiple of the 256 CUs.  Tile 23
 // (128 x 160) is for batches of 129 .. 160 rows, e.g. 30 devices x 5 draft rows: one token tile
-// instead of a full and a nearly empty one (O, gate/up and down 3-13 % faster at 150 rows on the
-// 7B shape, 12-20 % on the 13B shape).
-#define HAT_FOR_TILES(X, EPI)       \
-  X(0, 256, 256, 2, 2, 64, 2, EPI)  \
-  X(1, 256, 256, 2, 2, 32, 4, EPI)  \
-  X(2, 128, 256, 2, 2, 64, 3, EPI)  \
-  X(3, 256, 128, 2, 2, 64, 3, EPI)  \
-  X(4, 128, 128, 2, 2, 64, 4, EPI)  \
-  X(5, 256, 64, 4, 1, 64, 3, EPI)   \
-  X(6, 256, 32, 4, 1, 64, 4, EPI)   \
-  X(7, 128, 64, 2, 2, 64, 4, EPI)   \
-  X(8, 128, 32, 2, 1, 64, 4, EPI)   \
-  X(9, 64, 256, 1, 4, 64, 3, EPI)   \
-  X(10, 128, 128, 2, 2, 64, 2, EPI) \
-  X(11, 128, 128, 2, 2, 32, 4, EPI) \
-  X(12, 128, 64, 2, 2, 64, 3, EPI)  \
-  X(13, 192, 128, 2, 2, 64, 3, EPI) \
-  X(14, 96, 128, 1, 4, 64, 4, EPI)  \
-  X(15, 96, 256, 1, 4, 64, 3, EPI)  \
-  X(16, 192, 64, 2, 2, 64, 4, EPI)  \
-  X(17, 192, 256, 2, 2, 64, 2, EPI) \
-  X(18, 96, 64, 1, 2, 64, 4, EPI)   \
-  X(19, 256, 256, 4, 2, 32, 4, EPI) \
-  X(20, 256, 224, 4, 1, 64, 2, EPI) \
-  X(21, 256, 192, 2, 2, 32, 4, EPI) \
-  X(22, 256, 160, 4, 1, 64, 3, EPI) \
-  X(23, 128, 160, 4, 1, 64, 3, EPI)
+// instead of a full and a nearly empty one.
+// Waves: 64 x 128 and the like each, 12 operand reads for 32 MFMAs, where that makes eight wave tiles of whole 32-row panels; two
+// halves of K otherwise (192 x 128: 96 x 64 in halves of K 48.2 us, 96 x 32 53.7 us, on gate/up of the 7B shape at 256 rows).
+// Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
+// tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
+#define HAT_FOR_TILES(X, EPI)          \
+  X(0, 256, 256, 2, 4, 1, 32, 4, EPI)  \
+  X(1, 192, 128, 2, 4, 1, 32, 4, EPI)  \
+  X(2, 128, 256, 2, 4, 1, 64, 3, EPI)  \
+  X(3, 256, 128, 4, 2, 1, 64, 3, EPI)  \
+  X(4, 128, 128, 2, 4, 1, 64, 4, EPI)  \
+  X(5, 256, 64, 4, 1, 2, 64, 3, EPI)   \
+  X(6, 256, 32, 4, 1, 2, 64, 4, EPI)   \
+  X(7, 128, 64, 2, 2, 2, 64, 4, EPI)   \
+  X(8, 128, 32, 2, 1, 2, 64, 4, EPI)   \
+  X(9, 64, 256, 1, 4, 2, 64, 3, EPI)   \
+  X(10, 128, 128, 2, 2, 2, 64, 4, EPI) \
+  X(11, 128, 128, 2, 4, 1, 32, 4, EPI) \
+  X(12, 128, 64, 2, 4, 1, 64, 4, EPI)  \
+  X(13, 192, 128, 2, 2, 2, 64, 3, EPI) \
+  X(14, 96, 128, 1, 4, 2, 64, 4, EPI)  \
+  X(15, 96, 256, 1, 4, 2, 64, 3, EPI)  \
+  X(16, 192, 64, 2, 2, 2, 64, 4, EPI)  \
+  X(17, 192, 256, 2, 4, 1, 32, 4, EPI) \
+  X(18, 96, 64, 1, 2, 2, 64, 4, EPI)   \
+  X(19, 256, 256, 4, 2, 1, 32, 4, EPI) \
+  X(20, 256, 224, 4, 2, 1, 32, 4, EPI) \
+  X(21, 256, 192, 4, 2, 1, 32, 4, EPI) \
+  X(22, 256, 160, 4, 2, 1, 32, 4, EPI) \
+  X(23, 128, 160, 2, 2, 2, 64, 3, EPI)
 constexpr int kNumLdsTiles = 24;
 // the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
 // 32 x 96 measured level with or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
@@ -578,18 +605,18 @@ constexpr int kNumTiles = 28;
 struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
 // `planned`: offered to the automatic choice; the others are alternative stagings of the
 // same shapes, used only when forced
-constexpr bool kPlanned[kNumLdsTiles] = {false, true, true, true, true, true, true, true, true, true,
+constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, true, true, true, true,
                                       false, false, false, true, true, true, true, true, true, true,
                                       true, true, true, true};
 // Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, fitted to
 // sweeps at T = 512 .. 5220 (7B shapes, all four products, K split 1 .. 8); 0 = not measured
 // there, the tile is only offered to batches of at most kSmallT rows.
-constexpr float kEff[kNumLdsTiles] = {0.f, 0.585f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
+constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
                                    0.f, 0.f, 0.f, 0.514f, 0.f, 1.209f, 0.f, 0.504f, 0.f, 0.629f,
                                    0.518f, 0.565f, 0.564f, 0.f};
 constexpr int kSmallT = 384;
 constexpr TileInfo kTiles[kNumTiles] = {
-#define HAT_INFO(id, bf, bt, wf, wt, bkt, ns, epi) {bf, bt, (wf) * (wt), bkt, ns, kPlanned[id], kEff[id]},
+#define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kPlanned[id], kEff[id]},
     HAT_FOR_TILES(HAT_INFO, 0)
 #undef HAT_INFO
 // "stages" of a streaming tile: its register ring counted in 32-k pieces
@@ -600,14 +627,14 @@ constexpr TileInfo kTiles[kNumTiles] = {
 
 template <int EPI>
 hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
-#define HAT_TRY(id, bf, bt, wf, wt, bkt, ns, epi)                       \
+#define HAT_TRY(id, bf, bt, wf, wt, wk, bkt, ns, epi)                   \
   if (p.tile == id) {                                                   \
-    using TL = Tile<bf, bt, wf, wt, bkt, ns>;                           \
+    using TL = Tile<bf, bt, wf, wt, wk, bkt, ns>;                       \
     const int nT = (g.T + bt - 1) / bt, nF = (g.Nw + bf - 1) / bf;      \
     dim3 grid(nT * nF, 1, p.ksplit);                                    \
     if (p.full > 0) grid = dim3(p.full * nF + (nT - p.full) * nF * p.ksplit); \
-    auto kern = gemm_kernel<bf, bt, wf, wt, bkt, ns, epi>;              \
-    kern<<<grid, dim3(wf * wt * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
+    auto kern = gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>;          \
+    kern<<<grid, dim3(TL::NW * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
     return hipGetLastError();                                           \
   }
   if constexpr (EPI != HAT_EPI_QKV) {
@@ -631,9 +658,9 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
 template <int EPI>
 hipError_t attr_epi() {
   hipError_t e;
-#define HAT_ATTR(id, bf, bt, wf, wt, bkt, ns, epi)                                                        \
-  e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, bkt, ns, epi>,                         \
-                          hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, bkt, ns>::LDS_BYTES); \
+#define HAT_ATTR(id, bf, bt, wf, wt, wk, bkt, ns, epi)                                                    \
+  e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>,                     \
+                          hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, wk, bkt, ns>::LDS_BYTES); \
   if (e != hipSuccess) return e;
   HAT_FOR_TILES(HAT_ATTR, EPI)
 #undef HAT_ATTR
@@ -758,7 +785,7 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
     const int max_split = (g.epilogue == HAT_EPI_RESID && g.part) ? 16 : 1;
     const int lds = q.nstage * (q.bf + q.bt) * q.bkt * 2;
-    const int per_cu = std::max(1, std::min(160 * 1024 / lds, 8 / q.waves));
+    const int per_cu = std::max(1, std::min(160 * 1024 / lds, 2));
     for (int ks = 1; ks <= max_split; ++ks) {
       if (ks > 1 && (KT / ks < 4 || (long)ks * g.T > g.part_rows)) break;
       const double blocks = (double)nT * nF * ks;
@@ -775,7 +802,7 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
         else if (ks == 1) cyc += rows * 8.0 / 6.2;
         else cyc += rows * 8.0 * ks / 7.15;
       } else {
-        const double mfma_eff = q.waves == 8 ? 0.90 : 0.85;                     // two waves per SIMD fill more of the pipe
+        const double mfma_eff = q.bf * q.bt == 65536 ? 0.90 : 0.85;
         const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * mfma_eff);
         const double load_cyc = (q.bf + q.bt) * 64 * 2 / 36.0;
         const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.45 * std::min(mfma_cyc, load_cyc);

@@ -6,7 +6,8 @@
 //     ordered [k/8][row%32].  A lane of a 64-wide wavefront that needs MFMA
 //     32x32x16 operand rows (lane%32) and k-octet (lane/32) therefore reads
 //     16 bytes at lane*16 from a 1 KB block: global loads are fully coalesced and
-//     LDS reads are conflict-free, with no swizzle.
+//     LDS reads are conflict-free, with no swizzle.  The operand rows of MFMA 16x16x32 (lane%16, k-octet lane/16)
+//     are four runs of 256 bytes, 512 apart.
 //       element (r, k) of an [R, K] matrix, K % 8 == 0:
 //         ((r/32) * (K/8) + k/8) * 256 + (r%32) * 8 + k%8
 //
