@@ -559,7 +559,8 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // (128 x 160) is for batches of 129 .. 160 rows, e.g. 30 devices x 5 draft rows: one token tile
 // instead of a full and a nearly empty one.
 // Waves: 64 x 128 and the like each, 12 operand reads for 32 MFMAs, where that makes eight wave tiles of whole 32-row panels; two
-// halves of K otherwise (192 x 128: 96 x 64 in halves of K 48.2 us, 96 x 32 53.7 us, on gate/up of the 7B shape at 256 rows).
+// halves of K otherwise (192 x 128: 96 x 64 in halves of K 48.2 us, 96 x 32 53.7 us, on gate/up of the 7B shape at 256 rows), unless
+// the weight stream decides (128 x 160 at 150 rows, weights from HBM: O 15.1 us against 16.4 in halves of K, down 25.7 against 27.0).
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
 #define HAT_FOR_TILES(X, EPI)          \
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   X(20, 256, 224, 4, 2, 1, 32, 4, EPI) \
   X(21, 256, 192, 4, 2, 1, 32, 4, EPI) \
   X(22, 256, 160, 4, 2, 1, 32, 4, EPI) \
-  X(23, 128, 160, 2, 2, 2, 64, 3, EPI)
+  X(23, 128, 160, 4, 2, 1, 64, 3, EPI)
 constexpr int kNumLdsTiles = 24;
 // the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
 // 32 x 96 measured level with or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
