@@ -310,8 +310,8 @@ hat_status_t hat_mid_debug_create_host_only(const hat_mid_config_t* cfg, hat_mid
  * row or -1, segment start, first batch row, cache length, page-list offset, and for verify items
  * two words of per-row visibility bytes) and the split-KV merge items (8 words: first batch row,
  * rows, partial row of split 0, splits, partial rows between splits, 3 unused); cap_items bounds
- * each item array.  Partial rows of chunk items of at most 32 rows that stream the cache are held in fp32 and numbered after the
- * capacity of all others, which are held in fp16.  The segments' hidden pointers are checked for NULL only. */
+ * each item array.  Partial rows of chunk items that stream the cache are held in fp32 and numbered after the capacity of
+ * all others, which are held in fp16.  The segments' hidden pointers are checked for NULL only. */
 hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int32_t n_segs, int32_t* pos,
                                 int32_t* kv_dst, int32_t cap_rows, int32_t* chunk_items, int32_t* n_chunk_items,
                                 int32_t* verify_items, int32_t* n_verify_items, int32_t* merge_items,

@@ -66,7 +66,7 @@ struct Shapes {
   int verify_target;      // workgroups a verify-attention launch should reach
   int chunk_items_cap, verify_items_cap, merge_cap;
   int part_rows_cap;
-  int part32_cap;         // fp32 partial rows (narrow chunk items); their numbers follow those of the part_rows_cap others
+  int part32_cap;         // fp32 partial rows (chunk items that stream the cache); their numbers follow those of the part_rows_cap others
   int gemm_part_rows;     // rows of the split-K partial-sum buffer
   size_t plan_words;
 };
@@ -552,7 +552,7 @@ struct StepPlan {
   int T = 0, S = 0, n_append = 0;
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_vi = 0, o_mi = 0, words = 0;
-  int n_citems = 0, n_narrow = 0, n_vitems = 0, n_mitems = 0;
+  int n_citems = 0, n_narrow = 0, stream_blocks = 0, n_vitems = 0, n_mitems = 0;
 };
 
 // Host half of a step: validates every segment, commits the page movements, and writes the plan
@@ -733,8 +733,9 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // narrow item is so long that the common launch, which does not split it, would wait for it.  Measured in whole layers over 30
     // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
     // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
-    double total_cost = 0, narrow_cost = 0;
-    long narrow_keys = 0;
+    double total_cost = 0, narrow_cost = 0, stream_cost = 0, narrow_stream = 0;   // (rows x visible keys; streamed: in whole blocks of rows)
+    long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
+    int item_blocks = 0;
     int narrow_longest = 0;
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
@@ -742,17 +743,41 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
         const int need = segs[i].start_pos + q0 + nq;
         const double cost = (double)nq * (need - 0.5 * nq);
+        const int nb = (nq + HAT_NARROW_QROWS - 1) / HAT_NARROW_QROWS;
         if (nq > HAT_NARROW_QROWS) {
           total_cost += cost;
+          stream_cost += nb * HAT_NARROW_QROWS * (need - 0.5 * nq);
+          blocks += nb;
+          item_blocks = std::max(item_blocks, nb);
         } else {
           narrow_cost += cost;
+          narrow_stream += HAT_NARROW_QROWS * (need - 0.5 * nq);
+          ++narrow_blocks;
           narrow_keys += need;
           narrow_longest = std::max(narrow_longest, need);
         }
       }
     }
     const bool stream_narrow = total_cost == 0 || narrow_longest >= 1536;
-    if (!stream_narrow) total_cost += narrow_cost;
+    if (!stream_narrow) {
+      total_cost += narrow_cost;
+      stream_cost += narrow_stream;
+      blocks += narrow_blocks;
+    }
+    // Larger items are staged through LDS, cut along the keys and merged; or they stream the cache too, 32 rows to a
+    // workgroup and the keys whole as a rule.  Staging moves an eighth of the bytes, but its workgroups of 256 rows leave waves idle on
+    // shorter items, fill the chip in coarse rounds, and need the merge.  The line is where the two are level; attention
+    // and merge in us, staged -> streamed, against rows x keys x heads in millions (7B shape if not said otherwise):
+    //   1 x 64 over 1000: 26.7 -> 18.7 (2)      1 x 256 over 1280: 30.9 -> 20.0 (9)     1 x 512 over 1512: 53.0 -> 33.8 (21)
+    //   3 x 410 over 1900, hd 64: 69.7 -> 52.2 (34)     4 x 128 over 2100, 13B: 84 -> 71 (42)     1 x 256 over 7256: 77 -> 71 (58)
+    //   20 x 64 over 1564: 158 -> 132 (63)      1 x 512 over 4512: 94 -> 82 (70)        8 x 64 over 4160, 13B: 179 -> 169 (85)
+    //   3 x 512 over 2012: 127 -> 108 (86)      8 x 128 over 3128: 130 -> 132 (100)     4 x 256 over 3256: 122 -> 121 (102)
+    //   6 x 256 over 2256: 124 -> 131 (105)     2 x 256 over 5256, 13B: 118 -> 131 (105)    10 x 256 over 2256: 188 -> 207 (174)
+    // A raised attn_target asks for many key ranges, a lowered one for few workgroups.
+    const double work = stream_cost * s.H * s.hd / 128;
+    const bool stream_wide = item_blocks > 0 && s.attn_target <= 256 && work <= 95e6 * s.attn_target / 256;
+    sp->stream_blocks = stream_wide ? item_blocks : 0;
+    const int free_ranges = std::max(1, 256 / (int)std::min<long>(256, std::max<long>(1, blocks * s.H)));
     if (total_cost > 0 || narrow_keys > 0) {
       const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
       const double slots = std::max(1, s.attn_target / s.H);
@@ -765,9 +790,17 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           const double cost = (double)nq * (need - 0.5 * nq);
           const bool narrow = stream_narrow && nq <= HAT_NARROW_QROWS;
           int ns = narrow ? (int)((need + narrow_step - 1) / narrow_step) : (int)std::ceil(cost / cost_cap);
+          if (stream_wide && !narrow) {
+            // A wave takes about 2.4 us for 32 keys, a merge 6 to 7.  Where CUs are free, an item is cut if that saves more
+            // than it costs: 64 rows over 4064 keys 46 us whole, 30.6 + 6.1 in two ranges, 21.6 + 6.2 in four.  (Not next to narrow
+            // items, whose key ranges have the fp32 partial rows.)
+            ns = stream_narrow && narrow_keys > 0 ? 1 : std::min(free_ranges, 8);
+            if (need / 32.0 / 8 * 2.4 * (1.0 - 1.0 / ns) < 8.0) ns = 1;
+          }
           ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), narrow ? 32 : 16));
-          int& prow = narrow ? part_row32 : part_row;
-          const int prow_end = narrow ? s.part_rows_cap + s.part32_cap : s.part_rows_cap;
+          const bool fp32 = narrow || stream_wide;
+          int& prow = fp32 ? part_row32 : part_row;
+          const int prow_end = fp32 ? s.part_rows_cap + s.part32_cap : s.part_rows_cap;
           if ((int)citems.size() + ns > s.chunk_items_cap - 1 || prow + ns * nq > prow_end ||
               (int)mitems.size() + 9 >= s.merge_cap)
             ns = 1;
@@ -892,7 +925,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.part32_row0 = s.part_rows_cap;
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
-      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
+      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow; a.stream_blocks = sp.stream_blocks;
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
     if (sp.n_vitems > 0) {

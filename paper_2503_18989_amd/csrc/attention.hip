@@ -163,10 +163,16 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // columns of the MFMA are rows, so the stream pays for the same arithmetic and only the merge at the end grows.
 // Narrow items are bound by the cache stream and by latency, not by the matrix pipe: 8 x 32 rows over 4096 keys of the 13B
 // shape 164 -> 118 .. 121 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 20.8 us with the merge.  From 33 rows on every
-// form of this kernel that was built (two row blocks per wave, two sets of waves, two workgroups) measured level with or
+// form of this kernel that holds more rows per workgroup (two row blocks per wave, two sets of waves) measured level with or
 // behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
-template <int HD, bool KVF16, int ROWS>
-__global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
+// BLOCKS: chunk items of any size, a workgroup for each 32 of their rows (rblocks of them per item, idle ones leave at once).  The
+// row blocks of an item read the same pages, so they run on one XCD, next to each other, and without the non-temporal hint: 30.9 ->
+// 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 161 -> 140 for 1024 over 4096 of the 13B shape, 36.6 -> 21.6 for 3 x
+// 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
+// 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's key splits and merge.
+// NW waves share the keys: 8 where one workgroup per CU is all there is.
+template <int HD, bool KVF16, int ROWS, int NW, bool BLOCKS>
+__global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a, int rblocks) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
   constexpr int NC = HD / 32;  // 32-row blocks of O^T
   constexpr int REC = 2 * 16 * HD;  // elements of one (page, head) record
@@ -176,8 +182,23 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
   __shared__ __attribute__((aligned(16))) float lds_o[4][NARROW ? HD * (ROWS + 1) : ROWS * HD];
   __shared__ float lds_m[4][ROWS], lds_l[4][ROWS];
 
-  const HatAttnItem it = a.items[blockIdx.x];
-  const int head = blockIdx.y;
+  static_assert(!BLOCKS || NARROW, "row blocks of 32");
+  int item = blockIdx.x, head = blockIdx.y, rb = 0;
+  if constexpr (BLOCKS) {   // a contiguous run of (head, item, row block) per XCD, as consecutive workgroup ids go round the XCDs
+    const int total = a.H * a.n_items * rblocks, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
+    const int b = x * per + (x < rem ? x : rem) + (int)blockIdx.x / 8;
+    rb = rblocks - 1 - b % rblocks;   // the block with the most keys first
+    item = b / rblocks % a.n_items;
+    head = b / rblocks / a.n_items;
+  }
+  HatAttnItem it = a.items[item];
+  if constexpr (BLOCKS) {
+    it.q0 += rb * ROWS;
+    it.nq -= rb * ROWS;
+    if (it.nq <= 0) return;
+    it.nq = it.nq < ROWS ? it.nq : ROWS;
+    if (it.part_row >= 0) it.part_row += rb * ROWS;
+  }
   const SegInfo sg = seg_info(p, it);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, n = lane & 31;
@@ -218,16 +239,17 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
     recA = pool + (size_t)sg.pt[ia] * page_stride;
     recB = pool + (size_t)sg.pt[ib] * page_stride;
   };
+  auto page_load = [](const u32x4* q) { return BLOCKS ? *q : stream_load(q); };
   auto load_k = [&]() {
     const kv_t* krec = (n < 16) ? recA : recB;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) kraw[s] = stream_load((const u32x4*)(krec + ((2 * s + half) * 16 + (n & 15)) * 8));
+    for (int s = 0; s < NS; ++s) kraw[s] = page_load((const u32x4*)(krec + ((2 * s + half) * 16 + (n & 15)) * 8));
   };
   auto load_v = [&]() {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      varaw[c] = stream_load((const u32x4*)(recA + 16 * HD + c * 512 + lane * 8));
-      vbraw[c] = stream_load((const u32x4*)(recB + 16 * HD + c * 512 + lane * 8));
+      varaw[c] = page_load((const u32x4*)(recA + 16 * HD + c * 512 + lane * 8));
+      vbraw[c] = page_load((const u32x4*)(recB + 16 * HD + c * 512 + lane * 8));
     }
   };
   int pp = pair0 + wave;
@@ -236,7 +258,7 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
     load_k();
     load_v();
   }
-  for (; pp < pair1; pp += 4) {
+  for (; pp < pair1; pp += NW) {
     const int key0 = pp << 5;
     f32x16 sacc;
 #pragma unroll
@@ -249,8 +271,8 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
       va[c] = kv_to_f16<KVF16>(varaw[c]);
       vb[c] = kv_to_f16<KVF16>(vbraw[c]);
     }
-    if (pp + 4 < pair1) {
-      page_recs(pp + 4);
+    if (pp + NW < pair1) {
+      page_recs(pp + NW);
       load_k();
       load_v();
     }
@@ -284,8 +306,37 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
   }
   l_run += __shfl_xor(l_run, 32);
 
-  // merge the four waves (each saw a disjoint quarter of the keys)
-  if (n < it.nq) {
+  if constexpr (NW == 8) {   // waves 4 .. 7 hand their state to waves 0 .. 3, lane by lane
+    static_assert(sizeof(lds_o) >= 4 * 64 * NC * 16 * sizeof(float), "four waves' accumulators");
+    f32x4* buf = (f32x4*)&lds_o[0][0] + (wave & 3) * (NC * 4 * 64) + lane;
+    __shared__ float2 lds_ml[4][64];
+    if (wave >= 4) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) buf[(c * 4 + q) * 64] = f32x4{o[c][4 * q], o[c][4 * q + 1], o[c][4 * q + 2], o[c][4 * q + 3]};
+      lds_ml[wave - 4][lane] = make_float2(m_run, l_run);
+    }
+    __syncthreads();
+    if (wave < 4) {
+      const float2 other = lds_ml[wave][lane];
+      const float m = fmaxf(m_run, other.x), ms = m == -INFINITY ? 0.f : m;
+      const float fa = exp2f(m_run - ms), fb = exp2f(other.x - ms);
+      m_run = m;
+      l_run = l_run * fa + other.y * fb;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = buf[(c * 4 + q) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[c][4 * q + e] = o[c][4 * q + e] * fa + v[e] * fb;
+        }
+    }
+    __syncthreads();
+  }
+  // merge the four waves (each saw a disjoint share of the keys)
+  if (wave < 4 && n < it.nq) {
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -297,7 +348,7 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
   }
   __syncthreads();
   const int cells = (NARROW ? ROWS : it.nq) * (HD / 4);   // (row, 4 features) each
-  for (int idx = threadIdx.x; idx < cells; idx += 256) {
+  for (int idx = threadIdx.x; idx < cells; idx += NW * 64) {
     const int q = NARROW ? idx % ROWS : idx / (HD / 4), e = (NARROW ? idx / ROWS : idx % (HD / 4)) * 4;
     if (q >= it.nq) continue;
     float M = fmaxf(fmaxf(lds_m[0][q], lds_m[1][q]), fmaxf(lds_m[2][q], lds_m[3][q]));
@@ -312,7 +363,7 @@ __global__ __launch_bounds__(256, 2) void attn_verify_kernel(HatPlanDev p, HatAt
       for (int x = 0; x < 4; ++x) acc[x] += lds_o[w][q * RSTR + (e + x) * FSTR] * f;
     }
     // a partial result travels normalised by its own sum, and the merge weighs it by that sum: in the
-    // activation type for a verify item; in fp32 for a narrow one, whose key ranges are cut for the stream's sake
+    // activation type for a verify item; in fp32 for a chunk item, whose key ranges are cut for the stream's sake
     // where larger items keep one accumulator.  A key range that this row does not see at all has L = 0.
     const float inv = (it.part_row < 0 || L > 0.f) ? 1.0f / L : 0.f;
     f16x4 ov;
@@ -780,20 +831,29 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
 
 }  // namespace
 
-template <int ROWS>
-static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
-  dim3 grid(a.n_items, a.H);
-  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS><<<grid, 256, 0, st>>>(p, a);
-  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS><<<grid, 256, 0, st>>>(p, a);
+template <int ROWS, int NW, bool BLOCKS>
+static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, int rblocks, hipStream_t st) {
+  const dim3 grid = BLOCKS ? dim3(a.n_items * a.H * rblocks) : dim3(a.n_items, a.H);
+  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
+  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
+  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
+  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   const int wide = a.n_items - a.n_narrow;
-  if (wide > 0) {
+  if (wide > 0 && a.stream_blocks > 0) {
+    HatAttn w = a;
+    w.n_items = wide;
+    // One workgroup of eight waves or two of four fill a CU: eight waves where there is no second workgroup, or where their
+    // shorter rounds leave less of the last one empty (640 workgroups of 8 x 64 rows over 4160 keys: 165 us against 177).
+    const int wgs = wide * a.H * a.stream_blocks;
+    const hipError_t e = wgs <= 256 || (a.hd == 128 && wgs > 512 && wgs <= 768) ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, a.stream_blocks, st)
+                                                                              : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, a.stream_blocks, st);
+    if (e != hipSuccess) return e;
+  } else if (wide > 0) {
     dim3 grid(wide, a.H);
     if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
@@ -805,14 +865,14 @@ hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStrea
     HatAttn n = a;
     n.items = a.items + wide;
     n.n_items = a.n_narrow;
-    return launch_stream<HAT_NARROW_QROWS>(p, n, st);
+    return launch_stream<HAT_NARROW_QROWS, 4, false>(p, n, 1, st);
   }
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_verify(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  return launch_stream<HAT_MAX_VERIFY_ROWS>(p, a, st);
+  return launch_stream<HAT_MAX_VERIFY_ROWS, 4, false>(p, a, 1, st);
 }
 
 hipError_t hat_launch_attn_verify_probe(const HatPlanDev& p, const HatAttn& a, uint32_t* sink, hipStream_t st) {

@@ -157,12 +157,13 @@ struct HatAttn {
   int kv_f16;                // cache elements are fp16 (else bf16, widened to fp16 on their way to the MFMA)
   act_t* outP;               // P32 [., d]
   act_t* part_o;             // [part rows][H][hd] partial outputs, each normalised by its own sum
-  float* part_o32;           // the same of the partial rows numbered from part32_row0 on, in fp32: narrow chunk items
+  float* part_o32;           // the same of the partial rows numbered from part32_row0 on, in fp32: chunk items that stream the cache
   int part32_row0;
   float2* part_ml;           // [part rows][H] (running max in log2 units, sum)
   const HatAttnItem* items;
   int n_items;
   int n_narrow;              // chunk items: the last n_narrow of them have at most HAT_NARROW_QROWS rows
+  int stream_blocks;         // > 0: the other chunk items stream the cache too, in that many blocks of HAT_NARROW_QROWS rows at most
   int H, hd, d;
   int n_pages;               // pool capacity (pages per head and layer)
 };
