@@ -560,7 +560,8 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // instead of a full and a nearly empty one.
 // Waves: 64 x 128 and the like each, 12 operand reads for 32 MFMAs, where that makes eight wave tiles of whole 32-row panels; two
 // halves of K otherwise (192 x 128: 96 x 64 in halves of K 48.2 us, 96 x 32 53.7 us, on gate/up of the 7B shape at 256 rows), unless
-// the weight stream decides (128 x 160 at 150 rows, weights from HBM: O 15.1 us against 16.4 in halves of K, down 25.7 against 27.0).
+// the weight stream decides (weights from HBM, 128 x 160 at 150 rows: O 15.1 us against 16.4 in halves of K, down 25.7 against 27.0; 128 x 64 at 56 rows: 12.8
+// against 13.2 and 22.2 against 22.5).
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
 #define HAT_FOR_TILES(X, EPI)          \
@@ -571,12 +572,12 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   X(4, 128, 128, 2, 4, 1, 64, 4, EPI)  \
   X(5, 256, 64, 4, 1, 2, 64, 3, EPI)   \
   X(6, 256, 32, 4, 1, 2, 64, 4, EPI)   \
-  X(7, 128, 64, 2, 2, 2, 64, 4, EPI)   \
+  X(7, 128, 64, 2, 4, 1, 64, 4, EPI)   \
   X(8, 128, 32, 2, 1, 2, 64, 4, EPI)   \
   X(9, 64, 256, 1, 4, 2, 64, 3, EPI)   \
   X(10, 128, 128, 2, 2, 2, 64, 4, EPI) \
   X(11, 128, 128, 2, 4, 1, 32, 4, EPI) \
-  X(12, 128, 64, 2, 4, 1, 64, 4, EPI)  \
+  X(12, 128, 64, 2, 2, 2, 64, 4, EPI)  \
   X(13, 192, 128, 2, 2, 2, 64, 3, EPI) \
   X(14, 96, 128, 1, 4, 2, 64, 4, EPI)  \
   X(15, 96, 256, 1, 4, 2, 64, 3, EPI)  \
