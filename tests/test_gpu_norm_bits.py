@@ -47,3 +47,32 @@ def test_first_norm_bits(d, heads, T, profiled):
     gain = to_np(dev_weights(w)["attn_norm"]).astype(F)
     assert np.array_equal(got, norm_row_bits(x, gain, cfg["rms_eps"]))
     m.close()
+
+
+@pytest.mark.parametrize("d,T", [(192, 5), (2112, 33), (4160, 5), (6208, 17), (8192, 3)])   # one to four octets per thread, ragged and whole
+def test_norm_folds_partial_sums(d, T):
+    """The second norm adds the O product's partial sums (none, one group of four loads, a group and a remainder) to the residual.  A
+    zero down projection hands that residual out, so its norm can be stated bit for bit.  Against the unsplit product only the order
+    of the fp32 sums over K changes: each of the K terms' additions rounds by at most 2^-24 of the sum of their sizes."""
+    import torch
+    from paper_2503_18989_amd import HatMid, Segment
+    heads, f = d // 64, 64
+    cfg = dict(name="n", n_layers=1, d_model=d, n_heads=heads, head_dim=64, d_ffn=f, rms_eps=1e-6, rope_theta=1e4)
+    g = torch.Generator().manual_seed(d)
+    def mat(n, k):
+        return torch.randn((n, k), generator=g).mul_(0.02).to(torch.bfloat16)
+    w = dict(attn_norm=torch.ones(d, dtype=torch.bfloat16), ffn_norm=(1 + 0.1 * torch.randn(d, generator=g)).to(torch.bfloat16), wq=mat(d, d),
+             wk=mat(d, d), wv=mat(d, d), wo=mat(d, d), w_gate=mat(f, d), w_up=mat(f, d), w_down=torch.zeros((d, f), dtype=torch.bfloat16))
+    m = HatMid(cfg, [{k: v.cuda() for k, v in w.items()}], n_pages=8, max_devices=1, max_step_tokens=64, max_pos=128, io_dtype="f32")
+    x = torch.randn((T, d), generator=g)
+    whole = bound = None
+    for ks in (1, 2, 3, 4, 5, 6):
+        m.force_gemm(1, 4, ks)
+        out = to_np(m.forward([Segment(0, hi.CHUNK, 0, x.cuda())])[0]).astype(F)
+        got = to_np(m.debug_dump("xnorm2", T)).astype(np.float16)
+        assert np.array_equal(got, norm_row_bits(out, w["ffn_norm"].float().numpy(), cfg["rms_eps"])), ks
+        if whole is None:
+            attn = np.abs(to_np(m.debug_dump("attn", T)).astype(np.float64))
+            whole, bound = out, 2.0 ** -24 * d * (attn @ np.abs(w["wo"].float().numpy().astype(np.float64)).T + np.abs(x.numpy()))
+        assert np.all(np.abs(out.astype(np.float64) - whole) <= 2 * bound), ks
+    m.close()
