@@ -781,9 +781,15 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   for (int c = 0; c < kNumLdsTiles; ++c) {
     const TileInfo& q = kTiles[c];
     if (!q.planned) continue;
-    // 160/192/224-row token tiles: large batches only, except the 128 x 160 tile (23), which exists for batches
-    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %)
-    if (large ? q.eff == 0.f : ((q.bt & (q.bt - 1)) != 0 && !(c == 23 && g.T > 128 && g.T <= 160))) continue;
+    // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
+    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %).  Above 256 rows a third
+    // 128-row token tile or a second 256-row one is as empty.  The four products and the norms of a layer in us, without these tiles and with
+    // them, at 257, 320 and 365 rows: 7B shape 219 -> 193, 229 -> 202 (gate/up 84.1 -> 72.9 with 256 x 160, down 45.3 -> 39.8), 228 -> 227; 13B shape
+    // 282 -> 257, 301 -> 267, 305 -> 287; 8192 x 28672 760 -> 638, 823 -> 656, 814 -> 728; head dim 64 92.6 -> 89.7, 96.4 -> 92.3, 103.7 -> 102.8;
+    // 1024 x 2816 level.  No slower at any of nine batch sizes of seven widths.  384 rows, which leave no 128-row tile
+    // partly empty, keep those.
+    const bool tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && g.T > 128 && g.T <= 160;
+    if (large ? q.eff == 0.f : (q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
     const int max_split = (g.epilogue == HAT_EPI_RESID && g.part) ? 16 : 1;
     const int lds = q.nstage * (q.bf + q.bt) * q.bkt * 2;
