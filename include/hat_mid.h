@@ -321,6 +321,11 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
  * verify kernel's manner instead of staging it: items of at most 32 rows, unless they ride along with larger ones. */
 hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
 
+/* The other chunk items of that plan, cut into blocks of at most 32 rows, where these stream the cache as well (12 words each like the
+ * items, in the order of launch); none where they stage it.  blocks may be NULL to ask for the number only; HAT_EINVAL if there are
+ * more than cap_blocks. */
+hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks);
+
 /* ---- tuning aid ------------------------------------------------------------------ */
 
 /* Forces the tile shape and K split of one GEMM class in later forwards

@@ -64,7 +64,7 @@ struct Shapes {
   int Tcap;               // row capacity of activation buffers (multiple of 256)
   int attn_target;        // workgroups a chunk-attention launch should reach
   int verify_target;      // workgroups a verify-attention launch should reach
-  int chunk_items_cap, verify_items_cap, merge_cap;
+  int chunk_items_cap, chunk_blocks_cap, verify_items_cap, merge_cap;
   int part_rows_cap;
   int part32_cap;         // fp32 partial rows (chunk items that stream the cache); their numbers follow those of the part_rows_cap others
   int gemm_part_rows;     // rows of the split-K partial-sum buffer
@@ -99,6 +99,8 @@ Shapes make_shapes(const hat_mid_config_t& c) {
   // only as far as they allow -- the planner checks every capacity before it splits
   const int per_head = (kCapAttnTarget + s.H - 1) / s.H;
   s.chunk_items_cap = 2 * per_head + s.Tcap / 128 + c.max_devices + 2;
+  // row blocks of the chunk items that stream the cache: every key range once more, in launches that stay within a workgroup per CU
+  s.chunk_blocks_cap = s.Tcap / HAT_NARROW_QROWS + c.max_devices + 256;
   s.verify_items_cap = 2 * per_head + c.max_devices + 2;
   s.merge_cap = s.Tcap / 16 + s.Tcap / 128 + 2 * c.max_devices + 2;
   // n narrow items wanted: key ranges of sum / n keys leave fewer than 2 n + 1 ranges in the items that have more than one
@@ -106,7 +108,7 @@ Shapes make_shapes(const hat_mid_config_t& c) {
   s.part_rows_cap = HAT_CHUNK_QROWS * (2 * per_head + 2) + HAT_MAX_VERIFY * s.verify_items_cap;
   s.gemm_part_rows = 4096;
   s.plan_words = (size_t)3 * s.Tcap + 8 * ((size_t)s.Tcap / 16 + 2 * (size_t)c.max_devices + 2) + 8 * (size_t)c.max_devices + 16 + (size_t)c.n_pages + c.max_devices +
-                 12 * ((size_t)s.chunk_items_cap + s.verify_items_cap) + 8 * (size_t)s.merge_cap + 64;
+                 12 * ((size_t)s.chunk_items_cap + s.chunk_blocks_cap + s.verify_items_cap) + 8 * (size_t)s.merge_cap + 64;
   return s;
 }
 
@@ -237,6 +239,8 @@ struct hat_mid {
   bool host_only = false;                  // built by hat_mid_debug_create_host_only: no GPU memory, no HIP calls
   std::vector<int32_t> host_plan;          // its plan words
   int host_narrow = 0;                     // StepPlan::n_narrow of its last plan
+  size_t host_blocks = 0;                  // StepPlan::o_cb
+  int host_n_blocks = 0;                   // and n_cblocks of it
   int force_tile[4] = {-1, -1, -1, -1};   // tuning overrides per GEMM class (qkv, o, gate/up, down)
   int force_ksplit[4] = {0, 0, 0, 0};
 
@@ -551,8 +555,8 @@ hat_status_t hat_mid_kv_query(const hat_mid_t* h, int32_t device_id, int32_t* kv
 struct StepPlan {
   int T = 0, S = 0, n_append = 0;
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
-  size_t o_ci = 0, o_vi = 0, o_mi = 0, words = 0;
-  int n_citems = 0, n_narrow = 0, stream_blocks = 0, n_vitems = 0, n_mitems = 0;
+  size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
+  int n_citems = 0, n_narrow = 0, n_cblocks = 0, n_vitems = 0, n_mitems = 0;
 };
 
 // Host half of a step: validates every segment, commits the page movements, and writes the plan
@@ -639,7 +643,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
   for (int i = 0; i < S; ++i) n_append += ((segs[i].start_pos + segs[i].n - 1) >> 4) - (segs[i].start_pos >> 4) + 1;
   const size_t o_app = take(8 * (size_t)n_append, 4);
 
-  std::vector<HatAttnItem> citems, vitems;
+  std::vector<HatAttnItem> citems, cblocks, vitems;
   std::vector<HatMergeItem> mitems;
   {
     int t = 0, pt = 0;
@@ -735,7 +739,6 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
     double total_cost = 0, narrow_cost = 0, stream_cost = 0, narrow_stream = 0;   // (rows x visible keys; streamed: in whole blocks of rows)
     long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
-    int item_blocks = 0;
     int narrow_longest = 0;
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
@@ -748,7 +751,6 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           total_cost += cost;
           stream_cost += nb * HAT_NARROW_QROWS * (need - 0.5 * nq);
           blocks += nb;
-          item_blocks = std::max(item_blocks, nb);
         } else {
           narrow_cost += cost;
           narrow_stream += HAT_NARROW_QROWS * (need - 0.5 * nq);
@@ -758,7 +760,8 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         }
       }
     }
-    const bool stream_narrow = total_cost == 0 || narrow_longest >= 1536;
+    const bool any_wide = blocks > 0;
+    const bool stream_narrow = !any_wide || narrow_longest >= 1536;
     if (!stream_narrow) {
       total_cost += narrow_cost;
       stream_cost += narrow_stream;
@@ -775,8 +778,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     //   6 x 256 over 2256: 124 -> 131 (105)     2 x 256 over 5256, 13B: 118 -> 131 (105)    10 x 256 over 2256: 188 -> 207 (174)
     // A raised attn_target asks for many key ranges, a lowered one for few workgroups.
     const double work = stream_cost * s.H * s.hd / 128;
-    const bool stream_wide = item_blocks > 0 && s.attn_target <= 256 && work <= 95e6 * s.attn_target / 256;
-    sp->stream_blocks = stream_wide ? item_blocks : 0;
+    const bool stream_wide = any_wide && s.attn_target <= 256 && work <= 95e6 * s.attn_target / 256;
     const int free_ranges = std::max(1, 256 / (int)std::min<long>(256, std::max<long>(1, blocks * s.H)));
     if (total_cost > 0 || narrow_keys > 0) {
       const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
@@ -829,8 +831,19 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
     const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [&](const HatAttnItem& a) { return !stream_narrow || a.nq > HAT_NARROW_QROWS; });
     sp->n_narrow = (int)(citems.end() - narrow0);
+    if (stream_wide) {
+      for (auto it = citems.begin(); it != narrow0; ++it)
+        for (int r0 = (it->nq - 1) / HAT_NARROW_QROWS * HAT_NARROW_QROWS; r0 >= 0; r0 -= HAT_NARROW_QROWS) {   // the block with the most keys first
+          HatAttnItem b = *it;
+          b.q0 += r0;
+          b.nq = std::min(HAT_NARROW_QROWS, it->nq - r0);
+          if (b.part_row >= 0) b.part_row += r0;
+          cblocks.push_back(b);
+        }
+    }
   }
-  const size_t o_ci = take(12 * citems.size(), 4), o_vi = take(12 * vitems.size(), 4), o_mi = take(8 * mitems.size(), 8);
+  const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
+  const size_t o_mi = take(8 * mitems.size(), 8);
   const size_t plan_cap = h->plan_limit ? std::min(h->plan_limit, s.plan_words) : s.plan_words;
   if (w > plan_cap) {
     undo_rollback(h);
@@ -838,14 +851,15 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
   }
   static_assert(sizeof(HatAttnItem) == 48 && sizeof(HatMergeItem) == 32, "plan item sizes");
   if (!citems.empty()) memcpy(&P[o_ci], citems.data(), citems.size() * sizeof(HatAttnItem));
+  if (!cblocks.empty()) memcpy(&P[o_cb], cblocks.data(), cblocks.size() * sizeof(HatAttnItem));
   if (!vitems.empty()) memcpy(&P[o_vi], vitems.data(), vitems.size() * sizeof(HatAttnItem));
   if (!mitems.empty()) memcpy(&P[o_mi], mitems.data(), mitems.size() * sizeof(HatMergeItem));
 
   sp->T = T; sp->S = S; sp->n_append = n_append;
   sp->o_pos = o_pos; sp->o_dst = o_dst; sp->o_tseg = o_tseg; sp->o_toff = o_toff; sp->o_sstart = o_sstart;
   sp->o_spt = o_spt; sp->o_in = o_in; sp->o_out = o_out; sp->o_pt = o_pt; sp->o_app = o_app;
-  sp->o_ci = o_ci; sp->o_vi = o_vi; sp->o_mi = o_mi; sp->words = w;
-  sp->n_citems = (int)citems.size(); sp->n_vitems = (int)vitems.size(); sp->n_mitems = (int)mitems.size();
+  sp->o_ci = o_ci; sp->o_cb = o_cb; sp->o_vi = o_vi; sp->o_mi = o_mi; sp->words = w;
+  sp->n_citems = (int)citems.size(); sp->n_cblocks = (int)cblocks.size(); sp->n_vitems = (int)vitems.size(); sp->n_mitems = (int)mitems.size();
   return HAT_OK;
 }
 
@@ -925,7 +939,8 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.part32_row0 = s.part_rows_cap;
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
-      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow; a.stream_blocks = sp.stream_blocks;
+      a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
+      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks;
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
     if (sp.n_vitems > 0) {
@@ -1210,7 +1225,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
   if (n_chunk_items) *n_chunk_items = 0;
   if (n_verify_items) *n_verify_items = 0;
   if (n_merge_items) *n_merge_items = 0;
-  h->host_narrow = 0;
+  h->host_narrow = h->host_n_blocks = 0;
   if (n_segs == 0) return HAT_OK;
   try {
     StepPlan sp;
@@ -1219,6 +1234,8 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     if (rc != HAT_OK) return rc;
     undo_commit(h);
     h->host_narrow = sp.n_narrow;
+    h->host_blocks = sp.o_cb;
+    h->host_n_blocks = sp.n_cblocks;
     if (sp.T > cap_rows || std::max(sp.n_citems, std::max(sp.n_vitems, sp.n_mitems)) > cap_items)
       return fail(h, HAT_EINVAL, "output arrays too small for %d rows / %d, %d, %d items (the step has been planned)", sp.T,
                   sp.n_citems, sp.n_vitems, sp.n_mitems);
@@ -1240,6 +1257,15 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
 hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow) {
   if (!h || !h->host_only || !n_narrow) return HAT_EINVAL;
   *n_narrow = h->host_narrow;
+  return HAT_OK;
+}
+
+hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks) {
+  if (!h || !h->host_only || !n_blocks) return HAT_EINVAL;
+  *n_blocks = h->host_n_blocks;
+  if (!blocks) return HAT_OK;
+  if (h->host_n_blocks > cap_blocks) return HAT_EINVAL;
+  if (h->host_n_blocks > 0) memcpy(blocks, h->host_plan.data() + h->host_blocks, (size_t)h->host_n_blocks * sizeof(HatAttnItem));
   return HAT_OK;
 }
 

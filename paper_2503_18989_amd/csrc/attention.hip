@@ -165,14 +165,14 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // shape 164 -> 118 .. 121 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 20.8 us with the merge.  From 33 rows on every
 // form of this kernel that holds more rows per workgroup (two row blocks per wave, two sets of waves) measured level with or
 // behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
-// BLOCKS: chunk items of any size, a workgroup for each 32 of their rows (rblocks of them per item, idle ones leave at once).  The
+// BLOCKS: chunk items of any size, a workgroup for each 32 of their rows, which the planner lists as items of their own.  The
 // row blocks of an item read the same pages, so they run on one XCD, next to each other, and without the non-temporal hint: 30.9 ->
 // 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 161 -> 140 for 1024 over 4096 of the 13B shape, 36.6 -> 21.6 for 3 x
 // 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
 // 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's key splits and merge.
 // NW waves share the keys: 8 where one workgroup per CU is all there is.
 template <int HD, bool KVF16, int ROWS, int NW, bool BLOCKS>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a, int rblocks) {
+__global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
   constexpr int NC = HD / 32;  // 32-row blocks of O^T
   constexpr int REC = 2 * 16 * HD;  // elements of one (page, head) record
@@ -183,22 +183,14 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
   __shared__ float lds_m[4][ROWS], lds_l[4][ROWS];
 
   static_assert(!BLOCKS || NARROW, "row blocks of 32");
-  int item = blockIdx.x, head = blockIdx.y, rb = 0;
-  if constexpr (BLOCKS) {   // a contiguous run of (head, item, row block) per XCD, as consecutive workgroup ids go round the XCDs
-    const int total = a.H * a.n_items * rblocks, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
+  int item = blockIdx.x, head = blockIdx.y;
+  if constexpr (BLOCKS) {   // a contiguous run of (head, row block) per XCD, as consecutive workgroup ids go round the XCDs
+    const int total = a.H * a.n_items, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
     const int b = x * per + (x < rem ? x : rem) + (int)blockIdx.x / 8;
-    rb = rblocks - 1 - b % rblocks;   // the block with the most keys first
-    item = b / rblocks % a.n_items;
-    head = b / rblocks / a.n_items;
+    item = b % a.n_items;
+    head = b / a.n_items;
   }
-  HatAttnItem it = a.items[item];
-  if constexpr (BLOCKS) {
-    it.q0 += rb * ROWS;
-    it.nq -= rb * ROWS;
-    if (it.nq <= 0) return;
-    it.nq = it.nq < ROWS ? it.nq : ROWS;
-    if (it.part_row >= 0) it.part_row += rb * ROWS;
-  }
+  const HatAttnItem it = a.items[item];
   const SegInfo sg = seg_info(p, it);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, n = lane & 31;
@@ -832,26 +824,27 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
 }  // namespace
 
 template <int ROWS, int NW, bool BLOCKS>
-static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, int rblocks, hipStream_t st) {
-  const dim3 grid = BLOCKS ? dim3(a.n_items * a.H * rblocks) : dim3(a.n_items, a.H);
-  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
-  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
-  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
-  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a, rblocks);
+static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
+  const dim3 grid = BLOCKS ? dim3(a.n_items * a.H) : dim3(a.n_items, a.H);
+  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   const int wide = a.n_items - a.n_narrow;
-  if (wide > 0 && a.stream_blocks > 0) {
+  if (a.n_blocks > 0) {
     HatAttn w = a;
-    w.n_items = wide;
+    w.items = a.blocks;
+    w.n_items = a.n_blocks;
     // One workgroup of eight waves or two of four fill a CU: eight waves where there is no second workgroup, or where their
     // shorter rounds leave less of the last one empty (640 workgroups of 8 x 64 rows over 4160 keys: 165 us against 177).
-    const int wgs = wide * a.H * a.stream_blocks;
-    const hipError_t e = wgs <= 256 || (a.hd == 128 && wgs > 512 && wgs <= 768) ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, a.stream_blocks, st)
-                                                                              : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, a.stream_blocks, st);
+    const int wgs = a.n_blocks * a.H;
+    const hipError_t e = wgs <= 256 || (a.hd == 128 && wgs > 512 && wgs <= 768) ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, st)
+                                                                              : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, st);
     if (e != hipSuccess) return e;
   } else if (wide > 0) {
     dim3 grid(wide, a.H);
@@ -865,14 +858,14 @@ hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStrea
     HatAttn n = a;
     n.items = a.items + wide;
     n.n_items = a.n_narrow;
-    return launch_stream<HAT_NARROW_QROWS, 4, false>(p, n, 1, st);
+    return launch_stream<HAT_NARROW_QROWS, 4, false>(p, n, st);
   }
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_verify(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  return launch_stream<HAT_MAX_VERIFY_ROWS, 4, false>(p, a, 1, st);
+  return launch_stream<HAT_MAX_VERIFY_ROWS, 4, false>(p, a, st);
 }
 
 hipError_t hat_launch_attn_verify_probe(const HatPlanDev& p, const HatAttn& a, uint32_t* sink, hipStream_t st) {

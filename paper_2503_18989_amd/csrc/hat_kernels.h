@@ -163,7 +163,8 @@ struct HatAttn {
   const HatAttnItem* items;
   int n_items;
   int n_narrow;              // chunk items: the last n_narrow of them have at most HAT_NARROW_QROWS rows
-  int stream_blocks;         // > 0: the other chunk items stream the cache too, in that many blocks of HAT_NARROW_QROWS rows at most
+  const HatAttnItem* blocks; // n_blocks > 0: the other chunk items stream the cache too, as these items of at most HAT_NARROW_QROWS rows
+  int n_blocks;
   int H, hd, d;
   int n_pages;               // pool capacity (pages per head and layer)
 };

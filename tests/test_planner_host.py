@@ -273,3 +273,35 @@ def test_narrow_chunks_next_to_larger_ones_stream_only_when_long():
     lib.plan([(1, hi.VERIFY, 100, 8)])
     assert lib.narrow_items() == 0
     lib.close()
+
+
+def check_blocks(lib, plan):
+    """Streamed chunk items reach the launch as blocks of at most 32 rows: every row of every key range once, no empty block, the
+    blocks of a key range side by side with the one that sees most keys first."""
+    blocks = lib.blocks()
+    items = plan["chunk_items"][:len(plan["chunk_items"]) - lib.narrow_items()]
+    want = []
+    for it in items:
+        for r0 in reversed(range(0, it["nq"], 32)):
+            b = {k: it[k] for k in ("seg", "kv_begin", "kv_end", "start", "tok0", "kv_len", "pt_off")}
+            want.append(dict(b, q0=it["q0"] + r0, nq=min(32, it["nq"] - r0), part_row=it["part_row"] + r0 if it["part_row"] >= 0 else -1))
+    assert blocks == want
+    return len(blocks)
+
+
+@pytest.mark.parametrize("rows,start", [([33], 0), ([130, 64], 300), ([256] + [64] * 9, 500), ([257, 40, 7], 90), ([300], 1500), ([40, 17], 1700)])
+def test_streamed_chunks_are_listed_in_blocks_of_rows(rows, start):
+    lib, _ = both(3000, max_devices=16, max_step_tokens=2048, max_pos=2048)
+    if start:
+        for d in range(len(rows)):
+            lib.plan([(d, hi.CHUNK, 0, start)])
+    plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
+    n = check_blocks(lib, plan)
+    ranges = sum(-(-it["nq"] // 32) for it in plan["chunk_items"][:len(plan["chunk_items"]) - lib.narrow_items()])
+    assert n == ranges > 0                           # 26 blocks for 256 + 9 x 64 rows, where ten times the longest item's would be 80
+    lib.set_attn_targets(4096, 2048)                 # many key ranges: staged
+    plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
+    assert lib.blocks() == []
+    lib.plan([(0, hi.VERIFY, start, 5)])
+    assert lib.blocks() == []
+    lib.close()
