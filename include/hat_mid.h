@@ -323,8 +323,8 @@ hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
 
 /* The other chunk items of that plan, cut into blocks of at most 32 rows, where these stream the cache as well (12 words each like the
  * items, in the order of launch); none where they stage it.  blocks may be NULL to ask for the number only; HAT_EINVAL if there are
- * more than cap_blocks. */
-hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks);
+ * more than cap_blocks.  *waves (may be NULL): waves of a block's workgroup, 4 or 8; 0 without blocks. */
+hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks, int32_t* waves);
 
 /* ---- tuning aid ------------------------------------------------------------------ */
 

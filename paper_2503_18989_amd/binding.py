@@ -134,7 +134,7 @@ def load_library():
     lib.hat_mid_debug_plan_narrow.restype = i32
     lib.hat_mid_debug_plan_narrow.argtypes = [vp, pi]
     lib.hat_mid_debug_plan_blocks.restype = i32
-    lib.hat_mid_debug_plan_blocks.argtypes = [vp, pi, pi, i32]
+    lib.hat_mid_debug_plan_blocks.argtypes = [vp, pi, pi, i32, pi]
     f64 = C.c_double
     lib.hat_sched_create.restype = i32
     lib.hat_sched_create.argtypes = [C.POINTER(i32), i32, f64, C.POINTER(vp)]
@@ -423,8 +423,14 @@ class HatPlanner:
     def blocks(self, cap=4096):
         """The row blocks of the last plan's chunk items that stream the cache, narrow ones aside (hat_mid_debug_plan_blocks)."""
         n, raw = C.c_int32(), (C.c_int32 * (12 * cap))()
-        self._check(self.lib.hat_mid_debug_plan_blocks(self._handle, raw, C.byref(n), cap))
+        self._check(self.lib.hat_mid_debug_plan_blocks(self._handle, raw, C.byref(n), cap, None))
         return [dict(zip(self.ATTN_FIELDS, raw[12 * k:12 * k + 10])) for k in range(n.value)]
+
+    def block_waves(self):
+        """Waves of the workgroup that takes one of blocks(); 0 if there are none."""
+        n, w = C.c_int32(), C.c_int32()
+        self._check(self.lib.hat_mid_debug_plan_blocks(self._handle, None, C.byref(n), 0, C.byref(w)))
+        return w.value
 
     def release(self, device_id):
         self._check(self.lib.hat_mid_release(self._handle, device_id))

@@ -240,7 +240,7 @@ struct hat_mid {
   std::vector<int32_t> host_plan;          // its plan words
   int host_narrow = 0;                     // StepPlan::n_narrow of its last plan
   size_t host_blocks = 0;                  // StepPlan::o_cb
-  int host_n_blocks = 0;                   // and n_cblocks of it
+  int host_n_blocks = 0, host_block_waves = 0;   // n_cblocks and block_waves of it
   int force_tile[4] = {-1, -1, -1, -1};   // tuning overrides per GEMM class (qkv, o, gate/up, down)
   int force_ksplit[4] = {0, 0, 0, 0};
 
@@ -556,8 +556,43 @@ struct StepPlan {
   int T = 0, S = 0, n_append = 0;
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
-  int n_citems = 0, n_narrow = 0, n_cblocks = 0, n_vitems = 0, n_mitems = 0;
+  int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 8, n_vitems = 0, n_mitems = 0;
 };
+
+// Time in us of a launch of streamed row blocks with 8 or 4 waves each (the two template forms of attn_verify_kernel), `keys`
+// the keys that each block reads, `mbytes` the cache rows that the launch reads at least once.  One workgroup of eight waves, or two (head dim 64:
+// three) of four, are resident on a CU; a wave takes `step` for 32 keys, more as its CU fills, and a workgroup `block` beside them.  Fitted to
+// 2500 mixes of one to sixteen chunks of 20 .. 1024 rows over 0 .. 6000 keys with six head counts (error 5 .. 6 % on average), most of all to their order.
+// Eight waves shorten a workgroup, four get more out of a full CU and leave less of the chip idle in the last round.  us with 4 | 8
+// (workgroups; bf16 cache): 1 x 64 rows over 4000 keys of the 7B shape 64.9 | 46.0 (64), 1 x 256 over 1000 24.1 | 20.4 (256), 13B shape 29.8 | 33.1
+// (320), 8 x 64 over 4000 174 | 166 (640), 4 x 512 over 500 of the 7B shape 76.4 | 97.2 (2048), 4 x 128 over 2000 at head dim 64 34.0 | 36.1 (512).
+static double stream_us(const Shapes& s, int kv_f16, int waves, const std::vector<int>& keys, double mbytes) {
+  struct Cost { double launch, block, step, shared, per_mb; };
+  static const Cost k4[2][2] = {{{3.92, 3.30, 0.776, 0.005, 0.176}, {4.23, 2.70, 0.690, 0.005, 0.163}}, {{4.58, 4.44, 1.327, 0.357, 0.102}, {4.45, 3.65, 1.176, 0.437, 0.109}}};
+  static const Cost k8[2][2] = {{{4.91, 2.00, 1.069, 0, 0.126}, {4.79, 2.01, 0.826, 0, 0.143}}, {{4.52, 3.87, 1.831, 0, 0.090}, {3.96, 3.64, 1.686, 0, 0.102}}};
+  const Cost& c = (waves == 8 ? k8 : k4)[s.hd == 128][kv_f16 != 0];
+  const double n = (double)keys.size() * s.H, slots = waves == 8 ? 256 : s.hd == 128 ? 512 : 768;
+  std::vector<double> steps;
+  for (int k : keys) steps.push_back(std::max(1.0, (double)((k + 31) / 32) / waves));
+  std::sort(steps.begin(), steps.end());
+  auto mean = [&](size_t shortest) {
+    double sum = 0;
+    for (size_t i = 0; i < shortest; ++i) sum += steps[i];
+    return sum / shortest;
+  };
+  auto block_us = [&](double workgroups, double n_steps) {
+    return c.block + n_steps * (c.step + (waves == 8 ? 0 : c.shared * std::sqrt(std::min(1.0, std::max(0.0, workgroups - 256) / (slots - 256)))));
+  };
+  const double rounds = n / slots, whole = std::floor(rounds), rest = rounds - whole, longest = block_us(n, steps.back()), avg = block_us(n, mean(steps.size()));
+  double us = longest;
+  if (waves == 8) us = std::max(us, avg * std::ceil(rounds));
+  else if (rounds > 1) {   // the last round is one of the shortest blocks, with fewer workgroups to a CU
+    const size_t shortest = std::max<size_t>(1, (size_t)std::lround(rest * slots / s.H));
+    const double tail = rest > 0 ? std::pow(rest, 0.15) * block_us(rest * slots, mean(shortest)) : 0;
+    us = std::max(us, std::max(avg * rounds, avg * whole + tail) + 0.225 * (longest - avg));
+  }
+  return c.launch + us + c.per_mb * mbytes;
+}
 
 // Host half of a step: validates every segment, commits the page movements, and writes the plan
 // (positions, write targets, page lists, attention work lists) into P (capacity: plan_words).
@@ -738,10 +773,12 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
     // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
     double total_cost = 0, narrow_cost = 0, stream_cost = 0, narrow_stream = 0;   // (rows x visible keys; streamed: in whole blocks of rows)
+    double chunk_mb = 0;   // cache rows that chunks read
     long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
     int narrow_longest = 0;
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
+      chunk_mb += (segs[i].start_pos + segs[i].n) * 4e-6 * s.d;
       for (int q0 = 0; q0 < segs[i].n; q0 += HAT_CHUNK_QROWS) {
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
         const int need = segs[i].start_pos + q0 + nq;
@@ -840,6 +877,9 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           if (b.part_row >= 0) b.part_row += r0;
           cblocks.push_back(b);
         }
+      std::vector<int> keys;
+      for (const HatAttnItem& b : cblocks) keys.push_back(std::max(0, std::min(b.kv_end, b.start + b.q0 + b.nq) - b.kv_begin));
+      sp->block_waves = stream_us(s, c.kv_dtype == HAT_KV_F16, 8, keys, chunk_mb) <= stream_us(s, c.kv_dtype == HAT_KV_F16, 4, keys, chunk_mb) ? 8 : 4;
     }
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
@@ -940,7 +980,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
       a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
-      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks;
+      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves;
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
     if (sp.n_vitems > 0) {
@@ -1236,6 +1276,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     h->host_narrow = sp.n_narrow;
     h->host_blocks = sp.o_cb;
     h->host_n_blocks = sp.n_cblocks;
+    h->host_block_waves = sp.block_waves;
     if (sp.T > cap_rows || std::max(sp.n_citems, std::max(sp.n_vitems, sp.n_mitems)) > cap_items)
       return fail(h, HAT_EINVAL, "output arrays too small for %d rows / %d, %d, %d items (the step has been planned)", sp.T,
                   sp.n_citems, sp.n_vitems, sp.n_mitems);
@@ -1260,9 +1301,11 @@ hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow) {
   return HAT_OK;
 }
 
-hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks) {
+hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks,
+                                       int32_t* waves) {
   if (!h || !h->host_only || !n_blocks) return HAT_EINVAL;
   *n_blocks = h->host_n_blocks;
+  if (waves) *waves = h->host_n_blocks > 0 ? h->host_block_waves : 0;
   if (!blocks) return HAT_OK;
   if (h->host_n_blocks > cap_blocks) return HAT_EINVAL;
   if (h->host_n_blocks > 0) memcpy(blocks, h->host_plan.data() + h->host_blocks, (size_t)h->host_n_blocks * sizeof(HatAttnItem));

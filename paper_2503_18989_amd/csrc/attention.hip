@@ -170,7 +170,7 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 161 -> 140 for 1024 over 4096 of the 13B shape, 36.6 -> 21.6 for 3 x
 // 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
 // 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's key splits and merge.
-// NW waves share the keys: 8 where one workgroup per CU is all there is.
+// NW waves share the keys; the planner knows where four of them are faster and where eight.
 template <int HD, bool KVF16, int ROWS, int NW, bool BLOCKS>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
@@ -840,11 +840,7 @@ hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStrea
     HatAttn w = a;
     w.items = a.blocks;
     w.n_items = a.n_blocks;
-    // One workgroup of eight waves or two of four fill a CU: eight waves where there is no second workgroup, or where their
-    // shorter rounds leave less of the last one empty (640 workgroups of 8 x 64 rows over 4160 keys: 165 us against 177).
-    const int wgs = a.n_blocks * a.H;
-    const hipError_t e = wgs <= 256 || (a.hd == 128 && wgs > 512 && wgs <= 768) ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, st)
-                                                                              : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, st);
+    const hipError_t e = a.block_waves == 8 ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, st) : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, st);
     if (e != hipSuccess) return e;
   } else if (wide > 0) {
     dim3 grid(wide, a.H);

@@ -289,7 +289,7 @@ def check_blocks(lib, plan):
     return len(blocks)
 
 
-@pytest.mark.parametrize("rows,start", [([33], 0), ([130, 64], 300), ([256] + [64] * 9, 500), ([257, 40, 7], 90), ([300], 1500), ([40, 17], 1700)])
+@pytest.mark.parametrize("rows,start", [([33], 200), ([130, 64], 300), ([256] + [64] * 9, 500), ([257, 40, 7], 90), ([300], 1500), ([40, 17], 1700)])
 def test_streamed_chunks_are_listed_in_blocks_of_rows(rows, start):
     lib, _ = both(3000, max_devices=16, max_step_tokens=2048, max_pos=2048)
     if start:
@@ -304,4 +304,18 @@ def test_streamed_chunks_are_listed_in_blocks_of_rows(rows, start):
     assert lib.blocks() == []
     lib.plan([(0, hi.VERIFY, start, 5)])
     assert lib.blocks() == []
+    lib.close()
+
+
+@pytest.mark.parametrize("rows,start,waves", [([64], 900, 8), ([256], 900, 8),                # a workgroup per CU at most
+                                              ([120, 70, 90, 150, 160], 400, 4),              # 672: two rounds of short ones with one workgroup per CU
+                                              ([512], 1000, 4), ([512] * 4, 100, 4)])         # 512 and more
+def test_waves_of_a_row_block(rows, start, waves):
+    lib, _ = both(3000, max_devices=16, max_step_tokens=2048, max_pos=2048)
+    for d in range(len(rows)):
+        lib.plan([(d, hi.CHUNK, 0, start)])
+    plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
+    assert check_blocks(lib, plan) and lib.block_waves() == waves
+    lib.plan([(0, hi.VERIFY, start, 5)])
+    assert lib.block_waves() == 0
     lib.close()
