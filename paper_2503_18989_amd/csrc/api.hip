@@ -52,6 +52,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int round_up(int x, int a) { return (x + a - 1) / a * a; }
 
 constexpr int kCapAttnTarget = 2048;  // workgroup target that the work-list capacities are sized for
+constexpr int kAttnTarget = 256;      // one 8-wave workgroup per CU
 
 struct LayerDev {
   act_t *wqkv, *wo, *wgu, *wd;
@@ -93,7 +94,7 @@ Shapes make_shapes(const hat_mid_config_t& c) {
   s.Ngu = round_up(2 * s.Fpad, 256);
   s.Nd = round_up(s.d, 256);
   s.Tcap = round_up(c.max_step_tokens, 256);
-  s.attn_target = 256;  // one 8-wave workgroup per CU
+  s.attn_target = kAttnTarget;
   s.verify_target = 2048;
   // capacities are sized for this target; a larger one (hat_mid_debug_set_attn_targets) splits
   // only as far as they allow -- the planner checks every capacity before it splits
@@ -556,7 +557,7 @@ struct StepPlan {
   int T = 0, S = 0, n_append = 0;
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
-  int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 8, n_vitems = 0, n_mitems = 0;
+  int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 0, n_vitems = 0, n_mitems = 0;
 };
 
 // Time in us of a launch of streamed row blocks with 8 or 4 waves each (the two template forms of attn_verify_kernel), `keys`
@@ -592,6 +593,54 @@ static double stream_us(const Shapes& s, int kv_f16, int waves, const std::vecto
     us = std::max(us, std::max(avg * rounds, avg * whole + tail) + 0.225 * (longest - avg));
   }
   return c.launch + us + c.per_mb * mbytes;
+}
+
+// A chunk item and its key ranges (ns of `step` keys each).
+struct ChunkCut {
+  int seg, q0, nq, need, ns, step, part_row;
+  bool narrow;   // in the launch of the narrow items
+};
+
+// keys that each row block of the streamed items reads
+static std::vector<int> block_keys(const std::vector<ChunkCut>& cuts, const hat_mid_segment_t* segs) {
+  std::vector<int> keys;
+  for (const ChunkCut& u : cuts) {
+    if (u.narrow) continue;
+    for (int r0 = 0; r0 < u.nq; r0 += HAT_NARROW_QROWS) {
+      const int need = segs[u.seg].start_pos + u.q0 + std::min(r0 + HAT_NARROW_QROWS, u.nq);
+      for (int k = 0; k < u.ns; ++k) keys.push_back(std::max(0, std::min(need, (k + 1) * u.step) - k * u.step));
+    }
+  }
+  return keys;
+}
+
+// Time in us of the same items staged (attn_chunk_kernel): a workgroup takes `block`, and for each 64 keys `stage` and `wave` for each of its waves with
+// rows.  Fitted like stream_us, as is merge_us.
+static double staged_us(const Shapes& s, int kv_f16, const std::vector<ChunkCut>& cuts, double mbytes) {
+  struct Cost { double launch, block, stage, wave, per_mb; };
+  static const Cost k[2][2] = {{{0.02, 7.82, 0.768, 0.071, 0.054}, {3.64, 3.86, 0.565, 0.080, 0.150}}, {{0, 9.81, 0.951, 0.124, 0.068}, {0, 9.11, 1.377, 0.105, 0.004}}};
+  const Cost& c = k[s.hd == 128][kv_f16 != 0];
+  double longest = 0, sum = 0;
+  int n = 0;
+  for (const ChunkCut& u : cuts) {
+    if (u.narrow) continue;
+    for (int i = 0; i < u.ns; ++i, ++n) {
+      const double t = c.block + (std::min(u.step, u.need - i * u.step) + 63) / 64 * (c.stage + c.wave * ((u.nq + 31) / 32));
+      longest = std::max(longest, t);
+      sum += t;
+    }
+  }
+  const double rounds = n * s.H / 256.0, whole = std::floor(rounds), avg = sum / n;
+  double us = longest;
+  if (rounds > 1) us = std::max(us, avg * std::max(rounds, whole + std::pow(rounds - whole, 0.2)) + 0.4 * (longest - avg));
+  return c.launch + us + c.per_mb * mbytes;
+}
+static double merge_us(const Shapes& s, const std::vector<ChunkCut>& cuts, bool fp32, bool launched) {
+  double rows = 0;
+  for (const ChunkCut& u : cuts)
+    if (!u.narrow && u.ns > 1) rows += u.ns * u.nq;
+  if (rows == 0) return 0;
+  return (launched ? 0.0 : fp32 ? 5.5 : 6.0) + (fp32 ? 1.1e-6 : 0.8e-6) * rows * s.d;
 }
 
 // Host half of a step: validates every segment, commits the page movements, and writes the plan
@@ -772,8 +821,8 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // narrow item is so long that the common launch, which does not split it, would wait for it.  Measured in whole layers over 30
     // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
     // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
-    double total_cost = 0, narrow_cost = 0, stream_cost = 0, narrow_stream = 0;   // (rows x visible keys; streamed: in whole blocks of rows)
-    double chunk_mb = 0;   // cache rows that chunks read
+    double total_cost = 0, narrow_cost = 0;   // (rows x visible keys)
+    double chunk_mb = 0;                      // cache rows that chunks read
     long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
     int narrow_longest = 0;
     for (int i = 0; i < S; ++i) {
@@ -783,14 +832,11 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
         const int need = segs[i].start_pos + q0 + nq;
         const double cost = (double)nq * (need - 0.5 * nq);
-        const int nb = (nq + HAT_NARROW_QROWS - 1) / HAT_NARROW_QROWS;
         if (nq > HAT_NARROW_QROWS) {
           total_cost += cost;
-          stream_cost += nb * HAT_NARROW_QROWS * (need - 0.5 * nq);
-          blocks += nb;
+          blocks += (nq + HAT_NARROW_QROWS - 1) / HAT_NARROW_QROWS;
         } else {
           narrow_cost += cost;
-          narrow_stream += HAT_NARROW_QROWS * (need - 0.5 * nq);
           ++narrow_blocks;
           narrow_keys += need;
           narrow_longest = std::max(narrow_longest, need);
@@ -801,65 +847,81 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     const bool stream_narrow = !any_wide || narrow_longest >= 1536;
     if (!stream_narrow) {
       total_cost += narrow_cost;
-      stream_cost += narrow_stream;
       blocks += narrow_blocks;
     }
-    // Larger items are staged through LDS, cut along the keys and merged; or they stream the cache too, 32 rows to a
-    // workgroup and the keys whole as a rule.  Staging moves an eighth of the bytes, but its workgroups of 256 rows leave waves idle on
-    // shorter items, fill the chip in coarse rounds, and need the merge.  The line is where the two are level; attention
-    // and merge in us, staged -> streamed, against rows x keys x heads in millions (7B shape if not said otherwise):
-    //   1 x 64 over 1000: 26.7 -> 18.7 (2)      1 x 256 over 1280: 30.9 -> 20.0 (9)     1 x 512 over 1512: 53.0 -> 33.8 (21)
-    //   3 x 410 over 1900, hd 64: 69.7 -> 52.2 (34)     4 x 128 over 2100, 13B: 84 -> 71 (42)     1 x 256 over 7256: 77 -> 71 (58)
-    //   20 x 64 over 1564: 158 -> 132 (63)      1 x 512 over 4512: 94 -> 82 (70)        8 x 64 over 4160, 13B: 179 -> 169 (85)
-    //   3 x 512 over 2012: 127 -> 108 (86)      8 x 128 over 3128: 130 -> 132 (100)     4 x 256 over 3256: 122 -> 121 (102)
-    //   6 x 256 over 2256: 124 -> 131 (105)     2 x 256 over 5256, 13B: 118 -> 131 (105)    10 x 256 over 2256: 188 -> 207 (174)
-    // A raised attn_target asks for many key ranges, a lowered one for few workgroups.
-    const double work = stream_cost * s.H * s.hd / 128;
-    const bool stream_wide = any_wide && s.attn_target <= 256 && work <= 95e6 * s.attn_target / 256;
+    const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
+    const double cost_cap = std::max(256.0 * 256.0, total_cost / (3.0 * std::max(1, s.attn_target / s.H)));
     const int free_ranges = std::max(1, 256 / (int)std::min<long>(256, std::max<long>(1, blocks * s.H)));
-    if (total_cost > 0 || narrow_keys > 0) {
-      const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
-      const double slots = std::max(1, s.attn_target / s.H);
-      const double cost_cap = std::max(256.0 * 256.0, total_cost / (3.0 * slots));
+    // The chunk items with their key ranges, the larger ones staged or streamed; an item for whose ranges a buffer has no room stays whole.
+    auto cut_items = [&](bool stream_wide) {
+      std::vector<ChunkCut> cuts;
+      int row16 = part_row, row32 = part_row32, n_items = 0, n_merges = (int)mitems.size();
       for (int i = 0; i < S; ++i) {
         if (segs[i].kind != HAT_SEG_CHUNK) continue;
         for (int q0 = 0; q0 < segs[i].n; q0 += HAT_CHUNK_QROWS) {
-          const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
-          const int need = segs[i].start_pos + q0 + nq;
-          const double cost = (double)nq * (need - 0.5 * nq);
-          const bool narrow = stream_narrow && nq <= HAT_NARROW_QROWS;
-          int ns = narrow ? (int)((need + narrow_step - 1) / narrow_step) : (int)std::ceil(cost / cost_cap);
-          if (stream_wide && !narrow) {
+          ChunkCut u{};
+          u.seg = i; u.q0 = q0; u.nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
+          u.need = segs[i].start_pos + q0 + u.nq;
+          u.narrow = stream_narrow && u.nq <= HAT_NARROW_QROWS;
+          int ns = u.narrow ? (int)((u.need + narrow_step - 1) / narrow_step) : (int)std::ceil(u.nq * (u.need - 0.5 * u.nq) / cost_cap);
+          if (stream_wide && !u.narrow) {
             // A wave takes about 2.4 us for 32 keys, a merge 6 to 7.  Where CUs are free, an item is cut if that saves more
             // than it costs: 64 rows over 4064 keys 46 us whole, 30.6 + 6.1 in two ranges, 21.6 + 6.2 in four.  (Not next to narrow
             // items, whose key ranges have the fp32 partial rows.)
             ns = stream_narrow && narrow_keys > 0 ? 1 : std::min(free_ranges, 8);
-            if (need / 32.0 / 8 * 2.4 * (1.0 - 1.0 / ns) < 8.0) ns = 1;
+            if (u.need / 32.0 / 8 * 2.4 * (1.0 - 1.0 / ns) < 8.0) ns = 1;
           }
-          ns = std::max(1, std::min(std::min(ns, std::max(1, need / 256)), narrow ? 32 : 16));
-          const bool fp32 = narrow || stream_wide;
-          int& prow = fp32 ? part_row32 : part_row;
-          const int prow_end = fp32 ? s.part_rows_cap + s.part32_cap : s.part_rows_cap;
-          if ((int)citems.size() + ns > s.chunk_items_cap - 1 || prow + ns * nq > prow_end ||
-              (int)mitems.size() + 9 >= s.merge_cap)
+          ns = std::max(1, std::min(std::min(ns, std::max(1, u.need / 256)), u.narrow ? 32 : 16));
+          const bool fp32 = u.narrow || stream_wide;
+          int& row = fp32 ? row32 : row16;
+          if (n_items + ns > s.chunk_items_cap - 1 || row + ns * u.nq > (fp32 ? s.part_rows_cap + s.part32_cap : s.part_rows_cap) ||
+              n_merges + 9 >= s.merge_cap)
             ns = 1;
-          const int step = round_up((need + ns - 1) / ns, 64);
-          ns = (need + step - 1) / step;
-          for (int k = 0; k < ns; ++k) {
-            HatAttnItem it{};
-            it.seg = i; it.q0 = q0; it.nq = nq;
-            it.start = segs[i].start_pos; it.tok0 = P[o_toff + i]; it.kv_len = segs[i].start_pos + segs[i].n;
-            it.pt_off = P[o_spt + i];
-            it.kv_begin = k * step; it.kv_end = std::min(need, (k + 1) * step);
-            it.part_row = ns > 1 ? prow + k * nq : -1;
-            citems.push_back(it);
+          u.step = round_up((u.need + ns - 1) / ns, 64);
+          u.ns = (u.need + u.step - 1) / u.step;
+          u.part_row = u.ns > 1 ? row : -1;
+          if (u.ns > 1) {
+            row += u.ns * u.nq;
+            n_merges += (u.nq + 15) / 16;
           }
-          if (ns > 1) {
-            push_merge(P[o_toff + i] + q0, nq, prow, ns);
-            prow += ns * nq;
-          }
+          n_items += u.ns;
+          cuts.push_back(u);
         }
       }
+      return cuts;
+    };
+    // Larger items are staged through LDS, cut along the keys and merged; or they stream the cache too, 32 rows to a
+    // workgroup and the keys whole as a rule.  Staging moves an eighth of the bytes and shares the widening, but its workgroups of 256 rows
+    // leave waves idle on shorter items, fill the chip in coarse rounds, and need the merge.  Neither the rows x keys of a step nor its
+    // longest item says which is faster; the two times do.  Attention and merge in us, staged | streamed (bf16 cache):
+    //   7B shape: 1 x 256 over 1000 30.8 | 20.4, 4 x 512 over 500 89.7 | 76.4, 10 of 64 and 256 over 1000 75 | 58, but 8 x 128 over 3000 130 | 132,
+    //   8 of 87 .. 106 over 25 15.3 | 17.6; 64 heads: 12 of 200 .. 290 over 20 83 | 113, 1 x 1024 over 1000 135 | 125.
+    // Streaming has to be predicted 3 % ahead.  Over 820 mixes that the times were not fitted to, the choice is on average 0.3 % behind the fastest
+    // way; it is 3 % or more behind staging in 3 of them, 13 % at the most.
+    // A raised or lowered attn_target is a wish for the staged kernel's key ranges.
+    const int f16 = c.kv_dtype == HAT_KV_F16;
+    std::vector<ChunkCut> cuts = cut_items(false);
+    if (any_wide && s.attn_target == kAttnTarget) {
+      std::vector<ChunkCut> streamed = cut_items(true);
+      const bool merges = !mitems.empty() || narrow_keys > narrow_step;   // that a launch is needed for anyway
+      const std::vector<int> keys = block_keys(streamed, segs);
+      const double us8 = stream_us(s, f16, 8, keys, chunk_mb), us4 = stream_us(s, f16, 4, keys, chunk_mb);
+      if (std::min(us8, us4) + merge_us(s, streamed, true, merges) < 0.97 * (staged_us(s, f16, cuts, chunk_mb) + merge_us(s, cuts, false, merges))) {
+        cuts.swap(streamed);
+        sp->block_waves = us8 <= us4 ? 8 : 4;
+      }
+    }
+    for (const ChunkCut& u : cuts) {
+      for (int k = 0; k < u.ns; ++k) {
+        HatAttnItem it{};
+        it.seg = u.seg; it.q0 = u.q0; it.nq = u.nq;
+        it.start = segs[u.seg].start_pos; it.tok0 = P[o_toff + u.seg]; it.kv_len = segs[u.seg].start_pos + segs[u.seg].n;
+        it.pt_off = P[o_spt + u.seg];
+        it.kv_begin = k * u.step; it.kv_end = std::min(u.need, (k + 1) * u.step);
+        it.part_row = u.ns > 1 ? u.part_row + k * u.nq : -1;
+        citems.push_back(it);
+      }
+      if (u.ns > 1) push_merge(P[o_toff + u.seg] + u.q0, u.nq, u.part_row, u.ns);
     }
     auto by_cost = [](const HatAttnItem& a, const HatAttnItem& b) {
       return (long)(a.kv_end - a.kv_begin) * a.nq > (long)(b.kv_end - b.kv_begin) * b.nq;
@@ -868,7 +930,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
     const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [&](const HatAttnItem& a) { return !stream_narrow || a.nq > HAT_NARROW_QROWS; });
     sp->n_narrow = (int)(citems.end() - narrow0);
-    if (stream_wide) {
+    if (sp->block_waves > 0) {
       for (auto it = citems.begin(); it != narrow0; ++it)
         for (int r0 = (it->nq - 1) / HAT_NARROW_QROWS * HAT_NARROW_QROWS; r0 >= 0; r0 -= HAT_NARROW_QROWS) {   // the block with the most keys first
           HatAttnItem b = *it;
@@ -877,9 +939,6 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           if (b.part_row >= 0) b.part_row += r0;
           cblocks.push_back(b);
         }
-      std::vector<int> keys;
-      for (const HatAttnItem& b : cblocks) keys.push_back(std::max(0, std::min(b.kv_end, b.start + b.q0 + b.nq) - b.kv_begin));
-      sp->block_waves = stream_us(s, c.kv_dtype == HAT_KV_F16, 8, keys, chunk_mb) <= stream_us(s, c.kv_dtype == HAT_KV_F16, 4, keys, chunk_mb) ? 8 : 4;
     }
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
@@ -1265,7 +1324,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
   if (n_chunk_items) *n_chunk_items = 0;
   if (n_verify_items) *n_verify_items = 0;
   if (n_merge_items) *n_merge_items = 0;
-  h->host_narrow = h->host_n_blocks = 0;
+  h->host_narrow = h->host_n_blocks = h->host_block_waves = 0;
   if (n_segs == 0) return HAT_OK;
   try {
     StepPlan sp;
@@ -1305,7 +1364,7 @@ hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int3
                                        int32_t* waves) {
   if (!h || !h->host_only || !n_blocks) return HAT_EINVAL;
   *n_blocks = h->host_n_blocks;
-  if (waves) *waves = h->host_n_blocks > 0 ? h->host_block_waves : 0;
+  if (waves) *waves = h->host_block_waves;
   if (!blocks) return HAT_OK;
   if (h->host_n_blocks > cap_blocks) return HAT_EINVAL;
   if (h->host_n_blocks > 0) memcpy(blocks, h->host_plan.data() + h->host_blocks, (size_t)h->host_n_blocks * sizeof(HatAttnItem));

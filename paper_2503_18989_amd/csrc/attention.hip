@@ -167,9 +167,9 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
 // BLOCKS: chunk items of any size, a workgroup for each 32 of their rows, which the planner lists as items of their own.  The
 // row blocks of an item read the same pages, so they run on one XCD, next to each other, and without the non-temporal hint: 30.9 ->
-// 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 161 -> 140 for 1024 over 4096 of the 13B shape, 36.6 -> 21.6 for 3 x
-// 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
-// 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's key splits and merge.
+// 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 155 -> 138 for 1024 over 4096 of the 13B shape (fp16 cache; 167 both
+// ways with bf16), 36.6 -> 21.6 for 3 x 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
+// 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's idle waves, key splits and merge.
 // NW waves share the keys; the planner knows where four of them are faster and where eight.
 template <int HD, bool KVF16, int ROWS, int NW, bool BLOCKS>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {

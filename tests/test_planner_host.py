@@ -319,3 +319,24 @@ def test_waves_of_a_row_block(rows, start, waves):
     lib.plan([(0, hi.VERIFY, start, 5)])
     assert lib.block_waves() == 0
     lib.close()
+
+
+def test_chunks_stream_where_that_is_faster():
+    # measured (7B-shaped heads), staged against streamed in us: 30.8 | 20.4, 90 | 76, 75 | 58; 265 | 284 for 4096 rows
+    def plan(rows, start, target=256):
+        lib, _ = both(4000, max_devices=16, max_step_tokens=4096, max_pos=8192)
+        lib.set_attn_targets(target, 2048)
+        for d in range(len(rows) if start else 0):
+            for q in range(0, start, 4096):
+                lib.plan([(d, hi.CHUNK, q, min(4096, start - q))])
+        p = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
+        n = check_blocks(lib, p) if lib.blocks() else 0
+        assert (n > 0) == (lib.block_waves() > 0)
+        lib.close()
+        return n
+    for rows, start in [([256], 1000), ([512] * 4, 500), ([256] + [64] * 9, 1000)]:
+        assert plan(rows, start), (rows, start)
+        for target in (64, 255, 257, 4096):          # a wish for the staged kernel's key ranges
+            assert not plan(rows, start, target), (rows, start, target)
+    for rows, start in [([512] * 8, 2000), ([4096], 0), ([230] * 9, 30)]:
+        assert not plan(rows, start), (rows, start)
