@@ -851,9 +851,8 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     }
     const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
     const double cost_cap = std::max(256.0 * 256.0, total_cost / (3.0 * std::max(1, s.attn_target / s.H)));
-    const int free_ranges = std::max(1, 256 / (int)std::min<long>(256, std::max<long>(1, blocks * s.H)));
-    // The chunk items with their key ranges, the larger ones staged or streamed; an item for whose ranges a buffer has no room stays whole.
-    auto cut_items = [&](bool stream_wide) {
+    // The chunk items with their key ranges, the larger ones staged (ranges = 0) or streamed in that many ranges; an item for whose ranges a buffer has no room stays whole.
+    auto cut_items = [&](int ranges) {
       std::vector<ChunkCut> cuts;
       int row16 = part_row, row32 = part_row32, n_items = 0, n_merges = (int)mitems.size();
       for (int i = 0; i < S; ++i) {
@@ -863,16 +862,9 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           u.seg = i; u.q0 = q0; u.nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
           u.need = segs[i].start_pos + q0 + u.nq;
           u.narrow = stream_narrow && u.nq <= HAT_NARROW_QROWS;
-          int ns = u.narrow ? (int)((u.need + narrow_step - 1) / narrow_step) : (int)std::ceil(u.nq * (u.need - 0.5 * u.nq) / cost_cap);
-          if (stream_wide && !u.narrow) {
-            // A wave takes about 2.4 us for 32 keys, a merge 6 to 7.  Where CUs are free, an item is cut if that saves more
-            // than it costs: 64 rows over 4064 keys 46 us whole, 30.6 + 6.1 in two ranges, 21.6 + 6.2 in four.  (Not next to narrow
-            // items, whose key ranges have the fp32 partial rows.)
-            ns = stream_narrow && narrow_keys > 0 ? 1 : std::min(free_ranges, 8);
-            if (u.need / 32.0 / 8 * 2.4 * (1.0 - 1.0 / ns) < 8.0) ns = 1;
-          }
+          int ns = u.narrow ? (int)((u.need + narrow_step - 1) / narrow_step) : ranges > 0 ? ranges : (int)std::ceil(u.nq * (u.need - 0.5 * u.nq) / cost_cap);
           ns = std::max(1, std::min(std::min(ns, std::max(1, u.need / 256)), u.narrow ? 32 : 16));
-          const bool fp32 = u.narrow || stream_wide;
+          const bool fp32 = u.narrow || ranges > 0;
           int& row = fp32 ? row32 : row16;
           if (n_items + ns > s.chunk_items_cap - 1 || row + ns * u.nq > (fp32 ? s.part_rows_cap + s.part32_cap : s.part_rows_cap) ||
               n_merges + 9 >= s.merge_cap)
@@ -891,7 +883,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
       return cuts;
     };
     // Larger items are staged through LDS, cut along the keys and merged; or they stream the cache too, 32 rows to a
-    // workgroup and the keys whole as a rule.  Staging moves an eighth of the bytes and shares the widening, but its workgroups of 256 rows
+    // workgroup.  Staging moves an eighth of the bytes and shares the widening, but its workgroups of 256 rows
     // leave waves idle on shorter items, fill the chip in coarse rounds, and need the merge.  Neither the rows x keys of a step nor its
     // longest item says which is faster; the two times do.  Attention and merge in us, staged | streamed (bf16 cache):
     //   7B shape: 1 x 256 over 1000 30.8 | 20.4, 4 x 512 over 500 89.7 | 76.4, 10 of 64 and 256 over 1000 75 | 58, but 8 x 128 over 3000 130 | 132,
@@ -900,13 +892,20 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // way; it is 3 % or more behind staging in 3 of them, 13 % at the most.
     // A raised or lowered attn_target is a wish for the staged kernel's key ranges.
     const int f16 = c.kv_dtype == HAT_KV_F16;
-    std::vector<ChunkCut> cuts = cut_items(false);
+    std::vector<ChunkCut> cuts = cut_items(0);
     if (any_wide && s.attn_target == kAttnTarget) {
-      std::vector<ChunkCut> streamed = cut_items(true);
       const bool merges = !mitems.empty() || narrow_keys > narrow_step;   // that a launch is needed for anyway
-      const std::vector<int> keys = block_keys(streamed, segs);
-      const double us8 = stream_us(s, f16, 8, keys, chunk_mb), us4 = stream_us(s, f16, 4, keys, chunk_mb);
-      if (std::min(us8, us4) + merge_us(s, streamed, true, merges) < 0.97 * (staged_us(s, f16, cuts, chunk_mb) + merge_us(s, cuts, false, merges))) {
+      double best = 0.97 * (staged_us(s, f16, cuts, chunk_mb) + merge_us(s, cuts, false, merges));
+      // Streamed items are cut along the keys where CUs are free and the shorter workgroups are worth the merge: 64 rows of the 7B shape over
+      // 1000 keys 18.7 us whole, 18.9 in three ranges, over 4000 46.0 | 30.3, four 27.8.  Not next to narrow items, whose ranges have the fp32 partial rows.
+      const int most = stream_narrow && narrow_keys > 0 ? 1 : std::max(1, std::min(8, (int)(256 / (blocks * s.H))));
+      for (int ranges = 1; ranges <= most; ++ranges) {
+        std::vector<ChunkCut> streamed = cut_items(ranges);
+        const std::vector<int> keys = block_keys(streamed, segs);
+        const double us8 = stream_us(s, f16, 8, keys, chunk_mb), us4 = ranges > 1 ? us8 : stream_us(s, f16, 4, keys, chunk_mb);
+        const double us = std::min(us8, us4) + merge_us(s, streamed, true, merges);
+        if (us >= best) continue;
+        best = us;
         cuts.swap(streamed);
         sp->block_waves = us8 <= us4 ? 8 : 4;
       }

@@ -340,3 +340,19 @@ def test_chunks_stream_where_that_is_faster():
             assert not plan(rows, start, target), (rows, start, target)
     for rows, start in [([512] * 8, 2000), ([4096], 0), ([230] * 9, 30)]:
         assert not plan(rows, start), (rows, start)
+
+
+@pytest.mark.parametrize("rows,start,ranges", [([64], 600, 1), ([64], 1000, 1), ([64], 4000, 4), ([33], 6000, 4),        # measured: whole at 1000, four at 4000
+                                               ([256], 4000, 1),                                        # a workgroup per CU: none to spare
+                                               ([64, 20], 1600, 1)])                                    # next to a narrow item
+def test_key_ranges_of_streamed_chunks(rows, start, ranges):
+    lib, _ = both(3000, max_devices=2, max_step_tokens=4096, max_pos=8192)
+    for d in range(len(rows)):
+        for q in range(0, start, 2048):
+            lib.plan([(d, hi.CHUNK, q, min(2048, start - q))])
+    plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
+    check_items(plan, [(d, hi.CHUNK, start, n) for d, n in enumerate(rows)], [])
+    assert check_blocks(lib, plan) == ranges * -(-rows[0] // 32)
+    wide = [it for it in plan["chunk_items"] if it["nq"] > 32]
+    assert len(wide) == ranges and all((it["part_row"] < 0) == (ranges == 1) for it in wide)
+    lib.close()
