@@ -558,6 +558,7 @@ struct StepPlan {
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
   int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 0, n_vitems = 0, n_mitems = 0;
+  bool heads_inner = false;
 };
 
 // Time in us of a launch of streamed row blocks with 8 or 4 waves each (the two template forms of attn_verify_kernel), `keys`
@@ -938,6 +939,17 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           if (b.part_row >= 0) b.part_row += r0;
           cblocks.push_back(b);
         }
+      // The blocks of one head read the same pages, which favours a head at a time; but with more than a workgroup per CU the last head then starts
+      // its longest blocks when the others are nearly done.  So where the lengths differ by more than a tenth, the heads of an XCD go
+      // through the list together: 227, 256, 13, 256 and 104 rows over 971 .. 1364 keys at 32 heads of 64 46.3 -> 42.6 us, 3 x 65 over 808 .. 2867 at
+      // 64 heads 71 -> 56, and 2 .. 6 % on average over 120 such mixes; of equal lengths 8 x 64 over 4096 at 40 heads would lose 4 %.
+      double longest = 0, sum = 0;
+      for (const HatAttnItem& b : cblocks) {
+        const int keys = std::max(0, std::min(b.kv_end, b.start + b.q0 + b.nq) - b.kv_begin);
+        longest = std::max(longest, (double)keys);
+        sum += keys;
+      }
+      sp->heads_inner = s.H % 8 == 0 && cblocks.size() * s.H > 256 && longest * cblocks.size() > 1.1 * sum;
     }
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
@@ -1038,7 +1050,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
       a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
-      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves;
+      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves; a.heads_inner = sp.heads_inner;
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
     if (sp.n_vitems > 0) {

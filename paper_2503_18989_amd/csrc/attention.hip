@@ -187,8 +187,14 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
   if constexpr (BLOCKS) {   // a contiguous run of (head, row block) per XCD, as consecutive workgroup ids go round the XCDs
     const int total = a.H * a.n_items, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
     const int b = x * per + (x < rem ? x : rem) + (int)blockIdx.x / 8;
-    item = b % a.n_items;
-    head = b / a.n_items;
+    if (a.heads_inner) {   // H % 8 == 0: each block in all heads of the XCD before the next, so that the shortest start last
+      const int hx = a.H / 8, i = (int)blockIdx.x / 8;
+      item = i / hx;
+      head = x * hx + i % hx;
+    } else {
+      item = b % a.n_items;
+      head = b / a.n_items;
+    }
   }
   const HatAttnItem it = a.items[item];
   const SegInfo sg = seg_info(p, it);
