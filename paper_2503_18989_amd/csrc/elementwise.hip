@@ -137,10 +137,10 @@ __device__ __forceinline__ void fold_partials(f32x4& a, f32x4& b, const float* _
 }
 
 // ---------------------------------------------------------------- RMSNorm
-// A row of at most 8192 columns held by the 256 threads of a workgroup: thread i has octets i, i + 256, .. (V = 1 .. 4 of them).  At
-// most one memory round trip deep: a batch of a few hundred rows has one or two workgroups on a CU, so the kernel is bound by the
-// latency of the loads that wait for one another and not by bandwidth.  Every load is therefore issued before the first result is used, the
-// gain's among them, and none stands under a branch of its own octet (lanes beyond the row repeat its last octet).
+// A row of at most 8192 columns held by the 256 threads of a workgroup: thread i has octets i, i + 256, .. (V = 1 .. 4 of them).  A
+// batch of a few hundred rows has one or two workgroups on a CU, so the kernel is bound by the latency of the loads that wait for one another
+// and not by bandwidth.  Every load of the row, the gain and the first G partial sums is therefore issued before the first result is used (then G more
+// sums at a time), and none stands under a branch of its own octet (lanes beyond the row repeat its last octet).
 // Against a loop of guarded octets with the gain loaded after the sum: 5 rows of the 7B shape with two partial sums 4.55 -> 4.46 us, 77
 // rows 5.53 -> 5.18, with the gather 5.53 -> 4.60 (5 rows) and 7.77 -> 6.74 (256); the step of 5 rows 3027 -> 2974 us.
 __device__ __forceinline__ int row_octet(int v) { return (v * 256 + (int)threadIdx.x) * 8; }
@@ -190,7 +190,7 @@ __device__ __forceinline__ void norm_row(const f32x4 (&va)[V], const f32x4 (&vb)
 
 // one workgroup (256 threads) per row: x = resid + pending split-K partial sums, in ascending order of the split
 // (written back), y = x * rsqrt(mean(x^2) + eps) * gain as fp16 in P32 layout.
-template <int V>
+template <int V, int G>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ resid, const float* __restrict__ part,
                                                        int nparts, int T, const float* __restrict__ gain,
                                                        act_t* __restrict__ outP, int d, float eps) {
@@ -201,14 +201,14 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ resid,
   f32x4 va[V], vb[V], ga[V], gb[V];
   load_row<V>(va, vb, x, d);
   if (nparts == 0) load_row<V>(ga, gb, gain, d);
-  for (int q0 = 0; q0 < nparts; q0 += 4) {   // four splits in flight
-    f32x4 pa[4][V], pb[4][V];
+  for (int q0 = 0; q0 < nparts; q0 += G) {   // G splits in flight
+    f32x4 pa[G][V], pb[G][V];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < G; ++u)
       if (q0 + u < nparts) load_row<V>(pa[u], pb[u], pp + (size_t)(q0 + u) * pstride, d);
     if (q0 == 0) load_row<V>(ga, gb, gain, d);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < G; ++u)
       if (q0 + u < nparts) {
 #pragma unroll
         for (int v = 0; v < V; ++v)
@@ -601,7 +601,12 @@ hipError_t hat_launch_rmsnorm(float* resid, const float* part, int nparts, const
   if (groups && d <= 4096) rmsnorm_rows_kernel<4, 4096><<<(T + 3) / 4, 256, 0, st>>>(resid, part, nparts, T, gain, outP, d, eps);
   else if (groups) rmsnorm_rows_kernel<4, 8192><<<(T + 3) / 4, 256, 0, st>>>(resid, part, nparts, T, gain, outP, d, eps);
   else return with_row_octets(d, [&](auto v) {
-    rmsnorm_kernel<decltype(v)::value><<<T, 256, 0, st>>>(resid, part, nparts, T, gain, outP, d, eps);
+    // Four splits of a row of more than 4096 columns take 172 or 229 registers, two workgroups to a CU.  Beyond 512 rows the rest
+    // would wait for a second round: one split at a time then (90, 120 registers).  Norms of a layer in us with four | one: 640 rows of
+    // 5120 37.7 | 34.3, of 6144 38.4 | 34.6, of 8192 47.4 | 42.5; 512 of 8192 37.6, and 40.0 with a loop of one.
+    constexpr int V = decltype(v)::value;
+    if (V > 2 && T > 512) rmsnorm_kernel<V, (V > 2 ? 1 : 4)><<<T, 256, 0, st>>>(resid, part, nparts, T, gain, outP, d, eps);
+    else rmsnorm_kernel<V, 4><<<T, 256, 0, st>>>(resid, part, nparts, T, gain, outP, d, eps);
     return hipGetLastError();
   });
   return hipGetLastError();

@@ -49,7 +49,9 @@ def test_first_norm_bits(d, heads, T, profiled):
     m.close()
 
 
-@pytest.mark.parametrize("d,T", [(192, 5), (2112, 33), (4160, 5), (6208, 17), (8192, 3)])   # one to four octets per thread, ragged and whole
+@pytest.mark.parametrize("d,T", [(192, 5), (2112, 33), (4160, 5), (6208, 17), (8192, 3),    # one to four octets per thread, ragged and whole
+                                 (1024, 33),                                                # one octet, enough of K for the second group of four
+                                 (4160, 513), (6208, 513)])                                 # wide rows beyond 512: one sum at a time
 def test_norm_folds_partial_sums(d, T):
     """The second norm adds the O product's partial sums (none, one group of four loads, a group and a remainder) to the residual.  A
     zero down projection hands that residual out, so its norm can be stated bit for bit.  Against the unsplit product only the order
@@ -63,7 +65,7 @@ def test_norm_folds_partial_sums(d, T):
         return torch.randn((n, k), generator=g).mul_(0.02).to(torch.bfloat16)
     w = dict(attn_norm=torch.ones(d, dtype=torch.bfloat16), ffn_norm=(1 + 0.1 * torch.randn(d, generator=g)).to(torch.bfloat16), wq=mat(d, d),
              wk=mat(d, d), wv=mat(d, d), wo=mat(d, d), w_gate=mat(f, d), w_up=mat(f, d), w_down=torch.zeros((d, f), dtype=torch.bfloat16))
-    m = HatMid(cfg, [{k: v.cuda() for k, v in w.items()}], n_pages=8, max_devices=1, max_step_tokens=64, max_pos=128, io_dtype="f32")
+    m = HatMid(cfg, [{k: v.cuda() for k, v in w.items()}], n_pages=8 + T // 16, max_devices=1, max_step_tokens=64 + T, max_pos=128 + T, io_dtype="f32")
     x = torch.randn((T, d), generator=g)
     whole = bound = None
     for ks in (1, 2, 3, 4, 5, 6):
