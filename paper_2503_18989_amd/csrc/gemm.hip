@@ -702,7 +702,9 @@ hipError_t hat_gemm_init() {
 //  - O and down: K split until the workgroups fill the CUs once; the gain is the few partial sums (RMSNorm 8.2 -> 6.7),
 //    the products themselves are level (O 10.9 -> 10.3, down 20.3 -> 20.0 at 5 rows; 14.8 -> 14.2 and 26.1 -> 25.5 at 77).
 //    With the 160 panels of the 13B shape the CUs are not filled: up to 16 rows still 23.9 -> 20.4 with the norm, at
-//    32 rows 24.2 -> 25.8; at 33 .. 64 rows down loses more (22.9 -> 25.4) than the norm gains.
+//    32 rows 24.2 -> 25.8; at 33 .. 64 rows down loses more (22.9 -> 25.4) than the norm gains.  Nor are they with the 32 panels of
+//    1024 x 2816 in four pieces each, whose products are short: a layer of 17 rows 37.7 -> 35.2 with O streamed, 34.9 with down (32 rows:
+//    38.7 -> 36.4, 35.8).
 // Whole layers with and without it, weights out of reach of the caches, at eight widths from 1024 x 2816 to 8192 x 28672:
 //   rows          16                 32                 64                 96
 //   1024    47.2 ->  29.4      48.2 ->  37.5      46.8 ->  43.4      47.1 ->  43.2
@@ -730,7 +732,7 @@ static bool stream_plan(const HatGemm& g, HatGemmPlan* p) {
   const int tiles = g.Nw / (g.T <= 32 ? 32 : 64);
   if (g.T <= 32 && (long)g.Nw * g.K <= 1 << 18) return true;   // nothing to stream: the K split among a workgroup's waves is the gain
   while (p->ksplit < 4 && tiles * p->ksplit * 2 <= 256 && g.part && (long)p->ksplit * 2 * g.T <= g.part_rows) p->ksplit *= 2;
-  return tiles * p->ksplit >= (g.T <= 16 ? 128 : 192);
+  return tiles * p->ksplit >= (g.T <= 16 || p->ksplit == 4 ? 128 : 192);
 }
 
 HatGemmPlan hat_gemm_plan(const HatGemm& g) {

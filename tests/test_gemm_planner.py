@@ -158,3 +158,12 @@ def test_qkv_tiles_of_wide_models_do_not_run_over_into_a_second_round(lib):
     for d, T, want in [(5120, 17, 27), (5120, 32, 27), (5504, 16, 24), (5504, 17, 24), (6144, 24, 24), (6144, 25, -1), (8192, 32, -1)]:
         N = (3 * d + 255) // 256 * 256
         assert plan(lib, T, N, 3 * d, d, 3, 4096)[0] == want, (d, T)
+
+
+@pytest.mark.parametrize("T", [1, 16, 17, 24, 32, 33])
+def test_o_and_down_of_a_narrow_model_stream_up_to_32_rows(lib, T):
+    # 1024 x 2816: 32 panels in four pieces of K.  The 160 panels of the 13B shape stay whole and stream up to 16 rows
+    for K in (1024, 2816):
+        assert (plan(lib, T, 1024, 1024, K, 2, 4096) == (24, 4)) == (T <= 32)
+    for K in (5120, 13824):
+        assert (plan(lib, T, 5120, 5120, K, 2, 4096)[0] == 24) == (T <= 16)
