@@ -940,16 +940,17 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
           cblocks.push_back(b);
         }
       // The blocks of one head read the same pages, which favours a head at a time; but with more than a workgroup per CU the last head then starts
-      // its longest blocks when the others are nearly done.  So where the lengths differ by more than a tenth, the heads of an XCD go
-      // through the list together: 227, 256, 13, 256 and 104 rows over 971 .. 1364 keys at 32 heads of 64 46.3 -> 42.6 us, 3 x 65 over 808 .. 2867 at
-      // 64 heads 71 -> 56, and 2 .. 6 % on average over 120 such mixes; of equal lengths 8 x 64 over 4096 at 40 heads would lose 4 %.
+      // its longest blocks when the others are nearly done.  So where the lengths differ by more than a tenth and the longest is 800 keys, the
+      // heads of an XCD go through the list together: 227, 256, 13, 256 and 104 rows over 971 .. 1364 keys at 32 heads of 64 46.3 -> 42.6 us, 3 x 65
+      // over 808 .. 2867 at 64 heads 71 -> 56, 5 % on average over 140 such mixes (between 22 % ahead and 5 behind).  Over 110 of fewer keys
+      // it is level (14 % ahead to 8 behind; 576 rows of a new prompt at 32 heads of 64 7 % behind), of equal lengths 4 % behind (8 x 64 over 4096 at 40 heads).
       double longest = 0, sum = 0;
       for (const HatAttnItem& b : cblocks) {
         const int keys = std::max(0, std::min(b.kv_end, b.start + b.q0 + b.nq) - b.kv_begin);
         longest = std::max(longest, (double)keys);
         sum += keys;
       }
-      sp->heads_inner = s.H % 8 == 0 && cblocks.size() * s.H > 256 && longest * cblocks.size() > 1.1 * sum;
+      sp->heads_inner = s.H % 8 == 0 && cblocks.size() * s.H > 256 && longest >= 800 && longest * cblocks.size() > 1.1 * sum;
     }
   }
   const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
