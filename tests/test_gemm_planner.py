@@ -167,3 +167,18 @@ def test_o_and_down_of_a_narrow_model_stream_up_to_32_rows(lib, T):
         assert (plan(lib, T, 1024, 1024, K, 2, 4096) == (24, 4)) == (T <= 32)
     for K in (5120, 13824):
         assert (plan(lib, T, 5120, 5120, K, 2, 4096)[0] == 24) == (T <= 16)
+
+
+def test_token_tiles_between_the_powers_of_two_from_257_rows_on(lib):
+    # the steps of test_gpu_mid_rows_gemm.py: where a third 128-row token tile would be nearly empty, no product keeps it; 384 rows
+    # and 2048-wide models close to them stay with 64, 128 and 256 rows
+    def token_rows(d, f, T):
+        pad = lambda n: (n + 255) // 256 * 256
+        return [tile_info(lib, plan(lib, T, pad(n), o, k, e, 4096)[0])[1][1]
+                for n, o, k, e in ((3 * d, 3 * d, d, 0), (d, d, d, 2), (2 * f, f, d, 1), (d, d, f, 2))]
+    for T in (257, 320):
+        assert token_rows(4096, 11008, T) == [160] * 4
+        assert 160 in token_rows(2048, 5504, T)
+    assert 192 in token_rows(4096, 11008, 383) + token_rows(5120, 13824, 383)
+    for d, f in ((4096, 11008), (2048, 5504), (5120, 13824)):
+        assert all(bt in (64, 128, 256) for bt in token_rows(d, f, 384)), d

@@ -1,4 +1,5 @@
-"""GPU check of the products of 257 .. 384 rows, whose token tiles may be 160, 192 or 224 rows tall."""
+"""GPU check of the products of 257 .. 384 rows, whose token tiles may be 160, 192 or 224 rows tall (which of these steps have such
+tiles: test_gemm_planner.py)."""
 import pytest
 
 from gpu_util import progress, rel_l2, to_np

@@ -356,3 +356,20 @@ def test_key_ranges_of_streamed_chunks(rows, start, ranges):
     wide = [it for it in plan["chunk_items"] if it["nq"] > 32]
     assert len(wide) == ranges and all((it["part_row"] < 0) == (ranges == 1) for it in wide)
     lib.close()
+
+
+def test_partial_rows_of_staged_and_narrow_chunks_are_apart():
+    # a wide item that is staged in several key ranges (fp16 partial rows) next to a narrow one in several (fp32, numbered after them)
+    lib, _ = both(3000, max_devices=2, max_step_tokens=4096, max_pos=8192)
+    for d in (0, 1):
+        lib.plan([(d, hi.CHUNK, 0, 4000)])
+    plan = lib.plan([(0, hi.CHUNK, 4000, 64), (1, hi.CHUNK, 4000, 20)])
+    part_rows = []
+    check_items(plan, [(0, hi.CHUNK, 4000, 64), (1, hi.CHUNK, 4000, 20)], part_rows)
+    disjoint(part_rows)
+    n = lib.narrow_items()
+    wide, narrow = plan["chunk_items"][:-n], plan["chunk_items"][-n:]
+    assert lib.blocks() == [] and len(wide) > 1 and len(narrow) > 1
+    assert 0 <= min(it["part_row"] for it in wide)
+    assert max(it["part_row"] + it["nq"] for it in wide) <= min(it["part_row"] for it in narrow)
+    lib.close()
