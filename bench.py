@@ -522,7 +522,8 @@ def measured_peaks():
     from paper_2503_18989_amd.binding import measure_peak
     out = {}
     for kind, unit, peak in (("stream_read", "GB/s", PEAK_HBM), ("stream_read_nt", "GB/s", PEAK_HBM), ("copy", "GB/s", PEAK_HBM),
-                             ("mfma_f16", "TFLOP/s", PEAK_MFMA_BF16), ("lds_load", "GB/s", None)):
+                             ("mfma_f16", "TFLOP/s", PEAK_MFMA_BF16), ("mfma_f16_random", "TFLOP/s", PEAK_MFMA_BF16),
+                             ("mfma_f16_16x16x32_random", "TFLOP/s", PEAK_MFMA_BF16), ("lds_load", "GB/s", None)):
         r = measure_peak(kind, nbytes=(1 << 30) if kind != "copy" else (2 << 30), iters=20)
         e = {"value": r / (1e12 if unit == "TFLOP/s" else 1e9), "unit": unit}
         if peak:
@@ -533,7 +534,8 @@ def measured_peaks():
             e["bytes_per_clock_per_cu_at_2.4GHz"] = r / 256 / 2.4e9
         out[kind] = e
     out["note"] = ("stream_read*: 1 GiB read once per launch, every wave a contiguous span in 16 KB steps (16 loads of 16 bytes per "
-                   "lane in flight, 32 waves per CU); copy: 1 GiB read + 1 GiB written; mfma_f16: 32x32x16 fp16 matrix instructions only, two waves per SIMD; lds_load: direct-to-LDS "
+                   "lane in flight, 32 waves per CU); copy: 1 GiB read + 1 GiB written; mfma_f16: 32x32x16 fp16 matrix instructions only, two waves per SIMD; *_random: on random operands, which drive "
+                   "the chip into its power limit; lds_load: direct-to-LDS "
                    "loads of a cache-resident 1 MiB region, one 4-wave workgroup per CU, 16 loads in flight per wave")
     return out
 

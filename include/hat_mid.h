@@ -355,7 +355,8 @@ hat_status_t hat_mid_debug_gemm_split(int32_t T, int32_t Nw, int32_t Nout, int32
 /* Workgroup counts that the attention work lists aim for (chunk kernel, verify kernel): long key
  * ranges are split over several workgroups until a launch has about that many.  0 keeps a value.
  * For tests that force the split and unsplit paths, and for sweeps; the work-list capacities were
- * sized at create time, so a larger target splits only as far as they allow.  Results change only
+ * sized at create time, so a larger target splits only as far as they allow.  With a chunk target other than the default (256)
+ * chunk items of more than 32 rows are always staged, never streamed.  Results change only
  * in fp32 summation order. */
 hat_status_t hat_mid_debug_set_attn_targets(hat_mid_t* h, int32_t chunk_target, int32_t verify_target);
 
@@ -378,13 +379,15 @@ hat_status_t hat_mid_debug_set_verify_probe(hat_mid_t* h, int32_t on);
  * (1..1000) are timed with HIP events on hip_stream after one warm-up launch, and the call waits
  * for them.  *rate: bytes/s (STREAM_READ*, COPY: read + written bytes; LDS_LOAD: bytes moved into
  * LDS by direct-to-LDS loads from a 1 MiB cache-resident region, all CUs together) or FLOP/s
- * (MFMA_F16: 32x32x16 fp16 matrix instructions only, two waves per SIMD). */
+ * (MFMA_F16*: fp16 matrix instructions only, 32x32x16 if not said otherwise, two waves per SIMD). */
 typedef enum {
   HAT_PEAK_STREAM_READ = 0,
   HAT_PEAK_STREAM_READ_NT = 1,   /* the same with non-temporal loads */
   HAT_PEAK_COPY = 2,
   HAT_PEAK_MFMA_F16 = 3,
-  HAT_PEAK_LDS_LOAD = 4
+  HAT_PEAK_LDS_LOAD = 4,
+  HAT_PEAK_MFMA_F16_RANDOM = 5,          /* MFMA_F16 on random operands, eight at a time: the clock depends on what they toggle */
+  HAT_PEAK_MFMA_F16_16X16X32_RANDOM = 6  /* the same with 16x16x32 instructions, as the GEMMs use */
 } hat_peak_kind_t;
 hat_status_t hat_mid_debug_peak(int32_t kind, void* buf, size_t bytes, int32_t iters, void* hip_stream, double* rate);
 

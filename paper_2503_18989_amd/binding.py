@@ -347,7 +347,8 @@ class HatMid:
             pass
 
 
-PEAK_KINDS = {"stream_read": 0, "stream_read_nt": 1, "copy": 2, "mfma_f16": 3, "lds_load": 4}
+PEAK_KINDS = {"stream_read": 0, "stream_read_nt": 1, "copy": 2, "mfma_f16": 3, "lds_load": 4, "mfma_f16_random": 5,
+              "mfma_f16_16x16x32_random": 6}
 
 
 def measure_peak(kind, nbytes=1 << 30, iters=20):

@@ -79,8 +79,8 @@ struct Tile {
 // the issue of the next operand reads and loads (256 x 192 on four waves: 359 -> 437 us), so every large tile has eight
 // waves.  Where eight wave tiles would read too much LDS per product (192 x 128: 48 rows each), WK = 2 gives the two waves of a
 // SIMD the same output block and each half of a stage's k; they meet in LDS at the end.
-// Against the 32x32x16 loop on four waves, weights in reach of the caches: gate/up of the 7B shape at 256 rows 53.8 -> 48.2 us, QKV
-// 34.1 -> 30.9, O 16.9 -> 15.7, down 31.4 -> 28.3; 13B shape at 512 rows 138 -> 124, 81 -> 73.2 and (down) 76.9 -> 69.8.
+// Against the 32x32x16 loop on four waves, in steps (weights from HBM), QKV, gate/up and down: 13B shape at 512 rows 79 -> 73 us, 129 -> 115, 76 -> 72, at 4096 533 ->
+// 474, 948 -> 837, 504 -> 440; at 256 rows of the 7B shape, where the weight stream decides, level (39.0 -> 40.1, 61.2 -> 60.7, 36.4 -> 36.2).
 template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE, int EPI>
 __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
   using TL = Tile<BF, BT, WF, WT, WK, BKT, NSTAGE>;
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   // i+NSTAGE (into the buffer tile i just vacated) are slotted between the MFMAs of the
   // following KS k-steps, in KS parts: part 0 right after that boundary, parts 1.. over the next tile's k-steps 0..KS-2.
   // They are spread thinly because a direct-to-LDS load holds the issuing wave for on the order of a hundred cycles.
-  // `steady`: tile i + NSTAGE exists (and with several k-steps per tile, i is not the first), so nothing has to be asked.
+  // `steady`: tile i + NSTAGE exists, so nothing has to be asked (one k-step per tile only: see the loops below).
   auto kstep = [&](auto curc, auto ksc, int i, auto steadyc) {
     constexpr int cur = decltype(curc)::value, ks = decltype(ksc)::value;
     constexpr bool steady = decltype(steadyc)::value;
@@ -559,8 +559,8 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // (128 x 160) is for batches of 129 .. 160 rows, e.g. 30 devices x 5 draft rows: one token tile
 // instead of a full and a nearly empty one.
 // Waves: 64 x 128 and the like each, 12 operand reads for 32 MFMAs, where that makes eight wave tiles of whole 32-row panels; two
-// halves of K otherwise (192 x 128: 96 x 64 in halves of K 48.2 us, 96 x 32 53.7 us, on gate/up of the 7B shape at 256 rows), unless
-// the weight stream decides (weights from HBM, 128 x 160 at 150 rows: O 15.1 us against 16.4 in halves of K, down 25.7 against 27.0; 128 x 64 at 56 rows: 12.8
+// halves of K otherwise (192 x 128 on gate/up of the 7B shape with the weights in the caches, 256 rows: 96 x 64 in halves of K 48.2 us, 96 x 32
+// 53.7; from HBM the two are within 4 % of each other either way), unless the weight stream decides (weights from HBM, 128 x 160 at 150 rows: O 15.1 us against 16.4 in halves of K, down 25.7 against 27.0; 128 x 64 at 56 rows: 12.8
 // against 13.2 and 22.2 against 22.5).
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
@@ -612,7 +612,9 @@ constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, t
                                       true, true, true, true};
 // Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, fitted to
 // sweeps at T = 512 .. 5220 (7B shapes, all four products, K split 1 .. 8); 0 = not measured
-// there, the tile is only offered to batches of at most kSmallT rows.
+// there, the tile is only offered to batches of at most kSmallT rows.  The sweeps were of the 32x32x16 loops: these are weights
+// for the choice, not rates of the present ones.  What that costs where it was looked for: gate/up of the 13B shape at 384 rows 113 us where 256 x 192
+// takes 105, QKV of 2048 columns at 760 rows 29.7 where 128 x 160 takes 26.7, O, down and norms of the 7B shape at 512 rows 109 where 105 is possible.
 constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
                                    0.f, 0.f, 0.f, 0.514f, 0.f, 1.209f, 0.f, 0.504f, 0.f, 0.629f,
                                    0.518f, 0.565f, 0.564f, 0.f};
@@ -788,8 +790,9 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     // 128-row token tile or a second 256-row one is as empty.  The four products and the norms of a layer in us, without these tiles and with
     // them, at 257, 320 and 365 rows: 7B shape 219 -> 193, 229 -> 202 (gate/up 84.1 -> 72.9 with 256 x 160, down 45.3 -> 39.8), 228 -> 227; 13B shape
     // 282 -> 257, 301 -> 267, 305 -> 287; 8192 x 28672 760 -> 638, 823 -> 656, 814 -> 728; head dim 64 92.6 -> 89.7, 96.4 -> 92.3, 103.7 -> 102.8;
-    // 1024 x 2816 level.  No slower at any of nine batch sizes of seven widths.  384 rows, which leave no 128-row tile
-    // partly empty, keep those.
+    // 1024 x 2816 level.  No slower at any of nine batch sizes of seven widths.  384 rows are three whole 128-row
+    // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py): not the faster choice everywhere (a 13B-shaped layer 308 us, 289
+    // with the 192-row tile).
     const bool tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && g.T > 128 && g.T <= 160;
     if (large ? q.eff == 0.f : (q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;

@@ -1,6 +1,6 @@
 // Microbenchmarks of what this chip delivers through the instruction mixes the kernels of this
 // library are built from: streaming reads (plain and non-temporal), a copy, a matrix-core-only
-// loop, and the direct-to-LDS load path from cache-resident data.  They give the "measured peak"
+// loop (also on random operands), and the direct-to-LDS load path from cache-resident data.  They give the "measured peak"
 // next to the published one when a kernel's roofline fraction is read, and are reached through
 // hat_mid_debug_peak (include/hat_mid.h); bench.py --peaks prints them.
 #include <hip/hip_runtime.h>
@@ -65,6 +65,49 @@ __global__ __launch_bounds__(kThreads) void mfma_kernel(int iters, float* sink) 
   for (int a = 0; a < NACC; ++a)
 #pragma unroll
     for (int r = 0; r < 16; ++r) s += acc[a][r];
+  if (s == 12345.678f) *sink = s;
+}
+
+// The same on random operands in [-1, 1), eight rows and two columns of them in turn.  Random data drives the matrix pipes into the
+// chip's power limit, and the smaller instruction (16x16x32) takes less power for the same arithmetic.
+template <bool SMALL>
+__global__ __launch_bounds__(kThreads) void mfma_random_kernel(int iters, float* sink) {
+  constexpr int NA = 8, NB = 2, NR = SMALL ? 4 : 16;
+  typedef float acc_t __attribute__((ext_vector_type(NR)));
+  f16x8 x[NA], y[NB];
+  acc_t acc[NA];
+  uint32_t h = (blockIdx.x * kThreads + threadIdx.x) * 2654435761u + 12345u;
+  auto fill = [&](f16x8& v) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      h ^= h << 13;
+      h ^= h >> 17;
+      h ^= h << 5;
+      v[e] = (_Float16)((float)(int32_t)h * (1.0f / 2147483648.0f));
+    }
+  };
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    fill(x[a]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[a][r] = 0.f;
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) fill(y[b]);
+  for (int it = 0; it < iters; ++it) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        if constexpr (SMALL) acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[a], y[b], acc[a], 0, 0, 0);
+        else acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[a], y[b], acc[a], 0, 0, 0);
+      }
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) s += acc[a][r];
   if (s == 12345.678f) *sink = s;
 }
 
@@ -135,6 +178,16 @@ extern "C" hat_status_t hat_mid_debug_peak(int32_t kind, void* buf, size_t bytes
         const int loops = 4096;
         mfma_kernel<8><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);   // two workgroups = two waves per SIMD
         work = (double)cus * 2 * 4 * loops * 8 * (2.0 * 32 * 32 * 16);
+        return true;
+      }
+      case HAT_PEAK_MFMA_F16_RANDOM:
+      case HAT_PEAK_MFMA_F16_16X16X32_RANDOM: {
+        if (!buf || bytes < 256) return false;
+        const bool small = kind == HAT_PEAK_MFMA_F16_16X16X32_RANDOM;
+        const int loops = small ? 8192 : 4096;   // 4 ms: long enough for the clock to settle
+        if (small) mfma_random_kernel<true><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
+        else mfma_random_kernel<false><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
+        work = (double)cus * 2 * 4 * loops * 16 * (small ? 2.0 * 16 * 16 * 32 : 2.0 * 32 * 32 * 16);
         return true;
       }
       case HAT_PEAK_LDS_LOAD: {
