@@ -386,7 +386,7 @@ typedef enum {
   HAT_PEAK_COPY = 2,
   HAT_PEAK_MFMA_F16 = 3,
   HAT_PEAK_LDS_LOAD = 4,
-  HAT_PEAK_MFMA_F16_RANDOM = 5,          /* MFMA_F16 on random operands, eight at a time: the clock depends on what they toggle */
+  HAT_PEAK_MFMA_F16_RANDOM = 5,          /* MFMA_F16 on random operands: the clock depends on what they toggle */
   HAT_PEAK_MFMA_F16_16X16X32_RANDOM = 6  /* the same with 16x16x32 instructions, as the GEMMs use */
 } hat_peak_kind_t;
 hat_status_t hat_mid_debug_peak(int32_t kind, void* buf, size_t bytes, int32_t iters, void* hip_stream, double* rate);

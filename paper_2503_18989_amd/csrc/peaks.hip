@@ -68,14 +68,15 @@ __global__ __launch_bounds__(kThreads) void mfma_kernel(int iters, float* sink) 
   if (s == 12345.678f) *sink = s;
 }
 
-// The same on random operands in [-1, 1), eight rows and two columns of them in turn.  Random data drives the matrix pipes into the
-// chip's power limit, and the smaller instruction (16x16x32) takes less power for the same arithmetic.
-template <bool SMALL>
-__global__ __launch_bounds__(kThreads) void mfma_random_kernel(int iters, float* sink) {
-  constexpr int NA = 8, NB = 2, NR = SMALL ? 4 : 16;
+// The same on random operands in [-1, 1), as a wave of a product takes them: an MI x NJ block of outputs, back and forth along its
+// columns, two sets of operands in turn.  Random data drives the matrix pipes into the chip's power limit, and the smaller
+// instruction (16x16x32) takes less power for the same arithmetic.
+template <bool SMALL, int MI, int NJ>
+__global__ __launch_bounds__(kThreads, 2) void mfma_random_kernel(int iters, float* sink) {
+  constexpr int NR = SMALL ? 4 : 16;
   typedef float acc_t __attribute__((ext_vector_type(NR)));
-  f16x8 x[NA], y[NB];
-  acc_t acc[NA];
+  f16x8 x[2][MI], y[2][NJ];
+  acc_t acc[MI][NJ];
   uint32_t h = (blockIdx.x * kThreads + threadIdx.x) * 2654435761u + 12345u;
   auto fill = [&](f16x8& v) {
 #pragma unroll
@@ -87,28 +88,38 @@ __global__ __launch_bounds__(kThreads) void mfma_random_kernel(int iters, float*
     }
   };
 #pragma unroll
-  for (int a = 0; a < NA; ++a) {
-    fill(x[a]);
+  for (int s = 0; s < 2; ++s) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) acc[a][r] = 0.f;
+    for (int i = 0; i < MI; ++i) fill(x[s][i]);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) fill(y[s][j]);
   }
 #pragma unroll
-  for (int b = 0; b < NB; ++b) fill(y[b]);
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) acc[i][j][r] = 0.f;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int a = 0; a < NA; ++a) {
-        if constexpr (SMALL) acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[a], y[b], acc[a], 0, 0, 0);
-        else acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[a], y[b], acc[a], 0, 0, 0);
-      }
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int jj = 0; jj < NJ; ++jj) {
+          const int j = (i & 1) ? NJ - 1 - jj : jj;
+          if constexpr (SMALL) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[s][i], y[s][j], acc[i][j], 0, 0, 0);
+          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[s][i], y[s][j], acc[i][j], 0, 0, 0);
+        }
   }
-  float s = 0.f;
+  float sum = 0.f;
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int r = 0; r < NR; ++r) s += acc[a][r];
-  if (s == 12345.678f) *sink = s;
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) sum += acc[i][j][r];
+  if (sum == 12345.678f) *sink = sum;
 }
 
 // direct-to-LDS loads (16 bytes per lane, 1 KB per wave instruction) from a region small enough
@@ -184,10 +195,10 @@ extern "C" hat_status_t hat_mid_debug_peak(int32_t kind, void* buf, size_t bytes
       case HAT_PEAK_MFMA_F16_16X16X32_RANDOM: {
         if (!buf || bytes < 256) return false;
         const bool small = kind == HAT_PEAK_MFMA_F16_16X16X32_RANDOM;
-        const int loops = small ? 8192 : 4096;   // 4 ms: long enough for the clock to settle
-        if (small) mfma_random_kernel<true><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
-        else mfma_random_kernel<false><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
-        work = (double)cus * 2 * 4 * loops * 16 * (small ? 2.0 * 16 * 16 * 32 : 2.0 * 32 * 32 * 16);
+        const int loops = 4096;   // 2.5 ms a launch
+        if (small) mfma_random_kernel<true, 4, 4><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
+        else mfma_random_kernel<false, 2, 4><<<cus * 2, kThreads, 0, st>>>(loops, (float*)buf);
+        work = (double)cus * 2 * 4 * loops * (small ? 32 * 2.0 * 16 * 16 * 32 : 16 * 2.0 * 32 * 32 * 16);
         return true;
       }
       case HAT_PEAK_LDS_LOAD: {
