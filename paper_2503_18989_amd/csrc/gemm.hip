@@ -74,7 +74,7 @@ struct Tile {
 };
 
 // Matrix instruction: v_mfma_f32_16x16x32_f16.  Random operands drive the matrix pipes into the chip's power limit, and this
-// shape takes less power than 32x32x16: a loop of nothing but MFMAs runs at 1940 .. 1980 TFLOP/s against 1690 .. 1715 (2420 both on
+// shape takes less power than 32x32x16: a loop of nothing but MFMAs runs at 1920 .. 1980 TFLOP/s against 1640 .. 1715 (2420 both on
 // zeros), gate/up of 4096 rows (13B shape) at 1290 against 1155.  It needs two waves on a SIMD: with one, its 16 clocks do not hide
 // the issue of the next operand reads and loads (256 x 192 on four waves: 359 -> 437 us), so every large tile has eight
 // waves.  Where eight wave tiles would read too much LDS per product (192 x 128: 48 rows each), WK = 2 gives the two waves of a
