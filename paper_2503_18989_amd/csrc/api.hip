@@ -823,6 +823,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
     // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
     double total_cost = 0, narrow_cost = 0;   // (rows x visible keys)
+    double block_cost = 0, narrow_block = 0;  // the same of the items that may stream, in whole blocks of rows
     double chunk_mb = 0;                      // cache rows that chunks read
     long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
     int narrow_longest = 0;
@@ -836,8 +837,10 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         if (nq > HAT_NARROW_QROWS) {
           total_cost += cost;
           blocks += (nq + HAT_NARROW_QROWS - 1) / HAT_NARROW_QROWS;
+          block_cost += round_up(nq, HAT_NARROW_QROWS) * (need - 0.5 * nq);
         } else {
           narrow_cost += cost;
+          narrow_block += HAT_NARROW_QROWS * (need - 0.5 * nq);
           ++narrow_blocks;
           narrow_keys += need;
           narrow_longest = std::max(narrow_longest, need);
@@ -848,6 +851,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     const bool stream_narrow = !any_wide || narrow_longest >= 1536;
     if (!stream_narrow) {
       total_cost += narrow_cost;
+      block_cost += narrow_block;
       blocks += narrow_blocks;
     }
     const long narrow_step = std::max<long>(256, (narrow_keys / std::max(1, per_head * 3 / 8) + 127) / 128 * 128);
@@ -887,16 +891,22 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // workgroup.  Staging moves an eighth of the bytes and shares the widening, but its workgroups of 256 rows
     // leave waves idle on shorter items, fill the chip in coarse rounds, and need the merge.  Neither the rows x keys of a step nor its
     // longest item says which is faster; the two times do.  Attention and merge in us, staged | streamed (bf16 cache):
-    //   7B shape: 1 x 256 over 1000 30.8 | 20.4, 4 x 512 over 500 89.7 | 76.4, 10 of 64 and 256 over 1000 75 | 58, but 8 x 128 over 3000 130 | 132,
+    //   7B shape: 1 x 256 over 1000 30.8 | 20.4, 4 x 512 over 500 89.7 | 76.4, 10 of 64 and 256 over 1000 75 | 58, but 8 x 128 over 3000 128 | 134,
     //   8 of 87 .. 106 over 25 15.3 | 17.6; 64 heads: 12 of 200 .. 290 over 20 83 | 113, 1 x 1024 over 1000 135 | 125.
-    // Streaming has to be predicted 3 % ahead.  Over 820 mixes that the times were not fitted to, the choice is on average 0.3 % behind the fastest
-    // way; it is 3 % or more behind staging in 3 of them, 13 % at the most.
+    // Streaming has to be predicted 3 % ahead, 7 % in launches of more than 95 M rows x keys x heads, whose staged items fill the chip better than the
+    // prediction has it (8 x 128 over 3000).  Over 820 mixes that the times were not fitted to, the choice is on average 0.3 % behind the fastest
+    // way; it is 3 % or more behind staging in 2 %, 23 % at the most.
+    // The partial results of staged items are held in fp16.  So smaller launches than these stage only where staging leaves every
+    // item whole: otherwise 2 % of the mixes would be faster staged, mostly single chunks over long caches (128 rows over 4000 keys of the 7B
+    // shape 34.5 us, streamed in two ranges 35.7; 256 over 6000 of the 13B shape 95, streamed 105).
     // A raised or lowered attn_target is a wish for the staged kernel's key ranges.
     const int f16 = c.kv_dtype == HAT_KV_F16;
     std::vector<ChunkCut> cuts = cut_items(0);
     if (any_wide && s.attn_target == kAttnTarget) {
       const bool merges = !mitems.empty() || narrow_keys > narrow_step;   // that a launch is needed for anyway
-      double best = 0.97 * (staged_us(s, f16, cuts, chunk_mb) + merge_us(s, cuts, false, merges));
+      const double staged_merge = merge_us(s, cuts, false, merges);
+      const bool large = block_cost * s.H * s.hd / 128 > 95e6;
+      double best = staged_merge > 0 && !large ? 1e300 : (large ? 0.93 : 0.97) * (staged_us(s, f16, cuts, chunk_mb) + staged_merge);
       // Streamed items are cut along the keys where CUs are free and the shorter workgroups are worth the merge: 64 rows of the 7B shape over
       // 1000 keys 18.7 us whole, 18.9 in three ranges, over 4000 46.0 | 30.3, four 27.8.  Not next to narrow items, whose ranges have the fp32 partial rows.
       const int most = stream_narrow && narrow_keys > 0 ? 1 : std::max(1, std::min(8, (int)(256 / (blocks * s.H))));

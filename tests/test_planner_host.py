@@ -361,6 +361,7 @@ def test_key_ranges_of_streamed_chunks(rows, start, ranges):
 def test_partial_rows_of_staged_and_narrow_chunks_are_apart():
     # a wide item that is staged in several key ranges (fp16 partial rows) next to a narrow one in several (fp32, numbered after them)
     lib, _ = both(3000, max_devices=2, max_step_tokens=4096, max_pos=8192)
+    lib.set_attn_targets(257, 2048)                  # staged
     for d in (0, 1):
         lib.plan([(d, hi.CHUNK, 0, 4000)])
     plan = lib.plan([(0, hi.CHUNK, 4000, 64), (1, hi.CHUNK, 4000, 20)])
@@ -372,4 +373,23 @@ def test_partial_rows_of_staged_and_narrow_chunks_are_apart():
     assert lib.blocks() == [] and len(wide) > 1 and len(narrow) > 1
     assert 0 <= min(it["part_row"] for it in wide)
     assert max(it["part_row"] + it["nq"] for it in wide) <= min(it["part_row"] for it in narrow)
+    lib.close()
+
+
+@pytest.mark.parametrize("rows,start,millions", [([128], 4000, 17), ([256], 6000, 51), ([256, 40], 4500, 46), ([512], 3000, 53)])
+def test_small_steps_hold_no_partial_results_in_fp16(rows, start, millions):
+    # staged items hold the results of their key ranges in fp16, streamed ones in fp32 (numbered after the others): up to 95 M rows x
+    # keys x heads a step is staged only if no item is cut, however much faster that may be
+    lib, _ = both(4000, max_devices=8, max_step_tokens=4096, max_pos=8192)
+    for d in range(len(rows)):
+        for q in range(0, start, 2048):
+            lib.plan([(d, hi.CHUNK, q, min(2048, start - q))])
+    segs = [(d, hi.CHUNK, start, n) for d, n in enumerate(rows)]
+    lib.set_attn_targets(257, 2048)
+    fp16_rows = max(it["part_row"] for it in lib.plan(segs)["chunk_items"])
+    lib.set_attn_targets(256, 2048)
+    plan = lib.plan(segs)
+    assert fp16_rows >= 0                            # staged, these steps would be cut
+    assert lib.blocks() or not plan["merge_items"]
+    assert sum(-(-n // 32) * 32 * (start + n / 2) for n in rows) * SHAPE["n_heads"] / 1e6 == pytest.approx(millions, abs=2)
     lib.close()
