@@ -298,6 +298,8 @@ def test_streamed_chunks_are_listed_in_blocks_of_rows(rows, start):
     plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
     n = check_blocks(lib, plan)
     ranges = sum(-(-it["nq"] // 32) for it in plan["chunk_items"][:len(plan["chunk_items"]) - lib.narrow_items()])
+    with pytest.raises(HatError):
+        lib.blocks(cap=n - 1)
     assert n == ranges > 0                           # 26 blocks for 256 + 9 x 64 rows, where ten times the longest item's would be 80
     lib.set_attn_targets(4096, 2048)                 # many key ranges: staged
     plan = lib.plan([(d, hi.CHUNK, start, n) for d, n in enumerate(rows)])
