@@ -8,7 +8,8 @@ from gpu_util import Pair, rel_err
 from test_gpu_narrow_chunks import SHAPES, TOL
 
 pytestmark = pytest.mark.gpu
-# rows at the edges of a block and of an item, over no keys, a few, and enough for key ranges (from about 1000 keys on)
+
+
 def planned_blocks(cfg, segs, target=256):
     """(row blocks, waves of each) with which the library streams a step of (start, rows), one device each; (0, 0): staged"""
     from paper_2503_18989_amd import HatPlanner
@@ -23,6 +24,7 @@ def planned_blocks(cfg, segs, target=256):
     return r
 
 
+# rows at the edges of a block and of an item, over no keys, a few, and enough for key ranges (from about 1000 keys on)
 CASES = [([33, 64, 65, 96], [0, 15, 700, 1500]), ([255, 256, 257], [1290, 1, 47]), ([300, 40, 7, 128], [500, 1040, 33, 0])]
 
 
