@@ -441,7 +441,7 @@ static hat_status_t create_impl(const hat_mid_config_t* cfg, const hat_mid_layer
     const hat_mid_layer_weights_t& w = layers[l];
     LayerDev& ld = h->b.layers[l];
     if ((e = hat_launch_retile(ld.wqkv, s.Nqkv, s.d, (const bf16_t*)w.wq, (const bf16_t*)w.wk, (const bf16_t*)w.wv,
-                               s.d, s.d, 1, st)) != hipSuccess)
+                               s.d, s.d, s.hd == 64 ? HAT_RETILE_QKV64 : HAT_RETILE_QKV128, st)) != hipSuccess)
       return bail(e, "retile qkv");
     if ((e = hat_launch_retile(ld.wo, s.No, s.d, (const bf16_t*)w.wo, nullptr, nullptr, s.d, s.d, 0, st)) !=
         hipSuccess)
@@ -1047,14 +1047,17 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     g.epilogue = HAT_EPI_QKV;
     g.qkv = HatQkvOut{h->b.table, pd.kv_dst, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16};
     g.force_tile = h->force_tile[0];
-    const HatGemmPlan qp = hat_gemm_plan(g);
-    if (qp.tile >= 0) {
-      LAUNCH(h, st, HAT_K_GEMM_QKV, hat_launch_gemm(g, qp, st));
-    } else {
+    HatGemmPlan qp = hat_gemm_plan(g);   // a streaming tile, or none
+    // A forced LDS tile with a K split of one runs the product and the rotary launch apart, as the form that tests compare with.
+    const bool apart = qp.tile < 0 && h->force_tile[0] >= 0 && h->force_ksplit[0] > 0;
+    if (qp.tile < 0) {
       g.epilogue = HAT_EPI_P32;
-      if ((rc = run_gemm(HAT_K_GEMM_QKV, g)) != HAT_OK) return rc;
-      LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
+      qp = hat_gemm_plan(g);
+      if (!apart) g.epilogue = HAT_EPI_QKV;
     }
+    LAUNCH(h, st, HAT_K_GEMM_QKV, hat_launch_gemm(g, qp, st));
+    if (apart)
+      LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_append(pd, h->b.qkv, h->b.table, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16, st));
     HatAttn a{};
     a.qkv = h->b.qkv; a.pool_layer = pool_l; a.outP = h->b.attn; a.part_o = h->b.part_o; a.part_o32 = h->b.part_o32; a.part_ml = h->b.part_ml;
     a.part32_row0 = s.part_rows_cap;

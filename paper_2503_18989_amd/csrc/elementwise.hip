@@ -434,8 +434,13 @@ __global__ void retile_kernel(act_t* __restrict__ dst, int Nw, int Kd, const bf1
   int sr = -1;
   if (mode == 0) {
     if (R < n0) { src = s0; sr = R; }
-  } else if (mode == 1) {
-    if (R < 3 * n0) { src = R < n0 ? s0 : R < 2 * n0 ? s1 : s2; sr = R % n0; }
+  } else if (mode == HAT_RETILE_QKV64 || mode == HAT_RETILE_QKV128) {
+    if (R < 3 * n0) {
+      const int hd = mode == HAT_RETILE_QKV64 ? 64 : 128;
+      src = R < n0 ? s0 : R < 2 * n0 ? s1 : s2;
+      const int r = R % n0, p = (r % hd) >> 5, w = r & 31;
+      sr = r - r % hd + p * 16 + (w & 15) + (w < 16 ? 0 : hd / 2);
+    }
   } else {
     // gate/up: every 32-row block = 16 gate rows, then the up rows of the same 16 features
     const int blk = R >> 5, w = R & 31;

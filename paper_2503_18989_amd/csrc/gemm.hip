@@ -53,6 +53,83 @@ __device__ __forceinline__ void wait_vmcnt() { hat_wait_vmcnt<N>(); }
 template <int N>
 __device__ __forceinline__ void wait_operands(f16x8 (&v)[N]) { hat_wait_operands(v); }
 
+// The QKV result on its way out.  A thread has rows i0 .. i0+3 (lo; i0 < 16) and i0+16 .. i0+19 (hi) of a panel of W, which are features
+// f .. f+3 and f+hd/2 .. of a head (hat_launch_retile).  q and k are rotated in fp32 and rounded once; k and v go to the
+// token's cache slot.
+struct QkvPart {   // where a panel's features belong (uniform)
+  int which, head, f0;   // 0 q, 1 k, 2 v; its first feature, below hd/2
+};
+__device__ __forceinline__ QkvPart qkv_part(const HatQkvOut& o, int panel) {
+  const int ppd = o.hd >> 5, head3 = panel / ppd;   // panels per head
+  const int which = head3 / o.H;
+  return {which, head3 - which * o.H, (panel - head3 * ppd) * 16};
+}
+struct QkvAngles { f32x4 c01, c23; };   // (cos, sin) of four pairs
+__device__ __forceinline__ QkvAngles qkv_angles(const HatQkvOut& o, int tok, int f) {
+  const float2* t = o.table + (size_t)tok * (o.hd >> 1) + f;
+  return {*(const f32x4*)t, *(const f32x4*)(t + 2)};
+}
+// q, k and v saturate at the fp16 range before anything else happens to them
+__device__ __forceinline__ f32x4 saturate(f32x4 x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_fmed3f(x[e], -65504.f, 65504.f);
+  return x;
+}
+__device__ __forceinline__ void rotate(const QkvAngles& ang, f32x4& lo, f32x4& hi) {
+  const float c[4] = {ang.c01[0], ang.c01[2], ang.c23[0], ang.c23[2]}, s[4] = {ang.c01[1], ang.c01[3], ang.c23[1], ang.c23[3]};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = lo[e], b = hi[e];
+    lo[e] = a * c[e] - b * s[e];
+    hi[e] = b * c[e] + a * s[e];
+  }
+}
+__device__ __forceinline__ f16x4 to_act4(f32x4 x) { return __builtin_convertvector(saturate(x), f16x4); }
+__device__ __forceinline__ kvx4 to_kv4(f32x4 x, int kv_f16) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  if (kv_f16) return __builtin_bit_cast(kvx4, to_act4(x));
+  return __builtin_bit_cast(kvx4, __builtin_convertvector(x, bf16x4));
+}
+// Where the four features from `i0` of a panel on go for one token, apart from what is the same for all tokens: offsets of q in its
+// P32 row, of k in its tile, of v in its tile (relative to the head's pages).  A thread computes them once for all panels.
+struct QkvToken {
+  int q;
+  size_t k, v;
+};
+__device__ __forceinline__ QkvToken qkv_token(const HatGemm& g, int tok, int dst, int i0) {
+  const size_t page = (size_t)(dst >> 4) * kv_head_elems(g.qkv.hd);
+  const int slot = dst & 15;
+  return {(int)p32_index(tok, i0, g.Nout), page + ktile_index(slot, i0), page + 16 * g.qkv.hd + vtile_index(slot, i0)};
+}
+// lo: rows i0 .. i0+3 of the panel, hi: rows i0+16 .. (their partners)
+__device__ __forceinline__ void store_qkv(const HatGemm& g, const QkvPart& part, const QkvToken& t, const QkvAngles& ang, f32x4 lo, f32x4 hi) {
+  const HatQkvOut& o = g.qkv;
+  const int half = o.hd >> 1;
+  lo = saturate(lo);
+  hi = saturate(hi);
+  if (part.which < 2) rotate(ang, lo, hi);
+  if (part.which == 0) {
+    act_t* q = g.outP + (size_t)((part.head * o.hd + part.f0) >> 3) * 256 + t.q;
+    *(f16x4*)q = to_act4(lo);
+    *(f16x4*)(q + (half >> 3) * 256) = to_act4(hi);
+    return;
+  }
+  const kvx4 a = to_kv4(lo, o.kv_f16), b = to_kv4(hi, o.kv_f16);
+  kv_t* head = o.pool + (size_t)part.head * o.n_pages * kv_head_elems(o.hd);
+  if (part.which == 1) {
+    kv_t* k = head + ktile_index(0, part.f0) + t.k;
+    *(kvx4*)k = a;
+    *(kvx4*)(k + ktile_index(0, half)) = b;
+  } else {   // a V tile is feature-major: two-byte stores
+    kv_t* v = head + vtile_index(0, part.f0) + t.v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[8 * e] = a[e];
+      v[vtile_index(0, half) + 8 * e] = b[e];
+    }
+  }
+}
+
 template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE>
 struct Tile {
   static constexpr int NW = WF * WT * WK;
@@ -302,6 +379,28 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   // ---- epilogue.  lane: token = 16 * (token block) + lane%16 ; feature = f0 + 16i + 4*(lane/16) + r
   const int h4 = (lane >> 4) * 4, n = lane & 15;
   const int f_base = ft * BF + wf * MI * 16;
+  if constexpr (EPI == HAT_EPI_QKV) {
+    // All loads of a panel before its first store: behind a store that may alias, each would wait out a memory round trip of its own.
+    auto token = [&](int j) { return tt * BT + (wt + WT * (j0 + j)) * 16 + n; };
+    QkvToken t[NJO];
+#pragma unroll
+    for (int j = 0; j < NJO; ++j) t[j] = qkv_token(g, token(j), g.qkv.kv_dst[min(token(j), g.T - 1)], h4);
+#pragma unroll
+    for (int i = 0; i < MI; i += 2) {
+      const int fb = f_base + i * 16;
+      if (fb >= g.Nout) continue;
+      const QkvPart part = qkv_part(g.qkv, fb >> 5);
+      QkvAngles ang[NJO];
+      if (part.which < 2) {
+#pragma unroll
+        for (int j = 0; j < NJO; ++j) ang[j] = qkv_angles(g.qkv, min(token(j), g.T - 1), part.f0 + h4);
+      }
+#pragma unroll
+      for (int j = 0; j < NJO; ++j)
+        if (token(j) < g.T && j < jn) store_qkv(g, part, t[j], ang[j], acc[i][j], acc[i + 1][j]);
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < NJO; ++j) {
     const int tok = tt * BT + (wt + WT * (j0 + j)) * 16 + n;
@@ -311,10 +410,13 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
       for (int i = 0; i < MI; ++i) {
         const int fb = f_base + i * 16;
         if (fb >= g.Nout) continue;
+        // the feature of W's row fb (hat_launch_retile)
+        const int ppd = g.qkv.hd >> 5, panel = fb >> 5, head3 = panel / ppd;
+        const int f = head3 * g.qkv.hd + (panel - head3 * ppd) * 16 + (i & 1) * (g.qkv.hd >> 1);
         f16x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = to_act(acc[i][j][e]);
-        *(f16x4*)(g.outP + p32_index(tok, fb + h4, g.Nout)) = v;
+        *(f16x4*)(g.outP + p32_index(tok, f + h4, g.Nout)) = v;
       }
     } else if constexpr (EPI == HAT_EPI_SWIGLU) {
       // a 32-row block of W holds 16 gate rows then the 16 up rows of the same features
@@ -344,58 +446,6 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   }
 }
 
-// One thread's share of the QKV result: features i0 .. i0+3 of panel `panel` (lo) and their partners hd/2 further (hi) of
-// token tok.  q and k are rotated in fp32 and rounded once; k and v go to the token's cache slot.
-__device__ __forceinline__ void store_qkv(const HatGemm& g, int tok, int panel, int i0, f32x4 lo, f32x4 hi) {
-  const HatQkvOut& o = g.qkv;
-  const int ppd = o.hd >> 5;                 // panels per head
-  const int head3 = panel / ppd, which = head3 / o.H, head = head3 - which * o.H;
-  const int f = (panel % ppd) * 32 + i0, half = o.hd >> 1;   // feature within the head, below half
-  // q, k and v saturate at the fp16 range before anything else happens to them, as they do on their way through qkv
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    lo[e] = __builtin_amdgcn_fmed3f(lo[e], -65504.f, 65504.f);
-    hi[e] = __builtin_amdgcn_fmed3f(hi[e], -65504.f, 65504.f);
-  }
-  if (which < 2) {
-    const f32x4 c01 = *(const f32x4*)(o.table + (size_t)tok * half + f), c23 = *(const f32x4*)(o.table + (size_t)tok * half + f + 2);
-    const float c[4] = {c01[0], c01[2], c23[0], c23[2]}, s[4] = {c01[1], c01[3], c23[1], c23[3]};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = lo[e], b = hi[e];
-      lo[e] = a * c[e] - b * s[e];
-      hi[e] = b * c[e] + a * s[e];
-    }
-  }
-  if (which == 0) {
-    f16x4 a, b;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { a[e] = to_act(lo[e]); b[e] = to_act(hi[e]); }
-    *(f16x4*)(g.outP + p32_index(tok, head * o.hd + f, g.Nout)) = a;
-    *(f16x4*)(g.outP + p32_index(tok, head * o.hd + f + half, g.Nout)) = b;
-    return;
-  }
-  const int dst = o.kv_dst[tok], slot = dst & 15;
-  kv_t* rec = o.pool + ((size_t)head * o.n_pages + (dst >> 4)) * kv_head_elems(o.hd);
-  kvx4 a, b;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    a[e] = o.kv_f16 ? __builtin_bit_cast(kv_t, to_act(lo[e])) : __builtin_bit_cast(kv_t, (__bf16)lo[e]);
-    b[e] = o.kv_f16 ? __builtin_bit_cast(kv_t, to_act(hi[e])) : __builtin_bit_cast(kv_t, (__bf16)hi[e]);
-  }
-  if (which == 1) {
-    *(kvx4*)(rec + ktile_index(slot, f)) = a;
-    *(kvx4*)(rec + ktile_index(slot, f + half)) = b;
-  } else {   // a V tile is feature-major: two-byte stores (few rows take this way)
-    kv_t* vt = rec + 16 * o.hd;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vt[vtile_index(slot, f + e)] = a[e];
-      vt[vtile_index(slot, f + half + e)] = b[e];
-    }
-  }
-}
-
 template <int NP, int NT>
 struct StreamDepth {   // k-steps in flight per wave: what the register file holds next to the accumulators
   static constexpr int value = NP + NT <= 4 ? 8 : NP == 1 ? 6 : 4;
@@ -418,7 +468,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   constexpr int D = StreamDepth<NP, NT>::value;
   constexpr int TILES = NP * NT;
   constexpr int GRP = TILES < 2 ? TILES : 2;   // 32 x 32 tiles summed per LDS round
-  static_assert(TILES % GRP == 0 && (EPI != HAT_EPI_QKV || GRP == NP), "a round is whole, and holds a rotation pair's halves");
+  static_assert(TILES % GRP == 0, "a round is whole");
   __shared__ __attribute__((aligned(16))) f32x4 red[NW][GRP][4][64];
   // accumulators and ring, with 40 registers for addresses; two workgroups of the smallest tile on a CU, one of the others
   static_assert(TILES * 16 + D * (NP + NT) * 4 + 40 <= (TILES <= 1 ? 128 : 256), "a lane's registers");
@@ -429,20 +479,6 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   const int n = lane & 31, h = lane >> 5;
   const int nF = (EPI == HAT_EPI_QKV ? g.Nout : g.Nw) / (32 * NP);
   const int ft = blockIdx.x % nF, tt = blockIdx.x / nF;
-  // This lane's row of W.  With HAT_EPI_QKV a workgroup holds both halves of its rotation pairs (features i and i + hd/2
-  // of a head), so that a thread of the epilogue ends up with both: two panels hd/64 apart, or with one panel's
-  // worth of rows 16 rows from each of the two.
-  int panel0 = ft * NP, pstep = 1, row0 = 0, wrow = n, wpanel = 0;
-  if constexpr (EPI == HAT_EPI_QKV) {
-    pstep = g.qkv.hd >> 6;
-    const int pair = NP == 1 ? ft >> 1 : ft;
-    panel0 = pair / pstep * (2 * pstep) + pair % pstep;
-    if constexpr (NP == 1) {
-      row0 = (ft & 1) * 16;
-      wrow = row0 + (n & 15);
-      wpanel = n < 16 ? 0 : pstep;
-    }
-  }
   const int KS = g.K >> 4;                     // k-steps of 16
   const int part = blockIdx.z * NW + wave, parts = ksplit * NW;
   const int s0 = (int)((long)part * KS / parts), s1 = (int)((long)(part + 1) * KS / parts);
@@ -452,7 +488,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   const act_t* wsrc[NP];
   const act_t* xsrc[NT];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) wsrc[i] = g.W + (size_t)(panel0 + wpanel + i * pstep) * krow + (size_t)s0 * 512 + h * 256 + wrow * 8;
+  for (int i = 0; i < NP; ++i) wsrc[i] = g.W + (size_t)(ft * NP + i) * krow + (size_t)s0 * 512 + h * 256 + n * 8;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     int row = (tt * NT + j) * 32 + n;
@@ -525,10 +561,15 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
       return v;
     };
     if constexpr (EPI == HAT_EPI_QKV) {
-      // lower halves of the pairs: tile 0 of the round (upper: tile 1), or the tile's rows 0 .. 15 (upper: 16 .. 31)
-      const int tok = (tt * NT + t0 / NP) * 32 + n, q = wave;
-      if (q < (NP == 1 ? 2 : 4) && tok < g.T)
-        store_qkv(g, tok, panel0, row0 + 8 * q + 4 * h, total(0, q), NP == 1 ? total(0, q + 2) : total(1, q));
+      const int u = wave >> 1, q = wave & 1;   // rows 8 q .. of tile u of the round, and their partners 16 rows further
+      const int tok = (tt * NT + (t0 + u) / NP) * 32 + n;
+      if (u < GRP && tok < g.T) {
+        const QkvPart part = qkv_part(g.qkv, ft * NP + (t0 + u) % NP);
+        const int i0 = 8 * q + 4 * h;
+        const QkvToken t = qkv_token(g, tok, g.qkv.kv_dst[tok], i0);
+        const QkvAngles ang = part.which < 2 ? qkv_angles(g.qkv, tok, part.f0 + i0) : QkvAngles{};
+        store_qkv(g, part, t, ang, total(u, q), total(u, q + 2));
+      }
     } else {
       const int u = threadIdx.x >> 8, q = (threadIdx.x >> 6) & 3;
       const int tok = (tt * NT + (t0 + u) / NP) * 32 + n;
@@ -641,9 +682,7 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
     kern<<<grid, dim3(TL::NW * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
     return hipGetLastError();                                           \
   }
-  if constexpr (EPI != HAT_EPI_QKV) {
-    HAT_FOR_TILES(HAT_TRY, EPI)
-  }
+  HAT_FOR_TILES(HAT_TRY, EPI)
 #undef HAT_TRY
 #define HAT_TRY(id, np, nt, epi)                                                     \
   if constexpr (stream_built(id, epi)) {                                             \
@@ -690,6 +729,7 @@ hipError_t hat_gemm_init() {
   if ((e = attr_epi<HAT_EPI_P32>()) != hipSuccess) return e;
   if ((e = attr_epi<HAT_EPI_SWIGLU>()) != hipSuccess) return e;
   if ((e = attr_epi<HAT_EPI_RESID>()) != hipSuccess) return e;
+  if ((e = attr_epi<HAT_EPI_QKV>()) != hipSuccess) return e;
   return hipSuccess;
 }
 

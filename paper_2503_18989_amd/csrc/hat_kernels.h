@@ -17,14 +17,14 @@ constexpr int HAT_NARROW_QROWS = 32;   // chunk items of at most this many rows 
 
 // ---- GEMM: out[t, f] = sum_k X[t, k] * W[f, k], operands in P32 layout ------
 enum HatEpilogue {
-  HAT_EPI_P32 = 0,     // fp16 (act_t) result, P32 layout, row length Nout
+  HAT_EPI_P32 = 0,     // fp16 (act_t) result of the QKV product, P32 layout, row length Nout, features in order
   HAT_EPI_SWIGLU = 1,  // W rows interleaved (16 gate, 16 up): silu(gate)*up, P32, row length Nout
   HAT_EPI_RESID = 2,   // resid[t, f] += result  (fp32 row-major, leading dim Nout)
-  HAT_EPI_QKV = 3      // rotary embedding and KV append on the way out (few rows): q rotated to outP (P32, row
+  HAT_EPI_QKV = 3      // rotary embedding and KV append on the way out: q rotated to outP (P32, row
                        // length Nout, columns [0, Nout/3)), k rotated and v to the cache; k and v are not in outP
 };
 
-// what HAT_EPI_QKV needs besides the product
+// what HAT_EPI_QKV needs besides the product (HAT_EPI_P32: hd)
 struct HatQkvOut {
   const float2* table;    // [T][hd/2] (cos, sin)
   const int32_t* kv_dst;  // [T] page*16 + slot
@@ -63,10 +63,12 @@ hipError_t hat_gemm_init();  // one-time function attributes (dynamic LDS size)
 
 // ---- weight re-tiling (create time) -----------------------------------------
 // dst: P32 [Nw, Kd] in act_t (bf16 -> fp16 is exact for |w| in [2^-17, 65504]).  mode 0: row R <- src0[R] (R < n0), else 0.
-// mode 1 (qkv): rows [0,n0) <- src0, [n0,2n0) <- src1, [2n0,3n0) <- src2.
+// QKV modes (head dim 64, 128): rows [0,n0) <- src0, [n0,2n0) <- src1, [2n0,3n0) <- src2; within a head panel p of 32 rows = features
+// 16 p .. 16 p + 15, then their rotation partners hd/2 further, so that a lane of the product holds both halves of its pairs whatever the tile.
 // mode 2 (gate/up): row R: blk=R/32, w=R%32; f = 16*blk + w%16; (w<16 ? src0 : src1)[f], zero if f >= n0
 // (every 32-row block = 16 gate rows followed by the up rows of the same 16 features).
 // Source rows have Ks elements (Ks <= Kd; columns beyond Ks are zero).
+constexpr int HAT_RETILE_QKV64 = 1, HAT_RETILE_QKV128 = 3;
 hipError_t hat_launch_retile(act_t* dst, int Nw, int Kd, const bf16_t* src0, const bf16_t* src1,
                              const bf16_t* src2, int n0, int Ks, int mode, hipStream_t st);
 hipError_t hat_launch_bf16_to_f32(const bf16_t* src, float* dst, int n, hipStream_t st);
