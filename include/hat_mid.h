@@ -332,14 +332,14 @@ hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int3
  * (which: 0 = QKV, 1 = O, 2 = gate/up, 3 = down; tile: index into the library's
  * tile table, -1 = automatic choice; ksplit: 1 = none, only honoured where the
  * result is accumulated).  For sweeps of launch shapes; results do not change
- * beyond fp32 summation order, and for QKV by whether k and v are rounded to fp16 on their way to the cache type: the
- * streaming tiles (the last four) rotate and append by themselves.  A streaming tile that is not built for a class (tile
- * 27 for gate/up, 25 and 27 for O and down) leaves its choice automatic. */
+ * beyond fp32 summation order, except with tile 1 on QKV: there the product leaves q, k and v in fp16 and the rotary
+ * embedding and append are a launch behind it, while every other tile rotates and appends by itself and rounds once.  A
+ * streaming tile (the last four) that is not built for a class (tile 27 for gate/up, 25 and 27 for O and down) leaves its choice automatic. */
 hat_status_t hat_mid_debug_force_gemm(hat_mid_t* h, int32_t which, int32_t tile, int32_t ksplit);
 
 /* The automatic choice for a GEMM of T rows: Nw = weight rows (padded to 256), Nout = logical
  * output features, K = inner dimension (multiple of 64), epilogue 0 = fp16 output, 1 = SwiGLU, 3 = QKV with rotary
- * embedding and append (*tile -1: not for this batch, which takes epilogue 0 and a launch for the rest),
+ * embedding and append of few rows (*tile -1: not for this batch, which takes the tile of epilogue 0),
  * 2 = accumulate into the residual (the only one whose K may be split; part_rows = capacity of
  * the partial-sum buffer in rows, 0 = no buffer).  *ksplit is 1 also where only the last token tiles of a
  * large batch are split (hat_mid_debug_gemm_split tells).  Host code only, no GPU work; for tests of the

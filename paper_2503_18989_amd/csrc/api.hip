@@ -1048,8 +1048,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     g.qkv = HatQkvOut{h->b.table, pd.kv_dst, pool_l, c.n_pages, s.H, s.hd, c.kv_dtype == HAT_KV_F16};
     g.force_tile = h->force_tile[0];
     HatGemmPlan qp = hat_gemm_plan(g);   // a streaming tile, or none
-    // A forced LDS tile with a K split of one runs the product and the rotary launch apart, as the form that tests compare with.
-    const bool apart = qp.tile < 0 && h->force_tile[0] >= 0 && h->force_ksplit[0] > 0;
+    const bool apart = h->force_tile[0] == HAT_APART_TILE;
     if (qp.tile < 0) {
       g.epilogue = HAT_EPI_P32;
       qp = hat_gemm_plan(g);

@@ -631,6 +631,8 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   X(22, 256, 160, 4, 2, 1, 32, 4, EPI) \
   X(23, 128, 160, 4, 2, 1, 64, 3, EPI)
 constexpr int kNumLdsTiles = 24;
+// The QKV product without rotation and append is built for one tile, as the form that the others are compared with.
+constexpr bool lds_built(int id, int epi) { return epi != HAT_EPI_P32 || id == HAT_APART_TILE; }
 // the streaming kernel's tiles (32 NP features x 32 NT tokens): id, NP, NT.  Four waves instead of eight, 32 x 64 and
 // 32 x 96 measured level with or behind these at every size; 64 x 32 is for the QKV product of 17 .. 32 rows (see hat_gemm_plan).
 #define HAT_FOR_STREAM(X, EPI) \
@@ -673,7 +675,7 @@ constexpr TileInfo kTiles[kNumTiles] = {
 template <int EPI>
 hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
 #define HAT_TRY(id, bf, bt, wf, wt, wk, bkt, ns, epi)                   \
-  if (p.tile == id) {                                                   \
+  if constexpr (lds_built(id, epi)) if (p.tile == id) {                 \
     using TL = Tile<bf, bt, wf, wt, wk, bkt, ns>;                       \
     const int nT = (g.T + bt - 1) / bt, nF = (g.Nw + bf - 1) / bf;      \
     dim3 grid(nT * nF, 1, p.ksplit);                                    \
@@ -702,9 +704,11 @@ template <int EPI>
 hipError_t attr_epi() {
   hipError_t e;
 #define HAT_ATTR(id, bf, bt, wf, wt, wk, bkt, ns, epi)                                                    \
-  e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>,                     \
-                          hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, wk, bkt, ns>::LDS_BYTES); \
-  if (e != hipSuccess) return e;
+  if constexpr (lds_built(id, epi)) {                                                                     \
+    e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>,                   \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, wk, bkt, ns>::LDS_BYTES); \
+    if (e != hipSuccess) return e;                                                                        \
+  }
   HAT_FOR_TILES(HAT_ATTR, EPI)
 #undef HAT_ATTR
   return hipSuccess;

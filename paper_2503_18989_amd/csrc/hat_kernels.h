@@ -24,6 +24,8 @@ enum HatEpilogue {
                        // length Nout, columns [0, Nout/3)), k rotated and v to the cache; k and v are not in outP
 };
 
+// A forced tile (never a chosen one) whose QKV product has the HAT_EPI_P32 epilogue and a rotary and append launch behind it
+constexpr int HAT_APART_TILE = 1;
 // what HAT_EPI_QKV needs besides the product (HAT_EPI_P32: hd)
 struct HatQkvOut {
   const float2* table;    // [T][hd/2] (cos, sin)
