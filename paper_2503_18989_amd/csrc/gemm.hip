@@ -379,9 +379,53 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   // ---- epilogue.  lane: token = 16 * (token block) + lane%16 ; feature = f0 + 16i + 4*(lane/16) + r
   const int h4 = (lane >> 4) * 4, n = lane & 15;
   const int f_base = ft * BF + wf * MI * 16;
+  auto token = [&](int j) { return tt * BT + (wt + WT * (j0 + j)) * 16 + n; };
+  if constexpr (EPI == HAT_EPI_RESID) {
+    // fp32 result: added into the residual when K is not split, else stored as this
+    // split's partial sum (the next consumer of the residual folds the partials in)
+    const int row0 = tt0 * BT;   // first row of the partial sums
+    if (f_base >= g.Nout) return;
+    if (ksplit > 1) {
+      float* base = g.part + (size_t)((long)kz * (g.T - row0) - row0) * g.Nout + f_base + h4;
+#pragma unroll
+      for (int j = 0; j < NJO; ++j) {
+        if (token(j) >= g.T || j >= jn) continue;
+        float* p = base + (size_t)token(j) * g.Nout;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          if (f_base + i * 16 < g.Nout) *(f32x4*)(p + i * 16) = acc[i][j];
+      }
+      return;
+    }
+    // A thread's pieces of the residual (those beyond its end: a piece that is there) are read together, or in two halves where they do not fit the
+    // registers, before the first is written back.  One at a time, each read waits out a memory round trip and the store before it, as the two may
+    // alias: O and down of 2788 rows (7B shape) 98.4 -> 94.3 and 218.1 -> 212.5 us, of 4096 rows (13B shape) 195.9 -> 190.2 and 449.1 -> 444.6.  What is left of the
+    // update is its traffic, 92 MB that all workgroups of a single round move at the same time.
+    constexpr int H = MI * NJO <= 24 ? NJO : (NJO + 1) / 2;   // token blocks read together
+#pragma unroll
+    for (int jh = 0; jh < NJO; jh += H) {
+      f32x4 r[MI][H];
+#pragma unroll
+      for (int j = jh; j < jh + H && j < NJO; ++j) {
+        const float* p = g.resid + (size_t)min(token(j), g.T - 1) * g.Nout + f_base + h4;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) r[i][j - jh] = *(const f32x4*)(p + (f_base + i * 16 < g.Nout ? i * 16 : 0));
+      }
+      // (one wait for all of them: left to the compiler there is one for each token block, under its branch, and each waits for the stores before it too)
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+#pragma unroll
+      for (int j = jh; j < jh + H && j < NJO; ++j) {
+        if (token(j) >= g.T || j >= jn) continue;
+        float* p = g.resid + (size_t)token(j) * g.Nout + f_base + h4;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          if (f_base + i * 16 < g.Nout) *(f32x4*)(p + i * 16) = r[i][j - jh] + acc[i][j];
+      }
+    }
+    return;
+  }
   if constexpr (EPI == HAT_EPI_QKV) {
     // All loads of a panel before its first store: behind a store that may alias, each would wait out a memory round trip of its own.
-    auto token = [&](int j) { return tt * BT + (wt + WT * (j0 + j)) * 16 + n; };
     QkvToken t[NJO];
 #pragma unroll
     for (int j = 0; j < NJO; ++j) t[j] = qkv_token(g, token(j), g.qkv.kv_dst[min(token(j), g.T - 1)], h4);
@@ -403,7 +447,7 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   }
 #pragma unroll
   for (int j = 0; j < NJO; ++j) {
-    const int tok = tt * BT + (wt + WT * (j0 + j)) * 16 + n;
+    const int tok = token(j);
     if (tok >= g.T || j >= jn) continue;
     if constexpr (EPI == HAT_EPI_P32) {
 #pragma unroll
@@ -428,19 +472,6 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = to_act(silu_f(acc[i][j][e]) * acc[i + 1][j][e]);
         *(f16x4*)(g.outP + p32_index(tok, fb + h4, g.Nout)) = v;
-      }
-    } else {
-      // fp32 result: added into the residual when K is not split, else stored as this
-      // split's partial sum (the next consumer of the residual folds the partials in)
-      const int row0 = tt0 * BT;   // first row of the partial sums
-      float* outb = (ksplit == 1) ? g.resid : g.part;
-      const long shift = (ksplit == 1) ? 0 : (long)kz * (g.T - row0) - row0;   // uniform: no address registers across the loop
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const int fb = f_base + i * 16;
-        if (fb >= g.Nout) continue;
-        float* p = outb + (size_t)(tok + shift) * g.Nout + fb + h4;
-        *(f32x4*)p = ksplit == 1 ? *(const f32x4*)p + acc[i][j] : acc[i][j];
       }
     }
   }
