@@ -70,6 +70,8 @@ __device__ __forceinline__ float half_max(float x) {
 // non-temporal hint keeps the stream from displacing what other kernels left in the caches, and
 // measures 11 % faster on the verify-heavy workload (363 -> 325 us per launch).
 __device__ __forceinline__ u32x4 stream_load(const u32x4* p) { return __builtin_nontemporal_load(p); }
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+typedef __attribute__((address_space(1))) kv_t global_kv;
 
 // Online-softmax update for one 32-key S^T tile held as 16 accumulator values.
 // key of value r: key0 + 8*(r/4) + 4*half + r%4.  Returns probabilities as the
@@ -230,28 +232,41 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
   // raw registers, and travel while the current pair is soft-maxed and multiplied.  Two
   // workgroups share a CU (<= 256 VGPRs).
   u32x4 kraw[NS], varaw[NC], vbraw[NC];
+  // Page ids are scalar loads.  For chunk items those of the next pair but one are read a pair ahead, so that no page waits for its id (8 x 64 rows over 4096
+  // keys of the 13B shape 163 -> 157 us, 871 ragged rows at head dim 64 42.9 -> 40.8).  Verify items, which have more bytes in flight than the memory
+  // needs, are slower with it (30 caches of 1 k .. 8 k 299 -> 310).
+  int idA = 0, idB = 0;
   const kv_t *recA = pool, *recB = pool;
-  auto page_recs = [&](int pp) {   // wave-uniform: scalar loads of the two page ids
-    int ia = 2 * pp, ib = 2 * pp + 1;
-    ib = ib < sg.npages ? ib : sg.npages - 1;
-    recA = pool + (size_t)sg.pt[ia] * page_stride;
-    recB = pool + (size_t)sg.pt[ib] * page_stride;
+  auto page_ids = [&](int pp) {
+    const int p0 = __builtin_amdgcn_readfirstlane(pp);
+    idA = sg.pt[min(2 * p0, sg.npages - 1)];
+    idB = sg.pt[min(2 * p0 + 1, sg.npages - 1)];
   };
-  auto page_load = [](const u32x4* q) { return BLOCKS ? *q : stream_load(q); };
+  auto page_recs = [&](int pp) {
+    if (!NARROW) page_ids(pp);
+    recA = pool + (size_t)idA * page_stride;
+    recB = pool + (size_t)idB * page_stride;
+    if (NARROW) page_ids(pp + NW);
+  };
+  auto page_load = [](const global_u32x4* q) -> u32x4 { return BLOCKS ? *q : __builtin_nontemporal_load(q); };
   auto load_k = [&]() {
-    const kv_t* krec = (n < 16) ? recA : recB;
+    auto* krec = (const global_kv*)(((n < 16) ? recA : recB) + (half * 16 + (n & 15)) * 8);
+    asm volatile("" : "+v"(krec));   // (one address and immediate offsets)
 #pragma unroll
-    for (int s = 0; s < NS; ++s) kraw[s] = page_load((const u32x4*)(krec + ((2 * s + half) * 16 + (n & 15)) * 8));
+    for (int s = 0; s < NS; ++s) kraw[s] = page_load((const global_u32x4*)(krec + s * 256));
   };
   auto load_v = [&]() {
+    auto *va = (const global_kv*)(recA + 16 * HD + lane * 8), *vb = (const global_kv*)(recB + 16 * HD + lane * 8);
+    asm volatile("" : "+v"(va), "+v"(vb));
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      varaw[c] = page_load((const u32x4*)(recA + 16 * HD + c * 512 + lane * 8));
-      vbraw[c] = page_load((const u32x4*)(recB + 16 * HD + c * 512 + lane * 8));
+      varaw[c] = page_load((const global_u32x4*)(va + c * 512));
+      vbraw[c] = page_load((const global_u32x4*)(vb + c * 512));
     }
   };
   int pp = pair0 + wave;
   if (pp < pair1) {
+    if (NARROW) page_ids(pp);
     page_recs(pp);
     load_k();
     load_v();
@@ -389,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void attn_verify_probe_kernel(HatPlanDev p,
   const HatAttnItem it = a.items[blockIdx.x];
   const int head = blockIdx.y;
   const SegInfo sg = seg_info(p, it);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = lane >> 5, n = lane & 31;
   int kv_end = it.kv_end < sg.kv_len ? it.kv_end : sg.kv_len;
   const int pair0 = it.kv_begin >> 5, pair1 = (kv_end + 31) >> 5;
@@ -398,10 +413,8 @@ __global__ __launch_bounds__(256, 2) void attn_verify_probe_kernel(HatPlanDev p,
   u32x4 kraw[NS], varaw[NC], vbraw[NC];
   const kv_t *recA = pool, *recB = pool;
   auto page_recs = [&](int pp) {
-    int ia = 2 * pp, ib = 2 * pp + 1;
-    ib = ib < sg.npages ? ib : sg.npages - 1;
-    recA = pool + (size_t)sg.pt[ia] * REC;
-    recB = pool + (size_t)sg.pt[ib] * REC;
+    recA = pool + (size_t)sg.pt[2 * pp] * REC;
+    recB = pool + (size_t)sg.pt[min(2 * pp + 1, sg.npages - 1)] * REC;
   };
   auto load_all = [&]() {
     const kv_t* krec = (n < 16) ? recA : recB;
