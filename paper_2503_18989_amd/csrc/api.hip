@@ -1012,6 +1012,12 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   LAUNCH(h, st, HAT_K_GATHER, hat_launch_gather(pd, h->b.resid, s.d, c.io_dtype, st));
   if (!gather_norms) LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
 
+  // Verify items go along in the launch of the streamed chunk items: they fill what its last round leaves idle, and a launch is less.  The
+  // attention of a layer gains 2 .. 8 % of the layer where its workgroups have four waves (40 mixes of chunks of 20 .. 230 rows with 1 .. 20 drafts at three head
+  // counts).  With eight waves a verify item is short for them: as many items as leave each CU one gain the same, beyond a thousand
+  // they lose 3 .. 13 %.  Not where each kind is to be timed by itself.
+  const bool along = (sp.n_cblocks > 0 || sp.n_narrow > 0) && (sp.block_waves != 8 || sp.n_vitems * s.H <= 256) && !h->profiling && !h->verify_probe;
+
   int nparts = 0;  // split-K partial sums of the previous residual GEMM still to be folded in,
   int prow0 = 0;   // for the rows from this one on
   auto run_gemm = [&](int id, HatGemm& g) -> hat_status_t {
@@ -1064,9 +1070,12 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     if (sp.n_citems > 0) {
       a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
       a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves; a.heads_inner = sp.heads_inner;
+      if (along) {
+        a.verify = (const HatAttnItem*)(D + o_vi); a.n_verify = sp.n_vitems;
+      }
       LAUNCH(h, st, HAT_K_ATTN_CHUNK, hat_launch_attn_chunk(pd, a, st));
     }
-    if (sp.n_vitems > 0) {
+    if (sp.n_vitems > 0 && !along) {
       a.items = (const HatAttnItem*)(D + o_vi); a.n_items = sp.n_vitems;
       if (h->verify_probe)
         LAUNCH(h, st, HAT_K_ATTN_VERIFY, hat_launch_attn_verify_probe(pd, a, (uint32_t*)h->b.fixture_pages, st));

@@ -25,6 +25,8 @@
 // partials that attn_merge combines.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "hat_device_util.h"
 #include "hat_kernels.h"
 #include "hat_layout.h"
@@ -161,44 +163,41 @@ __device__ __forceinline__ f16x8 kv_to_f16(u32x4 raw) { return __builtin_bit_cas
 __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin_amdgcn_fmed3f(x, -65504.f, 65504.f); }
 
 // ------------------------------------------------------------------ verify
-// ROWS = 8: a verify segment, visibility of its own rows from the work item.  ROWS = 32: a narrow chunk item, causal; all 32
-// columns of the MFMA are rows, so the stream pays for the same arithmetic and only the merge at the end grows.
+// Three kinds of items stream the cache (stream_item).  A verify item: at most 8 rows, visibility of its own rows from the work item.  A narrow
+// chunk item, causal: all 32 columns of the MFMA are rows, so the stream pays for the same arithmetic and only the merge at the end grows.
 // Narrow items are bound by the cache stream and by latency, not by the matrix pipe: 8 x 32 rows over 4096 keys of the 13B
 // shape 164 -> 118 .. 121 us (floor 107), 30 rows over 2000 keys of the 7B shape 53.6 -> 20.8 us with the merge.  From 33 rows on every
 // form of this kernel that holds more rows per workgroup (two row blocks per wave, two sets of waves) measured level with or
 // behind the staged kernel below (157 .. 190 us against 175 at 8 x 64 rows, 26 .. 36 against 29 at 1 x 64).
-// BLOCKS: chunk items of any size, a workgroup for each 32 of their rows, which the planner lists as items of their own.  The
+// A row block: chunk items of any size, a workgroup for each 32 of their rows, which the planner lists as items of their own.  The
 // row blocks of an item read the same pages, so they run on one XCD, next to each other, and without the non-temporal hint: 30.9 ->
 // 20.0 us with the merge for 256 rows over 1280 keys of the 7B shape, 155 -> 138 for 1024 over 4096 of the 13B shape (fp16 cache; 167 both
 // ways with bf16), 36.6 -> 21.6 for 3 x 250 rows over 1000 keys at head dim 64.  Per row and key it moves eight times the cache bytes of the staged kernel (about
 // 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's idle waves, key splits and merge.
 // NW waves share the keys; the planner knows where four of them are faster and where eight.
-template <int HD, bool KVF16, int ROWS, int NW, bool BLOCKS>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
+// ROWS = 8 is the launch of verify items by themselves, ROWS = 32 that of the step's row blocks, narrow items and the verify items that go along
+// (enqueue_step): each kind is a copy of the code, as one that asks at run time took 28 registers more and spilled.  One launch
+// instead of three: 871 rows of ragged chunks and drafts at head dim 64 2301 -> 2118 us a step.
+template <int HD, int ROWS>
+struct StreamLds {   // where the waves' results meet
+  static constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
+  __attribute__((aligned(16))) float o[4][NARROW ? HD * (ROWS + 1) : ROWS * HD];
+  float m[4][ROWS], l[4][ROWS];
+  float2 ml[4][64];
+};
+// One item in one head.  A row block's pages are read by the blocks next to it too, the others' once (non-temporal loads).
+enum StreamKind { kBlock, kNarrow, kVerify };
+template <int HD, bool KVF16, int ROWS, int NW, StreamKind KIND>
+__device__ __forceinline__ void stream_item(const HatPlanDev& p, const HatAttn& a, const HatAttnItem& it, int head, StreamLds<HD, ROWS>& lds) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
   constexpr int NC = HD / 32;  // 32-row blocks of O^T
   constexpr int REC = 2 * 16 * HD;  // elements of one (page, head) record
   constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
   // element (row, feature) of a wave's result: feature-major for 32 rows, where lanes are rows (padded: no bank conflicts)
   constexpr int RSTR = NARROW ? 1 : HD, FSTR = NARROW ? ROWS + 1 : 1;
-  __shared__ __attribute__((aligned(16))) float lds_o[4][NARROW ? HD * (ROWS + 1) : ROWS * HD];
-  __shared__ float lds_m[4][ROWS], lds_l[4][ROWS];
-
-  static_assert(!BLOCKS || NARROW, "row blocks of 32");
-  int item = blockIdx.x, head = blockIdx.y;
-  if constexpr (BLOCKS) {   // a contiguous run of (head, row block) per XCD, as consecutive workgroup ids go round the XCDs
-    const int total = a.H * a.n_items, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
-    const int b = x * per + (x < rem ? x : rem) + (int)blockIdx.x / 8;
-    if (a.heads_inner) {   // H % 8 == 0: each block in all heads of the XCD before the next, so that the shortest start last
-      const int hx = a.H / 8, i = (int)blockIdx.x / 8;
-      item = i / hx;
-      head = x * hx + i % hx;
-    } else {
-      item = b % a.n_items;
-      head = b / a.n_items;
-    }
-  }
-  const HatAttnItem it = a.items[item];
+  constexpr bool verify = KIND == kVerify;
+  auto& lds_o = lds.o;
+  auto &lds_m = lds.m, &lds_l = lds.l;
   const SegInfo sg = seg_info(p, it);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, n = lane & 31;
@@ -248,7 +247,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
     recB = pool + (size_t)idB * page_stride;
     if (NARROW) page_ids(pp + NW);
   };
-  auto page_load = [](const global_u32x4* q) -> u32x4 { return BLOCKS ? *q : __builtin_nontemporal_load(q); };
+  auto page_load = [](const global_u32x4* q) -> u32x4 { return KIND != kBlock ? __builtin_nontemporal_load(q) : *q; };
   auto load_k = [&]() {
     auto* krec = (const global_kv*)(((n < 16) ? recA : recB) + (half * 16 + (n & 15)) * 8);
     asm volatile("" : "+v"(krec));   // (one address and immediate offsets)
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
       }
     }
     f16x8 p0, p1;
-    if (NARROW) {
+    if constexpr (!verify) {
       if (key0 + 31 > sg.start + it.q0) softmax_step<NC, 1>(sacc, scale_log2, key0, half, qpos, m_run, l_run, o, p0, p1);
       else softmax_step<NC, 0>(sacc, scale_log2, key0, half, 0, m_run, l_run, o, p0, p1);
     } else if (key0 + 31 >= sg.start) {
@@ -322,7 +321,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
   if constexpr (NW == 8) {   // waves 4 .. 7 hand their state to waves 0 .. 3, lane by lane
     static_assert(sizeof(lds_o) >= 4 * 64 * NC * 16 * sizeof(float), "four waves' accumulators");
     f32x4* buf = (f32x4*)&lds_o[0][0] + (wave & 3) * (NC * 4 * 64) + lane;
-    __shared__ float2 lds_ml[4][64];
+    auto& lds_ml = lds.ml;
     if (wave >= 4) {
 #pragma unroll
       for (int c = 0; c < NC; ++c)
@@ -386,11 +385,48 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev
       *(f16x4*)(a.outP + p32_index(sg.tok0 + it.q0 + q, head * HD + e, a.d)) = ov;
     } else {
       const size_t pr = (size_t)(it.part_row + q) * a.H + head;
-      if constexpr (NARROW) *(f32x4*)(a.part_o32 + (pr - (size_t)a.part32_row0 * a.H) * HD + e) = acc * inv;
+      if constexpr (!verify) *(f32x4*)(a.part_o32 + (pr - (size_t)a.part32_row0 * a.H) * HD + e) = acc * inv;
       else *(f16x4*)(a.part_o + pr * HD + e) = ov;
       if (e == 0) a.part_ml[pr] = make_float2(M, L);
     }
   }
+}
+template <int HD, bool KVF16, int ROWS, int NW>
+__global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
+  constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
+  __shared__ StreamLds<HD, ROWS> lds;
+  int item = blockIdx.x, head = blockIdx.y;
+  const HatAttnItem* items = a.items;
+  bool verify = false;
+  const bool block = NARROW && (int)blockIdx.x < a.n_blocks * a.H;
+  if (NARROW && !block) {   // the narrow chunk items, then the verify items, each in all heads
+    const int n = a.n_narrow + a.n_verify, i = (int)blockIdx.x - a.n_blocks * a.H;
+    head = i / n;
+    item = i - head * n;
+    items = a.items + (a.n_items - a.n_narrow);
+    if (item >= a.n_narrow) {
+      item -= a.n_narrow;
+      items = a.verify;
+      verify = true;
+    }
+  } else if (NARROW) {   // a contiguous run of (head, row block) per XCD, as consecutive workgroup ids go round the XCDs
+    items = a.blocks;
+    const int total = a.H * a.n_blocks, per = total / 8, rem = total % 8, x = (int)blockIdx.x % 8;
+    const int b = x * per + (x < rem ? x : rem) + (int)blockIdx.x / 8;
+    if (a.heads_inner) {   // H % 8 == 0: each block in all heads of the XCD before the next, so that the shortest start last
+      const int hx = a.H / 8, i = (int)blockIdx.x / 8;
+      item = i / hx;
+      head = x * hx + i % hx;
+    } else {
+      item = b % a.n_blocks;
+      head = b / a.n_blocks;
+    }
+  }
+  const HatAttnItem it = items[item];
+  if constexpr (!NARROW) stream_item<HD, KVF16, ROWS, NW, kVerify>(p, a, it, head, lds);
+  else if (block) stream_item<HD, KVF16, ROWS, NW, kBlock>(p, a, it, head, lds);
+  else if (verify) stream_item<HD, KVF16, ROWS, NW, kVerify>(p, a, it, head, lds);
+  else stream_item<HD, KVF16, ROWS, NW, kNarrow>(p, a, it, head, lds);
 }
 
 // ------------------------------------------------------------------ verify, loads only
@@ -842,45 +878,37 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(HatAttn a, const HatMer
 
 }  // namespace
 
-template <int ROWS, int NW, bool BLOCKS>
-static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
-  const dim3 grid = BLOCKS ? dim3(a.n_items * a.H) : dim3(a.n_items, a.H);
-  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
-  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
-  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
-  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS, NW, BLOCKS><<<grid, NW * 64, 0, st>>>(p, a);
+template <int ROWS, int NW>
+static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, dim3 grid, hipStream_t st) {
+  if (a.hd == 128 && a.kv_f16) attn_verify_kernel<128, true, ROWS, NW><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 128) attn_verify_kernel<128, false, ROWS, NW><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 64 && a.kv_f16) attn_verify_kernel<64, true, ROWS, NW><<<grid, NW * 64, 0, st>>>(p, a);
+  else if (a.hd == 64) attn_verify_kernel<64, false, ROWS, NW><<<grid, NW * 64, 0, st>>>(p, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   const int wide = a.n_items - a.n_narrow;
-  if (a.n_blocks > 0) {
-    HatAttn w = a;
-    w.items = a.blocks;
-    w.n_items = a.n_blocks;
-    const hipError_t e = a.block_waves == 8 ? launch_stream<HAT_NARROW_QROWS, 8, true>(p, w, st) : launch_stream<HAT_NARROW_QROWS, 4, true>(p, w, st);
-    if (e != hipSuccess) return e;
-  } else if (wide > 0) {
+  if (a.n_blocks == 0 && wide > 0) {
     dim3 grid(wide, a.H);
     if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else if (a.hd == 64 && a.kv_f16) attn_chunk_kernel<64, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else if (a.hd == 64) attn_chunk_kernel<64, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else return hipErrorInvalidValue;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  if (a.n_narrow > 0) {
-    HatAttn n = a;
-    n.items = a.items + wide;
-    n.n_items = a.n_narrow;
-    return launch_stream<HAT_NARROW_QROWS, 4, false>(p, n, st);
-  }
-  return hipGetLastError();
+  const int streamed = a.n_blocks + a.n_narrow + a.n_verify;
+  if (streamed == 0) return hipSuccess;
+  const dim3 grid(streamed * a.H);
+  return a.n_blocks > 0 && a.block_waves == 8 ? launch_stream<HAT_NARROW_QROWS, 8>(p, a, grid, st) : launch_stream<HAT_NARROW_QROWS, 4>(p, a, grid, st);
 }
 
 hipError_t hat_launch_attn_verify(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  return launch_stream<HAT_MAX_VERIFY_ROWS, 4, false>(p, a, st);
+  return launch_stream<HAT_MAX_VERIFY_ROWS, 4>(p, a, dim3(a.n_items, a.H), st);
 }
 
 hipError_t hat_launch_attn_verify_probe(const HatPlanDev& p, const HatAttn& a, uint32_t* sink, hipStream_t st) {
