@@ -319,6 +319,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(float* __restrict__ r
 }
 
 // ---------------------------------------------------------------- RoPE + KV append
+// The launch behind a QKV product without rotation (HAT_APART_TILE), which the others are compared with.
 // Two kinds of workgroups in one launch.
 //  (a) the first n_kblocks: one thread per (row, head, octet pair): octets o and o + hd/16 hold
 //      the two halves of 8 rotation pairs.  q is rotated in place (fp16); rotated k is rounded
