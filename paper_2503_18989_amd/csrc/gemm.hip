@@ -684,14 +684,11 @@ struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
 constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, true, true, true, true,
                                       false, false, false, true, true, true, true, true, true, true,
                                       true, true, true, true};
-// Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, fitted to
-// sweeps at T = 512 .. 5220 (7B shapes, all four products, K split 1 .. 8); 0 = not measured
-// there, the tile is only offered to batches of at most kSmallT rows.  The sweeps were of the 32x32x16 loops: these are weights
-// for the choice, not rates of the present ones.  What that costs where it was looked for: gate/up of the 13B shape at 384 rows 113 us where 256 x 192
-// takes 105, QKV of 2048 columns at 760 rows 29.7 where 128 x 160 takes 26.7, O, down and norms of the 7B shape at 512 rows 109 where 105 is possible.
-constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.538f, 0.533f, 0.916f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                                   0.f, 0.f, 0.f, 0.514f, 0.f, 1.209f, 0.f, 0.504f, 0.f, 0.629f,
-                                   0.518f, 0.565f, 0.564f, 0.f};
+// Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, and with it the constants of the large regime below: fitted to the choice
+// and not to the times (random search for the least loss against the best tile and K split), on 19 tiles at 9 batch sizes of 448 .. 2048 rows of the 7B, 13B and hd-64
+// shapes, all four products, the norms that K splits lengthen included.  Loss of a choice on average 1.6 -> 0.1 us there, 1.07 -> 0.3 at seven other sizes of 420 .. 1664
+// rows (the constants of the 32x32x16 loops before).  0 = never the best, offered to batches of at most kSmallT rows only.
+constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.527f, 0.570f, 1.339f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
 constexpr int kSmallT = 384;
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kPlanned[id], kEff[id]},
@@ -848,10 +845,10 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // MFMAs); the weight stream cannot beat ~5.5 TB/s, nor (Little's law) the bytes of W that
   // the resident workgroups' rings keep in flight divided by the ~1.2 us a load from HBM takes
   // under load -- which is what decides between shapes when there are few token rows.
-  // Above that (T = 512 .. 5220) a k-tile costs the larger of its MFMA time at the tile's own
-  // measured efficiency and its load time at 28 B/clk, a round of workgroups costs ~3.7 us of
+  // Above that a k-tile costs the larger of its MFMA time at the tile's own
+  // efficiency and its load time at 23.7 B/clk, a round of workgroups costs ~4.3 us of
   // prologue and drain, and the epilogue's traffic is not hidden: 14 B/clk per CU for the
-  // fp16 stores, 6.2 for the read-modify-write of the fp32 residual, 7.2 for split-K partial
+  // fp16 stores, 7.65 for the read-modify-write of the fp32 residual, 6.7 for split-K partial
   // sums (written here, read back by the consumer of the residual).
   double best_cost = 1e300, tail_cost = 1e300;
   HatGemmPlan tail{0, 1};
@@ -882,13 +879,13 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
       double cyc;
       if (large) {
         const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff);  // per k-tile, 4 SIMDs
-        const double load_cyc = (q.bf + q.bt) * 64 * 2 / 28.1;
-        const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.073 * std::min(mfma_cyc, load_cyc);
-        cyc = rounds * kt * tile_cyc + rounds * 8938.0;
+        const double load_cyc = (q.bf + q.bt) * 64 * 2 / 23.7;
+        const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.068 * std::min(mfma_cyc, load_cyc);
+        cyc = rounds * kt * tile_cyc + rounds * 10300.0;
         const double rows = (double)g.T * g.Nout / 256.0;                     // output elements per CU
         if (g.epilogue != HAT_EPI_RESID) cyc += rows * 2.0 / 14.0;
-        else if (ks == 1) cyc += rows * 8.0 / 6.2;
-        else cyc += rows * 8.0 * ks / 7.15;
+        else if (ks == 1) cyc += rows * 8.0 / 7.65;
+        else cyc += rows * 8.0 * ks / 6.73;
       } else {
         const double mfma_eff = q.bf * q.bt == 65536 ? 0.90 : 0.85;
         const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * mfma_eff);
@@ -918,11 +915,11 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     if (full < 1 || full >= nT) continue;
     for (int ks = 2; ks <= 8 && KT / ks >= 4 && (long)ks * (g.T - full * q.bt) <= g.part_rows; ++ks) {
       const double pieces = (double)(nT - full) * nF * ks - (256.0 * whole - (double)full * nF);   // idle CUs take some early
-      const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff), load_cyc = (q.bf + q.bt) * 64 * 2 / 28.1;
-      const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.073 * std::min(mfma_cyc, load_cyc);
+      const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff), load_cyc = (q.bf + q.bt) * 64 * 2 / 23.7;
+      const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.068 * std::min(mfma_cyc, load_cyc);
       const double part_rounds = std::ceil(pieces / 256.0);
-      double cyc = whole * ((KT + 2.0) * tile_cyc + 8938.0) + part_rounds * ((std::ceil((double)KT / ks) + 2.0) * tile_cyc + 8938.0);
-      cyc += full * q.bt * (double)g.Nout / 256.0 * 8.0 / 6.2 + (g.T - full * q.bt) * (double)g.Nout / 256.0 * 8.0 * ks / 7.15;
+      double cyc = whole * ((KT + 2.0) * tile_cyc + 10300.0) + part_rounds * ((std::ceil((double)KT / ks) + 2.0) * tile_cyc + 10300.0);
+      cyc += full * q.bt * (double)g.Nout / 256.0 * 8.0 / 7.65 + (g.T - full * q.bt) * (double)g.Nout / 256.0 * 8.0 * ks / 6.73;
       cyc += 12000.0;   // the norm that follows takes two launches
       if (cyc * 1.001 < tail_cost) { tail_cost = cyc * 1.001; tail.tile = c; tail.ksplit = ks; tail.full = full; }
     }
