@@ -91,25 +91,26 @@ __device__ __forceinline__ kvx4 to_kv4(f32x4 x, int kv_f16) {
   return __builtin_bit_cast(kvx4, __builtin_convertvector(x, bf16x4));
 }
 // Where the four features from `i0` of a panel on go for one token, apart from what is the same for all tokens: offsets of q in its
-// P32 row, of k in its tile, of v in its tile (relative to the head's pages).  A thread computes them once for all panels.
+// P32 row (from the workgroup's first row on: 32 bits do not hold an offset in a step of more than 2^31 / Nout rows), of k in its tile, of v in its tile
+// (relative to the head's pages).  A thread computes them once for all panels.
 struct QkvToken {
   int q;
   size_t k, v;
 };
-__device__ __forceinline__ QkvToken qkv_token(const HatGemm& g, int tok, int dst, int i0) {
+__device__ __forceinline__ QkvToken qkv_token(const HatGemm& g, int row0, int tok, int dst, int i0) {
   const size_t page = (size_t)(dst >> 4) * kv_head_elems(g.qkv.hd);
   const int slot = dst & 15;
-  return {(int)p32_index(tok, i0, g.Nout), page + ktile_index(slot, i0), page + 16 * g.qkv.hd + vtile_index(slot, i0)};
+  return {(int)p32_index(tok - row0, i0, g.Nout), page + ktile_index(slot, i0), page + 16 * g.qkv.hd + vtile_index(slot, i0)};
 }
-// lo: rows i0 .. i0+3 of the panel, hi: rows i0+16 .. (their partners)
-__device__ __forceinline__ void store_qkv(const HatGemm& g, const QkvPart& part, const QkvToken& t, const QkvAngles& ang, f32x4 lo, f32x4 hi) {
+// lo: rows i0 .. i0+3 of the panel, hi: rows i0+16 .. (their partners).  row0: the workgroup's first token, a multiple of 32
+__device__ __forceinline__ void store_qkv(const HatGemm& g, int row0, const QkvPart& part, const QkvToken& t, const QkvAngles& ang, f32x4 lo, f32x4 hi) {
   const HatQkvOut& o = g.qkv;
   const int half = o.hd >> 1;
   lo = saturate(lo);
   hi = saturate(hi);
   if (part.which < 2) rotate(ang, lo, hi);
   if (part.which == 0) {
-    act_t* q = g.outP + (size_t)((part.head * o.hd + part.f0) >> 3) * 256 + t.q;
+    act_t* q = g.outP + p32_index(row0, part.head * o.hd + part.f0, g.Nout) + t.q;
     *(f16x4*)q = to_act4(lo);
     *(f16x4*)(q + (half >> 3) * 256) = to_act4(hi);
     return;
@@ -426,9 +427,11 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   }
   if constexpr (EPI == HAT_EPI_QKV) {
     // All loads of a panel before its first store: behind a store that may alias, each would wait out a memory round trip of its own.
+    int row0 = tt * BT;
+    asm volatile("" : "+s"(row0));   // (or the offsets of q, the same in every workgroup, are computed before the loop and take registers through it)
     QkvToken t[NJO];
 #pragma unroll
-    for (int j = 0; j < NJO; ++j) t[j] = qkv_token(g, token(j), g.qkv.kv_dst[min(token(j), g.T - 1)], h4);
+    for (int j = 0; j < NJO; ++j) t[j] = qkv_token(g, row0, token(j), g.qkv.kv_dst[min(token(j), g.T - 1)], h4);
 #pragma unroll
     for (int i = 0; i < MI; i += 2) {
       const int fb = f_base + i * 16;
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
       }
 #pragma unroll
       for (int j = 0; j < NJO; ++j)
-        if (token(j) < g.T && j < jn) store_qkv(g, part, t[j], ang[j], acc[i][j], acc[i + 1][j]);
+        if (token(j) < g.T && j < jn) store_qkv(g, row0, part, t[j], ang[j], acc[i][j], acc[i + 1][j]);
     }
     return;
   }
@@ -597,9 +600,9 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
       if (u < GRP && tok < g.T) {
         const QkvPart part = qkv_part(g.qkv, ft * NP + (t0 + u) % NP);
         const int i0 = 8 * q + 4 * h;
-        const QkvToken t = qkv_token(g, tok, g.qkv.kv_dst[tok], i0);
+        const QkvToken t = qkv_token(g, tt * NT * 32, tok, g.qkv.kv_dst[tok], i0);
         const QkvAngles ang = part.which < 2 ? qkv_angles(g.qkv, tok, part.f0 + i0) : QkvAngles{};
-        store_qkv(g, part, t, ang, total(u, q), total(u, q + 2));
+        store_qkv(g, tt * NT * 32, part, t, ang, total(u, q), total(u, q + 2));
       }
     } else {
       const int u = threadIdx.x >> 8, q = (threadIdx.x >> 6) & 3;

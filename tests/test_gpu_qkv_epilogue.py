@@ -44,3 +44,28 @@ def test_every_lds_tile_rotates_and_appends(cfg, kv):
         for a, b in zip(step(tile), ref):
             assert np.max(np.abs(a - b)) <= 2.0 ** -7 * np.max(np.abs(b)), tile
     m.close()
+
+
+def test_queries_of_a_step_beyond_two_to_the_31_elements():
+    """91200 rows of the widest model: q, k and v of the rows from 87381 on lie more than 2^31 elements into their buffer.  The first and the last
+    devices of the batch against the same prompts one at a time (the bound of a shallow model, on what the layer added)."""
+    import torch
+    from gpu_util import added_err
+    from paper_2503_18989_amd import HatMid, Segment
+    d, n, devices = 8192, 912, 100
+    assert 3 * d * n * (devices - 1) > 2 ** 31
+    cfg = dict(n_layers=1, d_model=d, n_heads=64, head_dim=128, d_ffn=64, rms_eps=1e-6, rope_theta=1e4)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    shapes = dict(attn_norm=(d,), wq=(d, d), wk=(d, d), wv=(d, d), wo=(d, d), ffn_norm=(d,), w_gate=(64, d), w_up=(64, d), w_down=(d, 64))
+    w = {k: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(float(len(s) == 1), 0.02, generator=gen) for k, s in shapes.items()}
+    x = torch.empty((devices, n, d), device="cuda").normal_(generator=gen)
+    m = HatMid(cfg, [w], n_pages=devices * 57, max_devices=devices, max_step_tokens=devices * n, max_pos=n, io_dtype="f32")
+    got = m.forward([Segment(i, hi.CHUNK, 0, x[i]) for i in range(devices)])
+    torch.cuda.synchronize()
+    assert all(bool(torch.isfinite(y).all()) for y in got)
+    one = HatMid(cfg, [w], n_pages=57, max_devices=1, max_step_tokens=n, max_pos=n, io_dtype="f32")
+    for i in (0, 1, devices - 2, devices - 1):
+        ref = one.forward([Segment(0, hi.CHUNK, 0, x[i])])[0]
+        assert added_err(to_np(got[i]), to_np(ref), to_np(x[i])) <= 6e-3, i
+    m.close()
+    one.close()
