@@ -80,8 +80,9 @@ __device__ __forceinline__ void rotate(const QkvAngles& ang, f32x4& lo, f32x4& h
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float a = lo[e], b = hi[e];
-    lo[e] = a * c[e] - b * s[e];
-    hi[e] = b * c[e] + a * s[e];
+    // (which product is rounded first is written out: left to the compiler it is another one with each form of the code around it)
+    lo[e] = __builtin_fmaf(a, c[e], -(b * s[e]));
+    hi[e] = __builtin_fmaf(b, c[e], a * s[e]);
   }
 }
 __device__ __forceinline__ f16x4 to_act4(f32x4 x) { return __builtin_convertvector(saturate(x), f16x4); }
