@@ -269,7 +269,8 @@ typedef enum {
 /* on != 0: later forwards bracket every kernel launch with HIP events on the
  * launch stream.  Slows the step slightly; off by default.  A step of fewer than 1024 rows gathers, fills the rotary
  * table (counted under HAT_K_ROPE_APPEND) and applies the first norm in one launch; profiled, these are three, so that each
- * is timed by itself.  The results are the same bits.  Where the last rows of an O or down product are split along K
+ * is timed by itself.  The results are the same bits.  Verify items that would go along in the launch of the chunk items (hat_mid_debug_plan_along) are
+ * a launch of their own too: the times of the two classes add up to more than the joint launch takes, and with eight waves to a row block the results differ in fp32 summation order.  Where the last rows of an O or down product are split along K
  * (hat_mid_debug_gemm_split), the norm that follows is two launches. */
 hat_status_t hat_mid_set_profiling(hat_mid_t* h, int32_t on);
 
@@ -325,6 +326,10 @@ hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
  * items, in the order of launch); none where they stage it.  blocks may be NULL to ask for the number only; HAT_EINVAL if there are
  * more than cap_blocks.  *waves (may be NULL): waves of a block's workgroup, 4 or 8; 0 without blocks. */
 hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks, int32_t* waves);
+
+/* Whether the verify items of that plan go along in the launch of its streamed chunk items (a step that is profiled or probed
+ * launches them apart all the same). */
+hat_status_t hat_mid_debug_plan_along(const hat_mid_t* h, int32_t* along);
 
 /* ---- tuning aid ------------------------------------------------------------------ */
 

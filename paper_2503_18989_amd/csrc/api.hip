@@ -242,6 +242,7 @@ struct hat_mid {
   int host_narrow = 0;                     // StepPlan::n_narrow of its last plan
   size_t host_blocks = 0;                  // StepPlan::o_cb
   int host_n_blocks = 0, host_block_waves = 0;   // n_cblocks and block_waves of it
+  bool host_along = false;
   int force_tile[4] = {-1, -1, -1, -1};   // tuning overrides per GEMM class (qkv, o, gate/up, down)
   int force_ksplit[4] = {0, 0, 0, 0};
 
@@ -558,7 +559,7 @@ struct StepPlan {
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
   int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 0, n_vitems = 0, n_mitems = 0;
-  bool heads_inner = false;
+  bool heads_inner = false, along = false;
 };
 
 // Time in us of a launch of streamed row blocks with 8 or 4 waves each (the two template forms of attn_verify_kernel), `keys`
@@ -963,6 +964,18 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
       sp->heads_inner = s.H % 8 == 0 && cblocks.size() * s.H > 256 && longest >= 800 && longest * cblocks.size() > 1.1 * sum;
     }
   }
+  // Verify items go along in the launch of the streamed chunk items: they fill what its last round leaves idle, and a launch is less.
+  // Layer in us, two launches | one, 57 mixes of chunks of 2 .. 230 rows with 1, 8 and 30 drafts over 200 .. 8000 keys (7B, 13B and head-dim-64 shapes): 1.8 .. 2.0 % less at
+  // head dim 128, 4.7 % at 64; 100 rows next to 30 drafts over 1 .. 8 k 360 | 322 (head dim 64), 725 | 701 (7B).
+  // With eight waves a verify item is short for them: as many items as leave each CU one gain the same, beyond a thousand
+  // they lose 3 .. 13 %.  Next to narrow items alone the launch that is saved is what there is to gain, and at head dim 128 it no longer shows where the drafts read more
+  // than 1.5 GB: over 36 mixes level on average, but 17 .. 32 rows with 30 or 58 drafts over 1 .. 8 k 0 .. 3 % behind in 10 of 12 (13B shape 1083 | 1121);
+  // 16 such drafts (1.2 .. 1.5 GB) 0.7 % ahead.
+  double verify_gb = 0;
+  for (int i = 0; i < S; ++i)
+    if (segs[i].kind == HAT_SEG_VERIFY) verify_gb += (segs[i].start_pos + segs[i].n) * 4e-9 * s.d;
+  if (!vitems.empty() && (!cblocks.empty() || sp->n_narrow > 0))
+    sp->along = sp->block_waves == 8 ? vitems.size() * s.H <= 256 : !cblocks.empty() || s.hd == 64 || verify_gb <= 1.5;
   const size_t o_ci = take(12 * citems.size(), 4), o_cb = take(12 * cblocks.size(), 4), o_vi = take(12 * vitems.size(), 4);
   const size_t o_mi = take(8 * mitems.size(), 8);
   const size_t plan_cap = h->plan_limit ? std::min(h->plan_limit, s.plan_words) : s.plan_words;
@@ -1012,11 +1025,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
   LAUNCH(h, st, HAT_K_GATHER, hat_launch_gather(pd, h->b.resid, s.d, c.io_dtype, st));
   if (!gather_norms) LAUNCH(h, st, HAT_K_ROPE_APPEND, hat_launch_rope_table(pd, h->b.inv_freq, h->b.table, s.hd / 2, st));
 
-  // Verify items go along in the launch of the streamed chunk items: they fill what its last round leaves idle, and a launch is less.  The
-  // attention of a layer gains 2 .. 8 % of the layer where its workgroups have four waves (40 mixes of chunks of 20 .. 230 rows with 1 .. 20 drafts at three head
-  // counts).  With eight waves a verify item is short for them: as many items as leave each CU one gain the same, beyond a thousand
-  // they lose 3 .. 13 %.  Not where each kind is to be timed by itself.
-  const bool along = (sp.n_cblocks > 0 || sp.n_narrow > 0) && (sp.block_waves != 8 || sp.n_vitems * s.H <= 256) && !h->profiling && !h->verify_probe;
+  const bool along = sp.along && !h->profiling && !h->verify_probe;   // (each kind to be timed by itself)
 
   int nparts = 0;  // split-K partial sums of the previous residual GEMM still to be folded in,
   int prow0 = 0;   // for the rows from this one on
@@ -1358,6 +1367,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
   if (n_verify_items) *n_verify_items = 0;
   if (n_merge_items) *n_merge_items = 0;
   h->host_narrow = h->host_n_blocks = h->host_block_waves = 0;
+  h->host_along = false;
   if (n_segs == 0) return HAT_OK;
   try {
     StepPlan sp;
@@ -1369,6 +1379,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     h->host_blocks = sp.o_cb;
     h->host_n_blocks = sp.n_cblocks;
     h->host_block_waves = sp.block_waves;
+    h->host_along = sp.along;
     if (sp.T > cap_rows || std::max(sp.n_citems, std::max(sp.n_vitems, sp.n_mitems)) > cap_items)
       return fail(h, HAT_EINVAL, "output arrays too small for %d rows / %d, %d, %d items (the step has been planned)", sp.T,
                   sp.n_citems, sp.n_vitems, sp.n_mitems);
@@ -1401,6 +1412,12 @@ hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int3
   if (!blocks) return HAT_OK;
   if (h->host_n_blocks > cap_blocks) return HAT_EINVAL;
   if (h->host_n_blocks > 0) memcpy(blocks, h->host_plan.data() + h->host_blocks, (size_t)h->host_n_blocks * sizeof(HatAttnItem));
+  return HAT_OK;
+}
+
+hat_status_t hat_mid_debug_plan_along(const hat_mid_t* h, int32_t* along) {
+  if (!h || !h->host_only || !along) return HAT_EINVAL;
+  *along = h->host_along;
   return HAT_OK;
 }
 

@@ -231,9 +231,9 @@ __device__ __forceinline__ void stream_item(const HatPlanDev& p, const HatAttn& 
   // raw registers, and travel while the current pair is soft-maxed and multiplied.  Two
   // workgroups share a CU (<= 256 VGPRs).
   u32x4 kraw[NS], varaw[NC], vbraw[NC];
-  // Page ids are scalar loads.  For chunk items those of the next pair but one are read a pair ahead, so that no page waits for its id (8 x 64 rows over 4096
-  // keys of the 13B shape 163 -> 157 us, 871 ragged rows at head dim 64 42.9 -> 40.8).  Verify items, which have more bytes in flight than the memory
-  // needs, are slower with it (30 caches of 1 k .. 8 k 299 -> 310).
+  // Page ids are scalar loads.  In the launch of the chunk items those of the next pair but one are read a pair ahead, so that no page waits for its id (8 x 64
+  // rows over 4096 keys of the 13B shape 163 -> 157 us, 871 ragged rows at head dim 64 42.9 -> 40.8); also for the verify items that go along, whose layers are 0.3 %
+  // behind without it (57 mixes).  A launch of verify items alone, which has more bytes in flight than the memory needs, is slower with it (30 caches of 1 k .. 8 k 299 -> 310).
   int idA = 0, idB = 0;
   const kv_t *recA = pool, *recB = pool;
   auto page_ids = [&](int pp) {

@@ -395,3 +395,23 @@ def test_small_steps_hold_no_partial_results_in_fp16(rows, start, millions):
     assert lib.blocks() or not plan["merge_items"]
     assert sum(-(-n // 32) * 32 * (start + n / 2) for n in rows) * SHAPE["n_heads"] / 1e6 == pytest.approx(millions, abs=2)
     lib.close()
+
+
+@pytest.mark.parametrize("chunks,drafts,n,hd,along", [([(64, 900)], 200, 8, 128, True), ([(64, 900)], 200, 9, 128, False),        # eight waves: 256 items x heads
+                                                      ([(512, 1000)], 3500, 30, 128, True),                                      # four waves
+                                                      ([(20, 500)], 3500, 25, 128, True), ([(20, 500)], 3500, 30, 128, False),   # narrow alone: 1.4, 1.7 GB of drafts
+                                                      ([(20, 500)], 3500, 60, 64, True),                                         # (the same bytes at head dim 64)
+                                                      ([(512, 2000)] * 8, 200, 8, 128, False),                                   # staged
+                                                      ([(512, 2000)] * 8 + [(20, 1600)], 200, 8, 128, True),                     # staged, and a narrow launch
+                                                      ([(64, 900)], 0, 0, 128, False), ([], 500, 4, 128, False)])
+def test_verify_items_that_go_along(chunks, drafts, n, hd, along):
+    lib = HatPlanner(dict(SHAPE, head_dim=hd, d_model=hd * SHAPE["n_heads"]), 20000, max_devices=64, max_step_tokens=8192, max_pos=8192)
+    for d, (_, start) in enumerate(chunks):
+        lib.plan([(d, hi.CHUNK, 0, start)])
+    for d in range(n):
+        lib.plan([(len(chunks) + d, hi.CHUNK, 0, drafts)])
+    lib.plan([(d, hi.CHUNK, start, rows) for d, (rows, start) in enumerate(chunks)] + [(len(chunks) + d, hi.VERIFY, drafts, 5) for d in range(n)])
+    assert lib.verify_along() == along
+    lib.plan([])
+    assert not lib.verify_along()                     # (of the last plan)
+    lib.close()
