@@ -692,11 +692,16 @@ struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
 constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, true, true, true, true,
                                       false, false, false, true, true, true, true, true, true, true,
                                       true, true, true, true};
-// Share of the matrix peak that a tile's k-loop reaches when it is not load-bound, and with it the constants of the large regime below: fitted to the choice
-// and not to the times (random search for the least loss against the best tile and K split), on 19 tiles at 9 batch sizes of 448 .. 2048 rows of the 7B, 13B and hd-64
-// shapes, all four products, the norms that K splits lengthen included.  Loss of a choice on average 1.6 -> 0.1 us there, 1.07 -> 0.3 at seven other sizes of 420 .. 1664
-// rows (the constants of the 32x32x16 loops before).  0 = never the best, offered to batches of at most kSmallT rows only.
-constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.527f, 0.570f, 1.339f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
+// How fast a tile's k-loop is taken to be where it is not load-bound, against the matrix peak, and with it the constants of the large regime below: weights for the
+// choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: never the best beyond kSmallT rows).  Measured with all tiles, K splits and
+// split tails of the four products, norms included, at 36 batch sizes of 390 .. 4096 rows and seven widths (1024 x 2816 .. 8192 x 28672; the search had seen 9 sizes up to 2048
+// rows of three of them): the four choices of a layer lose 0.24 % of it on average at 20 of the sizes and 0.31 % at the other 16, where the constants of the 32x32x16
+// loops lost 1.78 and 1.85 %.  Of 1004 choices 303 changed with them, 256 to a product more than 1 % faster and 25 to one more than 1 % slower: gate/up of 8192 columns
+// at 1400 and 1664 rows 1056 -> 1117 and 1228 -> 1314 us, of 4096 at 3840 561 -> 578, QKV of 5120 at 2700 357 -> 374, the others less than 8 us.  192 x 256
+// stands at .535, not at the .543 of the search: with that the losses are 0.31 and 0.44 %.  Searched again on the 20 sizes of all widths, with a cost of its own for
+// the rotating epilogue, the constants come to 0.20 .. 0.23 % there and 0.32 .. 0.38 % at the other 16: what is left is the model's form (it counts whole
+// rounds of workgroups, where large products go by their padded work).
+constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.527f, 0.570f, 0.f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
 constexpr int kSmallT = 384;
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kPlanned[id], kEff[id]},
@@ -854,9 +859,10 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   // the resident workgroups' rings keep in flight divided by the ~1.2 us a load from HBM takes
   // under load -- which is what decides between shapes when there are few token rows.
   // Above that a k-tile costs the larger of its MFMA time at the tile's own
-  // efficiency and its load time at 23.7 B/clk, a round of workgroups costs ~4.3 us of
+  // weight (kEff) and its load time at 23.7 B/clk, a round of workgroups costs ~4.3 us of
   // prologue and drain, and the epilogue's traffic is not hidden: 14 B/clk per CU for the
-  // fp16 stores, 7.65 for the read-modify-write of the fp32 residual, 6.7 for split-K partial
+  // fp16 stores (the rotating epilogue of QKV, which costs more, is taken for one: its choices lose 0.03 % of a layer),
+  // 7.65 for the read-modify-write of the fp32 residual, 6.7 for split-K partial
   // sums (written here, read back by the consumer of the residual).
   double best_cost = 1e300, tail_cost = 1e300;
   HatGemmPlan tail{0, 1};
@@ -912,12 +918,11 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     // A last round that leaves most CUs idle: the token tiles that fill whole rounds stay whole, the rest is split
     // along K until its pieces fill about a round.  320 tiles on 256 CUs (4096 rows of the 13B shape) take 1.35 rounds
     // instead of 2.  The matrix pipes draw the chip's power limit in a step of this size (clock 1.6 GHz in a
-    // full round), so the idle CUs are not all loss.  Only where it is predicted to win by more than the cost model's rms error
-    // (4.5 %), and in at most 8 pieces.  Measured in whole layers, O and down each with and without it, at 100 batch sizes of six
-    // widths: where the rule takes it, 2756 -> 2655 us a layer (5120 x 13824, 4096 rows), 2292 -> 2213 (3213 rows), 2763 -> 2688 (6144 x
-    // 16384, 2785 rows), 4561 -> 4421 (8192 x 28672, 2260 rows), 8 us at the least for down, 0 to 20 for O; at predicted gains
-    // below it, or in 13 .. 16 pieces, 1 .. 9 us a layer lost at 2048 x 5504, 3072 x 8192 and 4096 x 11008 (2065 rows of
-    // 3072 x 8192, 16 pieces, predicted 5 %: 594 -> 598) and as often 4 .. 8 won.
+    // full round), so the idle CUs are not all loss.  Only where it is predicted to win by 4.5 %, and in at most 8 pieces.  O and down with their norms, whole against
+    // split in us: at the sizes of kEff the rule takes it 47 times, all at 5120, 6144 and 8192 columns.  Down gains each time, 10 .. 171 us (13B shape 4096 rows 544 -> 490,
+    // 3300 rows 465 -> 410; 6144 x 16384 2788 rows 558 -> 480; 8192 x 28672 2300 rows 1061 -> 890); O gains 1 .. 27 in 16 of 19 (3300 rows of 5120 218 -> 200) and
+    // loses 2 and twice 7 (3840 and 3450 rows of 6144, 3072 of 8192 392 -> 399).  Predicted below 4.5 % it gains 0 .. 6 at four sizes.  In 13 .. 16 pieces
+    // (2065 rows of 3072 x 8192, predicted 5 %) a layer lost 594 -> 598.
     if (!large || max_split == 1) continue;
     const int whole = nT * nF / 256, full = whole * 256 / nF;
     if (full < 1 || full >= nT) continue;
