@@ -178,17 +178,17 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // ROWS = 8 is the launch of verify items by themselves, ROWS = 32 that of the step's row blocks, narrow items and the verify items that go along
 // (enqueue_step): each kind is a copy of the code, as one that asks at run time took 28 registers more and spilled.  One launch
 // instead of three: 871 rows of ragged chunks and drafts at head dim 64 2301 -> 2118 us a step.
-template <int HD, int ROWS>
+template <int HD, int ROWS, int NW>
 struct StreamLds {   // where the waves' results meet
   static constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
   __attribute__((aligned(16))) float o[4][NARROW ? HD * (ROWS + 1) : ROWS * HD];
   float m[4][ROWS], l[4][ROWS];
-  float2 ml[4][64];
+  float2 ml[NW == 8 ? 4 : 1][NW == 8 ? 64 : 1];   // (eight waves only)
 };
 // One item in one head.  A row block's pages are read by the blocks next to it too, the others' once (non-temporal loads).
 enum StreamKind { kBlock, kNarrow, kVerify };
 template <int HD, bool KVF16, int ROWS, int NW, StreamKind KIND>
-__device__ __forceinline__ void stream_item(const HatPlanDev& p, const HatAttn& a, const HatAttnItem& it, int head, StreamLds<HD, ROWS>& lds) {
+__device__ __forceinline__ void stream_item(const HatPlanDev& p, const HatAttn& a, const HatAttnItem& it, int head, StreamLds<HD, ROWS, NW>& lds) {
   constexpr int NS = HD / 16;  // k-steps of Q K^T
   constexpr int NC = HD / 32;  // 32-row blocks of O^T
   constexpr int REC = 2 * 16 * HD;  // elements of one (page, head) record
@@ -394,7 +394,7 @@ __device__ __forceinline__ void stream_item(const HatPlanDev& p, const HatAttn& 
 template <int HD, bool KVF16, int ROWS, int NW>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_verify_kernel(HatPlanDev p, HatAttn a) {
   constexpr bool NARROW = ROWS > HAT_MAX_VERIFY_ROWS;
-  __shared__ StreamLds<HD, ROWS> lds;
+  __shared__ StreamLds<HD, ROWS, NW> lds;
   int item = blockIdx.x, head = blockIdx.y;
   const HatAttnItem* items = a.items;
   bool verify = false;
