@@ -569,6 +569,9 @@ struct StepPlan {
 // Eight waves shorten a workgroup, four get more out of a full CU and leave less of the chip idle in the last round.  us with 4 | 8
 // (workgroups; bf16 cache): 1 x 64 rows over 4000 keys of the 7B shape 64.9 | 46.0 (64), 1 x 256 over 1000 24.1 | 20.4 (256), 13B shape 29.8 | 33.1
 // (320), 8 x 64 over 4000 174 | 166 (640), 4 x 512 over 500 of the 7B shape 76.4 | 97.2 (2048), 4 x 128 over 2000 at head dim 64 34.0 | 36.1 (512).
+// These are times of the kernel before it read page ids ahead, which took 3 .. 9 % off all of them, and verify items that go along are not counted.  With the present kernel the choice
+// is 0.4 % of a layer behind the best of staged, eight and four waves over 90 other mixes (1 .. 12 chunks of 33 .. 500 rows over 0 .. 6000 keys; 2.8 % at the most, 302 + 355 rows over 5000 .. 5700 keys of the 7B
+// shape), where always staging is 3.8, always eight waves 2.0 and always four 0.6 % behind it.
 static double stream_us(const Shapes& s, int kv_f16, int waves, const std::vector<int>& keys, double mbytes) {
   struct Cost { double launch, block, step, shared, per_mb; };
   static const Cost k4[2][2] = {{{3.92, 3.30, 0.776, 0.005, 0.176}, {4.23, 2.70, 0.690, 0.005, 0.163}}, {{4.58, 4.44, 1.327, 0.357, 0.102}, {4.45, 3.65, 1.176, 0.437, 0.109}}};
@@ -819,10 +822,12 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // Items of at most HAT_NARROW_QROWS rows are bound by the cache stream: key ranges of about equal size instead, for
     // three eighths of verify_target workgroups (8 x 32 rows over 4096 keys: 118 us and 7 us of merging with 768 workgroups
     // wanted, 130 and 9 with 2048).
-    // Next to larger items that is a second launch and a merge (4 .. 14 us a layer with narrow items of 500 keys): only where a
+    // Next to larger items that is a merge, and next to staged ones a second launch (4 .. 14 us a layer with narrow items of 500 keys): only where a
     // narrow item is so long that the common launch, which does not split it, would wait for it.  Measured in whole layers over 30
-    // mixes (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
-    // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.
+    // mixes with a launch of their own (one or four items of 17 rows next to one to ten chunks of 128 .. 512 rows, three widths): streamed at 1000 keys
+    // between 11 us ahead and 13 behind, at 1400 between 20 ahead and 3 behind, at 2000 ahead by 7 .. 31 in all of them.  Next to larger items that stream there is no second
+    // launch, but still the merge: over 50 mixes with narrow items of 230 .. 1430 keys next to 1 .. 8
+    // chunks of 40 .. 512 rows a bound of 1024, 512 or 0 keys instead of 1536 costs 0.4, 1.1 and 0.9 % a layer on average (ahead in 21, 16 and 18 of them).
     double total_cost = 0, narrow_cost = 0;   // (rows x visible keys)
     double block_cost = 0, narrow_block = 0;  // the same of the items that may stream, in whole blocks of rows
     double chunk_mb = 0;                      // cache rows that chunks read
