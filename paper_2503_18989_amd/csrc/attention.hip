@@ -176,7 +176,7 @@ __device__ __forceinline__ _Float16 to_act(float x) { return (_Float16)__builtin
 // 0.26 us per 32 rows x 32 keys and CU against 0.17), which the planner weighs against that kernel's idle waves, key splits and merge.
 // NW waves share the keys; the planner knows where four of them are faster and where eight.
 // ROWS = 8 is the launch of verify items by themselves, ROWS = 32 that of the step's row blocks, narrow items and the verify items that go along
-// (enqueue_step): each kind is a copy of the code, as one that asks at run time took 28 registers more and spilled.  One launch
+// (plan_step): each kind is a copy of the code, as one that asks at run time took 28 registers more and spilled.  One launch
 // instead of three: 871 rows of ragged chunks and drafts at head dim 64 2301 -> 2118 us a step.
 template <int HD, int ROWS, int NW>
 struct StreamLds {   // where the waves' results meet
