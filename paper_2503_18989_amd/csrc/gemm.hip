@@ -11,14 +11,20 @@
 // of the P32 layout of the *next* operand, so every epilogue stores coalesced.
 //
 // Data movement: global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4),
-// no register staging, into a ring of NSTAGE k-tiles.  Measured on MI355X: a CU
-// sustains about 36-42 B/clk through these loads, each one holds the issuing wave
-// for on the order of a hundred cycles, and the ring depth beyond two tiles does not
-// matter -- so the refill is spread thinly between the MFMAs instead of issued in
-// bursts, and the tile shape (bytes moved per flop) decides the rest.  Because the
-// P32 panel slab of a k-tile is contiguous in memory and is kept contiguous in
+// no register staging, into a ring of k-tiles.  In the tiles of the largest batches the
+// multiplying waves load too, the refill spread thinly between the MFMAs, as a load holds
+// the issuing wave while it waits for its turn; the tile shape (bytes moved per flop)
+// decides the rest.  Because the P32 panel slab of a k-tile is contiguous in memory and is kept contiguous in
 // LDS, each wave instruction moves one 1 KB run, and an MFMA operand is one
 // ds_read_b128 at lane*16 + immediate, conflict-free without a swizzle.
+// Loader waves.  The tiles of batches up to a few hundred rows (G > 0) have waves that load and do nothing else, with scalar addresses, so that they
+// neither hold an MFMA wave while a load issues nor wait behind the matrix pipe for an address (a 64-bit vector address next to 32x32x16 MFMAs: one 1 KB load in 141
+// clocks a wave instead of 70).  That alone gains nothing (gate/up of 256 rows, 7B shape, 61 us both): what bounds these products is that a CU's loads return in order and
+// that about 32 KB of them can be on their way (a CU by itself streams weights at 54 B/ns with any number of loads issued: 32 KB in 0.6 us), so that X, which comes from
+// L2, waits behind W, which comes from HBM.  Loads alone of the 96 x 256 tile, W and X of each k-tile in turn: 46 us; W of two k-tiles, then X of the two:
+// 36.  So W is loaded G k-tiles at a time, into a ring of its own that is twice that long, and X in a shorter one; W that one token tile alone reads
+// is loaded non-temporally (W alone 31.7 -> 27.5 us).  Gate/up of 256 rows 61.2 -> 51.5 us, of 77 44.1 -> 39, QKV 43 -> 38, O 20.3 -> 19.1, down 36.9 -> 34.8.
+// The MFMA waves and the loader waves share the registers of a SIMD three ways (168 each), which the accumulators of the 192- and 256-row tiles do not leave.
 // LDS reads are issued from inline asm so that the compiler does not serialise
 // them behind the outstanding direct-to-LDS loads; the waits are explicit:
 // vmcnt for "my loads of this k-tile have landed", a barrier for "everyone's
@@ -132,9 +138,10 @@ __device__ __forceinline__ void store_qkv(const HatGemm& g, int row0, const QkvP
   }
 }
 
-template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE>
+template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE, int G>
 struct Tile {
-  static constexpr int NW = WF * WT * WK;
+  static constexpr int NW = WF * WT * WK;           // waves that multiply
+  static constexpr int NL = G > 0 ? BKT / 16 : 0;   // loader waves: each brings one of the 1 KB chunks of every slab
   static constexpr int MI = BF / WF / 16;   // 16-row feature blocks per wave
   static constexpr int NJ = BT / WT / 16;   // 16-row token blocks per wave
   static constexpr int PF = BF / 32, PT = BT / 32;
@@ -144,11 +151,13 @@ struct Tile {
   static constexpr int LPW = (NCH + NW - 1) / NW;  // direct-to-LDS loads per wave per stage (the last waves: one less, where they don't divide)
   static constexpr int STAGE = (PF + PT) * SLAB;
   static constexpr int KS = BKT / 32 / WK;      // k-steps of one wave per stage
-  static constexpr int LDS_BYTES = NSTAGE * STAGE;
+  static constexpr int WR = 2 * G;              // G > 0: k-tiles in the ring of W
+  static constexpr int LDS_BYTES = G > 0 ? (WR * PF + NSTAGE * PT) * SLAB : NSTAGE * STAGE;
   static_assert(BF % (WF * 32) == 0 && BT % (WT * 16) == 0 && (WT == 1 || WT % 2 == 0), "whole 32-row panels of features, 16-row blocks of tokens");
   static_assert(KS >= 1 && BKT % (32 * WK) == 0 && (WK == 1 || WK == 2), "whole k-steps");
-  static_assert(NSTAGE >= 2 && NSTAGE <= 4 && (NSTAGE - 1) * LPW <= 63, "wait_pending covers up to 3 pending tiles; vmcnt is 6 bits");
+  static_assert(G > 0 || (NSTAGE >= 2 && NSTAGE <= 4 && (NSTAGE - 1) * LPW <= 63), "wait_pending covers up to 3 pending tiles; vmcnt is 6 bits");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
+  static_assert(G == 0 || (NSTAGE >= 2 && NSTAGE <= G + 1 && (NSTAGE - 2) * PT + G * PF <= 63), "a tile of X is never before its tile of W");
   static_assert(WK == 1 || WF * WT * MI * NJ * 1024 <= LDS_BYTES, "the two halves of K meet in the ring");
 };
 
@@ -160,9 +169,9 @@ struct Tile {
 // SIMD the same output block and each half of a stage's k; they meet in LDS at the end.
 // Against the 32x32x16 loop on four waves, in steps (weights from HBM), QKV, gate/up and down: 13B shape at 512 rows 79 -> 73 us, 129 -> 115, 76 -> 72, at 4096 533 ->
 // 474, 948 -> 837, 504 -> 440; at 256 rows of the 7B shape, where the weight stream decides, level (39.0 -> 40.1, 61.2 -> 60.7, 36.4 -> 36.2).
-template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE, int EPI>
-__global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
-  using TL = Tile<BF, BT, WF, WT, WK, BKT, NSTAGE>;
+template <int BF, int BT, int WF, int WT, int WK, int BKT, int NSTAGE, int G, int EPI>
+__global__ __launch_bounds__((Tile<BF, BT, WF, WT, WK, BKT, NSTAGE, G>::NW + Tile<BF, BT, WF, WT, WK, BKT, NSTAGE, G>::NL) * 64) void gemm_kernel(HatGemm g, int ksplit, int full) {
+  using TL = Tile<BF, BT, WF, WT, WK, BKT, NSTAGE, G>;
   constexpr int MI = TL::MI, NJ = TL::NJ, PF = TL::PF, PT = TL::PT, SLAB = TL::SLAB, CPS = TL::CPS;
   constexpr int LPW = TL::LPW, STAGE = TL::STAGE, KS = TL::KS;
 
@@ -216,7 +225,69 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   const int KT = g.K / BKT;
   const int kt0 = (int)((long)kz * KT / ksplit);
   const int kt1 = (int)((long)(kz + 1) * KT / ksplit);
-  const int nkt = kt1 - kt0;
+  const int nkt = G > 0 ? __builtin_amdgcn_readfirstlane(kt1 - kt0) : kt1 - kt0;
+
+  if constexpr (G > 0) {
+    constexpr int WR = TL::WR;
+    if (wave >= TL::NW) {   // a loader wave: the same barriers as the others
+      const int lw = wave - TL::NW, lane16 = lane * 16;
+      const size_t krow = (size_t)(g.K >> 3) * 256;
+      const size_t k0 = (size_t)kt0 * (BKT / 8) * 256 + lw * 512;
+      const int fp = __builtin_amdgcn_readfirstlane(ft) * PF, tp = __builtin_amdgcn_readfirstlane(tt) * PT;
+      const void* wbase = hat_uniform(g.W + (size_t)fp * krow + k0);
+      const void* xbase = hat_uniform(g.X + (size_t)tp * krow + k0);
+      int w[PF], x[PT];   // bytes from there to each panel (beyond the last: that one again)
+#pragma unroll
+      for (int q = 0; q < PF; ++q) w[q] = min(q, (g.Nw >> 5) - 1 - fp) * (int)krow * 2;
+#pragma unroll
+      for (int q = 0; q < PT; ++q) x[q] = min(q, Tpanels - 1 - tp) * (int)krow * 2;
+      auto run = [&](auto auxc) {
+        int ws = 0, xs = 0;   // ring slots of the next tiles
+        auto load_w = [&](int t) {
+#pragma unroll
+          for (int q = 0; q < PF; ++q) hat_load_lds<decltype(auxc)::value>(wbase, lds + (ws * PF + q) * SLAB + lw * 1024, lane16, w[q] + t * SLAB);
+          ws = ws + 1 == WR ? 0 : ws + 1;
+        };
+        auto load_x = [&](int t) {
+#pragma unroll
+          for (int q = 0; q < PT; ++q) hat_load_lds<0>(xbase, lds + (WR * PF + xs * PT + q) * SLAB + lw * 1024, lane16, x[q] + t * SLAB);
+          xs = xs + 1 == NSTAGE ? 0 : xs + 1;
+        };
+        for (int t = 0; t < G && t < nkt; ++t) load_w(t);
+        for (int t = 0; t < NSTAGE - 1 && t < nkt; ++t) load_x(t);
+        int i = 0;
+        for (; i + 2 * G <= nkt; i += G)   // every tile that is to be loaded exists
+          static_for<G>([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            // behind X of tile i + p: X of the NSTAGE - 2 tiles after it, and a group of W if one was issued among them
+            constexpr int groups = p >= 1 && p <= NSTAGE - 2 ? 1 : 0;
+            wait_vmcnt<(NSTAGE - 2) * PT + groups * G * PF>();
+            __builtin_amdgcn_s_barrier();
+            if constexpr (p == 0)
+              for (int t = 0; t < G; ++t) load_w(i + G + t);
+            load_x(i + p + NSTAGE - 1);
+          });
+        for (const int i0 = i; i < nkt; ++i) {   // the last tiles: only X is counted
+          const int behind = min(NSTAGE - 2, nkt - 1 - i);
+          static_for<NSTAGE - 1>([&](auto b) {
+            if (behind == b) wait_vmcnt<decltype(b)::value * PT>();
+          });
+          __builtin_amdgcn_s_barrier();
+          if (i == i0)
+            for (int t = i + G; t < nkt; ++t) load_w(t);
+          if (i + NSTAGE - 1 < nkt) load_x(i + NSTAGE - 1);
+        }
+      };
+      if (nT == 1) run(std::integral_constant<int, 2>{});
+      else run(std::integral_constant<int, 0>{});
+      wait_vmcnt<0>();
+      if constexpr (WK == 2) {
+        __syncthreads();
+        __syncthreads();
+      }
+      return;
+    }
+  }
 
   // per-wave chunk sources (per-lane address); destinations are wave-uniform
   constexpr int EXTRA = TL::NCH % TL::NW;            // that many waves bring LPW chunks, the others one less (0: all bring LPW)
@@ -266,23 +337,33 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  if constexpr (G == 0) {
 #pragma unroll
-  for (int s = 0; s < NSTAGE; ++s)
-    if (s < nkt) {
+    for (int s = 0; s < NSTAGE; ++s)
+      if (s < nkt) {
 #pragma unroll
-      for (int c = 0; c < LPW; ++c) issue_chunk(s, c);
-    }
+        for (int c = 0; c < LPW; ++c) issue_chunk(s, c);
+      }
+  }
 
   // An operand is 16 rows x 32 k: lane l holds row l%16, k-octet l/16.  A wave's feature blocks are consecutive; its token
   // blocks are every WT-th of the tile, so that any number of them keeps the same distance in LDS for every wave.
   const uint32_t lane_off = lds_base + (lane >> 4) * 512 + (lane & 15) * 16 + wk * (KS * 2048);
   const uint32_t offW = lane_off + (wf * MI / 2) * SLAB;
-  const uint32_t offX = lane_off + PF * SLAB + (wt >> 1) * SLAB + (wt & 1) * 256;
+  const uint32_t offX = lane_off + (G > 0 ? TL::WR * PF : PF) * SLAB + (wt >> 1) * SLAB + (wt & 1) * 256;
   f16x8 a[2][MI], bb[2][NJ];
   constexpr int NMFMA = MI * NJ;
+  int wo = 0, xo = 0;   // (G > 0) the current tile's places in the rings
   auto read_operands = [&](auto setc, auto ksc, int i) {
     constexpr int set = decltype(setc)::value, ks = decltype(ksc)::value;
-    const uint32_t aW = offW + (i % NSTAGE) * STAGE, aX = offX + (i % NSTAGE) * STAGE;
+    uint32_t aW, aX;
+    if constexpr (G > 0) {
+      aW = offW + wo;
+      aX = offX + xo;
+    } else {
+      aW = offW + (i % NSTAGE) * STAGE;
+      aX = offX + (i % NSTAGE) * STAGE;
+    }
     static_for<MI>([&](auto ii) { a[set][ii] = lds_read<(ii / 2) * SLAB + (ii % 2) * 256 + ks * 2048>(aW); });
     static_for<NJ>([&](auto jj) {
       constexpr int off = WT == 1 ? (jj / 2) * SLAB + (jj % 2) * 256 : jj * (WT / 2) * SLAB;
@@ -307,9 +388,14 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
     if constexpr (ks + 1 < KS) {
       read_operands(next, std::integral_constant<int, ks + 1>{}, i);
     } else if (steady || i + 1 < nkt) {
-      const int after = nkt - 2 - i;  // tiles issued behind tile i+1
-      if (steady || after >= NSTAGE - 2) wait_tiles(std::integral_constant<int, NSTAGE - 2>{});
-      else wait_pending(after);
+      if constexpr (G == 0) {
+        const int after = nkt - 2 - i;  // tiles issued behind tile i+1
+        if (steady || after >= NSTAGE - 2) wait_tiles(std::integral_constant<int, NSTAGE - 2>{});
+        else wait_pending(after);
+      } else {
+        wo = wo + PF * SLAB == TL::WR * PF * SLAB ? 0 : wo + PF * SLAB;
+        xo = xo + PT * SLAB == NSTAGE * PT * SLAB ? 0 : xo + PT * SLAB;
+      }
       __builtin_amdgcn_s_barrier();
       read_operands(next, std::integral_constant<int, 0>{}, i + 1);
     }
@@ -326,7 +412,7 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
       static_for<CPP>([&](auto q) {
         constexpr int slot = q * NMFMA / CPP + NMFMA / CPP / 2;
         constexpr int c = part * CPP + q;
-        if constexpr (slot == n && c < LPW) {
+        if constexpr (G == 0 && slot == n && c < LPW) {
           if (steady || refill) issue_chunk(rtile, c);
         }
       });
@@ -339,7 +425,7 @@ __global__ __launch_bounds__(WF* WT* WK * 64) void gemm_kernel(HatGemm g, int ks
   constexpr std::integral_constant<int, 0> set0{};
   constexpr std::integral_constant<int, KS & 1> set1{};   // the register set on which an odd tile starts
   if (nkt > 0) {
-    wait_pending(nkt - 1 < NSTAGE - 1 ? nkt - 1 : NSTAGE - 1);
+    if constexpr (G == 0) wait_pending(nkt - 1 < NSTAGE - 1 ? nkt - 1 : NSTAGE - 1);
     __builtin_amdgcn_s_barrier();
     read_operands(set0, std::integral_constant<int, 0>{}, 0);
   }
@@ -631,9 +717,12 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
   }
 }
 
-// tile table: id, features x tokens, waves along features x tokens, halves of K, k per stage, stages.
-// Heights of 96 and 192 rows exist so that the tile count can match the 256 CUs where
+// tile table: id, features x tokens, waves along features x tokens, halves of K, k per stage, stages (of X, where W has a ring of its own), k-tiles of W
+// that are loaded together (0: no loader waves).  G and the stages of X are what 160 KB of LDS hold; k-tiles of 32 there measured 4 .. 6 us behind (barriers).
+// Heights of 64, 96 and 192 rows exist so that the tile count can match the 256 CUs where
 // 128 / 256 leave a quarter or a third of them idle (7B-shaped QKV and gate/up at T <= 256).
+// Without one of them the products of a layer lose, on average over seven widths and 22 batch sizes of 33 .. 3556 rows (at the most): 64 x 64 0.6 % (6.6), 64 x 128 0.5 (4.9), 96 x 256
+// 0.5 (6.0), 128 x 128 0.4 (6.2), 128 x 256 0.4 (7.4), 96 x 128 0.4 (4.3), 256 x 128 0.3 (6.3), 96 x 64 and 128 x 160 0.1 (4.0), 64 x 256 0.1 (2.0), 256 x 64 0.06 (4.6).
 // Tiles 20-22 take 224, 192 and 160 token rows: for batches whose row count leaves the last 256-row tile mostly empty
 // or the tile count just above a multiple of the 256 CUs.  Tile 23
 // (128 x 160) is for batches of 129 .. 160 rows, e.g. 30 devices x 5 draft rows: one token tile
@@ -645,30 +734,30 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
 #define HAT_FOR_TILES(X, EPI)          \
-  X(0, 256, 256, 2, 4, 1, 32, 4, EPI)  \
-  X(1, 192, 128, 2, 4, 1, 32, 4, EPI)  \
-  X(2, 128, 256, 2, 4, 1, 64, 3, EPI)  \
-  X(3, 256, 128, 4, 2, 1, 64, 3, EPI)  \
-  X(4, 128, 128, 2, 4, 1, 64, 4, EPI)  \
-  X(5, 256, 64, 4, 1, 2, 64, 3, EPI)   \
-  X(6, 256, 32, 4, 1, 2, 64, 4, EPI)   \
-  X(7, 128, 64, 2, 4, 1, 64, 4, EPI)   \
-  X(8, 128, 32, 2, 1, 2, 64, 4, EPI)   \
-  X(9, 64, 256, 1, 4, 2, 64, 3, EPI)   \
-  X(10, 128, 128, 2, 2, 2, 64, 4, EPI) \
-  X(11, 128, 128, 2, 4, 1, 32, 4, EPI) \
-  X(12, 128, 64, 2, 2, 2, 64, 4, EPI)  \
-  X(13, 192, 128, 2, 2, 2, 64, 3, EPI) \
-  X(14, 96, 128, 1, 4, 2, 64, 4, EPI)  \
-  X(15, 96, 256, 1, 4, 2, 64, 3, EPI)  \
-  X(16, 192, 64, 2, 2, 2, 64, 4, EPI)  \
-  X(17, 192, 256, 2, 4, 1, 32, 4, EPI) \
-  X(18, 96, 64, 1, 2, 2, 64, 4, EPI)   \
-  X(19, 256, 256, 4, 2, 1, 32, 4, EPI) \
-  X(20, 256, 224, 4, 2, 1, 32, 4, EPI) \
-  X(21, 256, 192, 4, 2, 1, 32, 4, EPI) \
-  X(22, 256, 160, 4, 2, 1, 32, 4, EPI) \
-  X(23, 128, 160, 4, 2, 1, 64, 3, EPI)
+  X(0, 256, 256, 2, 4, 1, 32, 4, 0, EPI)  \
+  X(1, 192, 128, 2, 4, 1, 32, 4, 0, EPI)  \
+  X(2, 128, 256, 2, 4, 1, 64, 3, 2, EPI)  \
+  X(3, 256, 128, 4, 2, 1, 64, 3, 0, EPI)  \
+  X(4, 128, 128, 2, 4, 1, 64, 4, 3, EPI)  \
+  X(5, 256, 64, 4, 1, 2, 64, 3, 2, EPI)   \
+  X(6, 256, 32, 4, 1, 2, 64, 3, 2, EPI)   \
+  X(7, 128, 64, 2, 4, 1, 64, 4, 4, EPI)   \
+  X(8, 128, 32, 2, 1, 2, 64, 4, 4, EPI)   \
+  X(9, 64, 256, 1, 8, 1, 64, 3, 3, EPI)   \
+  X(10, 128, 64, 2, 4, 1, 64, 4, 0, EPI)  \
+  X(11, 64, 64, 1, 2, 2, 64, 4, 6, EPI) \
+  X(12, 64, 128, 1, 4, 2, 64, 4, 6, EPI)  \
+  X(13, 192, 128, 2, 2, 2, 64, 3, 0, EPI) \
+  X(14, 96, 128, 1, 8, 1, 64, 4, 4, EPI)  \
+  X(15, 96, 256, 1, 8, 1, 64, 3, 2, EPI)  \
+  X(16, 192, 64, 2, 2, 2, 64, 3, 2, EPI)  \
+  X(17, 192, 256, 2, 4, 1, 32, 4, 0, EPI) \
+  X(18, 96, 64, 1, 2, 2, 64, 4, 4, EPI)   \
+  X(19, 256, 256, 4, 2, 1, 32, 4, 0, EPI) \
+  X(20, 256, 224, 4, 2, 1, 32, 4, 0, EPI) \
+  X(21, 256, 192, 4, 2, 1, 32, 4, 0, EPI) \
+  X(22, 256, 160, 4, 2, 1, 32, 4, 0, EPI) \
+  X(23, 128, 160, 4, 2, 1, 64, 3, 3, EPI)
 constexpr int kNumLdsTiles = 24;
 // The QKV product without rotation and append is built for one tile, as the form that the others are compared with.
 constexpr bool lds_built(int id, int epi) { return epi != HAT_EPI_P32 || id == HAT_APART_TILE; }
@@ -686,14 +775,9 @@ constexpr bool stream_built(int id, int epi) {
 constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26, kStream64x32 = 27;
 constexpr int kNumTiles = 28;
 
-struct TileInfo { int bf, bt, waves, bkt, nstage; bool planned; float eff; };
-// `planned`: offered to the automatic choice; the others are alternative stagings of the
-// same shapes, used only when forced
-constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, true, true, true, true,
-                                      false, false, false, true, true, true, true, true, true, true,
-                                      true, true, true, true};
+struct TileInfo { int bf, bt, waves, bkt, nstage; float eff; };
 // How fast a tile's k-loop is taken to be where it is not load-bound, against the matrix peak, and with it the constants of the large regime below: weights for the
-// choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: never the best beyond kSmallT rows).  Measured with all tiles, K splits and
+// choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: not offered; the loops of 128 x 256, 128 x 128, 96 x 128 and 128 x 160 were the multiplying waves' own then).  Measured with all tiles, K splits and
 // split tails of the four products, norms included, at 36 batch sizes of 390 .. 4096 rows and seven widths (1024 x 2816 .. 8192 x 28672; the search had seen 9 sizes up to 2048
 // rows of three of them): the four choices of a layer lose 0.24 % of it on average at 20 of the sizes and 0.31 % at the other 16, where the constants of the 32x32x16
 // loops lost 1.78 and 1.85 %.  Of 1004 choices 303 changed with them, 256 to a product more than 1 % faster and 25 to one more than 1 % slower: gate/up of 8192 columns
@@ -703,26 +787,34 @@ constexpr bool kPlanned[kNumLdsTiles] = {false, false, true, true, true, true, t
 // rounds of workgroups, where large products go by their padded work).
 constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.527f, 0.570f, 0.f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
 constexpr int kSmallT = 384;
+// Up to kMidT rows: us that a k-tile of 64 is taken to cost each tile (0: not offered), and what else the model counts (hat_gemm_plan).
+// Weights for the choice like kEff, searched on all tiles, one to eight pieces of K and the norms at 30 batch sizes of 33 .. 1100 rows and seven widths (1024 x 2816 .. 8192 x 28672): the choices
+// lose 0.24 % of a layer's products on average; searched on two thirds of the sizes 0.23 .. 0.30 % there and 0.30 .. 0.45 % on the others.  The constants before, with these
+// tiles, lost 2 .. 9 % (192 rows 8.1, 420 8.8, 256 6.3, 1024 3.0).
+constexpr int kMidT = 1100;
+constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.360f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
+struct MidCosts { double round, fraction, shared, part, tbs, stream, resid; };
+constexpr MidCosts kMid = {7.79, 0.192, 0.0730, 0.460, 6.01, 13.79, 0.506};
 constexpr TileInfo kTiles[kNumTiles] = {
-#define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kPlanned[id], kEff[id]},
+#define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id]},
     HAT_FOR_TILES(HAT_INFO, 0)
 #undef HAT_INFO
 // "stages" of a streaming tile: its register ring counted in 32-k pieces
-#define HAT_INFO(id, np, nt, epi) {32 * (np), 32 * (nt), 8, 32, StreamDepth<np, nt>::value / 2, false, 0.f},
+#define HAT_INFO(id, np, nt, epi) {32 * (np), 32 * (nt), 8, 32, StreamDepth<np, nt>::value / 2, 0.f},
     HAT_FOR_STREAM(HAT_INFO, 0)
 #undef HAT_INFO
 };
 
 template <int EPI>
 hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
-#define HAT_TRY(id, bf, bt, wf, wt, wk, bkt, ns, epi)                   \
+#define HAT_TRY(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi)                   \
   if constexpr (lds_built(id, epi)) if (p.tile == id) {                 \
-    using TL = Tile<bf, bt, wf, wt, wk, bkt, ns>;                       \
+    using TL = Tile<bf, bt, wf, wt, wk, bkt, ns, g_>;                       \
     const int nT = (g.T + bt - 1) / bt, nF = (g.Nw + bf - 1) / bf;      \
     dim3 grid(nT * nF, 1, p.ksplit);                                    \
     if (p.full > 0) grid = dim3(p.full * nF + (nT - p.full) * nF * p.ksplit); \
-    auto kern = gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>;          \
-    kern<<<grid, dim3(TL::NW * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
+    auto kern = gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, g_, epi>;          \
+    kern<<<grid, dim3((TL::NW + TL::NL) * 64), TL::LDS_BYTES, st>>>(g, p.ksplit, p.full); \
     return hipGetLastError();                                           \
   }
   HAT_FOR_TILES(HAT_TRY, EPI)
@@ -744,10 +836,10 @@ hipError_t launch_epi(const HatGemm& g, const HatGemmPlan& p, hipStream_t st) {
 template <int EPI>
 hipError_t attr_epi() {
   hipError_t e;
-#define HAT_ATTR(id, bf, bt, wf, wt, wk, bkt, ns, epi)                                                    \
+#define HAT_ATTR(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi)                                                    \
   if constexpr (lds_built(id, epi)) {                                                                     \
-    e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, epi>,                   \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, wk, bkt, ns>::LDS_BYTES); \
+    e = hipFuncSetAttribute((const void*)gemm_kernel<bf, bt, wf, wt, wk, bkt, ns, g_, epi>,                   \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::LDS_BYTES); \
     if (e != hipSuccess) return e;                                                                        \
   }
   HAT_FOR_TILES(HAT_ATTR, EPI)
@@ -851,15 +943,12 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   }
   HatGemmPlan stream{};
   if (stream_plan(g, &stream)) return stream;
-  // Two regimes, each with constants fitted to tile sweeps on MI355X (7B shapes).
-  // Up to kSmallT rows (T = 32 .. 384) the weight stream decides: a CU moves about 36 B/clk
-  // through direct-to-LDS loads, the MFMA loop runs at about 85 % of the matrix peak on its own,
-  // and the two overlap only partly (issuing the loads holds the waves that also issue the
-  // MFMAs); the weight stream cannot beat ~5.5 TB/s, nor (Little's law) the bytes of W that
-  // the resident workgroups' rings keep in flight divided by the ~1.2 us a load from HBM takes
-  // under load -- which is what decides between shapes when there are few token rows.
-  // Above that a k-tile costs the larger of its MFMA time at the tile's own
-  // weight (kEff) and its load time at 23.7 B/clk, a round of workgroups costs ~4.3 us of
+  // Two regimes, each a small cost model whose constants are searched for the least loss against the best measured tile and K split.
+  // Up to kMidT rows (kTau): a k-tile costs what it costs the tile, more where a panel of W is read by several token tiles; a round of workgroups costs
+  // its prologue and drain; the last round counts for less than a whole one; the partial sums of a K split, written here and read by the consumer of the
+  // residual, and the update of the fp32 residual cost by their rows; and the weight stream cannot be beaten.
+  // Above that (kEff) a k-tile costs the larger of its MFMA time at the tile's own
+  // weight and its load time at 23.7 B/clk, a round of workgroups costs ~4.3 us of
   // prologue and drain, and the epilogue's traffic is not hidden: 14 B/clk per CU for the
   // fp16 stores (the rotating epilogue of QKV, which costs more, is taken for one: its choices lose 0.03 % of a layer),
   // 7.65 for the read-modify-write of the fp32 residual, 6.7 for split-K partial
@@ -867,52 +956,47 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   double best_cost = 1e300, tail_cost = 1e300;
   HatGemmPlan tail{0, 1};
   const int KT = g.K / 64;
-  const bool large = g.T > kSmallT;
+  const bool large = g.T > kMidT;
   for (int c = 0; c < kNumLdsTiles; ++c) {
     const TileInfo& q = kTiles[c];
-    if (!q.planned) continue;
+    if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128)) continue;   // (tiles that are never the best there)
+    // 128 x 64 without loader waves (10) is offered where its panels of W are read by five and more token tiles, which then find them in L2: 300 rows of 1024 .. 3072 columns 2 .. 5 % of
+    // a layer's products ahead of the others; up to 256 rows its loader form (7) and 64 x 64 are.
+    if (!large && c == 10 && g.T <= 256) continue;
     // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
-    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %).  Above 256 rows a third
-    // 128-row token tile or a second 256-row one is as empty.  The four products and the norms of a layer in us, without these tiles and with
-    // them, at 257, 320 and 365 rows: 7B shape 219 -> 193, 229 -> 202 (gate/up 84.1 -> 72.9 with 256 x 160, down 45.3 -> 39.8), 228 -> 227; 13B shape
-    // 282 -> 257, 301 -> 267, 305 -> 287; 8192 x 28672 760 -> 638, 823 -> 656, 814 -> 728; head dim 64 92.6 -> 89.7, 96.4 -> 92.3, 103.7 -> 102.8;
-    // 1024 x 2816 level.  No slower at any of nine batch sizes of seven widths.  384 rows are three whole 128-row
-    // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py): not the faster choice everywhere (a 13B-shaped layer 308 us, 289
-    // with the 192-row tile).
-    const bool tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && g.T > 128 && g.T <= 160;
-    if (large ? q.eff == 0.f : (q.bt & (q.bt - 1)) != 0 && !tall) continue;
+    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %); O, gate/up and down of models from 4096 columns on take it there, narrower ones where
+    // it is predicted ahead (gate/up of 150 rows at 2048 columns 27 us, 96 x 128 21; at 4096 50.5, 96 x 256 49, which pads 256 rows).  Above 256 rows a third
+    // 128-row token tile or a second 256-row one is as empty: the four products and the norms of a layer at 257 and 320 rows 219 -> 193 and 229 -> 202 us (7B shape),
+    // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there.  384 rows are three whole 128-row
+    // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py).
+    const bool just160 = g.T > 128 && g.T <= 160, tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && just160;
+    if (just160 && c != 23 && std::min(g.Nout, g.K) >= 4096 && (g.epilogue == HAT_EPI_SWIGLU || g.epilogue == HAT_EPI_RESID)) continue;
+    if (g.T <= kSmallT && (q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
     const int max_split = (g.epilogue == HAT_EPI_RESID && g.part) ? 16 : 1;
-    const int lds = q.nstage * (q.bf + q.bt) * q.bkt * 2;
-    const int per_cu = std::max(1, std::min(160 * 1024 / lds, 2));
     for (int ks = 1; ks <= max_split; ++ks) {
       if (ks > 1 && (KT / ks < 4 || (long)ks * g.T > g.part_rows)) break;
       const double blocks = (double)nT * nF * ks;
       const double rounds = std::ceil(blocks / 256.0);
       const double kt = std::ceil((double)KT / ks) + 2.0;                     // + pipeline fill
-      double cyc;
+      const double rows = (double)g.T * g.Nout / 256.0;                       // output elements per CU
+      double cost;
       if (large) {
         const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * q.eff);  // per k-tile, 4 SIMDs
         const double load_cyc = (q.bf + q.bt) * 64 * 2 / 23.7;
         const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.068 * std::min(mfma_cyc, load_cyc);
-        cyc = rounds * kt * tile_cyc + rounds * 10300.0;
-        const double rows = (double)g.T * g.Nout / 256.0;                     // output elements per CU
+        double cyc = rounds * kt * tile_cyc + rounds * 10300.0;
         if (g.epilogue != HAT_EPI_RESID) cyc += rows * 2.0 / 14.0;
         else if (ks == 1) cyc += rows * 8.0 / 7.65;
         else cyc += rows * 8.0 * ks / 6.73;
+        const double hbm_cyc = 2.0 * g.Nw * g.K / 5.5e12 * 2.4e9 + 7000.0;
+        cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                             // tie-break below the HBM floor
       } else {
-        const double mfma_eff = q.bf * q.bt == 65536 ? 0.90 : 0.85;
-        const double mfma_cyc = 2.0 * q.bf * q.bt * 64 / (4 * 1017.0 * mfma_eff);
-        const double load_cyc = (q.bf + q.bt) * 64 * 2 / 36.0;
-        const double tile_cyc = std::max(mfma_cyc, load_cyc) + 0.45 * std::min(mfma_cyc, load_cyc);
-        cyc = rounds * kt * tile_cyc + rounds * 3000.0;
-        if (ks > 1) cyc += (double)ks * g.T * g.Nout * 8.0 / 256.0 / 12.0;    // partial write + read, per CU
+        const double r = (1 - kMid.fraction) * rounds + kMid.fraction * std::max(1.0, blocks / 256.0);
+        double us = r * (kt * kTau[c] * (nT > 1 ? 1 + kMid.shared : 1) + kMid.round);
+        if (g.epilogue == HAT_EPI_RESID) us += 1e-3 * rows * (ks > 1 ? ks * kMid.part : kMid.resid);
+        cost = std::max(us, 2e-6 * g.Nw * g.K / kMid.tbs + kMid.stream) + 0.02 * us;
       }
-      const double resident = std::min(blocks, 256.0 * per_cu);
-      const double inflight = resident * q.bf * q.bkt * 2.0 * (q.nstage - 1);
-      const double bw = std::min(5.5e12, inflight / 1.2e-6);
-      const double hbm_cyc = 2.0 * g.Nw * g.K / bw * 2.4e9 + 7000.0;
-      const double cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                // tie-break below the HBM floor
       if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; }
     }
     // A last round that leaves most CUs idle: the token tiles that fill whole rounds stay whole, the rest is split
