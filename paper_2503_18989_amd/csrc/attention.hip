@@ -75,11 +75,20 @@ __device__ __forceinline__ u32x4 stream_load(const u32x4* p) { return __builtin_
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 typedef __attribute__((address_space(1))) kv_t global_kv;
 
+// How far, in powers of two, a score may lie above the reference that its row's sums are kept
+// against (m_run) before they are scaled to a new one: probabilities are then at most 2^8
+// instead of 1, which fp16 holds with the same relative rounding and fp32 sums do not notice.
+// A new reference costs 64 multiplications a lane as soon as one of the wave's 32 rows needs it;
+// a running maximum over random keys needs it every few tiles, with the slack only the first tiles
+// do.  8 x 512 rows over 4096 keys (13B shape, bf16 cache) 478 -> 440 us, 4 x 512 over 7680 (7B)
+// 345 -> 318, ten chunks of 128 .. 512 rows 195 -> 179, 1 x 256 over 1024 20.7 -> 19.9.
+constexpr float kMaxSlack = 8.f;
+
 // Online-softmax update for one 32-key S^T tile held as 16 accumulator values.
 // key of value r: key0 + 8*(r/4) + 4*half + r%4.  Returns probabilities as the
-// two B operands (keys 0..15 / 16..31 of the tile) and rescales O when the running
-// maximum of any row of the wave moved.  MASK = 0 is for tiles that lie wholly
-// below every row's causal limit (no compares); 1 = causal (keys up to qpos); 2 = the
+// two B operands (keys 0..15 / 16..31 of the tile) and rescales O when a score of any row of
+// the wave lies more than kMaxSlack above the row's reference (m_run, in log2 units).
+// MASK = 0 is for tiles that lie wholly below every row's causal limit (no compares); 1 = causal (keys up to qpos); 2 = the
 // caller supplies the visibility of the lane's keys as a bit set (vis).  Scores are kept unscaled; the
 // softmax scale (times log2 e) is folded into the exponent's fma.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -103,23 +112,24 @@ __device__ __forceinline__ void softmax_step(const f32x16& s_acc, float scale_lo
     mx = fmaxf(mx, sr[r]);
   }
   mx = half_max(mx);
-  const float m_new = fmaxf(m_run, mx * scale_log2);   // running maximum in log2 units
-  const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-  float ps = 0.f;
-  float pv[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    pv[r] = __builtin_amdgcn_exp2f(fmaf(sr[r], scale_log2, -m_safe));
-    ps += pv[r];
-  }
-  if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {   // wave-uniform: some row's maximum moved
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+  const float mx_log2 = mx * scale_log2;
+  if (__builtin_amdgcn_ballot_w64(mx_log2 > m_run + kMaxSlack) != 0) {   // wave-uniform
+    const float m_new = fmaxf(m_run, mx_log2);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
     l_run *= alpha;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[c][r] *= alpha;
     m_run = m_new;
+  }
+  const float m_safe = m_run == -INFINITY ? 0.f : m_run;
+  float ps = 0.f;
+  float pv[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    pv[r] = __builtin_amdgcn_exp2f(fmaf(sr[r], scale_log2, -m_safe));
+    ps += pv[r];
   }
   l_run += ps;
 #pragma unroll
@@ -481,23 +491,6 @@ __global__ __launch_bounds__(256, 2) void attn_verify_probe_kernel(HatPlanDev p,
 }
 
 // ------------------------------------------------------------------ chunk
-// softmax_step in two parts, for the interior stages of the chunk kernel where the
-// matrix pipe should stay busy while the VALU does the exponentials: scores -> (maximum,
-// exponentials, row sum) touches only the score registers, so it can be scheduled among the
-// MFMAs that still accumulate into O; the O rescale and the fp16 pack follow.
-__device__ __forceinline__ void softmax_probs(f32x16& s, float scale_log2, float m_run, float& m_new, float& ps) {
-  float mx = s[0];
-#pragma unroll
-  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-  mx = half_max(mx);
-  m_new = fmaxf(m_run, mx * scale_log2);
-  ps = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -m_new));  // scores are finite here: m_new is too
-    ps += s[r];
-  }
-}
 __device__ __forceinline__ void probs_to_f16(const f32x16& pv, f16x8& p0, f16x8& p1) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -689,8 +682,8 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
         asm volatile("" : "+v"(mx));
       } else if constexpr (q == 1) {
-        mx = half_max(mx);
-        m_new = fmaxf(m_run, mx * scale_log2);
+        mx = half_max(mx) * scale_log2;
+        m_new = __builtin_amdgcn_ballot_w64(mx > m_run + kMaxSlack) != 0 ? fmaxf(m_run, mx) : m_run;
         asm volatile("" : "+v"(m_new));
         ps = 0.f;
       } else {
