@@ -3,7 +3,9 @@
 //   chunk  -- a prompt chunk of a device in the prefill phase (paper Sec. 2.1
 //             chunked prefill, Sec. 3.3): many query rows, matrix-core bound.
 //             One workgroup = 256 query rows (8 waves x 32) of one head; K/V tiles
-//             of 64 keys are staged in LDS and shared by the eight waves.
+//             are staged in LDS and shared by the eight waves: 64 keys at a time by
+//             these waves themselves (bf16 cache), or by four more that only load
+//             (fp16 cache).
 //   verify -- the draft sequence of a device in the decode phase verified in one
 //             step (Sec. 3.4), or a tree of candidates (Sec. 2.2) given as one
 //             visibility byte per row: at most 8 query rows against a long cache, HBM
@@ -501,7 +503,7 @@ __device__ __forceinline__ void probs_to_f16(const f32x16& pv, f16x8& p0, f16x8&
   }
 }
 
-template <int HD, bool KVF16>
+template <int HD>
 __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;
   constexpr int NC = HD / 32;
@@ -588,7 +590,7 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
   };
   auto lstore = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) *(u32x4*)(&lds[buf][(i * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<KVF16>(regs[i]);
+    for (int i = 0; i < LPT; ++i) *(u32x4*)(&lds[buf][(i * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<false>(regs[i]);
   };
   // general stage: causal masks, ragged ends, waves that skip a 32-key half
   auto compute = [&](int st, int buf) {
@@ -727,7 +729,7 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
         if constexpr (m < NS) {                                  // scores of A | widen next stage into LDS
           sA = __builtin_amdgcn_mfma_f32_32x32x16_f16(op[cur][j], qreg[m], m == 0 ? zero16 : sA, 0, 0, 0);
           if constexpr (m < LPT) {
-            if (do_store) *(u32x4*)(&lds[buf ^ 1][(m * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<KVF16>(regs[m]);
+            if (do_store) *(u32x4*)(&lds[buf ^ 1][(m * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<false>(regs[m]);
           }
         } else if constexpr (m < 2 * NS) {                       // scores of B | loads of stage st+2, softmax of A
           constexpr int q = m - NS;
@@ -806,6 +808,238 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
   }
 }
 
+// ------------------------------------------------------------------ ring
+// Chunk items whose pages need no widening (fp16 cache): eight waves of 32 rows compute and four
+// more load, straight from the cache into a ring in LDS.  Matrix cores and exponentials bound it;
+// in the chunk kernel the eight waves also load and store the stages between their own products
+// and meet every 64 keys.  Loads whose addresses are scalar cost the loader waves next to
+// nothing, a stage of 64 KB (128 keys at head dim 128) halves the barriers, and two of them are
+// what LDS holds: the next stage is on its way while one is read.  A wave reads each operand half a
+// product ahead.  8 x 512 rows over 4096 keys (13B shape) 428 us with the chunk kernel, 386 with
+// this one (two cards; 404 on a third), 1 x 1024 over 3072 127 -> 113, 1 x 256 over 1024 (7B) 21.5 -> 19.3.
+// A bf16 cache stays with the chunk kernel: with its widening in the loader waves 8 x 512 rows
+// took 435 us instead of 440, but ten chunks of 128 .. 512 rows 199 instead of 179.
+template <int HD>
+struct Ring {
+  static constexpr int ROW_WAVES = HAT_CHUNK_QROWS / 32, LOADERS = 4;
+  static constexpr int RECB = 2 * 16 * HD * 2;             // bytes of one (page, head) record
+  static constexpr int STAGE = 65536, SLOTS = 2;           // bytes of a stage, and how many of them LDS holds
+  static constexpr int PAGES = STAGE / RECB, KEYS = PAGES * 16;
+  static constexpr int LOADS = STAGE / 1024 / LOADERS;     // 1 KB loads of a loader wave per stage
+  static_assert(KEYS % 32 == 0, "whole tiles of 32 keys");
+  static_assert((RECB / 1024) % LOADERS == 0, "the j-th loads of the loader waves lie in one page");
+  static_assert((SLOTS - 2) * LOADS <= 63, "vmcnt has 6 bits");
+};
+template <int HD>
+__global__ __launch_bounds__((Ring<HD>::ROW_WAVES + Ring<HD>::LOADERS) * 64, 3) void attn_ring_kernel(HatPlanDev p, HatAttn a) {
+  constexpr int NS = HD / 16;
+  constexpr int NC = HD / 32;
+  constexpr int REC = 2 * 16 * HD;        // elements of one (page, head) record
+  using R = Ring<HD>;
+  constexpr int RECB = R::RECB, KEYS = R::KEYS, PAGES = R::PAGES, LOADS = R::LOADS, STAGE = R::STAGE, SLOTS = R::SLOTS;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+
+  const HatAttnItem it = a.items[blockIdx.x];
+  const int head = blockIdx.y;
+  const SegInfo sg = seg_info(p, it);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: per-wave decisions become scalar branches
+
+  // keys this item needs: [kv_begin, min(kv_end, last row's position + 1))
+  const int kv_end = min(it.kv_end, sg.start + it.q0 + it.nq);
+  const int n_stages = kv_end > it.kv_begin ? (kv_end - it.kv_begin + KEYS - 1) / KEYS : 0;
+
+  if (wave >= R::ROW_WAVES) {   // a loader wave
+    __builtin_amdgcn_s_setprio(2);
+    const unsigned char* pool = (const unsigned char*)(a.pool_layer + (size_t)head * a.n_pages * REC);  // this head's pages are contiguous
+    const int lw = wave - R::ROW_WAVES, lane16 = lane * 16, page0 = it.kv_begin >> 4;
+    constexpr int CPP = RECB / 1024;   // 1 KB pieces of a record: K's, then V's
+    // page ids are scalar loads, which the count of vector loads does not see
+    typedef const __attribute__((address_space(4))) int32_t* const_ids;
+    const const_ids pt = (const_ids)(uintptr_t)sg.pt;
+    int ids[PAGES];
+    auto page_ids = [&](int st) {
+#pragma unroll
+      for (int j = 0; j < PAGES; ++j) ids[j] = pt[min(page0 + st * PAGES + j, sg.npages - 1)];
+    };
+    int ls = 0;   // slot of the next stage to load
+    auto load = [&]() {
+      unsigned char* dst = lds + ls * STAGE + lw * 1024;
+      hat_static_for<LOADS>([&](auto jc) {
+        constexpr int c = decltype(jc)::value * R::LOADERS;
+        const void* rec = hat_uniform(pool + (size_t)ids[c / CPP] * RECB);
+        hat_load_lds<0>(rec, dst + c * 1024, lane16, (c % CPP + lw) * 1024);
+      });
+      ls = ls + 1 == SLOTS ? 0 : ls + 1;
+    };
+    for (int st = 0; st < SLOTS - 1 && st < n_stages; ++st) {
+      page_ids(st);
+      load();
+    }
+    int slot = 0;
+    for (int st = 0; st < n_stages; ++st) {
+      const int next = st + SLOTS - 1;
+      if (next < n_stages) page_ids(next);
+      const int behind = min(SLOTS - 2, n_stages - 1 - st);   // stages that may still be on their way
+      hat_static_for<SLOTS - 1>([&](auto bc) {
+        if (behind == bc) hat_wait_vmcnt<decltype(bc)::value * LOADS>();
+      });
+      if (it.kv_begin + (st + 1) * KEYS > sg.kv_len) {
+        // V rows at or beyond kv_len become zeros: stale memory there may hold NaN patterns, and
+        // 0 * NaN would poison the accumulator
+#pragma unroll 1
+        for (int c = lw; c < STAGE / 1024; c += R::LOADERS) {
+          const int sub = c % CPP - CPP / 2, h = ((sub * 64 + lane) >> 5) & 1;   // the lane's slot half
+          const int left = sg.kv_len - (it.kv_begin + st * KEYS + c / CPP * 16) - 4 * h;
+          if (sub < 0) continue;
+          u32x4* q = (u32x4*)(lds + slot * STAGE + c * 1024 + lane16);
+          u32x4 v = *q;
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            const int s0 = 8 * (d >> 1) + 2 * (d & 1);
+            v[d] = s0 >= left ? 0 : s0 + 1 >= left ? v[d] & 0xffffu : v[d];
+          }
+          *q = v;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+      __builtin_amdgcn_s_barrier();
+      if (next < n_stages) load();
+      slot = slot + 1 == SLOTS ? 0 : slot + 1;
+    }
+    return;
+  }
+
+  const int half = lane >> 5, n = lane & 31;
+  const int wq0 = it.q0 + 32 * wave;  // first row of this wave, relative to the segment
+  const int nq_w = min(32, it.nq - 32 * wave);   // valid rows of this wave
+  const bool wave_live = nq_w > 0;
+  int qi = wq0 + (n < nq_w ? n : (nq_w > 0 ? nq_w - 1 : 0));
+  if (!wave_live) qi = it.q0;  // idle wave: any in-range row
+  const int qrow = sg.tok0 + qi;
+  const int qpos = sg.start + qi;
+  const int wave_last_pos = wave_live ? sg.start + wq0 + nq_w - 1 : -1;
+  const int wave_first_pos = sg.start + wq0;
+  const float scale_log2 = kLog2e / sqrtf((float)HD);
+
+  f16x8 qreg[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    qreg[s] = *(const f16x8*)(a.qkv + p32_index(qrow, head * HD + (2 * s + half) * 8, 3 * a.d));
+
+  f32x16 o[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[c][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+  const uint32_t kaddr0 = lds_base + (n < 16 ? 0 : RECB) + (half * 16 + (n & 15)) * 16;
+  const uint32_t vaddr0 = lds_base + 16 * HD * 2 + lane * 16;
+  // 32 keys.  Operands are read half a product ahead: `first` holds the first half of K's, and on
+  // the way out that of the next tile, if it lies in this stage.
+  constexpr int HS = NS / 2;
+  static_assert(NC == NS / 2, "V has as many operands as K");
+  hat_f16x8 first[HS];
+  auto read_first = [&](uint32_t off) {
+    const uint32_t ka = kaddr0 + off;
+    hat_static_for<HS>([&](auto sc) { first[decltype(sc)::value] = hat_lds_read<decltype(sc)::value * 512>(ka); });
+  };
+  auto tile = [&](uint32_t off, int key0, bool mask, bool more) {
+    const uint32_t ka = kaddr0 + off, va = vaddr0 + off;
+    hat_f16x8 second[HS], v0[HS], v1[HS];
+    hat_static_for<HS>([&](auto sc) {
+      second[decltype(sc)::value] = hat_lds_read<(HS + decltype(sc)::value) * 512>(ka);
+    });
+    hat_wait_operands<HS>(first);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 sacc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    hat_static_for<HS>([&](auto sc) {
+      constexpr int s = decltype(sc)::value;
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(first[s], qreg[s], sacc, 0, 0, 0);
+    });
+    hat_wait_operands<0>(second);
+    __builtin_amdgcn_sched_barrier(0);
+    hat_static_for<HS>([&](auto sc) {
+      constexpr int s = decltype(sc)::value;
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(second[s], qreg[HS + s], sacc, 0, 0, 0);
+    });
+    auto read_v = [&](auto hc, hat_f16x8(&v)[HS]) {
+      constexpr int h = decltype(hc)::value;
+      hat_static_for<HS>([&](auto ic) {
+        constexpr int i = h * HS + decltype(ic)::value;
+        v[decltype(ic)::value] = hat_lds_read<(i % 2) * RECB + (i / 2) * 1024>(va);
+      });
+    };
+    f16x8 p0, p1;
+    auto pv = [&](auto hc, hat_f16x8(&v)[HS]) {
+      constexpr int h = decltype(hc)::value;
+      hat_static_for<HS>([&](auto ic) {
+        constexpr int i = h * HS + decltype(ic)::value;
+        o[i / 2] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v[decltype(ic)::value], (i % 2) ? p1 : p0, o[i / 2], 0, 0, 0);
+      });
+    };
+    constexpr std::integral_constant<int, 0> h0{};
+    constexpr std::integral_constant<int, 1> h1{};
+    __builtin_amdgcn_sched_barrier(0);
+    read_v(h0, v0);
+    if (mask) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (key0 + 8 * (r >> 2) + 4 * half + (r & 3) > qpos) sacc[r] = -INFINITY;
+    }
+    softmax_step<NC, 0>(sacc, scale_log2, key0, half, qpos, m_run, l_run, o, p0, p1);
+    __builtin_amdgcn_sched_barrier(0);
+    read_v(h1, v1);
+    hat_wait_operands<HS>(v0);
+    __builtin_amdgcn_sched_barrier(0);
+    pv(h0, v0);
+    __builtin_amdgcn_sched_barrier(0);
+    read_first(more ? off + 2 * RECB : off);
+    hat_wait_operands<HS>(v1);
+    __builtin_amdgcn_sched_barrier(0);
+    pv(h1, v1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int TILES = KEYS / 32;
+  uint32_t soff = 0;
+  for (int st = 0; st < n_stages; ++st) {
+    __builtin_amdgcn_s_barrier();
+    const int skey = it.kv_begin + st * KEYS;
+    // keys above the wave's last row and beyond the range are skipped
+    const int last = min(wave_last_pos + 1, kv_end);
+    const int n_tiles = last > skey ? min(TILES, (last - skey + 31) >> 5) : 0;
+    if (n_tiles > 0) read_first(soff);
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+      const int key0 = skey + t * 32;
+      tile(soff + t * (2 * RECB), key0, key0 + 31 > wave_first_pos, t + 1 < n_tiles);
+    }
+    if (n_tiles > 0) hat_wait_operands<0>(first);   // the last tile's read ahead
+    soff = soff + STAGE == SLOTS * STAGE ? 0 : soff + STAGE;
+  }
+  l_run += __shfl_xor(l_run, 32);
+
+  if (n >= nq_w) return;
+  const int row = wq0 + n;  // relative to segment
+  const size_t prow = (size_t)(it.part_row + 32 * wave + n) * a.H + head;
+  // a key range that lies beyond the row's position has no sum
+  const float inv = it.part_row < 0 || l_run > 0.f ? 1.0f / l_run : 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int f = 32 * c + 8 * g + 4 * half;
+      f16x4 ov;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ov[e] = to_act(o[c][4 * g + e] * inv);
+      if (it.part_row < 0) *(f16x4*)(a.outP + p32_index(sg.tok0 + row, head * HD + f, a.d)) = ov;
+      else *(f16x4*)(a.part_o + prow * HD + f) = ov;
+    }
+  if (it.part_row >= 0 && half == 0) a.part_ml[prow] = make_float2(m_run, l_run);
+}
+
 // ------------------------------------------------------------------ merge
 // one workgroup per (group of <= 16 rows, head); one thread per (row, 8 features)
 template <int HD, bool F32>
@@ -881,14 +1115,28 @@ static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, dim3 grid
   return hipGetLastError();
 }
 
+template <int HD>
+static void launch_ring(const HatPlanDev& p, const HatAttn& a, dim3 grid, hipStream_t st) {
+  using R = Ring<HD>;
+  attn_ring_kernel<HD><<<grid, (R::ROW_WAVES + R::LOADERS) * 64, R::SLOTS * R::STAGE, st>>>(p, a);
+}
+template <int HD>
+static hipError_t init_ring() {
+  return hipFuncSetAttribute((const void*)attn_ring_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<HD>::SLOTS * Ring<HD>::STAGE);
+}
+hipError_t hat_attn_init() {
+  const hipError_t e = init_ring<128>();
+  return e != hipSuccess ? e : init_ring<64>();
+}
+
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   const int wide = a.n_items - a.n_narrow;
   if (a.n_blocks == 0 && wide > 0) {
     dim3 grid(wide, a.H);
-    if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-    else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-    else if (a.hd == 64 && a.kv_f16) attn_chunk_kernel<64, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-    else if (a.hd == 64) attn_chunk_kernel<64, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    if (a.hd == 128 && a.kv_f16) launch_ring<128>(p, a, grid, st);
+    else if (a.hd == 128) attn_chunk_kernel<128><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 64 && a.kv_f16) launch_ring<64>(p, a, grid, st);
+    else if (a.hd == 64) attn_chunk_kernel<64><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else return hipErrorInvalidValue;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

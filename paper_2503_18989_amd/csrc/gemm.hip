@@ -867,7 +867,7 @@ hipError_t hat_gemm_init() {
   if ((e = attr_epi<HAT_EPI_SWIGLU>()) != hipSuccess) return e;
   if ((e = attr_epi<HAT_EPI_RESID>()) != hipSuccess) return e;
   if ((e = attr_epi<HAT_EPI_QKV>()) != hipSuccess) return e;
-  return hipSuccess;
+  return hat_attn_init();
 }
 
 // Where the streaming kernel is the faster one.  Swept over the 7B-, 13B- and hd-64-shaped layers at 5 .. 128 rows; times

@@ -51,10 +51,6 @@ __device__ __forceinline__ void hat_load_lds(const void* base, void* dst, int la
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00020000),
                                            (__attribute__((address_space(3))) void*)dst, 16, lane_bytes, bytes, 0, AUX);
 }
-// the same into registers
-__device__ __forceinline__ hat_u32x4 hat_load(const void* base, int lane_bytes, int bytes) {
-  return __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00020000), lane_bytes, bytes, 0);
-}
 template <int N>
 __device__ __forceinline__ void hat_wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -61,7 +61,7 @@ hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t s
 int hat_gemm_tile_count();
 // shape of tile `id` (features, tokens, waves, k per stage, stages); false if out of range
 bool hat_gemm_tile_info(int id, int* bf, int* bt, int* waves, int* bkt, int* nstage);
-hipError_t hat_gemm_init();  // one-time function attributes (dynamic LDS size)
+hipError_t hat_gemm_init();  // one-time function attributes (dynamic LDS size), those of hat_attn_init among them
 
 // ---- weight re-tiling (create time) -----------------------------------------
 // dst: P32 [Nw, Kd] in act_t (bf16 -> fp16 is exact for |w| in [2^-17, 65504]).  mode 0: row R <- src0[R] (R < n0), else 0.
@@ -175,6 +175,7 @@ struct HatAttn {
   int H, hd, d;
   int n_pages;               // pool capacity (pages per head and layer)
 };
+hipError_t hat_attn_init();
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st);
 hipError_t hat_launch_attn_verify(const HatPlanDev& p, const HatAttn& a, hipStream_t st);
 hipError_t hat_launch_attn_merge(const HatAttn& a, const HatMergeItem* items, int n_items, hipStream_t st);
