@@ -324,7 +324,8 @@ hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
 
 /* The other chunk items of that plan, cut into blocks of at most 32 rows, where these stream the cache as well (12 words each like the
  * items, in the order of launch); none where they stage it.  blocks may be NULL to ask for the number only; HAT_EINVAL if there are
- * more than cap_blocks.  *waves (may be NULL): waves of a block's workgroup, 4 or 8; 0 without blocks. */
+ * more than cap_blocks.  *waves (may be NULL): waves of a block's workgroup, 4 or 8; 0 without blocks,
+ * 2 where items of at most 64 rows each have a workgroup that reads their pages once (fp16 cache). */
 hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks, int32_t* waves);
 
 /* Whether the verify items of that plan go along in the launch of its streamed chunk items (a step that is profiled or probed

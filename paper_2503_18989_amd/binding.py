@@ -374,11 +374,12 @@ class HatPlanner:
     ATTN_FIELDS = ("seg", "q0", "nq", "kv_begin", "kv_end", "part_row", "start", "tok0", "kv_len", "pt_off", "vis_lo", "vis_hi")
     MERGE_FIELDS = ("row0", "nrows", "part_row", "nsplit", "stride")
 
-    def __init__(self, cfg, n_pages, max_devices=64, max_step_tokens=8192, max_pos=16384):
+    def __init__(self, cfg, n_pages, max_devices=64, max_step_tokens=8192, max_pos=16384, kv_dtype="bf16"):
         self.lib = load_library()
         self.max_step_tokens = max_step_tokens
         self.ccfg = Config(cfg["n_layers"], cfg["d_model"], cfg["n_heads"], cfg["head_dim"], cfg["d_ffn"],
-                           cfg["rms_eps"], cfg["rope_theta"], 16, n_pages, max_devices, max_step_tokens, max_pos, HAT_BF16, 0)
+                           cfg["rms_eps"], cfg["rope_theta"], 16, n_pages, max_devices, max_step_tokens, max_pos, HAT_BF16,
+                           KV_DTYPES[kv_dtype])
         self._handle = C.c_void_p()
         rc = self.lib.hat_mid_debug_create_host_only(C.byref(self.ccfg), C.byref(self._handle))
         if rc != 0:
@@ -430,7 +431,7 @@ class HatPlanner:
         return [dict(zip(self.ATTN_FIELDS, raw[12 * k:12 * k + 10])) for k in range(n.value)]
 
     def block_waves(self):
-        """Waves of the workgroup that takes one of blocks(); 0 if there are none."""
+        """Waves of the workgroup that takes one of blocks(); 0 if there are none, 2 where each item of at most 64 rows has its own."""
         n, w = C.c_int32(), C.c_int32()
         self._check(self.lib.hat_mid_debug_plan_blocks(self._handle, None, C.byref(n), 0, C.byref(w)))
         return w.value

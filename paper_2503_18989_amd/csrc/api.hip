@@ -572,14 +572,17 @@ struct StepPlan {
 // These are times of the kernel before it read page ids ahead, which took 3 .. 9 % off all of them, and verify items that go along are not counted.  With the present kernel the choice
 // is 0.4 % of a layer behind the best of staged, eight and four waves over 90 other mixes (1 .. 12 chunks of 33 .. 500 rows over 0 .. 6000 keys; 2.8 % at the most, 302 + 355 rows over 5000 .. 5700 keys of the 7B
 // shape), where always staging is 3.8, always eight waves 2.0 and always four 0.6 % behind it.
+// `waves` = 2: items of at most 64 rows, a workgroup of attn_ring_kernel each (head dim 128, fp16 cache; each of its two computing waves goes through all keys). Fitted to 88 mixes of 3 .. 24
+// such items (5.6 % off on average).
 static double stream_us(const Shapes& s, int kv_f16, int waves, const std::vector<int>& keys, double mbytes) {
   struct Cost { double launch, block, step, shared, per_mb; };
   static const Cost k4[2][2] = {{{3.92, 3.30, 0.776, 0.005, 0.176}, {4.23, 2.70, 0.690, 0.005, 0.163}}, {{4.58, 4.44, 1.327, 0.357, 0.102}, {4.45, 3.65, 1.176, 0.437, 0.109}}};
   static const Cost k8[2][2] = {{{4.91, 2.00, 1.069, 0, 0.126}, {4.79, 2.01, 0.826, 0, 0.143}}, {{4.52, 3.87, 1.831, 0, 0.090}, {3.96, 3.64, 1.686, 0, 0.102}}};
-  const Cost& c = (waves == 8 ? k8 : k4)[s.hd == 128][kv_f16 != 0];
+  static const Cost pair = {0, 8.89, 0.403, 0.400, 0.055};
+  const Cost& c = waves == 2 ? pair : (waves == 8 ? k8 : k4)[s.hd == 128][kv_f16 != 0];
   const double n = (double)keys.size() * s.H, slots = waves == 8 ? 256 : s.hd == 128 ? 512 : 768;
   std::vector<double> steps;
-  for (int k : keys) steps.push_back(std::max(1.0, (double)((k + 31) / 32) / waves));
+  for (int k : keys) steps.push_back(std::max(1.0, (double)((k + 31) / 32) / (waves == 2 ? 1 : waves)));
   std::sort(steps.begin(), steps.end());
   auto mean = [&](size_t shortest) {
     double sum = 0;
@@ -832,10 +835,11 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     double block_cost = 0, narrow_block = 0;  // the same of the items that may stream, in whole blocks of rows
     double chunk_mb = 0;                      // cache rows that chunks read
     long narrow_keys = 0, blocks = 0, narrow_blocks = 0;
-    int narrow_longest = 0;
+    int narrow_longest = 0, longest_chunk = 0;   // keys; rows
     for (int i = 0; i < S; ++i) {
       if (segs[i].kind != HAT_SEG_CHUNK) continue;
       chunk_mb += (segs[i].start_pos + segs[i].n) * 4e-6 * s.d;
+      longest_chunk = std::max(longest_chunk, segs[i].n);
       for (int q0 = 0; q0 < segs[i].n; q0 += HAT_CHUNK_QROWS) {
         const int nq = std::min(HAT_CHUNK_QROWS, segs[i].n - q0);
         const int need = segs[i].start_pos + q0 + nq;
@@ -855,6 +859,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     }
     const bool any_wide = blocks > 0;
     const bool stream_narrow = !any_wide || narrow_longest >= 1536;
+    const bool pairs_only = longest_chunk <= HAT_PAIR_QROWS && vitems.empty() && !(stream_narrow && narrow_blocks > 0);
     if (!stream_narrow) {
       total_cost += narrow_cost;
       block_cost += narrow_block;
@@ -908,6 +913,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // A raised or lowered attn_target is a wish for the staged kernel's key ranges.
     const int f16 = c.kv_dtype == HAT_KV_F16;
     std::vector<ChunkCut> cuts = cut_items(0);
+    double chosen_us = 0;
     if (any_wide && s.attn_target == kAttnTarget) {
       const bool merges = !mitems.empty() || narrow_keys > narrow_step;   // that a launch is needed for anyway
       const double staged_merge = merge_us(s, cuts, false, merges);
@@ -925,6 +931,21 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
         best = us;
         cuts.swap(streamed);
         sp->block_waves = us8 <= us4 ? 8 : 4;
+      }
+      chosen_us = best;
+    }
+    // Chunks of at most 64 rows with nothing beside them, fp16 cache, head dim 128: a small workgroup for each reads its pages once, where that is
+    // predicted 3 % ahead of the way chosen above.  That is in large steps: of 88 mixes of 3 .. 24 chunks of 33 .. 64 rows over 30 .. 8000 keys (16, 32 and 40
+    // heads) it takes 59, whose attention is 19 % faster on average and nowhere slower (8 x 64 over 4096 keys of the 13B shape 158 us streamed, 126);
+    // few or unequal ones leave CUs idle that four or eight waves to a block fill (2 x 40 over 3900 .. 5000 58 | 90).  Over a bf16 cache both computing
+    // waves have to widen what they read: 49 mixes, where predicted ahead 5 % on average but up to 13 % behind; at head dim 64 44 mixes, up to 15 % behind.
+    if (any_wide && s.attn_target == kAttnTarget && f16 && s.hd == 128 && pairs_only) {
+      std::vector<ChunkCut> whole = cut_items(1);
+      std::vector<int> keys;
+      for (const ChunkCut& u : whole) keys.push_back(u.need);
+      if (stream_us(s, f16, 2, keys, chunk_mb) < 0.97 * chosen_us) {
+        cuts.swap(whole);
+        sp->block_waves = 2;
       }
     }
     for (const ChunkCut& u : cuts) {
@@ -946,7 +967,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
     const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [&](const HatAttnItem& a) { return !stream_narrow || a.nq > HAT_NARROW_QROWS; });
     sp->n_narrow = (int)(citems.end() - narrow0);
-    if (sp->block_waves > 0) {
+    if (sp->block_waves > 2) {
       for (auto it = citems.begin(); it != narrow0; ++it)
         for (int r0 = (it->nq - 1) / HAT_NARROW_QROWS * HAT_NARROW_QROWS; r0 >= 0; r0 -= HAT_NARROW_QROWS) {   // the block with the most keys first
           HatAttnItem b = *it;

@@ -819,28 +819,36 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
 // this one (two cards; 404 on a third), 1 x 1024 over 3072 127 -> 113, 1 x 256 over 1024 (7B) 21.5 -> 19.3.
 // A bf16 cache stays with the chunk kernel: with its widening in the loader waves 8 x 512 rows
 // took 435 us instead of 440, but ten chunks of 128 .. 512 rows 199 instead of 179.
-template <int HD>
-struct Ring {
-  static constexpr int ROW_WAVES = HAT_CHUNK_QROWS / 32, LOADERS = 4;
+//
+// With two blocks of 32 rows (RB = 2) it takes chunks of at most 64 rows, an item each (the plan says
+// where): HBM bounds that, as a page is read once and by one workgroup, non-temporally.  One loader wave and two that
+// compute, with 48 of 64 KB on their way, leave room for a second workgroup on the CU.  The row blocks of the
+// streaming kernel read each page twice, through L2, and fill operand registers with it: 8 x 64 rows over 4096 keys (13B
+// shape) 158 us, here 126 (5.4 TB/s).
+template <int HD, int RB>
+struct Ring {   // for RB blocks of 32 rows
+  static constexpr int LOADERS = RB == 8 ? 4 : 1;
   static constexpr int RECB = 2 * 16 * HD * 2;             // bytes of one (page, head) record
-  static constexpr int STAGE = 65536, SLOTS = 2;           // bytes of a stage, and how many of them LDS holds
+  static constexpr int STAGE = RB == 8 ? 65536 : 16384;    // bytes of a stage,
+  static constexpr int SLOTS = RB == 8 ? 2 : 4;            // and how many of them LDS holds
   static constexpr int PAGES = STAGE / RECB, KEYS = PAGES * 16;
   static constexpr int LOADS = STAGE / 1024 / LOADERS;     // 1 KB loads of a loader wave per stage
   static_assert(KEYS % 32 == 0, "whole tiles of 32 keys");
   static_assert((RECB / 1024) % LOADERS == 0, "the j-th loads of the loader waves lie in one page");
   static_assert((SLOTS - 2) * LOADS <= 63, "vmcnt has 6 bits");
 };
-template <int HD>
-__global__ __launch_bounds__((Ring<HD>::ROW_WAVES + Ring<HD>::LOADERS) * 64, 3) void attn_ring_kernel(HatPlanDev p, HatAttn a) {
+template <int HD, int RB>
+__global__ __launch_bounds__((RB + Ring<HD, RB>::LOADERS) * 64, RB == 8 ? 3 : 2) void attn_ring_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;
   constexpr int NC = HD / 32;
   constexpr int REC = 2 * 16 * HD;        // elements of one (page, head) record
-  using R = Ring<HD>;
+  using R = Ring<HD, RB>;
   constexpr int RECB = R::RECB, KEYS = R::KEYS, PAGES = R::PAGES, LOADS = R::LOADS, STAGE = R::STAGE, SLOTS = R::SLOTS;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
-  const HatAttnItem it = a.items[blockIdx.x];
-  const int head = blockIdx.y;
+  // pages that nobody shares: the longest items first, in all heads
+  const HatAttnItem it = a.items[RB == 2 ? blockIdx.y : blockIdx.x];
+  const int head = RB == 2 ? blockIdx.x : blockIdx.y;
   const SegInfo sg = seg_info(p, it);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: per-wave decisions become scalar branches
@@ -849,10 +857,10 @@ __global__ __launch_bounds__((Ring<HD>::ROW_WAVES + Ring<HD>::LOADERS) * 64, 3) 
   const int kv_end = min(it.kv_end, sg.start + it.q0 + it.nq);
   const int n_stages = kv_end > it.kv_begin ? (kv_end - it.kv_begin + KEYS - 1) / KEYS : 0;
 
-  if (wave >= R::ROW_WAVES) {   // a loader wave
+  if (wave >= RB) {   // a loader wave
     __builtin_amdgcn_s_setprio(2);
     const unsigned char* pool = (const unsigned char*)(a.pool_layer + (size_t)head * a.n_pages * REC);  // this head's pages are contiguous
-    const int lw = wave - R::ROW_WAVES, lane16 = lane * 16, page0 = it.kv_begin >> 4;
+    const int lw = wave - RB, lane16 = lane * 16, page0 = it.kv_begin >> 4;
     constexpr int CPP = RECB / 1024;   // 1 KB pieces of a record: K's, then V's
     // page ids are scalar loads, which the count of vector loads does not see
     typedef const __attribute__((address_space(4))) int32_t* const_ids;
@@ -868,7 +876,7 @@ __global__ __launch_bounds__((Ring<HD>::ROW_WAVES + Ring<HD>::LOADERS) * 64, 3) 
       hat_static_for<LOADS>([&](auto jc) {
         constexpr int c = decltype(jc)::value * R::LOADERS;
         const void* rec = hat_uniform(pool + (size_t)ids[c / CPP] * RECB);
-        hat_load_lds<0>(rec, dst + c * 1024, lane16, (c % CPP + lw) * 1024);
+        hat_load_lds<RB == 2 ? 2 : 0>(rec, dst + c * 1024, lane16, (c % CPP + lw) * 1024);
       });
       ls = ls + 1 == SLOTS ? 0 : ls + 1;
     };
@@ -1115,27 +1123,33 @@ static hipError_t launch_stream(const HatPlanDev& p, const HatAttn& a, dim3 grid
   return hipGetLastError();
 }
 
-template <int HD>
+template <int HD, int RB>
 static void launch_ring(const HatPlanDev& p, const HatAttn& a, dim3 grid, hipStream_t st) {
-  using R = Ring<HD>;
-  attn_ring_kernel<HD><<<grid, (R::ROW_WAVES + R::LOADERS) * 64, R::SLOTS * R::STAGE, st>>>(p, a);
+  using R = Ring<HD, RB>;
+  attn_ring_kernel<HD, RB><<<grid, (RB + R::LOADERS) * 64, R::SLOTS * R::STAGE, st>>>(p, a);
 }
-template <int HD>
+template <int HD, int RB>
 static hipError_t init_ring() {
-  return hipFuncSetAttribute((const void*)attn_ring_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<HD>::SLOTS * Ring<HD>::STAGE);
+  return hipFuncSetAttribute((const void*)attn_ring_kernel<HD, RB>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<HD, RB>::SLOTS * Ring<HD, RB>::STAGE);
 }
 hipError_t hat_attn_init() {
-  const hipError_t e = init_ring<128>();
-  return e != hipSuccess ? e : init_ring<64>();
+  for (hipError_t e : {init_ring<128, 8>(), init_ring<64, 8>(), init_ring<128, 2>()})
+    if (e != hipSuccess) return e;
+  return hipSuccess;
 }
 
 hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStream_t st) {
   const int wide = a.n_items - a.n_narrow;
+  if (a.block_waves == 2 && wide > 0) {
+    if (a.hd != 128 || !a.kv_f16 || a.n_blocks + a.n_narrow + a.n_verify > 0) return hipErrorInvalidValue;
+    launch_ring<128, 2>(p, a, dim3(a.H, wide), st);
+    return hipGetLastError();
+  }
   if (a.n_blocks == 0 && wide > 0) {
     dim3 grid(wide, a.H);
-    if (a.hd == 128 && a.kv_f16) launch_ring<128>(p, a, grid, st);
+    if (a.hd == 128 && a.kv_f16) launch_ring<128, 8>(p, a, grid, st);
     else if (a.hd == 128) attn_chunk_kernel<128><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-    else if (a.hd == 64 && a.kv_f16) launch_ring<64>(p, a, grid, st);
+    else if (a.hd == 64 && a.kv_f16) launch_ring<64, 8>(p, a, grid, st);
     else if (a.hd == 64) attn_chunk_kernel<64><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else return hipErrorInvalidValue;
     const hipError_t e = hipGetLastError();

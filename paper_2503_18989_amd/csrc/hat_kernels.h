@@ -14,6 +14,7 @@ constexpr int HAT_MAX_VERIFY_ROWS = 8;  // query rows of a verify work item
 // workgroup loads and widens is shared by all of them)
 constexpr int HAT_CHUNK_QROWS = 256;
 constexpr int HAT_NARROW_QROWS = 32;   // chunk items of at most this many rows stream the cache like verify items
+constexpr int HAT_PAIR_QROWS = 64;     // rows of a chunk whose pages a workgroup of its own may read
 
 // ---- GEMM: out[t, f] = sum_k X[t, k] * W[f, k], operands in P32 layout ------
 enum HatEpilogue {
@@ -168,7 +169,7 @@ struct HatAttn {
   int n_items;
   int n_narrow;              // chunk items: the last n_narrow of them have at most HAT_NARROW_QROWS rows
   const HatAttnItem* blocks; // n_blocks > 0: the other chunk items stream the cache too, as these items of at most HAT_NARROW_QROWS rows
-  int n_blocks, block_waves; // four or eight waves to a block
+  int n_blocks, block_waves; // four or eight waves to a block; two (n_blocks = 0): the items have at most 64 rows and a small workgroup each
   const HatAttnItem* verify; // n_verify > 0: verify items that the launch of the streamed chunk items takes along
   int n_verify;
   int heads_inner;           // order of the workgroups of an XCD: each block in all its heads (H a multiple of 8), or each head's blocks in turn
