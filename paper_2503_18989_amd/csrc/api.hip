@@ -623,7 +623,8 @@ static std::vector<int> block_keys(const std::vector<ChunkCut>& cuts, const hat_
 }
 
 // Time in us of the same items staged (attn_chunk_kernel): a workgroup takes `block`, and for each 64 keys `stage` and `wave` for each of its waves with
-// rows.  Fitted like stream_us, as is merge_us.
+// rows.  Fitted like stream_us, as is merge_us.  Over an fp16 cache attn_ring_kernel takes these items; the constants are still those of attn_chunk_kernel there, which takes
+// 8 .. 12 % longer, so that a step near the line may stream where staging has become the faster way.
 static double staged_us(const Shapes& s, int kv_f16, const std::vector<ChunkCut>& cuts, double mbytes) {
   struct Cost { double launch, block, stage, wave, per_mb; };
   static const Cost k[2][2] = {{{0.02, 7.82, 0.768, 0.071, 0.054}, {3.64, 3.86, 0.565, 0.080, 0.150}}, {{0, 9.81, 0.951, 0.124, 0.068}, {0, 9.11, 1.377, 0.105, 0.004}}};

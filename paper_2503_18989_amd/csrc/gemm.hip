@@ -733,6 +733,7 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // against 13.2 and 22.2 against 22.5).
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
+// Neither regime offers tiles 0, 1, 6, 8 and 16: other forms of the same product, which hat_mid_debug_force_gemm takes and the offered tiles are tested against.
 #define HAT_FOR_TILES(X, EPI)          \
   X(0, 256, 256, 2, 4, 1, 32, 4, 0, EPI)  \
   X(1, 192, 128, 2, 4, 1, 32, 4, 0, EPI)  \
