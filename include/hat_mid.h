@@ -328,6 +328,10 @@ hat_status_t hat_mid_debug_plan_narrow(const hat_mid_t* h, int32_t* n_narrow);
  * 2 where items of at most 64 rows each have a workgroup that reads their pages once (fp16 cache). */
 hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int32_t* n_blocks, int32_t cap_blocks, int32_t* waves);
 
+/* Whether the chunk items that the plan stages are read by waves of their own into a ring of 64 KB stages (fp16 cache, items of enough keys);
+ * 0 where it stages none. */
+hat_status_t hat_mid_debug_plan_ring(const hat_mid_t* h, int32_t* ring);
+
 /* Whether the verify items of that plan go along in the launch of its streamed chunk items (a step that is profiled or probed
  * launches them apart all the same). */
 hat_status_t hat_mid_debug_plan_along(const hat_mid_t* h, int32_t* along);

@@ -26,7 +26,8 @@ EXPORTED_SYMBOLS = [
     "hat_mid_kv_export_static",
     "hat_mid_last_step_stats", "hat_mid_set_profiling", "hat_mid_kernel_times", "hat_mid_debug_dump", "hat_mid_debug_force_gemm",
     "hat_mid_debug_gemm_tile_count", "hat_mid_debug_gemm_tile_info", "hat_mid_debug_gemm_plan", "hat_mid_debug_gemm_split",
-    "hat_mid_debug_create_host_only", "hat_mid_debug_plan", "hat_mid_debug_plan_narrow", "hat_mid_debug_plan_blocks", "hat_mid_debug_plan_along",
+    "hat_mid_debug_create_host_only", "hat_mid_debug_plan", "hat_mid_debug_plan_narrow", "hat_mid_debug_plan_blocks", "hat_mid_debug_plan_ring",
+    "hat_mid_debug_plan_along",
     "hat_mid_debug_set_attn_targets", "hat_mid_debug_limit_plan", "hat_mid_debug_set_verify_probe", "hat_mid_debug_peak",
     "hat_sched_create", "hat_sched_destroy", "hat_sched_observe", "hat_sched_mu", "hat_sched_predict",
     "hat_sched_chunk_size", "hat_sched_parallel_draft_steps",
@@ -133,6 +134,8 @@ def load_library():
     lib.hat_mid_debug_plan.argtypes = [vp, C.POINTER(CSegment), i32, pi, pi, i32, pi, pi, pi, pi, pi, pi, i32]
     lib.hat_mid_debug_plan_narrow.restype = i32
     lib.hat_mid_debug_plan_narrow.argtypes = [vp, pi]
+    lib.hat_mid_debug_plan_ring.restype = i32
+    lib.hat_mid_debug_plan_ring.argtypes = [vp, pi]
     lib.hat_mid_debug_plan_along.restype = i32
     lib.hat_mid_debug_plan_along.argtypes = [vp, pi]
     lib.hat_mid_debug_plan_blocks.restype = i32
@@ -435,6 +438,12 @@ class HatPlanner:
         n, w = C.c_int32(), C.c_int32()
         self._check(self.lib.hat_mid_debug_plan_blocks(self._handle, None, C.byref(n), 0, C.byref(w)))
         return w.value
+
+    def staged_ring(self):
+        """Whether the last plan's staged chunk items take the ring kernel (hat_mid_debug_plan_ring)."""
+        n = C.c_int32()
+        self._check(self.lib.hat_mid_debug_plan_ring(self._handle, C.byref(n)))
+        return bool(n.value)
 
     def verify_along(self):
         """Whether the last plan's verify items go along in the launch of its streamed chunk items (hat_mid_debug_plan_along)."""

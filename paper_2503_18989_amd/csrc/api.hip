@@ -242,7 +242,7 @@ struct hat_mid {
   int host_narrow = 0;                     // StepPlan::n_narrow of its last plan
   size_t host_blocks = 0;                  // StepPlan::o_cb
   int host_n_blocks = 0, host_block_waves = 0;   // n_cblocks and block_waves of it
-  bool host_along = false;
+  bool host_along = false, host_ring = false;
   int force_tile[4] = {-1, -1, -1, -1};   // tuning overrides per GEMM class (qkv, o, gate/up, down)
   int force_ksplit[4] = {0, 0, 0, 0};
 
@@ -559,7 +559,7 @@ struct StepPlan {
   size_t o_pos = 0, o_dst = 0, o_tseg = 0, o_toff = 0, o_sstart = 0, o_spt = 0, o_in = 0, o_out = 0, o_pt = 0, o_app = 0;
   size_t o_ci = 0, o_cb = 0, o_vi = 0, o_mi = 0, words = 0;
   int n_citems = 0, n_narrow = 0, n_cblocks = 0, block_waves = 0, n_vitems = 0, n_mitems = 0;
-  bool heads_inner = false, along = false;
+  bool heads_inner = false, along = false, ring = false;
 };
 
 // Time in us of a launch of streamed row blocks with 8 or 4 waves each (the two template forms of attn_verify_kernel), `keys`
@@ -968,6 +968,16 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     std::stable_sort(vitems.begin(), vitems.end(), by_cost);
     const auto narrow0 = std::stable_partition(citems.begin(), citems.end(), [&](const HatAttnItem& a) { return !stream_narrow || a.nq > HAT_NARROW_QROWS; });
     sp->n_narrow = (int)(citems.end() - narrow0);
+    // Staged over an fp16 cache: by the ring kernel where a workgroup has on average as many keys as make up for a stage of 64 KB, of which one
+    // workgroup fits a CU; of the chunk kernel's, with stages of half (head dim 64: a quarter) of that, two do.  750 mixes of 1 .. 32 chunks of 33 .. 512 rows
+    // over 0 .. 4000 keys at 128, 600 at 64, ring against chunk kernel by keys a workgroup: head dim 128 below 64 1.07 times its time, 64 .. 128 level, 128 .. 192 0.88, more 0.9;
+    // head dim 64 below 64 1.33 (at the most 1.69), 64 .. 128 1.25, 128 .. 256 1.09, 256 .. 320 0.97, more 0.94.  With the lines here the choice is
+    // 0.2 and 0.4 % behind the faster of the two, always the ring kernel 0.7 and 7.8 %.  8 x 128 rows of new prompts at 64 heads of 64: chunk kernel 14.1 us, ring 18.8.
+    if (f16 && sp->block_waves == 0 && narrow0 != citems.begin()) {
+      double keys = 0;
+      for (auto it = citems.begin(); it != narrow0; ++it) keys += it->kv_end - it->kv_begin;
+      sp->ring = keys >= (s.hd == 128 ? 96.0 : 256.0) * (narrow0 - citems.begin());
+    }
     if (sp->block_waves > 2) {
       for (auto it = citems.begin(); it != narrow0; ++it)
         for (int r0 = (it->nq - 1) / HAT_NARROW_QROWS * HAT_NARROW_QROWS; r0 >= 0; r0 -= HAT_NARROW_QROWS) {   // the block with the most keys first
@@ -1105,7 +1115,7 @@ static hat_status_t enqueue_step(hat_mid_t* h, const StepPlan& sp, const int32_t
     a.H = s.H; a.hd = s.hd; a.d = s.d; a.n_pages = c.n_pages; a.kv_f16 = c.kv_dtype == HAT_KV_F16;
     if (sp.n_citems > 0) {
       a.items = (const HatAttnItem*)(D + o_ci); a.n_items = sp.n_citems; a.n_narrow = sp.n_narrow;
-      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves; a.heads_inner = sp.heads_inner;
+      a.blocks = (const HatAttnItem*)(D + sp.o_cb); a.n_blocks = sp.n_cblocks; a.block_waves = sp.block_waves; a.heads_inner = sp.heads_inner; a.ring = sp.ring;
       if (along) {
         a.verify = (const HatAttnItem*)(D + o_vi); a.n_verify = sp.n_vitems;
       }
@@ -1394,7 +1404,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
   if (n_verify_items) *n_verify_items = 0;
   if (n_merge_items) *n_merge_items = 0;
   h->host_narrow = h->host_n_blocks = h->host_block_waves = 0;
-  h->host_along = false;
+  h->host_along = h->host_ring = false;
   if (n_segs == 0) return HAT_OK;
   try {
     StepPlan sp;
@@ -1407,6 +1417,7 @@ hat_status_t hat_mid_debug_plan(hat_mid_t* h, const hat_mid_segment_t* segs, int
     h->host_n_blocks = sp.n_cblocks;
     h->host_block_waves = sp.block_waves;
     h->host_along = sp.along;
+    h->host_ring = sp.ring;
     if (sp.T > cap_rows || std::max(sp.n_citems, std::max(sp.n_vitems, sp.n_mitems)) > cap_items)
       return fail(h, HAT_EINVAL, "output arrays too small for %d rows / %d, %d, %d items (the step has been planned)", sp.T,
                   sp.n_citems, sp.n_vitems, sp.n_mitems);
@@ -1442,6 +1453,11 @@ hat_status_t hat_mid_debug_plan_blocks(const hat_mid_t* h, int32_t* blocks, int3
   return HAT_OK;
 }
 
+hat_status_t hat_mid_debug_plan_ring(const hat_mid_t* h, int32_t* ring) {
+  if (!h || !h->host_only || !ring) return HAT_EINVAL;
+  *ring = h->host_ring;
+  return HAT_OK;
+}
 hat_status_t hat_mid_debug_plan_along(const hat_mid_t* h, int32_t* along) {
   if (!h || !h->host_only || !along) return HAT_EINVAL;
   *along = h->host_along;

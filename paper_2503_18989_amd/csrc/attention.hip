@@ -4,8 +4,8 @@
 //             chunked prefill, Sec. 3.3): many query rows, matrix-core bound.
 //             One workgroup = 256 query rows (8 waves x 32) of one head; K/V tiles
 //             are staged in LDS and shared by the eight waves: 64 keys at a time by
-//             these waves themselves (bf16 cache), or by four more that only load
-//             (fp16 cache).
+//             these waves themselves, or (fp16 cache, all but short items) 64 KB at a time by four
+//             more that only load.
 //   verify -- the draft sequence of a device in the decode phase verified in one
 //             step (Sec. 3.4), or a tree of candidates (Sec. 2.2) given as one
 //             visibility byte per row: at most 8 query rows against a long cache, HBM
@@ -503,7 +503,7 @@ __device__ __forceinline__ void probs_to_f16(const f32x16& pv, f16x8& p0, f16x8&
   }
 }
 
-template <int HD>
+template <int HD, bool KVF16>
 __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlanDev p, HatAttn a) {
   constexpr int NS = HD / 16;
   constexpr int NC = HD / 32;
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
   };
   auto lstore = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) *(u32x4*)(&lds[buf][(i * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<false>(regs[i]);
+    for (int i = 0; i < LPT; ++i) *(u32x4*)(&lds[buf][(i * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<KVF16>(regs[i]);
   };
   // general stage: causal masks, ragged ends, waves that skip a 32-key half
   auto compute = [&](int st, int buf) {
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
         if constexpr (m < NS) {                                  // scores of A | widen next stage into LDS
           sA = __builtin_amdgcn_mfma_f32_32x32x16_f16(op[cur][j], qreg[m], m == 0 ? zero16 : sA, 0, 0, 0);
           if constexpr (m < LPT) {
-            if (do_store) *(u32x4*)(&lds[buf ^ 1][(m * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<false>(regs[m]);
+            if (do_store) *(u32x4*)(&lds[buf ^ 1][(m * NTH + threadIdx.x) * 16]) = kv_to_f16_bits<KVF16>(regs[m]);
           }
         } else if constexpr (m < 2 * NS) {                       // scores of B | loads of stage st+2, softmax of A
           constexpr int q = m - NS;
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(HAT_CHUNK_QROWS * 2) void attn_chunk_kernel(HatPlan
 // what LDS holds: the next stage is on its way while one is read.  A wave reads each operand half a
 // product ahead.  8 x 512 rows over 4096 keys (13B shape) 428 us with the chunk kernel, 386 with
 // this one (two cards; 404 on a third), 1 x 1024 over 3072 127 -> 113, 1 x 256 over 1024 (7B) 21.5 -> 19.3.
-// A bf16 cache stays with the chunk kernel: with its widening in the loader waves 8 x 512 rows
+// Items of few keys do not fill a stage and stay with the chunk kernel (the plan says where).  A bf16 cache does too: with its widening in the loader waves 8 x 512 rows
 // took 435 us instead of 440, but ten chunks of 128 .. 512 rows 199 instead of 179.
 //
 // With two blocks of 32 rows (RB = 2) it takes chunks of at most 64 rows, an item each (the plan says
@@ -1147,10 +1147,13 @@ hipError_t hat_launch_attn_chunk(const HatPlanDev& p, const HatAttn& a, hipStrea
   }
   if (a.n_blocks == 0 && wide > 0) {
     dim3 grid(wide, a.H);
-    if (a.hd == 128 && a.kv_f16) launch_ring<128, 8>(p, a, grid, st);
-    else if (a.hd == 128) attn_chunk_kernel<128><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
-    else if (a.hd == 64 && a.kv_f16) launch_ring<64, 8>(p, a, grid, st);
-    else if (a.hd == 64) attn_chunk_kernel<64><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    if (a.ring && !a.kv_f16) return hipErrorInvalidValue;
+    if (a.hd == 128 && a.ring) launch_ring<128, 8>(p, a, grid, st);
+    else if (a.hd == 128 && a.kv_f16) attn_chunk_kernel<128, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 128) attn_chunk_kernel<128, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 64 && a.ring) launch_ring<64, 8>(p, a, grid, st);
+    else if (a.hd == 64 && a.kv_f16) attn_chunk_kernel<64, true><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
+    else if (a.hd == 64) attn_chunk_kernel<64, false><<<grid, HAT_CHUNK_QROWS * 2, 0, st>>>(p, a);
     else return hipErrorInvalidValue;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

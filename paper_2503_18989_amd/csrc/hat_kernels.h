@@ -170,6 +170,7 @@ struct HatAttn {
   int n_narrow;              // chunk items: the last n_narrow of them have at most HAT_NARROW_QROWS rows
   const HatAttnItem* blocks; // n_blocks > 0: the other chunk items stream the cache too, as these items of at most HAT_NARROW_QROWS rows
   int n_blocks, block_waves; // four or eight waves to a block; two (n_blocks = 0): the items have at most 64 rows and a small workgroup each
+  int ring;                  // the staged items: by the ring kernel (fp16 cache)
   const HatAttnItem* verify; // n_verify > 0: verify items that the launch of the streamed chunk items takes along
   int n_verify;
   int heads_inner;           // order of the workgroups of an XCD: each block in all its heads (H a multiple of 8), or each head's blocks in turn
