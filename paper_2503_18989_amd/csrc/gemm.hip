@@ -792,10 +792,15 @@ constexpr int kSmallT = 384;
 // Weights for the choice like kEff, searched on all tiles, one to eight pieces of K and the norms at 30 batch sizes of 33 .. 1100 rows and seven widths (1024 x 2816 .. 8192 x 28672): the choices
 // lose 0.24 % of a layer's products on average; searched on two thirds of the sizes 0.23 .. 0.30 % there and 0.30 .. 0.45 % on the others.  The constants before, with these
 // tiles, lost 2 .. 9 % (192 rows 8.1, 420 8.8, 256 6.3, 1024 3.0).
-constexpr int kMidT = 1100;
-constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.360f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
-struct MidCosts { double round, fraction, shared, part, tbs, stream, resid; };
-constexpr MidCosts kMid = {7.79, 0.192, 0.0730, 0.460, 6.01, 13.79, 0.506};
+// 128 x 64 without loader waves (10) starts and ends sooner than its loader form (7), which takes less for a k-tile whose panel of W nobody else reads: a round of its own.  It and the constants of up
+// to kFewT rows were searched again with up to 14 pieces of K at eleven widths from 256 x 704 to 7168 x 18944, on two cards: the choices are 1.1 % behind the best of O, down and the products that do not stream up to 64 rows,
+// 0.2 .. 0.8 % from there to 384 and 1.2 % beyond (with 10 offered at 257 .. 384 rows only and one set of constants 2.3, 0.3 .. 1.3 and 2.3 %).  The products and norms of a
+// layer in us: 64 rows of 3072 columns 93.5 -> 89.0, 53 of 4096 120.6 -> 114.8, 512 of 256 46.1 -> 44.4; at 22 other sizes of 18 widths nowhere more than 1.2 % slower.
+constexpr int kMidT = 1100, kFewT = 64;
+constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.350f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
+constexpr float tau(int tile, bool few) { return !few ? kTau[tile] : tile == 10 ? 0.42f : tile == 11 ? 0.31f : tile == 18 ? 0.353f : kTau[tile]; }
+struct MidCosts { double round, round_plain, fraction, shared, part, part_few, tbs, stream, resid; };
+constexpr MidCosts kMid = {7.79, 7.2, 0.192, 0.0730, 0.460, 0.37, 6.01, 13.79, 0.506};
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id]},
     HAT_FOR_TILES(HAT_INFO, 0)
@@ -957,13 +962,11 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   double best_cost = 1e300, tail_cost = 1e300;
   HatGemmPlan tail{0, 1};
   const int KT = g.K / 64;
-  const bool large = g.T > kMidT;
+  const bool large = g.T > kMidT, few = g.T <= kFewT;
   for (int c = 0; c < kNumLdsTiles; ++c) {
     const TileInfo& q = kTiles[c];
-    if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128)) continue;   // (tiles that are never the best there)
-    // 128 x 64 without loader waves (10) is offered where its panels of W are read by five and more token tiles, which then find them in L2: 300 rows of 1024 .. 3072 columns 2 .. 5 % of
-    // a layer's products ahead of the others; up to 256 rows its loader form (7) and 64 x 64 are.
-    if (!large && c == 10 && g.T <= 256) continue;
+    // (0: tiles that are never the best there; beyond kSmallT rows nor are 64-row token tiles with loader waves)
+    if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128 && c != 10)) continue;
     // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
     // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %); O, gate/up and down of models from 4096 columns on take it there, narrower ones where
     // it is predicted ahead (gate/up of 150 rows at 2048 columns 27 us, 96 x 128 21; at 4096 50.5, 96 x 256 49, which pads 256 rows).  Above 256 rows a third
@@ -994,8 +997,8 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
         cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                             // tie-break below the HBM floor
       } else {
         const double r = (1 - kMid.fraction) * rounds + kMid.fraction * std::max(1.0, blocks / 256.0);
-        double us = r * (kt * kTau[c] * (nT > 1 ? 1 + kMid.shared : 1) + kMid.round);
-        if (g.epilogue == HAT_EPI_RESID) us += 1e-3 * rows * (ks > 1 ? ks * kMid.part : kMid.resid);
+        double us = r * (kt * tau(c, few) * (nT > 1 ? 1 + kMid.shared : 1) + (c == 10 ? kMid.round_plain : kMid.round));
+        if (g.epilogue == HAT_EPI_RESID) us += 1e-3 * rows * (ks > 1 ? ks * (few ? kMid.part_few : kMid.part) : kMid.resid);
         cost = std::max(us, 2e-6 * g.Nw * g.K / kMid.tbs + kMid.stream) + 0.02 * us;
       }
       if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; }
