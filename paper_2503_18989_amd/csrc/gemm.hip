@@ -778,15 +778,17 @@ constexpr int kNumTiles = 28;
 
 struct TileInfo { int bf, bt, waves, bkt, nstage; float eff; };
 // How fast a tile's k-loop is taken to be where it is not load-bound, against the matrix peak, and with it the constants of the large regime below: weights for the
-// choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: not offered; the loops of 128 x 256, 128 x 128, 96 x 128 and 128 x 160 were the multiplying waves' own then).  Measured with all tiles, K splits and
+// choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: not offered).  All loops were the multiplying waves' own
+// then, with 128 x 64 in the form that is tile 10 now.  Measured with those tiles, K splits and
 // split tails of the four products, norms included, at 36 batch sizes of 390 .. 4096 rows and seven widths (1024 x 2816 .. 8192 x 28672; the search had seen 9 sizes up to 2048
-// rows of three of them): the four choices of a layer lose 0.24 % of it on average at 20 of the sizes and 0.31 % at the other 16, where the constants of the 32x32x16
-// loops lost 1.78 and 1.85 %.  Of 1004 choices 303 changed with them, 256 to a product more than 1 % faster and 25 to one more than 1 % slower: gate/up of 8192 columns
-// at 1400 and 1664 rows 1056 -> 1117 and 1228 -> 1314 us, of 4096 at 3840 561 -> 578, QKV of 5120 at 2700 357 -> 374, the others less than 8 us.  192 x 256
-// stands at .535, not at the .543 of the search: with that the losses are 0.31 and 0.44 %.  Searched again on the 20 sizes of all widths, with a cost of its own for
-// the rotating epilogue, the constants come to 0.20 .. 0.23 % there and 0.32 .. 0.38 % at the other 16: what is left is the model's form (it counts whole
+// rows of three of them): the four choices of a layer lost 0.24 % of it on average at 20 of the sizes and 0.31 % at the other 16.  Searched again on the 20 sizes of all widths, with a cost of its own for
+// the rotating epilogue, the constants came to 0.20 .. 0.23 % there and 0.32 .. 0.38 % at the other 16: what is left is the model's form (it counts whole
 // rounds of workgroups, where large products go by their padded work).
-constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.527f, 0.570f, 0.f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
+// Of the tiles with loader waves four are offered here.  Over 20 sizes of 1101 .. 4096 rows and eight widths they take, of the time of those earlier loops, 128 x 256 0.90 .. 0.99, 128 x 128 0.89 .. 1.02,
+// 96 x 128 0.90 .. 1.00 and 128 x 160 0.89 .. 1.04 (the higher ones at 256 and 1024 columns), so their weights are on the low side: the present choices lose 0.4 .. 1.4 % of a
+// layer at 1024 .. 5120 and 8192 columns and 2.6 % at 6144.  128 x 64 with loader waves (7) takes 0.98 .. 1.09 times as long
+// as without (10), 1.03 .. 1.07 for O and down of 256 and 1024 columns, which take this tile.
+constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.527f, 0.570f, 0.f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
 constexpr int kSmallT = 384;
 // Up to kMidT rows: us that a k-tile of 64 is taken to cost each tile (0: not offered), and what else the model counts (hat_gemm_plan).
 // Weights for the choice like kEff, searched on all tiles, one to eight pieces of K and the norms at 30 batch sizes of 33 .. 1100 rows and seven widths (1024 x 2816 .. 8192 x 28672): the choices
