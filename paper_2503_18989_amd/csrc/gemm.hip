@@ -970,13 +970,12 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     // (0: tiles that are never the best there; beyond kSmallT rows nor are 64-row token tiles with loader waves)
     if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128 && c != 10)) continue;
     // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
-    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %); O, gate/up and down of models from 4096 columns on take it there, narrower ones where
-    // it is predicted ahead (gate/up of 150 rows at 2048 columns 27 us, 96 x 128 21; at 4096 50.5, 96 x 256 49, which pads 256 rows).  Above 256 rows a third
+    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %) and competes with the others there: most O, gate/up and down products from 4096 columns on take it (gate/up of the
+    // 7B shape at 150 rows 46 us, 96 x 256, which pads 256 rows, 47), but not O of 4096 columns (64 x 256: 17.9 -> 17.2) nor gate/up of 7168, where its 296 workgroups go round twice (157 us, 192 x 256 142).  Above 256 rows a third
     // 128-row token tile or a second 256-row one is as empty: the four products and the norms of a layer at 257 and 320 rows 219 -> 193 and 229 -> 202 us (7B shape),
     // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there.  384 rows are three whole 128-row
     // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py).
-    const bool just160 = g.T > 128 && g.T <= 160, tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && just160;
-    if (just160 && c != 23 && std::min(g.Nout, g.K) >= 4096 && (g.epilogue == HAT_EPI_SWIGLU || g.epilogue == HAT_EPI_RESID)) continue;
+    const bool tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && g.T > 128 && g.T <= 160;
     if (g.T <= kSmallT && (q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
     const int max_split = (g.epilogue == HAT_EPI_RESID && g.part) ? 16 : 1;

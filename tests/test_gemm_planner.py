@@ -84,7 +84,7 @@ def test_small_batches_keep_power_of_two_token_tiles_and_large_ones_use_the_big_
             bt = tile_info(lib, tile)[1][1]
             # the one exception: 129 .. 160 rows may take the 160-row token tile (one token tile instead of two)
             assert bt & (bt - 1) == 0 or (bt == 160 and 128 < T <= 160), "%s at T=%d took a %d-row token tile" % (name, T, bt)
-    for name in ("o7", "gu7", "down7", "o13", "gu13", "down13"):     # 30 devices x 5 draft rows: the verify-heavy batch
+    for name in ("gu7", "down7", "o13", "gu13", "down13"):     # 30 devices x 5 draft rows: the verify-heavy batch (O of the 7B shape measured faster with 64 x 256)
         Nw, Nout, K, epi = SHAPES[name]
         tile, _ = plan(lib, 150, Nw, Nout, K, epi, 4096)
         assert tile_info(lib, tile)[1][:2] == (128, 160), name
@@ -213,3 +213,12 @@ def test_large_batches_do_not_take_64_token_rows_with_loader_waves(lib):
             taken |= {(name, plan(lib, T, (N + 255) // 256 * 256, o, K, e, 4096)[0]) for T in range(1101, 4097, 7)}
     assert all(tile not in (7, 11, 18) for _, tile in taken)
     assert ("tiny", 10) in taken and ("1k", 10) in taken
+
+
+@pytest.mark.parametrize("T", [129, 147, 160])
+def test_no_tile_is_prescribed_for_129_to_160_rows(lib, T):
+    # gate/up of 7168 columns: 128 x 160 makes 296 workgroups, a second round for 40 of them (157 us); tiles that go round once take 142
+    N, f = 37888, 18944
+    bf, bt = tile_info(lib, plan(lib, T, N, f, 7168, 1, 4096)[0])[1][:2]
+    assert -(-N // bf) * -(-T // bt) <= 256, (bf, bt)
+    assert tile_info(lib, plan(lib, T, 4096, 4096, 4096, 2, 4096)[0])[1][:2] == (64, 256)      # O of the 7B shape with its norm, 129 .. 160 rows: 0.6 .. 0.9 us ahead of 128 x 160
