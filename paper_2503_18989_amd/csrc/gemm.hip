@@ -970,8 +970,9 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     // (0: tiles that are never the best there; beyond kSmallT rows nor are 64-row token tiles with loader waves)
     if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128 && c != 10)) continue;
     // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
-    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %) and competes with the others there: most O, gate/up and down products from 4096 columns on take it (gate/up of the
-    // 7B shape at 150 rows 46 us, 96 x 256, which pads 256 rows, 47), but not O of 4096 columns (64 x 256: 17.9 -> 17.2) nor gate/up of 7168, where its 296 workgroups go round twice (157 us, 192 x 256 142).  Above 256 rows a third
+    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %) and competes with the others there: most O, gate/up and down products from 4096 columns on take it (gate/up of 150 rows, in
+    // steps: 13B shape 64.6 us, next best 69.0; 7B shape 50.3, where 96 x 256, which pads 256 rows, would take 47.9), but not O of 4096 columns (64 x 256: 17.9 -> 17.2) nor gate/up of 7168, where
+    // its 296 workgroups go round twice (157 us, 192 x 256 142).  Above 256 rows a third
     // 128-row token tile or a second 256-row one is as empty: the four products and the norms of a layer at 257 and 320 rows 219 -> 193 and 229 -> 202 us (7B shape),
     // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there.  384 rows are three whole 128-row
     // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py).
