@@ -974,10 +974,10 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
     // steps: 13B shape 64.6 us, next best 69.0; 7B shape 50.3, where 96 x 256, which pads 256 rows, would take 47.9), but not O of 4096 columns (64 x 256: 17.9 -> 17.2) nor gate/up of 7168, where
     // its 296 workgroups go round twice (157 us, 192 x 256 142).  Above 256 rows a third
     // 128-row token tile or a second 256-row one is as empty: the four products and the norms of a layer at 257 and 320 rows 219 -> 193 and 229 -> 202 us (7B shape),
-    // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there.  384 rows are three whole 128-row
-    // tiles and keep the tiles up to 256 rows by definition (test_gemm_planner.py).
-    const bool tall = g.T > 256 ? g.T % 128 != 0 : c == 23 && g.T > 128 && g.T <= 160;
-    if (g.T <= kSmallT && (q.bt & (q.bt - 1)) != 0 && !tall) continue;
+    // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there; at 384 rows, three whole 128-row tiles but also two of 192, 309 -> 292 (13B; gate/up 117.5 -> 103.0) and
+    // 860 -> 751 (8192 columns).
+    const bool tall = g.T > 256 || (c == 23 && g.T > 128 && g.T <= 160);
+    if ((q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
     const int max_split = (g.epilogue == HAT_EPI_RESID && g.part) ? 16 : 1;
     for (int ks = 1; ks <= max_split; ++ks) {
