@@ -25,7 +25,8 @@ EXPORTED_SYMBOLS = [
     "hat_mid_destroy", "hat_mid_last_error", "hat_mid_kv_query", "hat_mid_kv_compact", "hat_mid_kv_import", "hat_mid_kv_export",
     "hat_mid_kv_export_static",
     "hat_mid_last_step_stats", "hat_mid_set_profiling", "hat_mid_kernel_times", "hat_mid_debug_dump", "hat_mid_debug_force_gemm",
-    "hat_mid_debug_gemm_tile_count", "hat_mid_debug_gemm_tile_info", "hat_mid_debug_gemm_plan", "hat_mid_debug_gemm_split",
+    "hat_mid_debug_gemm_tile_count", "hat_mid_debug_gemm_tile_info", "hat_mid_debug_gemm_tile_resources",
+    "hat_mid_debug_gemm_plan", "hat_mid_debug_gemm_split",
     "hat_mid_debug_create_host_only", "hat_mid_debug_plan", "hat_mid_debug_plan_narrow", "hat_mid_debug_plan_blocks", "hat_mid_debug_plan_ring",
     "hat_mid_debug_plan_along",
     "hat_mid_debug_set_attn_targets", "hat_mid_debug_limit_plan", "hat_mid_debug_set_verify_probe", "hat_mid_debug_peak",
@@ -115,6 +116,8 @@ def load_library():
     lib.hat_mid_debug_gemm_tile_count.argtypes = []
     lib.hat_mid_debug_gemm_tile_info.restype = i32
     lib.hat_mid_debug_gemm_tile_info.argtypes = [i32] + [C.POINTER(i32)] * 5
+    lib.hat_mid_debug_gemm_tile_resources.restype = i32
+    lib.hat_mid_debug_gemm_tile_resources.argtypes = [i32] + [C.POINTER(i32)] * 2
     lib.hat_mid_debug_gemm_plan.restype = i32
     lib.hat_mid_debug_gemm_plan.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     lib.hat_mid_debug_gemm_split.restype = i32

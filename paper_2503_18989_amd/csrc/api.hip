@@ -1484,6 +1484,13 @@ hat_status_t hat_mid_debug_gemm_tile_info(int32_t tile, int32_t* features, int32
   if (stages) *stages = ns;
   return HAT_OK;
 }
+hat_status_t hat_mid_debug_gemm_tile_resources(int32_t tile, int32_t* loader_waves, int32_t* lds_bytes) {
+  int nl, lds;
+  if (!hat_gemm_tile_resources(tile, &nl, &lds)) return HAT_EINVAL;
+  if (loader_waves) *loader_waves = nl;
+  if (lds_bytes) *lds_bytes = lds;
+  return HAT_OK;
+}
 
 hat_status_t hat_mid_debug_set_attn_targets(hat_mid_t* h, int32_t chunk_target, int32_t verify_target) {
   if (!h || chunk_target < 0 || verify_target < 0) return HAT_EINVAL;

@@ -24,7 +24,8 @@
 // L2, waits behind W, which comes from HBM.  Loads alone of the 96 x 256 tile, W and X of each k-tile in turn: 46 us; W of two k-tiles, then X of the two:
 // 36.  So W is loaded G k-tiles at a time, into a ring of its own that is twice that long, and X in a shorter one; W that one token tile alone reads
 // is loaded non-temporally (W alone 31.7 -> 27.5 us).  Gate/up of 256 rows 61.2 -> 51.5 us, of 77 44.1 -> 39, QKV 43 -> 38, O 20.3 -> 19.1, down 36.9 -> 34.8.
-// The MFMA waves and the loader waves share the registers of a SIMD three ways (168 each), which the accumulators of the 192- and 256-row tiles do not leave.
+// The MFMA waves and the loader waves share the registers of a SIMD three ways (168 each).  The accumulators of tiles of 192 and 256 features with 160 and more token rows, and of 192 x 128
+// with the halves of K on different waves, do not leave that many.  192 x 128 on 2 x 4 waves and 256 x 128 would (117 and 137 registers, 144 and 160 KB of LDS); they have not been measured.
 // LDS reads are issued from inline asm so that the compiler does not serialise
 // them behind the outstanding direct-to-LDS loads; the waits are explicit:
 // vmcnt for "my loads of this k-tile have landed", a barrier for "everyone's
@@ -157,6 +158,9 @@ struct Tile {
   static_assert(KS >= 1 && BKT % (32 * WK) == 0 && (WK == 1 || WK == 2), "whole k-steps");
   static_assert(G > 0 || (NSTAGE >= 2 && NSTAGE <= 4 && (NSTAGE - 1) * LPW <= 63), "wait_pending covers up to 3 pending tiles; vmcnt is 6 bits");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
+  // registers of a lane: accumulators, two sets of operands, and what addresses and counters take
+  static constexpr int REGS = MI * NJ * 4 + 2 * (MI + NJ) * 4 + 32;
+  static_assert(REGS <= 512 / ((NW + NL + 3) / 4), "the waves of a SIMD share its registers");
   static_assert(G == 0 || (NSTAGE >= 2 && NSTAGE <= G + 1 && (NSTAGE - 2) * PT + G * PF <= 63), "a tile of X is never before its tile of W");
   static_assert(WK == 1 || WF * WT * MI * NJ * 1024 <= LDS_BYTES, "the two halves of K meet in the ring");
 };
@@ -733,7 +737,8 @@ __global__ __launch_bounds__(512, NP* NT <= 1 ? 4 : 2) void gemm_stream_kernel(H
 // against 13.2 and 22.2 against 22.5).
 // Stages of 32 k let a wave hold both register sets and still have four stages; fewer, longer ones measured level (128-row
 // tiles) or behind (256 x 256 at 4096 rows: 900 us with 4 x 32, 967 with 2 x 64, 919 with 5 x 32).
-// Neither regime offers tiles 0, 1, 6, 8 and 16: other forms of the same product, which hat_mid_debug_force_gemm takes and the offered tiles are tested against.
+// Neither regime offers tiles 0, 1, 6, 8 and 16.  1 is the product whose rotation and append are a launch of their own, which the others are compared with; the others are taken by
+// their number only (hat_mid_debug_force_gemm).
 #define HAT_FOR_TILES(X, EPI)          \
   X(0, 256, 256, 2, 4, 1, 32, 4, 0, EPI)  \
   X(1, 192, 128, 2, 4, 1, 32, 4, 0, EPI)  \
@@ -776,7 +781,7 @@ constexpr bool stream_built(int id, int epi) {
 constexpr int kStream32 = 24, kStream64 = 25, kStream96 = 26, kStream64x32 = 27;
 constexpr int kNumTiles = 28;
 
-struct TileInfo { int bf, bt, waves, bkt, nstage; float eff; };
+struct TileInfo { int bf, bt, waves, bkt, nstage; float eff; int loaders, lds; };   // (waves that multiply, waves that load)
 // How fast a tile's k-loop is taken to be where it is not load-bound, against the matrix peak, and with it the constants of the large regime below: weights for the
 // choice, found by random search for the least loss against the best tile and K split and not fitted to the times (0: not offered).  All loops were the multiplying waves' own
 // then, with 128 x 64 in the form that is tile 10 now.  Measured with those tiles, K splits and
@@ -804,11 +809,11 @@ constexpr float tau(int tile, bool few) { return !few ? kTau[tile] : tile == 10 
 struct MidCosts { double round, round_plain, fraction, shared, part, part_few, tbs, stream, resid; };
 constexpr MidCosts kMid = {7.79, 7.2, 0.192, 0.0730, 0.460, 0.37, 6.01, 13.79, 0.506};
 constexpr TileInfo kTiles[kNumTiles] = {
-#define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id]},
+#define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id], Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::NL, Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::LDS_BYTES},
     HAT_FOR_TILES(HAT_INFO, 0)
 #undef HAT_INFO
 // "stages" of a streaming tile: its register ring counted in 32-k pieces
-#define HAT_INFO(id, np, nt, epi) {32 * (np), 32 * (nt), 8, 32, StreamDepth<np, nt>::value / 2, 0.f},
+#define HAT_INFO(id, np, nt, epi) {32 * (np), 32 * (nt), 8, 32, StreamDepth<np, nt>::value / 2, 0.f, 0, 8 * ((np) * (nt) < 2 ? 1 : 2) * 4096},
     HAT_FOR_STREAM(HAT_INFO, 0)
 #undef HAT_INFO
 };
@@ -866,6 +871,13 @@ bool hat_gemm_tile_info(int id, int* bf, int* bt, int* waves, int* bkt, int* nst
   if (waves) *waves = q.waves;
   if (bkt) *bkt = q.bkt;
   if (nstage) *nstage = q.nstage;
+  return true;
+}
+
+bool hat_gemm_tile_resources(int id, int* loaders, int* lds) {
+  if (id < 0 || id >= kNumTiles) return false;
+  if (loaders) *loaders = kTiles[id].loaders;
+  if (lds) *lds = kTiles[id].lds;
   return true;
 }
 

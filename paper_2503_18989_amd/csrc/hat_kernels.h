@@ -60,8 +60,10 @@ struct HatGemmPlan {
 HatGemmPlan hat_gemm_plan(const HatGemm& g);
 hipError_t hat_launch_gemm(const HatGemm& g, const HatGemmPlan& p, hipStream_t st);
 int hat_gemm_tile_count();
-// shape of tile `id` (features, tokens, waves, k per stage, stages); false if out of range
+// shape of tile `id` (features, tokens, waves that multiply, k per stage, stages -- of X, with loader waves); false if out of range
 bool hat_gemm_tile_info(int id, int* bf, int* bt, int* waves, int* bkt, int* nstage);
+// its loader waves and the bytes of LDS of a workgroup; false if out of range
+bool hat_gemm_tile_resources(int id, int* loaders, int* lds);
 hipError_t hat_gemm_init();  // one-time function attributes (dynamic LDS size), those of hat_attn_init among them
 
 // ---- weight re-tiling (create time) -----------------------------------------

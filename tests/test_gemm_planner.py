@@ -69,10 +69,19 @@ def test_tile_table_fits_the_hardware(lib):
         assert rc == 0
         assert bf % 32 == 0 and bt % 32 == 0 and bk % 16 == 0 and 2 <= ns <= 4
         assert waves in (2, 4, 8)
-        assert ns * (bf + bt) * bk * 2 <= 160 * 1024, "ring of tile %d exceeds the LDS of a CU" % t
-        # accumulators (fp32, 64 lanes per wave) + operands must fit the register file of the waves' SIMDs
+        loaders, lds = C.c_int32(-1), C.c_int32(-1)
+        assert lib.hat_mid_debug_gemm_tile_resources(t, C.byref(loaders), C.byref(lds)) == 0
+        streaming = t >= n - 4
+        if loaders.value:   # a ring of W that is longer than that of X
+            assert not streaming and loaders.value == bk // 16 and lds.value > ns * (bf + bt) * bk * 2
+        elif not streaming:
+            assert lds.value == ns * (bf + bt) * bk * 2
+        assert 0 < lds.value <= 160 * 1024, "rings of tile %d exceed the LDS of a CU" % t
+        # accumulators (fp32, 64 lanes per wave) + operands must fit the register file of the waves' SIMDs, which the loader waves share
         acc_regs = bf * bt // (waves * 64)
-        assert acc_regs <= (256 if waves == 8 else 512) - 56, "tile %d: %d accumulator registers per lane" % (t, acc_regs)
+        simd_waves = -(-(waves + loaders.value) // 4)
+        assert acc_regs <= 512 // simd_waves - 56, "tile %d: %d accumulator registers per lane" % (t, acc_regs)
+    assert lib.hat_mid_debug_gemm_tile_resources(n, None, None) == -1 and lib.hat_mid_debug_gemm_tile_resources(0, None, None) == 0
     assert tile_info(lib, n)[0] == -1 and tile_info(lib, -1)[0] == -1
     assert lib.hat_mid_debug_gemm_tile_info(0, None, None, None, None, None) == 0
 
