@@ -19,7 +19,7 @@ def test_more_than_one_gpu_is_refused_with_a_message():
 
 def test_recorded_traffic_readers_parse_the_committed_summaries():
     # kernel names in the legs summary contain a space ("<128, false>"): the reader must not split on it
-    for k in ("attn_verify_kernel<128, false>", "attn_chunk_kernel<128, false>", "attn_chunk_kernel<128, true>"):
+    for k in ("attn_verify_kernel<128, false>", "attn_chunk_kernel<128, false>", "attn_ring_kernel<128, 8>"):
         v = bench.recorded_leg_traffic(k)
         assert v is not None and v > 1e8, k
     assert bench.recorded_leg_traffic("no_such_kernel") is None
