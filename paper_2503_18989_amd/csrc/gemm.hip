@@ -799,16 +799,15 @@ constexpr int kSmallT = 384;
 // Weights for the choice like kEff, searched on all tiles, one to eight pieces of K and the norms at 30 batch sizes of 33 .. 1100 rows and seven widths (1024 x 2816 .. 8192 x 28672): the choices
 // lose 0.24 % of a layer's products on average; searched on two thirds of the sizes 0.23 .. 0.30 % there and 0.30 .. 0.45 % on the others.  The constants before, with these
 // tiles, lost 2 .. 9 % (192 rows 8.1, 420 8.8, 256 6.3, 1024 3.0).
-// 128 x 64 without loader waves (10) starts and ends sooner than its loader form (7), which takes less for a k-tile whose panel of W nobody else reads: a round of its own, and a dearer k-tile up to
-// kFewT rows.  There W comes from HBM with little else to do, and a piece of K costs the norm behind it more: constants of their own for O and down of so few rows, each forced by itself in steps of
-// 6 GB of weights (ten widths, 33 .. 64 rows; all four products forced in a few layers, W stays partly in the 256 MB cache and looks up to 12 % faster).  Their choices are 0.9 % behind the best product and norm
-// (1.6 % without tile 10).  From 65 rows on the choices are 0.2 .. 0.8 % behind up to 384 and 1.2 % beyond at eleven widths from 256 x 704 to 7168 x 18944 (with tile 10 at 257 .. 384 rows only 0.3 .. 1.3 and 2.3).
-// Products and norms of a layer in us: 49 rows of 4096 columns 119.1 -> 117.8 (down 24.4 -> 22.2, the norms 13.6 -> 14.5), 512 of 256 columns 46.1 -> 44.4.
+// 128 x 64 without loader waves (10) starts and ends sooner than its loader form (7), which takes less for a k-tile whose panel of W nobody else reads: a round of its own.  It and the constants of up
+// to kFewT rows were searched again with up to 14 pieces of K at eleven widths from 256 x 704 to 7168 x 18944, on two cards: the choices are 1.1 % behind the best of O, down and the products that do not stream up to 64 rows,
+// 0.2 .. 0.8 % from there to 384 and 1.2 % beyond (with 10 offered at 257 .. 384 rows only and one set of constants 2.3, 0.3 .. 1.3 and 2.3 %).  The products and norms of a
+// layer in us: 64 rows of 3072 columns 93.5 -> 89.0, 53 of 4096 120.6 -> 114.8, 512 of 256 46.1 -> 44.4; at 22 other sizes of 18 widths nowhere more than 1.2 % slower.
 constexpr int kMidT = 1100, kFewT = 64;
-constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.360f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
-constexpr float tau(int tile, bool few) { return !few ? kTau[tile] : tile == 10 ? 0.42f : tile == 11 ? 0.28f : kTau[tile]; }
+constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.350f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
+constexpr float tau(int tile, bool few) { return !few ? kTau[tile] : tile == 10 ? 0.42f : tile == 11 ? 0.31f : tile == 18 ? 0.353f : kTau[tile]; }
 struct MidCosts { double round, round_plain, fraction, shared, part, part_few, tbs, stream, resid; };
-constexpr MidCosts kMid = {7.79, 7.1, 0.192, 0.0730, 0.460, 0.72, 6.01, 13.79, 0.506};
+constexpr MidCosts kMid = {7.79, 7.2, 0.192, 0.0730, 0.460, 0.37, 6.01, 13.79, 0.506};
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id], Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::NL, Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::LDS_BYTES},
     HAT_FOR_TILES(HAT_INFO, 0)
