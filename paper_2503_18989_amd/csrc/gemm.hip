@@ -792,22 +792,23 @@ struct TileInfo { int bf, bt, waves, bkt, nstage; float eff; int loaders, lds; }
 // Of the tiles with loader waves four are offered here.  Over 20 sizes of 1101 .. 4096 rows and eight widths they take, of the time of those earlier loops, 128 x 256 0.90 .. 0.99, 128 x 128 0.89 .. 1.02,
 // 96 x 128 0.90 .. 1.00 and 128 x 160 0.89 .. 1.04 (the higher ones at 256 and 1024 columns), so their weights are on the low side: the present choices lose 0.4 .. 1.4 % of a
 // layer at 1024 .. 5120 and 8192 columns and 2.6 % at 6144.  128 x 64 with loader waves (7) takes 0.98 .. 1.09 times as long
-// as without (10), 1.03 .. 1.07 for O and down of 256 and 1024 columns, which take this tile.
+// as without (10), 1.03 .. 1.07 for O and down of 256 and 1024 columns, which take this tile (all these with events around each launch); whole steps of 256 .. 1792 columns take 1 .. 3 % less with 10
+// (1101 rows of 256 columns 39.2 -> 37.8 us a layer, 2000 of 1024 103.0 -> 102.0).
 constexpr float kEff[kNumLdsTiles] = {0.f, 0.f, 0.537f, 0.533f, 0.744f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.679f, 0.f, 0.f, 0.527f, 0.570f, 0.f, 0.f, 0.535f, 0.f, 0.645f, 0.584f, 0.542f, 0.534f, 0.531f};
 constexpr int kSmallT = 384;
 // Up to kMidT rows: us that a k-tile of 64 is taken to cost each tile (0: not offered), and what else the model counts (hat_gemm_plan).
 // Weights for the choice like kEff, searched on all tiles, one to eight pieces of K and the norms at 30 batch sizes of 33 .. 1100 rows and seven widths (1024 x 2816 .. 8192 x 28672): the choices
 // lose 0.24 % of a layer's products on average; searched on two thirds of the sizes 0.23 .. 0.30 % there and 0.30 .. 0.45 % on the others.  The constants before, with these
 // tiles, lost 2 .. 9 % (192 rows 8.1, 420 8.8, 256 6.3, 1024 3.0).
-// 128 x 64 without loader waves (10) starts and ends sooner than its loader form (7), which takes less for a k-tile whose panel of W nobody else reads: a round of its own.  It and the constants of up
-// to kFewT rows were searched again with up to 14 pieces of K at eleven widths from 256 x 704 to 7168 x 18944, on two cards: the choices are 1.1 % behind the best of O, down and the products that do not stream up to 64 rows,
-// 0.2 .. 0.8 % from there to 384 and 1.2 % beyond (with 10 offered at 257 .. 384 rows only and one set of constants 2.3, 0.3 .. 1.3 and 2.3 %).  The products and norms of a
-// layer in us: 64 rows of 3072 columns 93.5 -> 89.0, 53 of 4096 120.6 -> 114.8, 512 of 256 46.1 -> 44.4; at 22 other sizes of 18 widths nowhere more than 1.2 % slower.
-constexpr int kMidT = 1100, kFewT = 64;
-constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.350f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
-constexpr float tau(int tile, bool few) { return !few ? kTau[tile] : tile == 10 ? 0.42f : tile == 11 ? 0.31f : tile == 18 ? 0.353f : kTau[tile]; }
-struct MidCosts { double round, round_plain, fraction, shared, part, part_few, tbs, stream, resid; };
-constexpr MidCosts kMid = {7.79, 7.2, 0.192, 0.0730, 0.460, 0.37, 6.01, 13.79, 0.506};
+// 128 x 64 without loader waves (10) starts and ends sooner than its loader form (7), which takes less for a k-tile whose panel of W nobody else reads: a round of its own, searched at eleven widths from
+// 256 x 704 to 7168 x 18944.  It is offered from 257 rows on, where its panels of W are read by five and more token tiles, which then find them in L2.  Whole steps, us a layer, without it | with it: 512 rows of 256 columns 36.6 | 34.5,
+// of 512 columns 46.6 | 43.4, 441 rows of 1024 55.6 | 54.9, 320 of 1280 58.5 | 57.9; at 236 sizes of 257 .. 1100 rows and thirteen widths up to 7 % less, nowhere more than 0.5 % more.
+// Below it loses as often as it gains (33 .. 128 rows 0.6 .. 2.4 % of a layer at 1024 and 2560 .. 4608 columns).  Times of single launches with events around them show it ahead there: such launches favour the tiles without loader waves by
+// about 1 us, so choices are compared in whole steps that are not profiled.
+constexpr int kMidT = 1100;
+constexpr float kTau[kNumLdsTiles] = {0.f, 0.f, 0.725f, 0.866f, 0.474f, 0.844f, 0.f, 0.405f, 0.f, 0.491f, 0.360f, 0.238f, 0.328f, 0.684f, 0.403f, 0.606f, 0.f, 1.046f, 0.338f, 1.306f, 1.204f, 1.045f, 0.951f, 0.590f};
+struct MidCosts { double round, round_plain, fraction, shared, part, tbs, stream, resid; };
+constexpr MidCosts kMid = {7.79, 7.1, 0.192, 0.0730, 0.460, 6.01, 13.79, 0.506};
 constexpr TileInfo kTiles[kNumTiles] = {
 #define HAT_INFO(id, bf, bt, wf, wt, wk, bkt, ns, g_, epi) {bf, bt, (wf) * (wt) * (wk), bkt, ns, kEff[id], Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::NL, Tile<bf, bt, wf, wt, wk, bkt, ns, g_>::LDS_BYTES},
     HAT_FOR_TILES(HAT_INFO, 0)
@@ -976,18 +977,18 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
   double best_cost = 1e300, tail_cost = 1e300;
   HatGemmPlan tail{0, 1};
   const int KT = g.K / 64;
-  const bool large = g.T > kMidT, few = g.T <= kFewT;
+  const bool large = g.T > kMidT;
   for (int c = 0; c < kNumLdsTiles; ++c) {
     const TileInfo& q = kTiles[c];
     // (0: tiles that are never the best there; beyond kSmallT rows nor are 64-row token tiles with loader waves)
-    if (large ? q.eff == 0.f : kTau[c] == 0.f || (g.T > kSmallT && q.bt < 128 && c != 10)) continue;
+    if (large ? q.eff == 0.f : kTau[c] == 0.f || (c == 10 ? g.T <= 256 : g.T > kSmallT && q.bt < 128)) continue;
     // 160/192/224-row token tiles: not up to 256 rows, except the 128 x 160 tile (23), which exists for batches
-    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %) and competes with the others there: most O, gate/up and down products from 4096 columns on take it (gate/up of 150 rows, in
-    // steps: 13B shape 64.6 us, next best 69.0; 7B shape 50.3, where 96 x 256, which pads 256 rows, would take 47.9), but not O of 4096 columns (64 x 256: 17.9 -> 17.2) nor gate/up of 7168, where
-    // its 296 workgroups go round twice (157 us, 192 x 256 142).  Above 256 rows a third
+    // of 129 .. 160 rows (a second, mostly empty 128-row token tile costs them 15-20 %) and competes with the others there: most O, gate/up and down products from 4096 columns on take it, but not O of 4096 columns
+    // (64 x 256: a step of 150 rows 150.9 -> 149.8 us a layer) nor gate/up of 7168, where its 296 workgroups go round twice (192 x 256: 129 rows 355.5 -> 343.3).  Gate/up of the 7B shape at 150 rows takes it, 50.3 us,
+    // where 96 x 256, which pads 256 rows, would take 47.9.  Above 256 rows a third
     // 128-row token tile or a second 256-row one is as empty: the four products and the norms of a layer at 257 and 320 rows 219 -> 193 and 229 -> 202 us (7B shape),
-    // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there; at 384 rows, three whole 128-row tiles but also two of 192, 309 -> 292 (13B; gate/up 117.5 -> 103.0) and
-    // 860 -> 751 (8192 columns).
+    // 282 -> 257 and 301 -> 267 (13B) when these tiles were offered there; at 384 rows, three whole 128-row
+    // tiles but also two of 192, steps take 318 -> 304 us a layer (13B), 431 -> 393 (6144 columns) and 883 -> 766 (8192).
     const bool tall = g.T > 256 || (c == 23 && g.T > 128 && g.T <= 160);
     if ((q.bt & (q.bt - 1)) != 0 && !tall) continue;
     const int nT = (g.T + q.bt - 1) / q.bt, nF = (g.Nw + q.bf - 1) / q.bf;
@@ -1011,8 +1012,8 @@ HatGemmPlan hat_gemm_plan(const HatGemm& g) {
         cost = std::max(cyc, hbm_cyc) + 1e-3 * cyc;                             // tie-break below the HBM floor
       } else {
         const double r = (1 - kMid.fraction) * rounds + kMid.fraction * std::max(1.0, blocks / 256.0);
-        double us = r * (kt * tau(c, few) * (nT > 1 ? 1 + kMid.shared : 1) + (c == 10 ? kMid.round_plain : kMid.round));
-        if (g.epilogue == HAT_EPI_RESID) us += 1e-3 * rows * (ks > 1 ? ks * (few ? kMid.part_few : kMid.part) : kMid.resid);
+        double us = r * (kt * kTau[c] * (nT > 1 ? 1 + kMid.shared : 1) + (c == 10 ? kMid.round_plain : kMid.round));
+        if (g.epilogue == HAT_EPI_RESID) us += 1e-3 * rows * (ks > 1 ? ks * kMid.part : kMid.resid);
         cost = std::max(us, 2e-6 * g.Nw * g.K / kMid.tbs + kMid.stream) + 0.02 * us;
       }
       if (cost < best_cost) { best_cost = cost; best.tile = c; best.ksplit = ks; }

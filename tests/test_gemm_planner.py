@@ -180,7 +180,7 @@ def test_o_and_down_of_a_narrow_model_stream_up_to_32_rows(lib, T):
 
 def test_token_tiles_between_the_powers_of_two_from_257_rows_on(lib):
     # the steps of test_gpu_mid_rows_gemm.py: where a third 128-row token tile would be nearly empty, no product keeps it; 384 rows are two whole
-    # 192-row tiles too, which gate/up of the wide models goes by (13B shape 115 -> 101 us), while 2048-wide models stay with 64, 128 and 256 rows there
+    # 192-row tiles too, which gate/up of the wide models goes by (steps of the 13B shape 318 -> 304 us a layer), while 2048-wide models stay with 64, 128 and 256 rows there
     def token_rows(d, f, T):
         pad = lambda n: (n + 255) // 256 * 256
         return [tile_info(lib, plan(lib, T, pad(n), o, k, e, 4096)[0])[1][1]
@@ -202,12 +202,11 @@ def test_tails_that_measured_faster_are_split(lib, d, f, T, first, ks):
     assert tuple(x.value for x in v) == (19, first, ks)
 
 
-def test_a_tile_without_loader_waves_where_its_products_are_short(lib):
-    # 128 x 64 rows, the multiplying waves load (tile 10): O and down of a few dozen rows and narrow models from a few hundred rows on measured 3 .. 15 % faster with it
-    # than with the tiles of loader waves
-    for d, f in ((2560, 6912), (3072, 8192), (4096, 11008)):
-        for T in (33, 48, 57):
-            assert plan(lib, T, d, d, f, 2, 4096)[0] == 10, (d, T)
+def test_narrow_models_take_a_tile_without_loader_waves_from_257_rows_on(lib):
+    # 128 x 64 rows, the multiplying waves load (tile 10): steps of 385 .. 1100 rows of these models measured 4 .. 7 % faster with it than with the tiles of loader waves.  Up to 256 rows it is not offered
+    for name, (d, f) in WIDTHS.items():
+        for N, o, K, e in ((3 * d, 3 * d, d, 0), (d, d, d, 2), (2 * f, f, d, 1), (d, d, f, 2)):
+            assert all(plan(lib, T, (N + 255) // 256 * 256, o, K, e, 4096)[0] != 10 for T in range(1, 257, 5)), (name, N, K)
     for d, f in ((256, 704), (512, 1408)):
         for T in (385, 512, 640):
             for N, o, K, e in ((3 * d, 3 * d, d, 0), (d, d, d, 2), (d, d, f, 2)):
@@ -227,8 +226,8 @@ def test_large_batches_do_not_take_64_token_rows_with_loader_waves(lib):
 
 @pytest.mark.parametrize("T", [129, 147, 160])
 def test_no_tile_is_prescribed_for_129_to_160_rows(lib, T):
-    # gate/up of 7168 columns: 128 x 160 makes 296 workgroups, a second round for 40 of them (157 us); tiles that go round once take 142
+    # gate/up of 7168 columns: 128 x 160 makes 296 workgroups, a second round for 40 of them; with tiles that go round once a step of 129 rows takes 343 us a layer instead of 356
     N, f = 37888, 18944
     bf, bt = tile_info(lib, plan(lib, T, N, f, 7168, 1, 4096)[0])[1][:2]
     assert -(-N // bf) * -(-T // bt) <= 256, (bf, bt)
-    assert tile_info(lib, plan(lib, T, 4096, 4096, 4096, 2, 4096)[0])[1][:2] == (64, 256)      # O of the 7B shape with its norm, 129 .. 160 rows: 0.6 .. 0.9 us ahead of 128 x 160
+    assert tile_info(lib, plan(lib, T, 4096, 4096, 4096, 2, 4096)[0])[1][:2] == (64, 256)      # O of the 7B shape: a step of 150 rows 150.9 -> 149.8 us a layer
