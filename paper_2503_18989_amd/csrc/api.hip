@@ -623,8 +623,8 @@ static std::vector<int> block_keys(const std::vector<ChunkCut>& cuts, const hat_
 }
 
 // Time in us of the same items staged (attn_chunk_kernel): a workgroup takes `block`, and for each 64 keys `stage` and `wave` for each of its waves with
-// rows.  Fitted like stream_us, as is merge_us.  Over an fp16 cache attn_ring_kernel takes these items; the constants are still those of attn_chunk_kernel there, which takes
-// 8 .. 12 % longer, so that a step near the line may stream where staging has become the faster way.
+// rows.  Fitted like stream_us, as is merge_us.  Over an fp16 cache attn_ring_kernel takes the items of more than a few keys; the constants are those of attn_chunk_kernel there, which takes
+// 8 .. 12 % longer with them, so that a step near the line may stream where staging has become the faster way.
 static double staged_us(const Shapes& s, int kv_f16, const std::vector<ChunkCut>& cuts, double mbytes) {
   struct Cost { double launch, block, stage, wave, per_mb; };
   static const Cost k[2][2] = {{{0.02, 7.82, 0.768, 0.071, 0.054}, {3.64, 3.86, 0.565, 0.080, 0.150}}, {{0, 9.81, 0.951, 0.124, 0.068}, {0, 9.11, 1.377, 0.105, 0.004}}};
@@ -972,7 +972,7 @@ static hat_status_t plan_step(hat_mid_t* h, const hat_mid_segment_t* segs, int32
     // workgroup fits a CU; of the chunk kernel's, with stages of half (head dim 64: a quarter) of that, two do.  750 mixes of 1 .. 32 chunks of 33 .. 512 rows
     // over 0 .. 4000 keys at 128, 600 at 64, ring against chunk kernel by keys a workgroup: head dim 128 below 64 1.07 times its time, 64 .. 128 level, 128 .. 192 0.88, more 0.9;
     // head dim 64 below 64 1.33 (at the most 1.69), 64 .. 128 1.25, 128 .. 256 1.09, 256 .. 320 0.97, more 0.94.  With the lines here the choice is
-    // 0.2 and 0.4 % behind the faster of the two, always the ring kernel 0.7 and 7.8 %.  8 x 128 rows of new prompts at 64 heads of 64: chunk kernel 14.1 us, ring 18.8.
+    // 0.2 and 0.4 % behind the faster of the two, always the ring kernel 0.7 and 7.8 %; whole steps of 874 other mixes put the lines at the same place.  8 x 128 rows of new prompts at 64 heads of 64: chunk kernel 14.1 us, ring 18.8.
     if (f16 && sp->block_waves == 0 && narrow0 != citems.begin()) {
       double keys = 0;
       for (auto it = citems.begin(); it != narrow0; ++it) keys += it->kv_end - it->kv_begin;
